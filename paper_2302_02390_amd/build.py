@@ -28,6 +28,8 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=o
 # bucket size -> (lanes per bucket G, rows per wave R, waves per bucket W): bucket = 4 * G * R * W
 WAVE_SHAPES = {128: (8, 4, 1), 256: (16, 4, 1), 512: (32, 4, 1), 1024: (64, 4, 1), 2048: (64, 4, 2),
                4096: (64, 4, 4)}
+# team shapes of the tile kernel, which serves every other bucket size: (waves, rows)
+TILE_SHAPES = [(1, 4), (1, 6), (1, 8), (4, 4), (4, 6), (4, 8)]
 
 
 def _units():
@@ -38,6 +40,8 @@ def _units():
     # the weight quantizer alone also as two waves per 1024-bucket (its faster shape; the other modes are not)
     units.append(("qsdp_wave_1024w2.o", "qsdp_wave_inst.hip",
                   ["-DQSDP_G=64", "-DQSDP_R=2", "-DQSDP_W=2", "-DQSDP_B=1024", "-DQSDP_WEIGHT_ONLY=1024w2"]))
+    for w, r in TILE_SHAPES:
+        units.append((f"qsdp_tile_{w}_{r}.o", "qsdp_tile_inst.hip", [f"-DQSDP_TILE_W={w}", f"-DQSDP_TILE_R={r}"]))
     return units
 
 

@@ -1,5 +1,5 @@
 // C ABI of the QSDP codec library: argument validation, launch planning, and the kernels
-// that are not specialised per bucket shape (block kernel, decoder).
+// that are not specialised per bucket shape (decoders, level fit).
 #include "../../include/qsdp.h"
 
 #include <cmath>
@@ -9,22 +9,6 @@
 #include "qsdp_launch.hpp"
 
 namespace qsdp {
-
-hipError_t launch_block(int mode, const Params& p, unsigned grid, hipStream_t s) {
-    switch (mode) {
-        case MODE_GRAD: hipLaunchKernelGGL(block_kernel<MODE_GRAD>, dim3(grid), dim3(256), 0, s, p, p.segs); break;
-        case MODE_WEIGHT: hipLaunchKernelGGL(block_kernel<MODE_WEIGHT>, dim3(grid), dim3(256), 0, s, p, p.segs); break;
-        case MODE_FUSED: hipLaunchKernelGGL(block_kernel<MODE_FUSED>, dim3(grid), dim3(256), 0, s, p, p.segs); break;
-        case MODE_FUSED_CODES: hipLaunchKernelGGL(block_kernel<MODE_FUSED_CODES>, dim3(grid), dim3(256), 0, s, p, p.segs); break;
-        case MODE_LEVELS: hipLaunchKernelGGL(block_kernel<MODE_LEVELS>, dim3(grid), dim3(256), 0, s, p, p.segs); break;
-        case MODE_ADAMW: hipLaunchKernelGGL(block_kernel<MODE_ADAMW>, dim3(grid), dim3(256), 0, s, p, p.segs); break;
-        case MODE_ADAMW_CODES: hipLaunchKernelGGL(block_kernel<MODE_ADAMW_CODES>, dim3(grid), dim3(256), 0, s, p, p.segs); break;
-        case MODE_RECV: hipLaunchKernelGGL(block_kernel<MODE_RECV>, dim3(grid), dim3(256), 0, s, p, p.segs); break;
-        case MODE_RECV_ADAMW: hipLaunchKernelGGL(block_kernel<MODE_RECV_ADAMW>, dim3(grid), dim3(256), 0, s, p, p.segs); break;
-        default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-}
 
 // Which bucket-index scheme the decoder kernels use for this call (tile = elements per wave).
 static int bucket_indexing(const DequantParams& p, bool bf16) {
@@ -188,8 +172,14 @@ WaveLauncher wave_launcher(int bucket, int* buckets_per_wave) {
     }
 }
 
-// Buckets go to the wave kernel of the bucket's shape when there is one for (bucket, stored
-// code width; for MODE_RECV also the width of the peers' codes), else to the block kernel.
+typedef hipError_t (*TileLauncher)(int, const Params&, const TileArgs&, unsigned, hipStream_t);
+
+TileLauncher tile_launcher(const TilePlan& t) {
+    if (t.waves == 1) return t.rows == 4 ? launch_tile_1_4 : t.rows == 6 ? launch_tile_1_6 : launch_tile_1_8;
+    return t.rows == 4 ? launch_tile_4_4 : t.rows == 6 ? launch_tile_4_6 : launch_tile_4_8;
+}
+
+// Buckets go to the wave kernel of the bucket's shape when there is one, else to the tile kernel.
 // p.num_buckets must be set.
 int run(int mode, Params p, int stored_bits, hipStream_t s) {
     const uint64_t nb = p.num_buckets;
@@ -203,8 +193,7 @@ int run(int mode, Params p, int stored_bits, hipStream_t s) {
         wl = launch_wave_1024w2;
         bpw = 0;
     }
-    const bool peer_bits_ok = !mode_reads_peers(mode) || (p.gbits != 0 && wave_bits_supported(p.gbits));
-    if (wl != nullptr && wave_bits_supported(stored_bits) && peer_bits_ok) {
+    if (wl != nullptr) {
         // 4 waves per workgroup, each on bpw buckets; or one workgroup per bucket
         const uint64_t blocks = bpw > 0 ? ceil_div(ceil_div(nb, (uint64_t)bpw), 4) : nb;
         // The learned-level encoders set up lookup tables per workgroup: their workgroups stay resident
@@ -212,8 +201,11 @@ int run(int mode, Params p, int stored_bits, hipStream_t s) {
         const unsigned cap = mode_is_levels(mode) ? kLevelsGrid : kMaxGrid;
         if (wl(mode, stored_bits, p, capped_grid(blocks, cap), s) != hipSuccess) return QSDP_ELAUNCH;
     } else {
-        if (launch_block(mode == MODE_LEVELS_COIN ? MODE_LEVELS : mode, p, capped_grid(nb), s) != hipSuccess)
-            return QSDP_ELAUNCH;
+        const TilePlan t = tile_plan(p.bucket);
+        const uint64_t units = ceil_div(nb, (uint64_t)t.buckets);
+        const uint64_t blocks = t.waves == 1 ? ceil_div(units, 4) : units;
+        const TileArgs a = {units, t.buckets, t.lanes_log2, t.group_magic, word_magic(stored_bits > 0 ? stored_bits : 8)};
+        if (tile_launcher(t)(mode, p, a, capped_grid(blocks), s) != hipSuccess) return QSDP_ELAUNCH;
     }
     return QSDP_OK;
 }
@@ -435,7 +427,6 @@ int qsdp_quantize_levels_stochastic(const float* v, uint64_t n, int bits, int bu
         return QSDP_EALIGN;
     Params p = {};
     set_common(p, n, bucket, seed, index_offset, 0.0f);
-    p.flags = FLAG_LEVELS_STOCHASTIC;
     p.xin = v;
     p.levels = levels;
     p.codes = codes;
@@ -848,7 +839,6 @@ int qsdp_quantize_levels_segmented(const float* v, const qsdp_segment* table, ui
     p.segs = reinterpret_cast<const Segment*>(table);
     p.nseg = nseg;
     p.num_buckets = total_buckets;
-    p.flags = stochastic ? FLAG_LEVELS_STOCHASTIC : 0u;
     p.xin = v;
     p.levels = levels;
     p.levels_per_tensor = 1u;

@@ -43,15 +43,11 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
 }
 
 // Rounding uniforms of a row pair: the 16-bit integers h of the lane's eight elements, still packed
-// two to a word (low half first). Lane l holds elements (r*G + l)*4 .. +3 of rows r = 2c and 2c+1.
-// A Philox block (8 elements) spans the lane pair (l even, l+1) of one row: the even lane computes
-// the block of row 2c, the odd lane that of row 2c+1, and the pair swaps the halves the other needs.
-// w[0..1] serve row 2c, w[2..3] row 2c+1. bucket_block = index of the bucket's first block.
-template <int G>
-__device__ __forceinline__ void grad_uniforms_rows(uint64_t bucket_block, int c, int l, uint32_t k0,
-                                                   uint32_t k1, uint32_t (&h)[4]) {
-    const int odd = l & 1;
-    const uint64_t block = bucket_block + (uint64_t)(((2 * c + odd) * G + (l - odd)) >> 1);
+// two to a word (low half first). A Philox block (8 elements) spans the lane pair (l even, l+1) of one
+// row: the even lane computes the block of the pair's first row, the odd lane that of its second row
+// (`block` is the lane's own), and the pair swaps the halves the other needs.
+// h[0..1] serve the first row, h[2..3] the second.
+__device__ __forceinline__ void uniforms_of_pair(uint64_t block, int odd, uint32_t k0, uint32_t k1, uint32_t (&h)[4]) {
     uint32_t w[4];
     philox4x32_10((uint32_t)block, (uint32_t)(block >> 32), 0u, 0u, k0, k1, w);
     const uint32_t send0 = odd ? w[0] : w[2];
@@ -59,8 +55,17 @@ __device__ __forceinline__ void grad_uniforms_rows(uint64_t bucket_block, int c,
     // every lane has a partner, so the destination's previous value never shows
     const uint32_t recv0 = (uint32_t)__builtin_amdgcn_mov_dpp((int)send0, 0xB1, 0xF, 0xF, true);
     const uint32_t recv1 = (uint32_t)__builtin_amdgcn_mov_dpp((int)send1, 0xB1, 0xF, 0xF, true);
-    h[0] = odd ? recv0 : w[0]; h[1] = odd ? recv1 : w[1];  // row 2c
-    h[2] = odd ? w[2] : recv0; h[3] = odd ? w[3] : recv1;  // row 2c+1
+    h[0] = odd ? recv0 : w[0]; h[1] = odd ? recv1 : w[1];
+    h[2] = odd ? w[2] : recv0; h[3] = odd ? w[3] : recv1;
+}
+
+// The same for rows 2c and 2c+1 of a bucket whose lane l holds elements (r*G + l)*4 .. +3 of every row r.
+// bucket_block = index of the bucket's first block.
+template <int G>
+__device__ __forceinline__ void grad_uniforms_rows(uint64_t bucket_block, int c, int l, uint32_t k0,
+                                                   uint32_t k1, uint32_t (&h)[4]) {
+    const int odd = l & 1;
+    uniforms_of_pair(bucket_block + (uint64_t)(((2 * c + odd) * G + (l - odd)) >> 1), odd, k0, k1, h);
 }
 
 // The 16-bit uniform of element i (0..7) of a row pair out of the packed words above.

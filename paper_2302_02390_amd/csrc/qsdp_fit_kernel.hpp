@@ -1,10 +1,24 @@
 // Level fitting (Algorithm 1 in batched form).
 #pragma once
 
-#include "qsdp_block_kernel.hpp"  // block_minmax
 #include "qsdp_params.hpp"
 
 namespace qsdp {
+
+// Minimum and maximum over the 256 threads of a workgroup.
+__device__ __forceinline__ void block_minmax(float& lo, float& hi, float* red /* 8 floats */) {
+    lo = group_min<64>(lo);
+    hi = group_max<64>(hi);
+    const int wave = threadIdx.x >> 6;
+    __syncthreads();  // red may still be read from a previous use
+    if ((threadIdx.x & 63) == 0) {
+        red[wave] = lo;
+        red[4 + wave] = hi;
+    }
+    __syncthreads();
+    lo = fminf(fminf(red[0], red[1]), fminf(red[2], red[3]));
+    hi = fmaxf(fmaxf(red[4], red[5]), fmaxf(red[6], red[7]));
+}
 
 // ---------------------------------------------------------------------------------------
 // Level fitting (Algorithm 1 in batched form): ONE workgroup walks the buckets in order, since

@@ -14,16 +14,16 @@
 //     bucket takes a guarded element-wise path of the same kernel. Buckets larger than one
 //     wave's tile are shared by the W waves of a workgroup (B = 4*G*R*W, G = 64): each wave
 //     owns a contiguous 1/W of the bucket and the waves combine their min/max through LDS.
-//   * block kernel: one 256-thread workgroup per bucket, staged in LDS; any bucket size, any
-//     bits. Used for the bucket sizes the wave kernels are not instantiated for (several times
-//     slower: the values make a round trip through LDS and the codes are packed bit by bit).
+//   * tile kernels: any bucket size (a multiple of 32), run-time code width: a wave or four waves on as many
+//     whole buckets as fit; used for the bucket sizes the wave kernels are not instantiated for.
 // The modes and parameters are in qsdp_params.hpp, the two encoder families in qsdp_wave_kernel.hpp and
-// qsdp_block_kernel.hpp, the decoders and the element-wise decode-and-sum in qsdp_decoders.hpp, the
+// qsdp_tile_kernel.hpp, the decoders and the element-wise decode-and-sum in qsdp_decoders.hpp, the
 // level fit in qsdp_fit_kernel.hpp.
 #pragma once
 
 #include "qsdp_params.hpp"
+#include "qsdp_tile_plan.hpp"
 #include "qsdp_wave_kernel.hpp"
-#include "qsdp_block_kernel.hpp"
+#include "qsdp_tile_kernel.hpp"
 #include "qsdp_decoders.hpp"
 #include "qsdp_fit_kernel.hpp"

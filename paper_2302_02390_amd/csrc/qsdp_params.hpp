@@ -1,4 +1,4 @@
-// Launch parameters shared by the encoder kernels (wave and block kernels): the modes, the
+// Launch parameters shared by the encoder kernels (wave and tile kernels): the modes, the
 // parameter block, the Philox key of a launch, the step arithmetic between the two quantizers,
 // and the lookup of a bucket's tensor in a multi-tensor call.
 #pragma once
@@ -7,7 +7,7 @@
 
 namespace qsdp {
 
-// Largest bucket any kernel accepts (the block kernel and the level fit stage one bucket in LDS).
+// Largest bucket any kernel accepts (the tile kernel's largest team holds one in registers, the level fit in LDS).
 constexpr int kMaxBucket = 8192;
 
 // What one launch of an encoder kernel does:
@@ -31,9 +31,8 @@ constexpr int kMaxBucket = 8192;
 // MODE_FUSED_CODES, the moments in fp32).
 // MODE_SUM: only the first half of MODE_RECV: out = alpha * (sum of the decoded peer slices).
 // MODE_LEVELS_COIN: MODE_LEVELS with the unbiased coin flip between the two enclosing levels
-// instead of the nearest level (wave kernels only: a kernel of its own so that the nearest-level
-// encoder does not carry the registers of the rounding uniforms; the block kernel takes
-// MODE_LEVELS with FLAG_LEVELS_STOCHASTIC).
+// instead of the nearest level (a kernel of its own so that the nearest-level encoder does not carry
+// the registers of the rounding uniforms).
 enum Mode { MODE_GRAD = 0, MODE_WEIGHT = 1, MODE_FUSED = 2, MODE_FUSED_CODES = 3, MODE_LEVELS = 4,
             MODE_ADAMW = 5, MODE_RECV = 6, MODE_RECV_ADAMW = 7, MODE_SUM = 8, MODE_LEVELS_COIN = 9,
             MODE_ADAMW_CODES = 10 };
@@ -140,9 +139,7 @@ __device__ __forceinline__ float step_value(const Params& p, float x, float ghat
 
 // Quantizer variants (same values as the QSDP_FLAG_* of the C header)
 // FLAG_KEEP_MASTER (step modes): x receives the updated value itself, the codes still Q^w of it
-// FLAG_LEVELS_STOCHASTIC (internal, MODE_LEVELS): coin-flip rounding between the enclosing levels
-enum : uint32_t { FLAG_GRAD_SHIFT = 1u, FLAG_NO_SHIFT = 2u, FLAG_SYMMETRIC = 4u, FLAG_KEEP_MASTER = 8u,
-                  FLAG_LEVELS_STOCHASTIC = 0x100u };
+enum : uint32_t { FLAG_GRAD_SHIFT = 1u, FLAG_NO_SHIFT = 2u, FLAG_SYMMETRIC = 4u, FLAG_KEEP_MASTER = 8u };
 
 struct Shifts {
     float xi;    // weight shift
@@ -186,6 +183,7 @@ __device__ __forceinline__ Segment find_segment(const Segment* __restrict__ segs
 // elements. gb0: a wave-uniform bucket <= gb (see find_segment).
 struct BucketRef {
     uint64_t e0;
+    uint64_t left;    // elements of the tensor from e0 on
     uint32_t m;
     uint32_t tensor;  // index in the segment table (0 for a single tensor)
 };
@@ -204,6 +202,7 @@ __device__ __forceinline__ BucketRef locate_bucket(const Params& p, const Segmen
         ref.e0 = gb * B;
         left = p.n - ref.e0;
     }
+    ref.left = left;
     ref.m = left < B ? (uint32_t)left : B;
     return ref;
 }

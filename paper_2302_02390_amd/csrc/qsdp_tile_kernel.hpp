@@ -1,0 +1,606 @@
+// Tile kernel: the encoders and steps for any bucket size (a multiple of 32 up to kMaxBucket) and any code width, both
+// run-time values. Serves the bucket sizes the wave kernels are not instantiated for.
+//
+// A team of W waves works on a tile of P whole consecutive buckets, i.e. on one contiguous piece of the vector and of
+// the code stream: slot s of the tile is its elements 4s .. 4s+3, lane t of the team holds slots r*64W + t of every
+// row r, so each load and store instruction of a wave is one contiguous KiB whatever the bucket size, and the values
+// stay in registers. A bucket is k = B/32 groups of eight slots. Groups are aligned to eight lanes of a row, so a
+// group's minimum and maximum take three DPP steps; the team's 8*W*R group results go through LDS, 2^lanes_log2 lanes
+// combine those of one bucket, and the bucket's grid comes back with one 16-byte LDS read per row.
+//
+// Bound by HBM where a tile is well filled: the step with code output on 125 million parameters in buckets of 768 (W8
+// G8) takes 0.268 ms = 6.1 TB/s, against 1.33 ms for a workgroup per bucket that stages its values in LDS and packs
+// its codes bit by bit; buckets of 96 on 8 million parameters 0.022 against 0.353 ms. P is the largest count that fits
+// (qsdp_tile_plan.hpp), so few slots idle; leaving out the arithmetic of a wave's idle rows by branches cost the full
+// tiles 3-10 % (the rows no longer overlap) and won 4 % at the worst fill, so it is not done.
+#pragma once
+
+#include "qsdp_params.hpp"
+#include "qsdp_wave_kernel.hpp"  // widen16
+
+namespace qsdp {
+
+template <int R, int W>
+struct TileLds {
+    static constexpr int kTeam = 64 * W;
+    static constexpr int kSlots = kTeam * R;
+    static constexpr int kGroups = kSlots / 8;
+    f4 grid[kGroups];            // per bucket: what its elements need of its grid
+    u4 where[kGroups];           // per bucket, tiles that are not contiguous: {offset in the tile, elements, tensor}
+    u2 part[kGroups];            // per group: {min, max}
+    uint32_t stage[kSlots + 4];  // packed codes: one word of 4 codes per slot, or the tile's code stream
+};
+
+template <int W>
+__device__ __forceinline__ void team_sync() {
+    if constexpr (W == 1) {  // LDS traffic of one wave is processed in order; keep the compiler from reordering it
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    } else {
+        __syncthreads();
+    }
+}
+
+// Minimum and maximum over aligned runs of 2^log2 lanes (log2 uniform); all lanes take part.
+__device__ __forceinline__ void lanes_minmax(float& lo, float& hi, int log2) {
+    if (log2 >= 1) { lo = fminf(lo, dpp_move<0xB1>(lo)); hi = fmaxf(hi, dpp_move<0xB1>(hi)); }
+    if (log2 >= 2) { lo = fminf(lo, dpp_move<0x4E>(lo)); hi = fmaxf(hi, dpp_move<0x4E>(hi)); }
+    if (log2 >= 3) { lo = fminf(lo, dpp_move<0x141>(lo)); hi = fmaxf(hi, dpp_move<0x141>(hi)); }
+    if (log2 >= 4) { lo = fminf(lo, dpp_move<0x140>(lo)); hi = fmaxf(hi, dpp_move<0x140>(hi)); }
+    if (log2 >= 5) {
+        float a, b;
+        swap16(lo, a, b); lo = fminf(a, b);
+        swap16(hi, a, b); hi = fmaxf(a, b);
+    }
+    if (log2 >= 6) {
+        float a, b;
+        swap32(lo, a, b); lo = fminf(a, b);
+        swap32(hi, a, b); hi = fmaxf(a, b);
+    }
+}
+
+// Code of z among the K = 2^bits levels lv (LDS or global memory), by the plain definitions: nearest level (ties and
+// equal levels: the lowest index) ...
+__device__ __forceinline__ uint32_t nearest_level_any(float z, const float* lv, int K) {
+    int j = 0;  // ends as the number of levels < z among the first K-1
+    for (int step = K >> 1; step >= 1; step >>= 1)
+        if (lv[j + step - 1] < z) j += step;
+    const int below = j > 0 ? j - 1 : 0;
+    int c = fabsf(z - lv[j]) < fabsf(z - lv[below]) ? j : below;
+    while (c > 0 && lv[c - 1] == lv[c]) --c;
+    return (uint32_t)c;
+}
+
+// ... or the coin flip between the two enclosing levels, h the element's 16-bit uniform.
+__device__ __forceinline__ uint32_t stochastic_level_any(float z, float h, const float* lv, int K) {
+    int cnt = 0;  // levels <= z among the first K-1, then the last one
+    for (int step = K >> 1; step >= 1; step >>= 1)
+        if (lv[cnt + step - 1] <= z) cnt += step;
+    if (cnt == K - 1 && lv[K - 1] <= z) ++cnt;
+    if (cnt == 0) return 0u;
+    const int i = cnt - 1;
+    if (i == K - 1) return (uint32_t)i;
+    const float q = lv[i];
+    const float p = (z - q) * (1.0f / (lv[i + 1] - q));
+    return (uint32_t)i + ((65535.5f - h) < p * 65536.0f ? 1u : 0u);
+}
+
+// What the launch adds to Params: the number of tiles (a 64-bit division in every wave's prologue otherwise), the
+// tile's shape (see TilePlan) and ceil(2^18 / width) of the stored codes.
+struct TileArgs {
+    uint64_t tiles;
+    int buckets, lanes_log2;
+    uint32_t group_magic, word_magic;
+};
+
+template <int MODE, int R, int W>
+__global__ void __launch_bounds__(256) tile_kernel(const Params p, const Segment* __restrict__ segs, const TileArgs a) {
+    static_assert(R % 2 == 0 && R <= kTileMaxRows && (W == 1 || W == 4), "shape");
+    typedef TileLds<R, W> Lds;
+    constexpr int TEAM = Lds::kTeam;
+    constexpr bool kWritesX = MODE == MODE_FUSED || MODE == MODE_ADAMW || mode_is_recv(MODE);
+    constexpr bool kLevels = mode_is_levels(MODE);
+    __shared__ Lds lds_all[4 / W];
+    __shared__ float level_tables[kLevels ? 4 / W : 1][kLevels ? 256 : 1];
+    const uint32_t wave_in_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int tid = W == 1 ? (int)(threadIdx.x & 63) : (int)threadIdx.x;
+    Lds& lds = lds_all[W == 1 ? wave_in_block : 0];
+    float* level_table = level_tables[W == 1 ? (kLevels ? wave_in_block : 0) : 0];
+    uint32_t loaded_tensor = ~0u;  // whose level table the team holds
+
+    const int B = p.bucket;
+    const int k = B >> 5;      // groups of a bucket
+    const int S = B >> 2;      // slots of a bucket
+    const int P = a.buckets;   // buckets of a full tile
+    const float Lg = (float)((1 << p.gbits) - 1);
+    const uint32_t top16_g = (uint32_t)((1 << p.gbits) - 1) << 16;
+    const float Lw = (float)((1 << p.wbits) - 1);
+    const Divider div = {p.delta, p.inv_delta, p.delta_pow2 != 0};
+    const bool lattice = p.delta > 0.0f;
+    const bool symmetric = (p.flags & FLAG_SYMMETRIC) != 0;
+    const bool grad_shift = (p.flags & FLAG_GRAD_SHIFT) != 0;
+    const bool keep_master = kWritesX && (p.flags & FLAG_KEEP_MASTER) != 0;
+    const PhiloxKey key = launch_key(p);
+    const Shifts shifts = draw_shifts(p, key, MODE != MODE_GRAD && !kLevels);
+    const float xi = shifts.xi;
+    uint32_t saturated = 0;
+
+    const uint64_t unit0 = W == 1 ? (uint64_t)blockIdx.x * 4u + wave_in_block : blockIdx.x;
+    const uint64_t unit_stride = W == 1 ? (uint64_t)gridDim.x * 4u : gridDim.x;
+    // row r of this lane: its slot; bucket of a slot in the tile
+    auto slot_of = [&](int r) { return r * TEAM + tid; };
+    auto bucket_of_slot = [&](int slot) { return (int)(((uint32_t)slot >> 3) * a.group_magic >> 16); };
+
+    for (uint64_t unit = unit0; unit < a.tiles; unit += unit_stride) {
+        // keeps what follows from the lane's number alone (slots, buckets, offsets of every row) out of registers that
+        // live across the loop
+        asm volatile("" : "+v"(tid));
+        const int odd = tid & 1;
+        const uint64_t bucket0 = unit * (uint64_t)P;
+        const uint64_t left = p.num_buckets - bucket0;
+        const int here = left < (uint64_t)P ? (int)left : P;  // buckets of this tile
+        const BucketRef first = locate_bucket(p, segs, bucket0, bucket0, (uint32_t)B);
+        const uint64_t e0 = first.e0;
+        // contiguous: P full buckets of one tensor
+        const bool whole = here == P && first.left >= (uint64_t)P * (uint64_t)B;
+        const uint64_t word0 = bucket0 * (uint64_t)(B >> 5);  // times the code width: the tile's first code word
+        const int used = here * S;                            // slots of these buckets
+        if (W > 1) team_sync<W>();  // the previous tile's LDS reads are done
+        if (__builtin_expect(!whole, 0)) {
+            if (tid < P) {
+                u4 w = {0u, 0u, 0u, 0u};
+                if (tid < here) {
+                    const BucketRef ref = locate_bucket(p, segs, bucket0, bucket0 + (uint64_t)tid, (uint32_t)B);
+                    w[0] = (uint32_t)(ref.e0 - e0);
+                    w[1] = ref.m;
+                    w[2] = ref.tensor;
+                }
+                lds.where[tid] = w;
+            }
+            team_sync<W>();
+        }
+        // Offset from e0 of the first element of a slot, and how many of its four elements exist, in a tile that is
+        // not contiguous.
+        struct Place { uint32_t rel; int count; };
+        auto place = [&](int slot) -> Place {
+            asm volatile("" : "+v"(slot));  // not worth keeping for the unlikely path
+            const int b = bucket_of_slot(slot);
+            if (b >= here) return {0u, 0};
+            const u4 w = lds.where[b];
+            const int off = (slot - b * S) * 4;
+            const int c = (int)w[1] - off;
+            return {w[0] + (uint32_t)off, c < 0 ? 0 : c > 4 ? 4 : c};
+        };
+        // In a contiguous one slot s is elements 4s .. 4s+3; the slots past the last bucket read the tile's first
+        // elements instead: in bounds, and their values go nowhere.
+        auto load = [&](const float* base, float (&v)[R][4]) {
+            const char* at = reinterpret_cast<const char*>(base + e0);
+            if (__builtin_expect(whole, 1)) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const uint32_t s = slot_of(r) < used ? (uint32_t)slot_of(r) : 0u;
+                    const f4 x = __builtin_nontemporal_load(reinterpret_cast<const f4*>(at + s * 16u));
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[r][i] = x[i];
+                }
+            } else {
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const Place s = place(slot_of(r));
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[r][i] = i < s.count ? (base + e0 + s.rel)[i] : 0.0f;
+                }
+            }
+        };
+        auto load_half = [&](const void* base, bool bf16, float (&v)[R][4]) {
+            const uint16_t* first_half = static_cast<const uint16_t*>(base) + e0;
+            uint32_t h[R][2];
+            if (__builtin_expect(whole, 1)) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const uint32_t s = slot_of(r) < used ? (uint32_t)slot_of(r) : 0u;
+                    const u2 x = __builtin_nontemporal_load(
+                        reinterpret_cast<const u2*>(reinterpret_cast<const char*>(first_half) + s * 8u));
+                    h[r][0] = x[0];
+                    h[r][1] = x[1];
+                }
+            } else {
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const Place s = place(slot_of(r));
+                    h[r][0] = h[r][1] = 0u;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (i < s.count) h[r][i >> 1] |= (uint32_t)first_half[s.rel + i] << (16 * (i & 1));
+                }
+            }
+            if (bf16) {
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[r][i] = widen16<true>(i & 1 ? h[r][i >> 1] >> 16 : h[r][i >> 1] & 0xFFFFu);
+            } else {
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[r][i] = widen16<false>(i & 1 ? h[r][i >> 1] >> 16 : h[r][i >> 1] & 0xFFFFu);
+            }
+        };
+        auto store = [&](float* base, const float (&v)[R][4]) {
+            char* at = reinterpret_cast<char*>(base + e0);
+            if (__builtin_expect(whole, 1)) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const f4 x = {v[r][0], v[r][1], v[r][2], v[r][3]};
+                    if (slot_of(r) < used) __builtin_nontemporal_store(x, reinterpret_cast<f4*>(at + (uint32_t)slot_of(r) * 16u));
+                }
+            } else {
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const Place s = place(slot_of(r));
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (i < s.count) (base + e0 + s.rel)[i] = v[r][i];
+                }
+            }
+        };
+        auto store_half = [&](void* base, bool f16, const float (&v)[R][4]) {
+            uint16_t* first_half = static_cast<uint16_t*>(base) + e0;
+            if (__builtin_expect(whole, 1)) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const u2 x = {half_bits(v[r][0], f16) | (half_bits(v[r][1], f16) << 16),
+                                  half_bits(v[r][2], f16) | (half_bits(v[r][3], f16) << 16)};
+                    if (slot_of(r) < used)
+                        __builtin_nontemporal_store(
+                            x, reinterpret_cast<u2*>(reinterpret_cast<char*>(first_half) + (uint32_t)slot_of(r) * 8u));
+                }
+            } else {
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const Place s = place(slot_of(r));
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (i < s.count) first_half[s.rel + i] = (uint16_t)half_bits(v[r][i], f16);
+                }
+            }
+        };
+        // Rounding uniforms of rows 2cp and 2cp + 1: the pair's even lane draws the block of the first, its odd lane
+        // that of the second.
+        auto uniforms = [&](int cp, uint32_t (&h)[4]) {
+            const int slot = (2 * cp + odd) * TEAM + tid - odd;
+            const uint32_t rel = __builtin_expect(whole, 1) ? (uint32_t)slot * 4u : place(slot).rel;
+            uniforms_of_pair(p.block0 + (e0 >> 3) + (rel >> 3), odd, key.k0, key.k1, h);
+        };
+        // Minimum and maximum of every bucket of the tile, then its grid: make(lo, hi, bucket in the tile) in the
+        // lanes that combine that bucket, the result in lds.grid for all.
+        auto bucket_grids = [&](const float (&v)[R][4], auto make) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                float lo = fminf(fminf(v[r][0], v[r][1]), fminf(v[r][2], v[r][3]));
+                float hi = fmaxf(fmaxf(v[r][0], v[r][1]), fmaxf(v[r][2], v[r][3]));
+                if (__builtin_expect(!whole, 0)) {
+                    const int c = place(slot_of(r)).count;
+                    lo = __builtin_inff();
+                    hi = -__builtin_inff();
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        lo = i < c ? fminf(lo, v[r][i]) : lo;
+                        hi = i < c ? fmaxf(hi, v[r][i]) : hi;
+                    }
+                }
+                lo = group_min<8>(lo);
+                hi = group_max<8>(hi);
+                if ((tid & 7) == 0) {
+                    const u2 e = {__float_as_uint(lo), __float_as_uint(hi)};
+                    lds.part[slot_of(r) >> 3] = e;
+                }
+            }
+            team_sync<W>();
+            const int b = tid >> a.lanes_log2;
+            float lo = __builtin_inff(), hi = -__builtin_inff();
+            if (b < here)
+                for (int i = tid & ((1 << a.lanes_log2) - 1); i < k; i += 1 << a.lanes_log2) {
+                    const u2 e = lds.part[b * k + i];
+                    lo = fminf(lo, __uint_as_float(e[0]));
+                    hi = fmaxf(hi, __uint_as_float(e[1]));
+                }
+            lanes_minmax(lo, hi, a.lanes_log2);
+            const f4 g = make(lo, hi, b);
+            if (b < here && (tid & ((1 << a.lanes_log2) - 1)) == 0) lds.grid[b] = g;
+            team_sync<W>();
+        };
+        auto first_of_bucket = [&](int b) { return b < here && (tid & ((1 << a.lanes_log2) - 1)) == 0; };
+        auto write_meta = [&](int b, float base, float scale) {
+            if (first_of_bucket(b)) {
+                const u2 m = {__float_as_uint(base), __float_as_uint(scale)};
+                *reinterpret_cast<u2*>(p.meta + 2 * (bucket0 + (uint64_t)b)) = m;
+            }
+        };
+        // The `bits` wide codes of the tile: words of the code stream that starts at `words`, fetched now ...
+        auto fetch_words = [&](const uint32_t* words, int bits, uint32_t (&w)[R]) {
+            const int total = used * bits >> 3;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int i = slot_of(r);
+                w[r] = i < total ? __builtin_nontemporal_load(words + i) : 0u;
+            }
+        };
+        // ... and taken apart: the four codes of each of the lane's slots. The stage holds no other words then.
+        auto unpack = [&](const uint32_t (&w)[R], int bits, float (&c)[R][4]) {
+            if (bits != 8) {  // at 8 bits word s is slot s
+                team_sync<W>();
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    if (r * 8 < R * bits) lds.stage[slot_of(r)] = w[r];
+                team_sync<W>();
+            }
+            const uint32_t mask = (1u << bits) - 1u;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                uint32_t q = w[r];
+                if (bits != 8) {
+                    const uint32_t bit = (uint32_t)(slot_of(r) * 4 * bits);
+                    const uint64_t two = (uint64_t)lds.stage[bit >> 5] | ((uint64_t)lds.stage[(bit >> 5) + 1] << 32);
+                    q = (uint32_t)(two >> (bit & 31u));
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) c[r][i] = (float)((q >> (i * bits)) & mask);
+            }
+        };
+        // The reverse: pack the codes and write the tile's part of the code stream. Slots past a short bucket's end
+        // carry zeros.
+        auto store_words = [&](const uint32_t (&code)[R][4], int bits) {
+            uint32_t* out = p.codes + word0 * (uint64_t)bits;
+            if (bits != 8) team_sync<W>();
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                uint32_t q = code[r][0] | (code[r][1] << bits) | (code[r][2] << (2 * bits)) | (code[r][3] << (3 * bits));
+                if (__builtin_expect(!whole, 0)) {
+                    const int c = place(slot_of(r)).count;
+                    if (c < 4) q &= (1u << (c * bits)) - 1u;
+                }
+                if (bits != 8) lds.stage[slot_of(r)] = q;
+                else if (slot_of(r) < used) __builtin_nontemporal_store(q, out + slot_of(r));
+            }
+            if (bits == 8) return;
+            team_sync<W>();
+            const int total = used * bits >> 3;
+            for (int w = tid; w < total; w += TEAM) {
+                int s = (int)((uint32_t)(8 * w) * a.word_magic >> 18);  // slot of the word's first bit
+                int at = s * 4 * bits - 32 * w;                         // where its codes start: at or before bit 0
+                uint32_t word = lds.stage[s] >> -at;
+                for (at += 4 * bits; at < 32; at += 4 * bits) word |= lds.stage[++s] << at;
+                __builtin_nontemporal_store(word, out + w);
+            }
+        };
+
+        float w[R][4];  // the values that get weight-quantized
+        if constexpr (mode_local_gradient(MODE)) {
+            float gv[R][4];
+            float mom[R][4], var[R][4];  // AdamW modes only
+            uint32_t old_words[R];       // code-resident modes only
+            if constexpr (mode_codes_resident(MODE))
+                fetch_words(p.codes + word0 * (uint64_t)p.wbits, p.wbits, old_words);
+            if (mode_mixed_precision(MODE) && p.g_half != 0u) load_half(p.g, p.g_half == 1u, gv);
+            else load(p.g, gv);
+            if constexpr (MODE == MODE_FUSED || MODE == MODE_ADAMW) load(p.x, w);
+            if constexpr (mode_local_adamw(MODE)) {
+                load(p.mom, mom);
+                load(p.var, var);
+            }
+            if constexpr (mode_codes_resident(MODE)) {
+                unpack(old_words, p.wbits, w);
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const int b = bucket_of_slot(slot_of(r));
+                    const float* m = p.meta + 2 * (bucket0 + (uint64_t)(b < here ? b : 0));
+                    const float base = m[0], scale = m[1];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) w[r][i] = fmaf(w[r][i], scale, base);
+                }
+            }
+            bucket_grids(gv, [&](float lo, float hi, int b) -> f4 {
+                const MinMaxGrid g = make_minmax_grid(lo, hi, Lg, symmetric);
+                const float base = grad_shift ? fmaf(shifts.xi_g, g.scale, g.lo) : g.lo;
+                if constexpr (MODE == MODE_GRAD) write_meta(b, base, g.scale);
+                return f4{g.lo, g.inv, g.scale, base};
+            });
+            uint32_t code[MODE == MODE_GRAD ? R : 1][4];
+#pragma unroll
+            for (int cp = 0; cp < R / 2; ++cp) {
+                uint32_t h[4] = {0u, 0u, 0u, 0u};
+                if (!grad_shift) uniforms(cp, h);
+#pragma unroll
+                for (int half = 0; half < 2; ++half) {
+                    const int r = 2 * cp + half;
+                    const f4 gr = lds.grid[bucket_of_slot(slot_of(r))];
+                    const MinMaxGrid grid = {gr[0], gr[2], gr[1]};
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        if constexpr (MODE == MODE_GRAD) {
+                            code[r][i] = grad_shift ? (uint32_t)weight_code_minmax(gv[r][i], grid, Lg, shifts.xi_g)
+                                                    : grad_code_int(gv[r][i], grid, top16_g, uniform16(h, 4 * half + i));
+                        } else {
+                            const float c = grad_shift ? weight_code_minmax(gv[r][i], grid, Lg, shifts.xi_g)
+                                                       : grad_code(gv[r][i], grid, top16_g, uniform16(h, 4 * half + i));
+                            w[r][i] = step_value<MODE>(p, w[r][i], fmaf(c, grid.scale, gr[3]), mom[r][i], var[r][i]);
+                        }
+                    }
+                }
+            }
+            if constexpr (mode_local_adamw(MODE)) {
+                store(p.mom, mom);
+                store(p.var, var);
+            }
+            if constexpr (MODE == MODE_GRAD) {
+                store_words(code, p.gbits);
+                continue;
+            }
+        } else if constexpr (mode_is_recv(MODE)) {
+            load(p.x, w);
+            float mom[R][4], var[R][4];  // MODE_RECV_ADAMW only
+            if constexpr (MODE == MODE_RECV_ADAMW) {
+                load(p.mom, mom);
+                load(p.var, var);
+            }
+            // ghat = alpha * (((d_0 + d_1) + d_2) + ...), the words of two peers in flight at a time
+            float sum[R][4];
+            const uint32_t* words = p.peer_codes + word0 * (uint64_t)p.gbits;
+            for (int peer0 = 0; peer0 < p.npeers; peer0 += 2) {
+                const bool two = peer0 + 1 < p.npeers;
+                const uint64_t next = two ? peer0 + 1 : peer0;  // past the last peer: read that one again, in bounds
+                uint32_t words_a[R], words_b[R];
+                fetch_words(words + (uint64_t)peer0 * p.peer_codes_stride_words, p.gbits, words_a);
+                fetch_words(words + next * p.peer_codes_stride_words, p.gbits, words_b);
+                f4 meta = {0.0f, 0.0f, 0.0f, 0.0f};
+                if (tid < here) {
+                    const float* m = p.peer_meta + (uint64_t)peer0 * p.peer_meta_stride_floats + 2 * (bucket0 + (uint64_t)tid);
+                    const float* m2 = p.peer_meta + next * p.peer_meta_stride_floats + 2 * (bucket0 + (uint64_t)tid);
+                    meta = f4{m[0], m[1], m2[0], m2[1]};
+                }
+                team_sync<W>();  // the previous pair's meta has been read
+                if (tid < here) lds.grid[tid] = meta;
+                float c[R][4];
+                unpack(words_a, p.gbits, c);
+                team_sync<W>();
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const f4 m = lds.grid[bucket_of_slot(slot_of(r))];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const float d = fmaf(c[r][i], m[1], m[0]);
+                        sum[r][i] = peer0 == 0 ? d : sum[r][i] + d;
+                    }
+                }
+                if (two) {
+                    unpack(words_b, p.gbits, c);
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        const f4 m = lds.grid[bucket_of_slot(slot_of(r))];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) sum[r][i] = sum[r][i] + fmaf(c[r][i], m[3], m[2]);
+                    }
+                }
+            }
+            team_sync<W>();
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    w[r][i] = step_value<MODE>(p, w[r][i], p.alpha * sum[r][i], mom[r][i], var[r][i]);
+            if constexpr (MODE == MODE_RECV_ADAMW) {
+                store(p.mom, mom);
+                store(p.var, var);
+            }
+        } else {
+            load(p.xin, w);
+        }
+
+        // the full-precision partition keeps the updated value itself
+        if (kWritesX && keep_master) store(p.x, w);
+
+        uint32_t code[R][4];
+        if constexpr (kLevels) {
+            const int K = 1 << p.wbits;
+            const uint32_t tensor = p.levels_per_tensor != 0u ? first.tensor : 0u;
+            if (whole && tensor != loaded_tensor) {  // the tile lies in one tensor: its table comes into LDS
+                team_sync<W>();
+                for (int i = tid; i < K; i += TEAM) level_table[i] = p.levels[(uint64_t)tensor * K + i];
+                loaded_tensor = tensor;
+            }
+            bucket_grids(w, [&](float lo, float hi, int b) -> f4 {  // (its barriers publish the table too)
+                const MinMaxGrid g = make_minmax_grid(lo, hi, 1.0f, false);
+                write_meta(b, g.lo, g.scale);
+                return f4{g.lo, g.inv, 0.0f, 0.0f};
+            });
+#pragma unroll
+            for (int cp = 0; cp < R / 2; ++cp) {
+                uint32_t h[4] = {0u, 0u, 0u, 0u};
+                if constexpr (MODE == MODE_LEVELS_COIN) uniforms(cp, h);
+#pragma unroll
+                for (int half = 0; half < 2; ++half) {
+                    const int r = 2 * cp + half;
+                    const int b = bucket_of_slot(slot_of(r));
+                    const f4 gr = lds.grid[b];
+                    if (__builtin_expect(whole, 1)) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const float z = (w[r][i] - gr[0]) * gr[1];
+                            code[r][i] = MODE == MODE_LEVELS_COIN
+                                             ? stochastic_level_any(z, (float)uniform16(h, 4 * half + i), level_table, K)
+                                             : nearest_level_any(z, level_table, K);
+                        }
+                    } else {  // a tile over several tensors reads each one's table where it is
+                        const float* table = p.levels;
+                        if (p.levels_per_tensor != 0u) table += (uint64_t)(b < here ? lds.where[b][2] : 0u) * K;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const float z = (w[r][i] - gr[0]) * gr[1];
+                            code[r][i] = MODE == MODE_LEVELS_COIN
+                                             ? stochastic_level_any(z, (float)uniform16(h, 4 * half + i), table, K)
+                                             : nearest_level_any(z, table, K);
+                        }
+                    }
+                }
+            }
+            store_words(code, p.wbits);
+            continue;
+        }
+
+        const bool emit = MODE == MODE_WEIGHT || mode_codes_resident(MODE) || p.codes != nullptr;
+        bucket_grids(w, [&](float lo, float hi, int b) -> f4 {
+            float base, scale, origin, inv = 0.0f;
+            if (lattice) {
+                lo = lo + 0.0f;
+                origin = rintf(div_delta(lo, div) - xi);
+                base = (origin + xi) * p.delta;
+                scale = p.delta;
+            } else {
+                const MinMaxGrid g = make_minmax_grid(lo, hi, Lw, symmetric);
+                base = fmaf(xi, g.scale, g.lo);
+                scale = g.scale;
+                origin = g.lo;
+                inv = g.inv;
+            }
+            if (emit) write_meta(b, base, scale);
+            return f4{origin, inv, scale, base};
+        });
+        const bool want16 = (MODE == MODE_FUSED || MODE == MODE_ADAMW) && p.x16 != nullptr;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const f4 gr = lds.grid[bucket_of_slot(slot_of(r))];
+            const MinMaxGrid grid = {gr[0], gr[2], gr[1]};
+            if (lattice) {
+                const int n = __builtin_expect(whole, 1) ? (slot_of(r) < used ? 4 : 0) : place(slot_of(r)).count;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    uint32_t over = 0;
+                    const float c = weight_code_lattice(w[r][i], div, xi, gr[0], Lw, over);
+                    saturated += i < n ? over : 0u;
+                    code[r][i] = (uint32_t)c;
+                    w[r][i] = fmaf(c, gr[2], gr[3]);
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float c = weight_code_minmax(w[r][i], grid, Lw, xi);
+                    code[r][i] = (uint32_t)c;
+                    w[r][i] = fmaf(c, gr[2], gr[3]);
+                }
+            }
+        }
+        if (kWritesX && !keep_master) store(p.x, w);
+        if (want16) store_half(p.x16, p.x16_f16 != 0u, w);
+        if (emit) store_words(code, p.wbits);
+    }
+
+    if (MODE != MODE_GRAD && !kLevels && p.n_saturated != nullptr) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) saturated += __shfl_down(saturated, off, 64);
+        if ((threadIdx.x & 63) == 0 && saturated != 0) atomicAdd(p.n_saturated, (unsigned long long)saturated);
+    }
+}
+
+}  // namespace qsdp
