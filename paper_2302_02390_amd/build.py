@@ -30,6 +30,8 @@ WAVE_SHAPES = {128: (8, 4, 1), 256: (16, 4, 1), 512: (32, 4, 1), 1024: (64, 4, 1
                4096: (64, 4, 4)}
 # team shapes of the tile kernel, which serves every other bucket size: (waves, rows)
 TILE_SHAPES = [(1, 4), (1, 6), (1, 8), (4, 4), (4, 6), (4, 8)]
+# shapes of the level fit: (values per lane, waves per batch), for buckets of up to 64 * values * waves
+FIT_SHAPES = [(2, 1), (4, 1), (8, 1), (16, 1), (16, 2), (16, 4), (16, 8)]
 
 
 def _units():
@@ -42,6 +44,8 @@ def _units():
                   ["-DQSDP_G=64", "-DQSDP_R=2", "-DQSDP_W=2", "-DQSDP_B=1024", "-DQSDP_WEIGHT_ONLY=1024w2"]))
     for w, r in TILE_SHAPES:
         units.append((f"qsdp_tile_{w}_{r}.o", "qsdp_tile_inst.hip", [f"-DQSDP_TILE_W={w}", f"-DQSDP_TILE_R={r}"]))
+    for v, w in FIT_SHAPES:
+        units.append((f"qsdp_fit_{v}_{w}.o", "qsdp_fit_inst.hip", [f"-DQSDP_FIT_V={v}", f"-DQSDP_FIT_W={w}"]))
     return units
 
 

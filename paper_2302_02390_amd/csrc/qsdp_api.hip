@@ -97,19 +97,15 @@ hipError_t launch_dequant_seg(int bits, bool bf16, const DequantSegParams& q, un
     }
 }
 
-hipError_t launch_fit_levels(const FitParams& p, unsigned grid, hipStream_t s) {
-    switch (p.bits) {
-        case 1: hipLaunchKernelGGL(fit_levels_kernel<1>, dim3(grid), dim3(256), 0, s, p); break;
-        case 2: hipLaunchKernelGGL(fit_levels_kernel<2>, dim3(grid), dim3(256), 0, s, p); break;
-        case 3: hipLaunchKernelGGL(fit_levels_kernel<3>, dim3(grid), dim3(256), 0, s, p); break;
-        case 4: hipLaunchKernelGGL(fit_levels_kernel<4>, dim3(grid), dim3(256), 0, s, p); break;
-        case 5: hipLaunchKernelGGL(fit_levels_kernel<5>, dim3(grid), dim3(256), 0, s, p); break;
-        case 6: hipLaunchKernelGGL(fit_levels_kernel<6>, dim3(grid), dim3(256), 0, s, p); break;
-        case 7: hipLaunchKernelGGL(fit_levels_kernel<7>, dim3(grid), dim3(256), 0, s, p); break;
-        case 8: hipLaunchKernelGGL(fit_levels_kernel<8>, dim3(grid), dim3(256), 0, s, p); break;
-        default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+// The smallest shape that holds a bucket.
+static hipError_t launch_fit_levels(const FitParams& p, unsigned grid, hipStream_t s) {
+    if (p.bucket <= 128) return launch_fit_2_1(p, grid, s);
+    if (p.bucket <= 256) return launch_fit_4_1(p, grid, s);
+    if (p.bucket <= 512) return launch_fit_8_1(p, grid, s);
+    if (p.bucket <= 1024) return launch_fit_16_1(p, grid, s);
+    if (p.bucket <= 2048) return launch_fit_16_2(p, grid, s);
+    if (p.bucket <= 4096) return launch_fit_16_4(p, grid, s);
+    return launch_fit_16_8(p, grid, s);
 }
 
 hipError_t launch_dequant(int bits, bool bf16, const DequantParams& p, dim3 grid, hipStream_t s) {

@@ -5,31 +5,33 @@
 
 namespace qsdp {
 
-// Minimum and maximum over the 256 threads of a workgroup.
-__device__ __forceinline__ void block_minmax(float& lo, float& hi, float* red /* 8 floats */) {
-    lo = group_min<64>(lo);
-    hi = group_max<64>(hi);
-    const int wave = threadIdx.x >> 6;
-    __syncthreads();  // red may still be read from a previous use
-    if ((threadIdx.x & 63) == 0) {
-        red[wave] = lo;
-        red[4 + wave] = hi;
-    }
-    __syncthreads();
-    lo = fminf(fminf(red[0], red[1]), fminf(red[2], red[3]));
-    hi = fmaxf(fmaxf(red[4], red[5]), fmaxf(red[6], red[7]));
-}
-
 // ---------------------------------------------------------------------------------------
-// Level fitting (Algorithm 1 in batched form): ONE workgroup walks the buckets in order, since
-// every batch starts from the levels the previous one left. Per bucket: stage the values in
-// LDS, block min/max, assign every value to its nearest level (levels frozen), accumulate
-// exact 32.32 fixed-point sums and counts per level with LDS atomics (order independent, so the
-// result is reproducible), then level k takes its count_k steps of rate lr towards the mean
-// of its values at once, in binary64: q <- q - (1 - (1-lr)^c)(q - mean). The chain of batches is
-// kept short: the next batch's values are fetched while the current one is processed, the
-// powers (1-lr)^c come from an LDS table filled once by repeated multiplication (the order in
-// which single steps compound), and small level tables are accumulated per wave.
+// Level fitting: a workgroup walks the buckets of its tensor in order, since every batch starts from the levels the
+// previous one left. Per batch every value goes to its nearest level (levels frozen); level k then takes its count_k
+// steps of rate lr towards the mean of its values at once, in binary64: q <- q - (1 - (1-lr)^c)(q - mean), with the
+// mean of exact 32.32 fixed-point sums.
+//
+// The serial chain of batches bounds this, so the chain holds as little as possible. What a batch needs from the levels
+// is, for each pair of neighbours, how many values lie on the lower one's side and their sum; the normalised values
+// themselves do not depend on the levels. Producer waves therefore sort the coming batches into cells of the unit interval
+// (a counting sort: one LDS atomic per value returns the place within the cell and adds up count and sum, packed
+// into one word; a prefix sum over the cells follows), and one consumer wave walks the chain: a lane per pair of
+// neighbours reads the prefix at the cell of the midpoint, compares the few values of that cell with the two levels, and
+// has count and sum below the boundary; differences between lanes are the levels' own. No barrier and no atomic is left
+// in the chain; two LDS round trips for the boundary, one for the powers of 1 - lr and the reciprocals of the counts.
+// A team of W producer waves sorts a batch (the values stay in registers, at most 16 to a lane) and P teams make a round:
+// W = 1, P = 6 for buckets of up to 1024 values (one wave needs no barrier between its passes, and six of them sort as
+// fast as the consumer walks), W = 2, 4, 8 and P = 8 / W up to 2048, 4096, 8192 with a barrier after each of the four
+// passes. The consumer meanwhile walks the P batches of the round before; the slots are double-buffered.
+//
+// Measured (us per batch, 5-bit table, Gaussian values, buckets of 128 / 1024 / 4096 / 8192): 0.45 / 0.57 / 1.8 / 3.5,
+// against 1.27 / 2.6 / 10.7 / 21 for a workgroup that stages one batch in LDS and assigns value by value with a barrier
+// around each part; the 292 tables of the 350M model 2.85 -> 0.59 ms. The chain is latency: about 1,100 cycles of
+// dependent LDS reads and binary64 steps per batch up to 1024 values, the sorting beyond.
+//
+// The boundary search needs levels that ascend by more than 2^-20 within [0, 1] (then the comparison of the two
+// rounded distances is monotone in the value and flips within 2^-22 of the midpoint) and cells that are not
+// crowded. A batch for which that does not hold is assigned value by value, by the same wave.
 // ---------------------------------------------------------------------------------------
 struct FitParams {
     const float* v;
@@ -42,22 +44,333 @@ struct FitParams {
     float lr;
 };
 
+// Shape of a workgroup: W waves to a batch of up to 64 * W * VPT values.
+template <int BMAX, int C>
+struct FitSlot;
+
+template <int VPT, int W>
+struct FitShape {
+    static constexpr int kBucketMax = 64 * W * VPT;
+    static constexpr int kBatches = W == 1 ? 6 : 8 / W;          // P, batches per round
+    static constexpr int kProducers = kBatches * W;              // producer waves; the consumer is one more
+    static constexpr int kThreads = 64 * (kProducers + 1);
+    static constexpr int kBarriers = W == 1 ? 1 : 4;             // per round
+    // about a cell per value, as far as the 2 P slots leave LDS to spare
+    static constexpr int kCells = kBucketMax <= 512 ? kBucketMax : kBucketMax <= 2048 ? 512 : 1024;
+    using Slot = FitSlot<kBucketMax, kCells>;
+};
+
+// Count and sum of a set of normalised values in one word: sum of at most 2^13 values of at most 2^32 below, count above.
+constexpr int kFitCountShift = 46;
+constexpr uint64_t kFitSumMask = (1ull << kFitCountShift) - 1;
+
+// z (in [0, 1]) in 32.32 fixed point, truncated: exact scaling, the integer and the fraction converted apart.
+__device__ __forceinline__ uint64_t fit_fixed(float z) {
+    const uint32_t whole = (uint32_t)z;
+    return ((uint64_t)whole << 32) | (uint32_t)((z - (float)whole) * 4294967296.0f);
+}
+
+// The cell of a value (or of a boundary): C cells of equal width from `from` on, what lies outside them in the first and
+// the last. Monotone, and in range whatever the argument (the conversion saturates).
+struct FitCells {
+    float from, per_unit;
+};
+template <int C>
+__device__ __forceinline__ uint32_t fit_cell(float z, FitCells cells) {
+    const uint32_t c = (uint32_t)((z - cells.from) * cells.per_unit);
+    return c < (uint32_t)C ? c : (uint32_t)(C - 1);
+}
+
+// The cells for a batch: over its mean +- four times its mean magnitude, within its range [lo, hi]. That is the whole
+// range for Gaussian weights; for heavy-tailed gradients it keeps the cells where the values are (a range stretched
+// by one outlier would put most of a batch into a few cells).
+template <int C>
+__device__ __forceinline__ FitCells fit_cells(const MinMaxGrid& grid, float hi, float mean, float magnitude) {
+    const float from = fmaxf(grid.lo, mean - 4.0f * magnitude);
+    const float to = fminf(hi, mean + 4.0f * magnitude);
+    const float width = (to - from) * grid.inv;
+    const FitCells inner = {(from - grid.lo) * grid.inv, (float)C / width};
+    const FitCells all = {0.0f, (float)C};
+    return width > 0x1p-20f && width <= 2.0f ? inner : all;
+}
+
+// v of the next / previous lane of the wave (the last / first lane gets 0).
+__device__ __forceinline__ uint32_t next_lane(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x130, 0xF, 0xF, true);  // wave_shl:1
+}
+__device__ __forceinline__ uint32_t previous_lane(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x138, 0xF, 0xF, true);  // wave_shr:1
+}
+
+// Sum over the lanes of a wave, in all of them (any order: it only places the cells).
+__device__ __forceinline__ float fit_wave_sum(float v) {
+    v += dpp_move<0xB1>(v);
+    v += dpp_move<0x4E>(v);
+    v += dpp_move<0x141>(v);
+    v += dpp_move<0x140>(v);
+    float a, b;
+    swap16(v, a, b);
+    v = a + b;
+    swap32(v, a, b);
+    return a + b;
+}
+
+// Inclusive prefix sum over the lanes of a wave.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint64_t fit_scan_step(uint64_t v) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, ROWS, 0xF, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), CTRL, ROWS, 0xF, false);
+    return v + (((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ uint64_t fit_wave_scan(uint64_t v) {
+    v = fit_scan_step<0x111, 0xF>(v);  // row_shr:1, 2, 4, 8: within rows of 16 lanes
+    v = fit_scan_step<0x112, 0xF>(v);
+    v = fit_scan_step<0x114, 0xF>(v);
+    v = fit_scan_step<0x118, 0xF>(v);
+    v = fit_scan_step<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
+    v = fit_scan_step<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
+// Sum over the lanes l, l + 64/S, l + 2 * 64/S, ... (S = 1, 2, 4).
+template <int S>
+__device__ __forceinline__ uint64_t fit_sum_subs(uint64_t v) {
+    if constexpr (S >= 2) {
+        const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)v, false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(v >> 32), (uint32_t)(v >> 32), false, false);
+        v = (((uint64_t)hi[0] << 32) | lo[0]) + (((uint64_t)hi[1] << 32) | lo[1]);
+    }
+    if constexpr (S >= 4) {
+        const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)v, (uint32_t)v, false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(v >> 32), (uint32_t)(v >> 32), false, false);
+        v = (((uint64_t)hi[0] << 32) | lo[0]) + (((uint64_t)hi[1] << 32) | lo[1]);
+    }
+    return v;
+}
+
+// Adds to a word in LDS and returns what it held. Relaxed: the callers put their own fences, and an ordered atomic would
+// wait for each one before the next.
+__device__ __forceinline__ uint64_t fit_add(uint64_t* word, uint64_t v) {
+    return __hip_atomic_fetch_add(word, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// LDS traffic of one wave is processed in order; this keeps the compiler from reordering it.
+__device__ __forceinline__ void fit_wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// (1 - lr)^c by repeated multiplication, the order in which c single steps compound, for c up to the bucket size: every
+// power up to kFine with the reciprocal of the count, beyond that every kStep-th.
+struct FitPowers {
+    static constexpr int kFine = 1024, kStep = 16, kCoarse = (kMaxBucket - kFine) / kStep + 1;
+    struct Entry {
+        double moved, reciprocal;  // 1 - (1-lr)^c, 1 / c
+    };
+    Entry fine[kFine + 1];
+    double coarse[kCoarse];
+
+    __device__ void fill(int top, double one_minus, int lane) {  // one wave
+        double keep = 1.0, mine = 1.0;
+        const int fine_top = top < kFine ? top : kFine;
+        for (int c0 = 0; c0 <= fine_top; c0 += 64) {
+            for (int i = 0; i < 64; ++i) {
+                mine = lane == i ? keep : mine;
+                if (c0 + i < fine_top) keep *= one_minus;  // ends as the power fine_top
+            }
+            const int c = c0 + lane;
+            if (c <= fine_top) {
+                const Entry e = {1.0 - mine, 1.0 / (double)(c > 0 ? c : 1)};
+                fine[c] = e;
+            }
+        }
+        for (int k = 0; kFine + k * kStep <= top; ++k) {
+            if (lane == 0) coarse[k] = keep;
+            for (int i = 0; i < kStep; ++i) keep *= one_minus;
+        }
+    }
+
+    // Where the level q lands after the c values of fixed-point sum `total` that are its own (c = 0: it stays); c at
+    // most kFine.
+    static __device__ __forceinline__ float step(float level, uint32_t c, uint64_t total, Entry e) {
+        // total / c rounded once: t * (1/c) is off by at most 2 ulp, the remainder is exact (c is below 2^11, so it has
+        // at most 12 bits more than an ulp), and the corrected quotient is within 2^-50 ulp of t / c, which, t and c
+        // being integers below 2^46 and 2^11, is never closer than 2^-12 ulp to a rounding boundary without being
+        // a binary64 number itself
+        const double q = (double)level, t = (double)total;
+        const double a = t * e.reciprocal;
+        const double mean = fma(fma(-a, (double)c, t), e.reciprocal, a) * (1.0 / 4294967296.0);
+        return (float)(q - e.moved * (q - mean));
+    }
+
+    // The same for any c.
+    __device__ float step_any(float level, uint32_t c, uint64_t total, double one_minus) const {
+        if (c <= (uint32_t)kFine) return step(level, c, total, fine[c]);
+        const int k = ((int)c - kFine) / kStep;
+        double keep = coarse[k];
+        for (int i = kFine + k * kStep; i < (int)c; ++i) keep *= one_minus;
+        const double q = (double)level;
+        const double mean = ((double)total / (double)c) * (1.0 / 4294967296.0);
+        return (float)(q - (1.0 - keep) * (q - mean));
+    }
+};
+
+// A batch as the consumer reads it: the values grouped by cell (ascending cells, any order within one), and for every cell
+// count and sum of the values in the cells before it; cell C: of all values.
+// The prefix sum gives a lane kOwn cells in a row; one word of padding after each of these runs keeps the lanes off one
+// another's banks (without it all 64 lanes meet in two banks: 0.15 us more per batch of 1024).
+template <int BMAX, int C>
+struct FitSlot {
+    static constexpr int kOwn = C / 64;
+    static __device__ __forceinline__ uint32_t at(uint32_t c) { return c + (kOwn > 1 ? c / kOwn : 0u); }
+    uint64_t cell[C + 64 + 1];  // cell c at at(c)
+    float z[BMAX + 1];          // one to spare, where lanes without a value write
+    FitCells cells;
+};
+
+// Level k of the table for lane l: k = 64 * i + (l mod (64 / S)), i < M. S lanes share a level's work.
 template <int BITS>
-__global__ void __launch_bounds__(256) fit_levels_kernel(const FitParams p) {
-    constexpr int K = 1 << BITS;
-    constexpr int kCopies = K <= 16 ? 4 : 1;  // small tables: one accumulator set per wave (fewer atomic collisions)
-    constexpr int kKeepMax = 2048;            // (1 - lr)^c is tabulated up to this count
-    constexpr int kPre = 8;                   // values per thread fetched one batch ahead (buckets up to 2048)
-    __shared__ float val[kMaxBucket];
-    __shared__ float lv[K];
-    __shared__ long long sum[kCopies][K];
-    __shared__ unsigned int count[kCopies][K];
-    __shared__ double keep_tab[kKeepMax + 1];
-    __shared__ float red[8];
-    const int tid = threadIdx.x;
-    const int copy = kCopies == 1 ? 0 : (tid >> 6);
+struct FitLanes {
+    static constexpr int K = 1 << BITS;
+    static constexpr int S = K <= 16 ? 4 : K <= 32 ? 2 : 1;
+    static constexpr int M = K <= 64 ? 1 : K / 64;
+};
+
+// One batch of the chain. lv[i]: the lane's levels, updated. lv_shared, acc: K entries of LDS each, for batches that are
+// assigned value by value.
+template <int BITS, typename Slot, int C>
+__device__ __forceinline__ void fit_batch(const Slot& slot, int m, const FitPowers& powers, double one_minus,
+                                          FitCells cells, float (&lv)[FitLanes<BITS>::M], float* lv_shared,
+                                          uint64_t* acc, int lane) {
+    constexpr int K = FitLanes<BITS>::K, S = FitLanes<BITS>::S, M = FitLanes<BITS>::M;
+    constexpr int U = M == 4 ? 2 : 4;  // values a lane reads at once
+    // values in a boundary's cells from which the plain assignment of the batch is faster
+    const uint32_t crowded = (uint32_t)(m * S * U / (48 * M)) + 64u;
+    const int sub = S > 1 ? lane / (64 / S) : 0;
+    const int k0 = S > 1 ? lane % (64 / S) : lane;
+    uint64_t upto[M];  // count and sum of the values of levels 0 .. k
+    float hi[M];
+    uint32_t pos[M], end[M];
+    bool plain = false;
+#pragma unroll
+    for (int i = 0; i < M; ++i) {
+        const int k = 64 * i + k0;
+        hi[i] = __uint_as_float(next_lane(__float_as_uint(lv[i])));
+        if (i + 1 < M) {
+            const float following = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lv[i + 1 < M ? i + 1 : 0]), 0));
+            hi[i] = lane == 63 ? following : hi[i];
+        }
+        const bool inner = k < K - 1;
+        const bool ok = inner ? hi[i] - lv[i] > 0x1p-20f && lv[i] >= 0.0f && hi[i] <= 1.0f : true;
+        const float mid = 0.5f * (lv[i] + hi[i]);
+        // past the last boundary: everything, no value left to compare
+        const uint32_t first = inner ? fit_cell<C>(mid - 0x1p-21f, cells) : (uint32_t)C;
+        const uint32_t last = inner ? fit_cell<C>(mid + 0x1p-21f, cells) + 1u : (uint32_t)C;
+        upto[i] = slot.cell[Slot::at(first)];
+        end[i] = (uint32_t)(slot.cell[Slot::at(last)] >> kFitCountShift);
+        pos[i] = (uint32_t)(upto[i] >> kFitCountShift);
+        plain = plain || !ok || end[i] - pos[i] > crowded;
+    }
+    uint64_t own[M];
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(plain) == 0, 1)) {
+#pragma unroll
+        for (int i = 0; i < M; ++i) {
+            uint64_t below = 0;
+            uint32_t p = pos[i] + sub;
+            do {
+                float z[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const uint32_t at = p + u * S;
+                    z[u] = slot.z[at < end[i] ? at : 0u];
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    // on the lower level's side: below 1 (the upper level is at most 1 and closer), so 32 bits hold it
+                    const bool lower = p + u * S < end[i] && !(fabsf(z[u] - hi[i]) < fabsf(z[u] - lv[i]));
+                    const uint32_t fixed = (uint32_t)(z[u] * 4294967296.0f);
+                    below += ((uint64_t)(lower ? 1u << (kFitCountShift - 32) : 0u) << 32) | (lower ? fixed : 0u);
+                }
+                p += S * U;
+            } while (__builtin_amdgcn_ballot_w64(p < end[i]) != 0);
+            upto[i] += fit_sum_subs<S>(below);
+        }
+#pragma unroll
+        for (int i = 0; i < M; ++i) {
+            uint32_t lo_prev = previous_lane((uint32_t)upto[i]), hi_prev = previous_lane((uint32_t)(upto[i] >> 32));
+            if (i > 0) {
+                const uint64_t preceding = upto[i > 0 ? i - 1 : 0];
+                const uint32_t lo_63 = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)preceding, 63);
+                const uint32_t hi_63 = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(preceding >> 32), 63);
+                lo_prev = lane == 0 ? lo_63 : lo_prev;
+                hi_prev = lane == 0 ? hi_63 : hi_prev;
+            }
+            const uint64_t prev = 64 * i + k0 == 0 ? 0ull : ((uint64_t)hi_prev << 32) | lo_prev;
+            own[i] = upto[i] - prev;
+        }
+    } else {
+        // value by value against the table in LDS
+        fit_wave_sync();
+#pragma unroll
+        for (int i = 0; i < M; ++i) {
+            const int k = 64 * i + k0;
+            if (sub == 0 && k < K) {
+                lv_shared[k] = lv[i];
+                acc[k] = 0;
+            }
+        }
+        fit_wave_sync();
+        for (int p = lane; p < m; p += 64 * 4) {  // four values a lane at once: the searches' LDS reads overlap
+            float z[4];
+            int k[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) z[u] = slot.z[p + 64 * u < m ? p + 64 * u : p];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) k[u] = nearest_level<BITS>(z[u], lv_shared);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (p + 64 * u < m) fit_add(&acc[k[u]], (1ull << kFitCountShift) | fit_fixed(z[u]));
+        }
+        fit_wave_sync();
+#pragma unroll
+        for (int i = 0; i < M; ++i) {
+            const int k = 64 * i + k0;
+            own[i] = k < K ? acc[k] : 0;
+        }
+        fit_wave_sync();
+    }
+    bool many = false;
+#pragma unroll
+    for (int i = 0; i < M; ++i) many = many || (uint32_t)(own[i] >> kFitCountShift) > (uint32_t)FitPowers::kFine;
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(many) == 0, 1)) {
+        FitPowers::Entry e[M];
+#pragma unroll
+        for (int i = 0; i < M; ++i) e[i] = powers.fine[own[i] >> kFitCountShift];
+#pragma unroll
+        for (int i = 0; i < M; ++i)
+            lv[i] = FitPowers::step(lv[i], (uint32_t)(own[i] >> kFitCountShift), own[i] & kFitSumMask, e[i]);
+    } else {
+#pragma unroll
+        for (int i = 0; i < M; ++i)
+            lv[i] = powers.step_any(lv[i], (uint32_t)(own[i] >> kFitCountShift), own[i] & kFitSumMask, one_minus);
+    }
+}
+
+template <int BITS, int VPT, int W>
+__global__ void __launch_bounds__((FitShape<VPT, W>::kThreads)) fit_levels_kernel(const FitParams p) {
+    using Shape = FitShape<VPT, W>;
+    using Slot = typename Shape::Slot;
+    constexpr int C = Shape::kCells, P = Shape::kBatches, K = 1 << BITS;
+    constexpr int M = FitLanes<BITS>::M, S = FitLanes<BITS>::S;
+    __shared__ Slot slots[2 * P];
+    __shared__ FitPowers powers;
+    __shared__ float lv_shared[K];
+    __shared__ uint64_t acc[K];
+    __shared__ float red[P][4][W];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int B = p.bucket;
-    const bool prefetch = B <= 256 * kPre;
     // this workgroup's tensor: the whole vector, or tensor blockIdx.x of a multi-tensor fit
     const float* v = p.v;
     float* levels = p.levels;
@@ -70,86 +383,144 @@ __global__ void __launch_bounds__(256) fit_levels_kernel(const FitParams p) {
         num_batches = (n + (uint64_t)B - 1) / (uint64_t)B;
         if (p.num_batches > 0 && p.num_batches < num_batches) num_batches = p.num_batches;
     }
-    for (int k = tid; k < K; k += 256) lv[k] = levels[k];
-    const double one_minus = 1.0 - (double)p.lr;
-    if (tid == 0) {
-        // (1 - lr)^c by repeated multiplication, the order in which c single steps compound
-        double keep = 1.0;
-        keep_tab[0] = 1.0;
-        const int top = B < kKeepMax ? B : kKeepMax;
-        for (int c = 1; c <= top; ++c) {
-            keep *= one_minus;
-            keep_tab[c] = keep;
-        }
-    }
-    float nxt[kPre];
-    auto fetch = [&](uint64_t j) {
-        const uint64_t e0 = j * (uint64_t)B;
-        const int m = (int)((n - e0 < (uint64_t)B) ? (n - e0) : (uint64_t)B);
-#pragma unroll
-        for (int q = 0; q < kPre; ++q) {
-            const int i = tid + 256 * q;
-            nxt[q] = i < m ? v[e0 + i] : 0.0f;
-        }
+    if (num_batches == 0) return;
+    auto batch_size = [&](uint64_t j) -> int {  // j < num_batches
+        const uint64_t left = n - j * (uint64_t)B;
+        return left < (uint64_t)B ? (int)left : B;
     };
-    if (prefetch && num_batches > 0) fetch(0);
-    for (uint64_t j = 0; j < num_batches; ++j) {
-        const uint64_t e0 = j * (uint64_t)B;
-        const int m = (int)((n - e0 < (uint64_t)B) ? (n - e0) : (uint64_t)B);
-        __syncthreads();  // previous batch's level update and LDS reads are complete (and keep_tab is written)
-        float lo = __builtin_inff(), hi = -__builtin_inff();
-        if (prefetch) {
+    const uint64_t rounds = (num_batches + P - 1) / P;  // of the consumer; the producers are one ahead
+    const double one_minus = 1.0 - (double)p.lr;
+
+    if (wave == Shape::kProducers) {
+        // the consumer: round r walks the batches that were sorted in round r - 1
+        __builtin_amdgcn_s_setprio(3);
+        float lv[M];
 #pragma unroll
-            for (int q = 0; q < kPre; ++q) {
-                const int i = tid + 256 * q;
-                if (i < m) {
-                    val[i] = nxt[q];
-                    lo = fminf(lo, nxt[q]);
-                    hi = fmaxf(hi, nxt[q]);
+        for (int i = 0; i < M; ++i) {
+            const int k = 64 * i + (S > 1 ? lane % (64 / S) : lane);
+            lv[i] = k < K ? levels[k] : 0.0f;
+        }
+        powers.fill(B, one_minus, lane);
+        for (int i = 0; i < Shape::kBarriers; ++i) __syncthreads();  // the producers' first round
+        for (uint64_t r = 0; r < rounds; ++r) {
+            const int buffer = (int)(r & 1u) * P;
+            FitCells cells[P];
+#pragma unroll
+            for (int i = 0; i < P; ++i) cells[i] = slots[buffer + i].cells;
+#pragma unroll
+            for (int i = 0; i < P; ++i) {
+                if (r * P + i < num_batches)
+                    fit_batch<BITS, Slot, C>(slots[buffer + i], batch_size(r * P + i), powers, one_minus, cells[i], lv,
+                                             lv_shared, acc, lane);
+                for (int b = 0; b < (W == 1 ? (i == P - 1 ? 1 : 0) : Shape::kBarriers / P); ++b) __syncthreads();
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < M; ++i) {
+            const int k = 64 * i + (S > 1 ? lane % (64 / S) : lane);
+            if ((S == 1 || lane < 64 / S) && k < K) levels[k] = lv[i];
+        }
+    } else {
+        // between the passes of a team
+        auto team_sync = [] {
+            if constexpr (W > 1) __syncthreads(); else fit_wave_sync();
+        };
+        // a producer: batch r * P + team in round r, this wave's 1/W of it; past the last batch the last one again (nobody
+        // reads it). Lanes past the end of a batch carry its last value: it changes no minimum or maximum, it counts
+        // nothing and lands in the spare place.
+        const int team = wave / W, part = wave % W;
+        const int scanner = W == 2 ? team / 2 : W == 4 ? team : 0;  // of the team's waves: on another SIMD for every team
+        const int first = part * 64 + lane;  // value q of the lane: first + q * 64 * W
+        float next[VPT];
+        auto batch = [&](uint64_t r) -> uint64_t {
+            const uint64_t j = r * P + team;
+            return j < num_batches ? j : num_batches - 1;
+        };
+        auto fetch = [&](uint64_t j) {
+            const int m = batch_size(j);
+            const float* src = v + j * (uint64_t)B;
+#pragma unroll
+            for (int q = 0; q < VPT; ++q) {
+                const int i = first + q * 64 * W;
+                next[q] = src[i < m ? i : m - 1];
+            }
+        };
+        fetch(batch(0));
+        for (uint64_t r = 0; r <= rounds; ++r) {
+            const int m = batch_size(batch(r));
+            Slot& slot = slots[(int)(r & 1u) * P + team];
+            float z[VPT];
+            float lo = next[0], hi = next[0], sum = 0.0f, absolute = 0.0f;
+#pragma unroll
+            for (int q = 0; q < VPT; ++q) {
+                z[q] = next[q];
+                lo = fminf(lo, z[q]);
+                hi = fmaxf(hi, z[q]);
+                sum += z[q];
+                absolute += fabsf(z[q]);
+            }
+            fetch(batch(r + 1));  // in flight while this batch is sorted
+            for (int c = first; c < C + 64; c += 64 * W) slot.cell[c] = 0;  // all but the last, written below
+            lo = group_min<64>(lo);
+            hi = group_max<64>(hi);
+            sum = fit_wave_sum(sum);
+            absolute = fit_wave_sum(absolute);
+            if constexpr (W > 1) {
+                if (lane == 0) {
+                    red[team][0][part] = lo;
+                    red[team][1][part] = hi;
+                    red[team][2][part] = sum;
+                    red[team][3][part] = absolute;
                 }
-            }
-            if (j + 1 < num_batches) fetch(j + 1);  // in flight while this batch is processed
-        } else {
-            for (int i = tid; i < m; i += 256) {
-                const float x = v[e0 + i];
-                val[i] = x;
-                lo = fminf(lo, x);
-                hi = fmaxf(hi, x);
-            }
-        }
-        for (int k = tid; k < kCopies * K; k += 256) {
-            (&sum[0][0])[k] = 0;
-            (&count[0][0])[k] = 0u;
-        }
-        block_minmax(lo, hi, red);  // contains the barriers that publish sum/count = 0 too
-        const MinMaxGrid grid = make_minmax_grid(lo, hi, 1.0f, false);
-        for (int i = tid; i < m; i += 256) {
-            const float z = (val[i] - grid.lo) * grid.inv;
-            const int k = nearest_level<BITS>(z, lv);
-            atomicAdd(reinterpret_cast<unsigned long long*>(&sum[copy][k]),
-                      (unsigned long long)(long long)(z * 4294967296.0f));
-            atomicAdd(&count[copy][k], 1u);
-        }
-        __syncthreads();
-        for (int k = tid; k < K; k += 256) {
-            unsigned int c = 0;
-            long long total = 0;  // exact integer sums: any order of accumulation gives the same value
+                __syncthreads();
+                sum = absolute = 0.0f;
 #pragma unroll
-            for (int w = 0; w < kCopies; ++w) {
-                c += count[w][k];
-                total += sum[w][k];
+                for (int w = 0; w < W; ++w) {
+                    lo = fminf(lo, red[team][0][w]);
+                    hi = fmaxf(hi, red[team][1][w]);
+                    sum += red[team][2][w];
+                    absolute += red[team][3][w];
+                }
+            } else {
+                fit_wave_sync();
             }
-            if (c != 0u) {
-                double keep = keep_tab[c < (unsigned)kKeepMax ? c : (unsigned)kKeepMax];
-                for (unsigned int t = kKeepMax; t < c; ++t) keep *= one_minus;
-                const double mean = ((double)total / (double)c) * (1.0 / 4294967296.0);
-                const double q = (double)lv[k];
-                lv[k] = (float)(q - (1.0 - keep) * (q - mean));
+            const MinMaxGrid grid = make_minmax_grid(lo, hi, 1.0f, false);
+            const FitCells cells = fit_cells<C>(grid, hi, sum * (1.0f / (64 * W * VPT)), absolute * (1.0f / (64 * W * VPT)));
+            uint32_t cell[VPT];
+            uint64_t held[VPT];  // the cell's word before this value came (both halves used: half of one dropped costs a wait)
+#pragma unroll
+            for (int q = 0; q < VPT; ++q) {
+                z[q] = (z[q] - grid.lo) * grid.inv;
+                cell[q] = Slot::at(fit_cell<C>(z[q], cells));
+                const uint64_t one = (1ull << kFitCountShift) | fit_fixed(z[q]);
+                const uint64_t there = first + q * 64 * W < m ? ~0ull : 0ull;
+                held[q] = fit_add(&slot.cell[cell[q]], one & there);
             }
+            team_sync();
+            if (part == scanner) {
+                constexpr int kOwn = Slot::kOwn;
+                uint64_t* own = &slot.cell[Slot::at(lane * kOwn)];
+                uint64_t before[kOwn], total = 0;
+#pragma unroll
+                for (int c = 0; c < kOwn; ++c) {
+                    before[c] = total;
+                    total += own[c];
+                }
+                const uint64_t incl = fit_wave_scan(total);
+#pragma unroll
+                for (int c = 0; c < kOwn; ++c) own[c] = before[c] + (incl - total);
+                if (lane == 63) slot.cell[Slot::at(C)] = incl;
+                if (lane == 0) slot.cells = cells;
+            }
+            team_sync();
+#pragma unroll
+            for (int q = 0; q < VPT; ++q) {
+                const uint32_t to = (uint32_t)((slot.cell[cell[q]] + held[q]) >> kFitCountShift);
+                slot.z[first + q * 64 * W < m ? to : (uint32_t)Shape::kBucketMax] = z[q];
+            }
+            __syncthreads();
         }
     }
-    __syncthreads();
-    for (int k = tid; k < K; k += 256) levels[k] = lv[k];
 }
 
 }  // namespace qsdp

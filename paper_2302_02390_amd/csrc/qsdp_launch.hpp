@@ -1,6 +1,6 @@
 // Host-side launch interface between the C ABI (qsdp_api.hip) and the kernel translation
 // units. Wave kernels are instantiated per bucket shape in qsdp_wave_inst.hip, compiled
-// once per (G, P) pair, tile kernels per team shape in qsdp_tile_inst.hip.
+// once per (G, P) pair, tile kernels per team shape in qsdp_tile_inst.hip, the level fit per shape in qsdp_fit_inst.hip.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -32,8 +32,18 @@ QSDP_DECLARE_TILE(4, 6)
 QSDP_DECLARE_TILE(4, 8)
 #undef QSDP_DECLARE_TILE
 
+// One launcher per shape (values per lane, waves per batch) of the level fit.
+#define QSDP_DECLARE_FIT(V, W) hipError_t launch_fit_##V##_##W(const FitParams& p, unsigned grid, hipStream_t s);
+QSDP_DECLARE_FIT(2, 1)
+QSDP_DECLARE_FIT(4, 1)
+QSDP_DECLARE_FIT(8, 1)
+QSDP_DECLARE_FIT(16, 1)
+QSDP_DECLARE_FIT(16, 2)
+QSDP_DECLARE_FIT(16, 4)
+QSDP_DECLARE_FIT(16, 8)
+#undef QSDP_DECLARE_FIT
+
 hipError_t launch_dequant(int bits, bool bf16, const DequantParams& p, dim3 grid, hipStream_t s);
-hipError_t launch_fit_levels(const FitParams& p, unsigned grid, hipStream_t s);
 hipError_t launch_dequant_add(int bits, const DequantAddParams& p, unsigned grid, hipStream_t s);
 
 }  // namespace qsdp

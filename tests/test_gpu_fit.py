@@ -1,0 +1,61 @@
+"""The level fit against the oracle, bit for bit, where its kernel can go wrong: the smallest and largest bucket of each
+launch shape, every table width, rounds that are not full, a short last batch, one batch only; batches that leave the
+boundary search (levels that coincide, values crowded into few cells by an outlier, constant buckets) and counts past the
+table of powers."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ref
+from paper_2302_02390_amd import binding as qb
+from gpu_util import DEV, np_f32, synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _same(v, bits, B, lr, levels, cap=0):
+    lv = torch.from_numpy(levels.copy()).to(DEV)
+    qb.qsdp_fit_levels(torch.from_numpy(v).to(DEV), bits, B, lr, lv, cap)
+    want = ref.fit_levels(v, bits, B, lr, levels.copy(), max_batches=cap)
+    return np.array_equal(np_f32(lv).view(np.uint32), want.view(np.uint32))
+
+
+@pytest.mark.parametrize("B", [32, 96, 128, 160, 256, 288, 512, 544, 1024, 1056, 2048, 2080, 4096, 4128, 8192])
+@pytest.mark.parametrize("batches,cut", [(1, 0), (1, 31), (6, 0), (7, 3), (26, 17)])
+def test_shapes(B, batches, cut):
+    x, g = synth(batches * B - cut, B + batches)
+    for bits in range(1, 9):
+        for v in (x, g):
+            assert _same(v, bits, B, 0.01, ref.levels_uniform(bits)), (bits, B)
+
+
+@pytest.mark.parametrize("B", [64, 1024, 2048, 8192])
+@pytest.mark.parametrize("bits", [1, 2, 4, 5, 6, 7, 8])
+def test_batches_without_a_boundary_search(B, bits):
+    rng = np.random.default_rng(B + bits)
+    n, K = 9 * B - 5, 1 << bits
+    x, _ = synth(n, B)
+    outlier = (1.0 + 1e-4 * rng.standard_normal(n)).astype(np.float32)  # crowded: all but one value per bucket
+    outlier[::B] = 1e3
+    constant = np.repeat(rng.standard_normal(9).astype(np.float32), B)[:n]
+    two = np.where(rng.random(n) < 0.97, 0.25, -4.0).astype(np.float32)  # two values: most of a bucket on one level
+    equal = ref.levels_uniform(bits)
+    equal[-2] = 1.0
+    close = np.float32(0.5) + np.arange(K, dtype=np.float32) * np.float32(2.0 ** -22)  # gaps below the search's bound
+    for v in (x, outlier, constant, two):
+        for levels in (ref.levels_uniform(bits), equal, close):
+            assert _same(v, bits, B, 0.02, levels), (B, bits)
+
+
+def test_offset_data_and_tensors_that_start_anywhere():
+    B, bits, sizes = 1024, 5, [8, 40 * 1024 + 8, 1024, 24, 13 * 1024 + 40]
+    x, g = synth(sum(sizes), 5)
+    for v in (x, (g + 3.0).astype(np.float32)):
+        segs = qb.Segments(sizes, B, DEV)
+        levels = qb.levels_uniform(bits, DEV).repeat(len(sizes), 1).contiguous()
+        qb.qsdp_fit_levels_segmented(torch.from_numpy(v).to(DEV), segs, bits, 0.01, levels, 30)
+        o = 0
+        for t, s in enumerate(sizes):
+            want = ref.fit_levels(v[o:o + s].copy(), bits, B, 0.01, ref.levels_uniform(bits), max_batches=30)
+            assert np.array_equal(np_f32(levels[t]).view(np.uint32), want.view(np.uint32)), t
+            o += s
