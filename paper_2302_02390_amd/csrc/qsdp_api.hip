@@ -11,8 +11,8 @@
 namespace qsdp {
 
 // Which bucket-index scheme the decoder kernels use for this call (tile = elements per wave).
-static int bucket_indexing(const DequantParams& p, bool bf16) {
-    const uint32_t tile32 = (uint32_t)kDequantRows * 64u * (bf16 ? 8u : 4u) / 32u;
+static int bucket_indexing(const DequantParams& p, bool bf16, int rows = kDequantRows) {
+    const uint32_t tile32 = (uint32_t)rows * 64u * (bf16 ? 8u : 4u) / 32u;
     if (p.bucket32 % tile32 == 0) return BK_TILE_UNIFORM;
     return p.bucket32_shift >= 0 ? BK_SHIFT : BK_DIVIDE;
 }
@@ -73,7 +73,7 @@ void dequant_seg_launch(int bk, const DequantSegParams& q, unsigned grid, hipStr
 
 template <int BITS>
 hipError_t dequant_seg_go(bool bf16, const DequantSegParams& q, unsigned grid, hipStream_t s) {
-    const int bk = bucket_indexing(q.d, bf16);
+    const int bk = bucket_indexing(q.d, bf16, seg_rows(bf16));
     const bool lut = q.d.levels != nullptr;  // one table per tensor
     if (bf16 && lut) dequant_seg_launch<BITS, true, true>(bk, q, grid, s);
     else if (bf16) dequant_seg_launch<BITS, true, false>(bk, q, grid, s);
@@ -862,6 +862,10 @@ static int dequantize_segmented_common(const float* levels, const uint32_t* code
     q.d.levels = levels;
     q.segs = reinterpret_cast<const Segment*>(table);
     q.nseg = nseg;
+    const bool half = out_dtype != QSDP_F32;
+    q.d.ntiles = ceil_div(q.d.n, (uint64_t)seg_rows(half) * 64u * (half ? 8u : 4u));
+    q.run = seg_run(half, levels != nullptr, q.d.ntiles);
+    grid = capped_grid(ceil_div(q.d.ntiles, 4u * (uint64_t)q.run));
     if (launch_dequant_seg(bits, out_dtype != QSDP_F32, q, grid, static_cast<hipStream_t>(stream)) != hipSuccess)
         return QSDP_ELAUNCH;
     return QSDP_OK;

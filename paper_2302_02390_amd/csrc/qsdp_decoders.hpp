@@ -76,6 +76,21 @@ __device__ __forceinline__ uint64_t bucket_of(uint64_t e, const DequantParams& p
     return e32 / p.bucket32;
 }
 
+// A lane's decoded elements of a row as one 16-byte store.
+template <bool BF16>
+__device__ __forceinline__ void store_decoded(const DequantParams& p, uint64_t e, const float (&o)[BF16 ? 8 : 4]) {
+    if constexpr (BF16) {
+        const bool f16 = p.out_f16 != 0;
+        u4 w;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w[i] = half_bits(o[2 * i], f16) | (half_bits(o[2 * i + 1], f16) << 16);
+        __builtin_nontemporal_store(w, reinterpret_cast<u4*>(static_cast<uint16_t*>(p.out) + e));
+    } else {
+        const f4 a = {o[0], o[1], o[2], o[3]};
+        __builtin_nontemporal_store(a, reinterpret_cast<f4*>(static_cast<float*>(p.out) + e));
+    }
+}
+
 // `lut` = the level table in LDS (learned levels: the code indexes it), or nullptr (uniform
 // levels: the code is the level). BF16 selects the 2-byte output path (8 elements per 16-byte
 // store): bf16, or binary16 when p.out_f16 is set (a wave-uniform choice of the conversion).
@@ -91,15 +106,7 @@ __device__ __forceinline__ void decode_store(const DequantParams& p, uint64_t e,
     }
     const bool f16 = BF16 && p.out_f16 != 0;
     if (whole) {
-        if (BF16) {
-            u4 w;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) w[i] = half_bits(o[2 * i], f16) | (half_bits(o[2 * i + 1], f16) << 16);
-            __builtin_nontemporal_store(w, reinterpret_cast<u4*>(static_cast<uint16_t*>(p.out) + e));
-        } else {
-            const f4 a = {o[0], o[1], o[2], o[3]};
-            __builtin_nontemporal_store(a, reinterpret_cast<f4*>(static_cast<float*>(p.out) + e));
-        }
+        store_decoded<BF16>(p, e, o);
     } else {
         for (int i = 0; i < E; ++i) {
             if (e + i < limit) {
@@ -175,19 +182,35 @@ __global__ void __launch_bounds__(256) dequant_kernel(const DequantParams p) {
 // Decoder for a multi-tensor code buffer: slot s of the padded code stream (bucket s / B of the
 // whole buffer) belongs to the tensor whose bucket range holds that bucket and lands at element
 // seg.offset + (s - seg.first_bucket * B) of the flat output, if the tensor has that element.
-// Same tiling as dequant_kernel over SLOTS (p.n = number of slots). The tensor of a tile's
-// first slot is found by a wave-uniform search (scalar loads, see find_segment). A tile that
-// lies inside that tensor's elements (the common case) is decoded without per-lane control
-// flow; a tile that reaches a tensor's padding or the next tensor goes lane by lane, each lane
-// walking on from the tile's tensor to its own. LUT: learned levels, one table of 2^BITS floats
-// per tensor at d.levels (tensor t's at d.levels + t * 2^BITS); a wave keeps the table of its
-// tile's tensor in an LDS slot of its own and reads the tables through global memory on the
-// lane-by-lane path.
+// Same tiling as dequant_kernel over SLOTS (p.n = number of slots). A wave takes `run` consecutive
+// tiles: the tensor of the first tile's first slot is found by a wave-uniform search (scalar loads,
+// see find_segment), from there it walks on. The codes and meta of a tile are addressed by slot alone,
+// so those of the first tile are requested before the search and those of the next one before a tile
+// is decoded. A tile that lies inside its tensor's elements (the common case) is decoded without
+// per-lane control flow; a tile that reaches a tensor's padding or the next tensor goes lane by lane,
+// each lane walking on from the tile's tensor to its own. LUT: learned levels, one table of 2^BITS floats
+// per tensor at d.levels (tensor t's at d.levels + t * 2^BITS). Up to 6 bits the lanes of a wave hold
+// the table of its tensor, one level each, and look it up by lane permutation (no LDS to fill, no
+// bank conflicts); wider tables go to an LDS slot of the wave. The lane-by-lane path reads them
+// through global memory.
+// What bounds it: the tables, segment search and codes of a wave that decodes one tile are a chain of round trips to
+// memory before its first store. Rows and run below were measured on the 350M model in 292 tensors, inputs not in
+// cache (us, 5 bit -> bf16 / 4 bit -> fp32 / 8 bit -> fp32 of 177M elements; one tile of 2 rows a wave, tables in LDS:
+// 235 / 353 / 265, uniform levels 192 / 328 / 180): 2 rows, run 2: 193 / 316 / 195, uniform 177 / 304 / 170; 4 rows, run
+// 1: 204 / 280 / 178, uniform 172 / 300 / 193; 4 rows, run 2: 197 / 307 / 194, uniform 175 / 295 / 172.
 // ---------------------------------------------------------------------------------------
+constexpr int seg_rows(bool bf16) { return bf16 ? 2 : 4; }
+
+// Consecutive tiles of a wave: two, so that a search and a table serve both and the second tile's codes are under way while
+// the first is decoded; one for tables with fp32 output (280 against 307 us above: four rows in flight are enough there) and
+// where a buffer has too few tiles to give every resident wave of the chip (256 compute units x 32) two.
+inline uint32_t seg_run(bool bf16, bool lut, uint64_t ntiles) { return ntiles < 2 * 8192u || (!bf16 && lut) ? 1u : 2u; }
+
 struct DequantSegParams {
     DequantParams d;  // d.n: slots (total buckets * bucket); d.out: the flat output
     const Segment* segs;
     uint32_t nseg;
+    uint32_t run;  // consecutive tiles of a wave
 };
 
 template <int BITS, bool BF16, int BK, bool LUT>
@@ -195,10 +218,10 @@ __global__ void __launch_bounds__(256) dequant_seg_kernel(const DequantSegParams
                                                           const Segment* __restrict__ segs) {
     const DequantParams& p = q.d;
     constexpr int K = 1 << BITS;
-    __shared__ float lut_all[LUT ? 4 * K : 1];
-    uint32_t loaded_tensor = ~0u;  // wave-uniform: whose table the wave's slot holds
+    constexpr bool kLanes = LUT && BITS <= 6, kShared = LUT && !kLanes;
+    __shared__ float lut_all[kShared ? 4 * K : 1];
     constexpr int E = BF16 ? 8 : 4;
-    constexpr int U = kDequantRows;
+    constexpr int U = seg_rows(BF16);
     constexpr uint64_t T = (uint64_t)U * 64 * E;
     const int lane = threadIdx.x & 63;
     const uint32_t wave_in_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -206,54 +229,93 @@ __global__ void __launch_bounds__(256) dequant_seg_kernel(const DequantSegParams
     const uint64_t nwaves = (uint64_t)gridDim.x * waves_per_block;
     const uint64_t last_word = p.nwords - 1;
     const uint64_t B = (uint64_t)p.bucket32 * 32u;
-    for (uint64_t tile = (uint64_t)blockIdx.x * waves_per_block + wave_in_block; tile < p.ntiles;
-         tile += nwaves) {
-        const uint64_t s0 = tile * T;
-        const uint64_t bucket0 = (uint32_t)(s0 >> 5) / p.bucket32;  // wave-uniform
-        uint32_t tensor0;
-        const Segment seg0 = find_segment(segs, q.nseg, bucket0, bucket0, &tensor0);
-        const uint64_t e0 = seg0.offset + (s0 - seg0.first_bucket * B);  // element of slot s0
-        const uint64_t end0 = seg0.offset + seg0.n;
-        if (e0 + T <= end0) {
-            float* lut = lut_all + (LUT ? wave_in_block * K : 0);
-            if (LUT && tensor0 != loaded_tensor) {
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // earlier reads of the slot are done
-                __builtin_amdgcn_wave_barrier();
-                for (int k = lane; k < K; k += 64) lut[k] = p.levels[(uint64_t)tensor0 * K + k];
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                loaded_tensor = tensor0;
-            }
-            uint64_t bits[U];
-            float base[U], scale[U];
+    float* lut = lut_all + (kShared ? wave_in_block * K : 0);
+    float lane_level = 0.0f;
+    uint32_t loaded_tensor = ~0u;  // wave-uniform: whose table the wave holds
+    struct Row {
+        uint64_t bits;
+        float base, scale;
+    };
+    auto first_bucket_of = [&](uint64_t tile) -> uint64_t { return (uint32_t)((tile * T) >> 5) / p.bucket32; };
+    auto fetch = [&](uint64_t tile, Row (&row)[U]) {
+        const uint64_t bucket0 = first_bucket_of(tile);
+        const bool whole = (tile + 1) * T <= p.n;  // wave-uniform
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const uint64_t s = s0 + (uint64_t)(u * 64 * E + lane * E);
-                bits[u] = load_bits<E * BITS>(p.codes, s * BITS, last_word);
-                const uint64_t bucket = BK == BK_TILE_UNIFORM ? bucket0 : bucket_of<BK>(s, p);
-                base[u] = p.meta[2 * bucket];
-                scale[u] = p.meta[2 * bucket + 1];
-            }
+        for (int u = 0; u < U; ++u) {
+            uint64_t s = tile * T + (uint64_t)(u * 64 * E + lane * E);
+            if (!whole) s = s < p.n ? s : 0;
+            row[u].bits = load_bits<E * BITS>(p.codes, s * BITS, last_word);
+            const uint64_t bucket = BK == BK_TILE_UNIFORM ? bucket0 : bucket_of<BK>(s, p);
+            row[u].base = p.meta[2 * bucket];
+            row[u].scale = p.meta[2 * bucket + 1];
+        }
+    };
+    for (uint64_t tile0 = ((uint64_t)blockIdx.x * waves_per_block + wave_in_block) * q.run; tile0 < p.ntiles;
+         tile0 += nwaves * q.run) {
+        const uint64_t tile_end = tile0 + q.run < p.ntiles ? tile0 + q.run : p.ntiles;
+        Row row[U], next[U];
+        fetch(tile0, row);
+        uint32_t tensor;
+        const uint64_t start = first_bucket_of(tile0);
+        Segment seg = find_segment(segs, q.nseg, start, start, &tensor);
+        for (uint64_t tile = tile0; tile < tile_end; ++tile) {
+            if (tile + 1 < tile_end) fetch(tile + 1, next);
+            const uint64_t s0 = tile * T;
+            const uint64_t bucket0 = first_bucket_of(tile);
+            while (tensor + 1 < q.nseg && segs[tensor + 1].first_bucket <= bucket0) seg = segs[++tensor];
+            const uint64_t e0 = seg.offset + (s0 - seg.first_bucket * B);  // element of slot s0
+            const uint64_t end0 = seg.offset + seg.n;
+            if (e0 + T <= end0) {
+                if (kLanes && tensor != loaded_tensor) {
+                    lane_level = p.levels[(uint64_t)tensor * K + (lane & (K - 1))];
+                    loaded_tensor = tensor;
+                }
+                if (kShared && tensor != loaded_tensor) {
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // earlier reads of the slot are done
+                    __builtin_amdgcn_wave_barrier();
+                    for (int k = lane; k < K; k += 64) lut[k] = p.levels[(uint64_t)tensor * K + k];
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    loaded_tensor = tensor;
+                }
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                decode_store<BITS, BF16, LUT>(p, e0 + (uint64_t)(u * 64 * E + lane * E), bits[u], base[u], scale[u],
-                                              true, lut, end0);
-        } else {
-            for (int u = 0; u < U; ++u) {
-                const uint64_t s = s0 + (uint64_t)(u * 64 * E + lane * E);
-                if (s < p.n) {
-                    const uint64_t bucket = bucket_of<BK>(s, p);
-                    uint32_t tensor;
-                    const Segment seg = find_segment(segs, q.nseg, bucket0, bucket, &tensor);
-                    const uint64_t e = seg.offset + (s - seg.first_bucket * B);
-                    const uint64_t end = seg.offset + seg.n;
-                    if (e < end) {
-                        const uint64_t bits = load_bits<E * BITS>(p.codes, s * BITS, last_word);
-                        decode_store<BITS, BF16, LUT>(p, e, bits, p.meta[2 * bucket], p.meta[2 * bucket + 1],
-                                                      e + E <= end, LUT ? p.levels + (uint64_t)tensor * K : nullptr, end);
+                for (int u = 0; u < U; ++u) {
+                    const uint64_t e = e0 + (uint64_t)(u * 64 * E + lane * E);
+                    if constexpr (kLanes) {
+                        float o[E];
+#pragma unroll
+                        for (int i = 0; i < E; ++i) {
+                            const int at = (int)((uint32_t)(row[u].bits >> (i * BITS)) & (K - 1)) << 2;  // lane * 4
+                            o[i] = fmaf(__int_as_float(__builtin_amdgcn_ds_bpermute(at, __float_as_int(lane_level))),
+                                        row[u].scale, row[u].base);
+                        }
+                        store_decoded<BF16>(p, e, o);
+                    } else {
+                        decode_store<BITS, BF16, LUT>(p, e, row[u].bits, row[u].base, row[u].scale, true, lut, end0);
                     }
                 }
+            } else {
+                for (int u = 0; u < U; ++u) {
+                    const uint64_t s = s0 + (uint64_t)(u * 64 * E + lane * E);
+                    if (s < p.n) {
+                        const uint64_t bucket = bucket_of<BK>(s, p);
+                        Segment mine = seg;
+                        uint32_t t = tensor;
+                        while (t + 1 < q.nseg && segs[t + 1].first_bucket <= bucket) mine = segs[++t];
+                        const uint64_t e = mine.offset + (s - mine.first_bucket * B);
+                        const uint64_t end = mine.offset + mine.n;
+                        if (e < end) {
+                            const uint64_t bits = load_bits<E * BITS>(p.codes, s * BITS, last_word);
+                            decode_store<BITS, BF16, LUT>(p, e, bits, p.meta[2 * bucket], p.meta[2 * bucket + 1],
+                                                          e + E <= end, LUT ? p.levels + (uint64_t)t * K : nullptr, end);
+                        }
+                    }
+                }
+            }
+            if (tile + 1 < tile_end) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) row[u] = next[u];
             }
         }
     }
