@@ -125,7 +125,6 @@ hipError_t launch_dequant(int bits, bool bf16, const DequantParams& p, dim3 grid
 namespace {
 
 constexpr unsigned kMaxGrid = 1u << 20;
-constexpr unsigned kLevelsGrid = 1u << 15;
 
 // Workgroups to launch for `blocks` units of work: all of them up to kMaxGrid, the kernels stride
 // beyond that. QSDP_DEBUG_MAXGRID (the library's one debug switch) lowers the cap so that the
@@ -175,6 +174,20 @@ TileLauncher tile_launcher(const TilePlan& t) {
     return t.rows == 4 ? launch_tile_4_4 : t.rows == 6 ? launch_tile_4_6 : launch_tile_4_8;
 }
 
+// Workgroups of a learned-level encoder, given the number that would take one tile per wave (`waves` to a workgroup). A workgroup
+// sets up tables before its first tile, so it takes several: 16 for the nearest level, 32 for the coin flip with its
+// larger share of instructions, fewer where that would leave compute units without work (five workgroups each).
+// Measured (us, tiles per workgroup 12-20 / 16-32 / 24-48 / 32-64; nearest level, coin flip): 350M model in 292
+// tensors 317, 362 / 292, 346 / 302, 347 / 312, 331; 104M in buckets of 256, 128: 86, 136 / 89, 132 / 94, 132 / 101, 141;
+// 125M in buckets of 2048, 4096: 111, 143 / 113, 145 / 117, 143 / 118, 149.
+uint64_t level_blocks(int mode, uint64_t blocks, int waves) {
+    const uint64_t tiles = mode == MODE_LEVELS_COIN ? 32 : 16;
+    const uint64_t want = ceil_div(blocks * (uint64_t)waves, tiles);
+    const uint64_t resident = 5u * 256u;
+    const uint64_t most = want > resident ? want : resident;
+    return blocks < most ? blocks : most;
+}
+
 // Buckets go to the wave kernel of the bucket's shape when there is one, else to the tile kernel.
 // p.num_buckets must be set.
 int run(int mode, Params p, int stored_bits, hipStream_t s) {
@@ -191,11 +204,9 @@ int run(int mode, Params p, int stored_bits, hipStream_t s) {
     }
     if (wl != nullptr) {
         // 4 waves per workgroup, each on bpw buckets; or one workgroup per bucket
-        const uint64_t blocks = bpw > 0 ? ceil_div(ceil_div(nb, (uint64_t)bpw), 4) : nb;
-        // The learned-level encoders set up lookup tables per workgroup: their workgroups stay resident
-        // and stride over the buckets (measured best around 128 workgroups per compute unit).
-        const unsigned cap = mode_is_levels(mode) ? kLevelsGrid : kMaxGrid;
-        if (wl(mode, stored_bits, p, capped_grid(blocks, cap), s) != hipSuccess) return QSDP_ELAUNCH;
+        uint64_t blocks = bpw > 0 ? ceil_div(ceil_div(nb, (uint64_t)bpw), 4) : nb;
+        if (mode_is_levels(mode)) blocks = level_blocks(mode, blocks, bpw > 0 ? 4 : p.bucket / 1024);
+        if (wl(mode, stored_bits, p, capped_grid(blocks), s) != hipSuccess) return QSDP_ELAUNCH;
     } else {
         const TilePlan t = tile_plan(p.bucket);
         const uint64_t units = ceil_div(nb, (uint64_t)t.buckets);

@@ -16,14 +16,15 @@
 //     owns a contiguous 1/W of the bucket and the waves combine their min/max through LDS.
 //   * tile kernels: any bucket size (a multiple of 32), run-time code width: a wave or four waves on as many
 //     whole buckets as fit; used for the bucket sizes the wave kernels are not instantiated for.
-// The modes and parameters are in qsdp_params.hpp, the two encoder families in qsdp_wave_kernel.hpp and
-// qsdp_tile_kernel.hpp, the decoders and the element-wise decode-and-sum in qsdp_decoders.hpp, the
+// The modes and parameters are in qsdp_params.hpp, the two encoder families in qsdp_wave_kernel.hpp (with the learned-level
+// modes in qsdp_levels_kernel.hpp) and qsdp_tile_kernel.hpp, the decoders and the element-wise decode-and-sum in qsdp_decoders.hpp, the
 // level fit in qsdp_fit_kernel.hpp.
 #pragma once
 
 #include "qsdp_params.hpp"
 #include "qsdp_tile_plan.hpp"
 #include "qsdp_wave_kernel.hpp"
+#include "qsdp_levels_kernel.hpp"
 #include "qsdp_tile_kernel.hpp"
 #include "qsdp_decoders.hpp"
 #include "qsdp_fit_kernel.hpp"

@@ -7,9 +7,6 @@
 
 // Workgroups (of 4 waves) per compute unit the compiler has to leave room for, i.e. waves per SIMD: caps the
 // registers of a kernel. 1 = no constraint.
-#ifndef QSDP_LEVELS_MIN_BLOCKS
-#define QSDP_LEVELS_MIN_BLOCKS 4
-#endif
 #ifndef QSDP_ADAMW_MIN_BLOCKS
 #define QSDP_ADAMW_MIN_BLOCKS 1
 #endif
@@ -371,63 +368,13 @@ __device__ __forceinline__ void sum_peer_slices(const Params& p, uint8_t* stage,
     }
 }
 
-// The learned-level encoders over a lane's rows: v -> codes (MODE_LEVELS: nearest level; MODE_LEVELS_COIN:
-// coin flip between the enclosing levels). MASKED: only the lanes with `mine` keep their codes (a pass
-// over the lanes of one tensor of a multi-tensor call).
-template <int MODE, int G, int R, int BITS, bool MASKED, bool BY_CELL>
-__device__ __forceinline__ void encode_levels_by(const float (&v)[R][4], uint32_t (&code)[R][4], bool mine, float lo,
-                                                 float inv_cells, const float* lv, const LevelCell* cells,
-                                                 const LevelNear* near, const LevelCoin* coin,
-                                                 const LevelPivots& pivots, uint64_t block_e0, int l, PhiloxKey key) {
-    constexpr bool by_cell = BY_CELL;
-    if constexpr (MODE == MODE_LEVELS_COIN) {
-#pragma unroll
-        for (int cp = 0; cp < R / 2; ++cp) {
-            uint32_t h[4];
-            grad_uniforms_rows<G>(block_e0, cp, l, key.k0, key.k1, h);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int r = 2 * cp + (i >> 2);
-                const float z = (v[r][i & 3] - lo) * inv_cells;
-                const uint32_t c = stochastic_level<BITS>(z, (float)uniform16(h, i), lv, cells, coin, pivots, by_cell);
-                code[r][i & 3] = (!MASKED || mine) ? c : code[r][i & 3];
-            }
-        }
-    } else {
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float z = (v[r][i] - lo) * inv_cells;
-                const uint32_t c = nearest_level<BITS>(z, lv, cells, near, pivots, by_cell);
-                code[r][i] = (!MASKED || mine) ? c : code[r][i];
-            }
-    }
-}
-
-// by_cell (wave-uniform) picks the counting method once for all of the lane's elements, so that each
-// method is straight-line code over the rows and the LDS reads of different elements overlap.
-template <int MODE, int G, int R, int BITS, bool MASKED>
-__device__ __forceinline__ void encode_levels(const float (&v)[R][4], uint32_t (&code)[R][4], bool mine, float lo,
-                                              float inv_cells, const float* lv, const LevelCell* cells,
-                                              const LevelNear* near, const LevelCoin* coin, const LevelPivots& pivots,
-                                              bool by_cell, uint64_t block_e0, int l, PhiloxKey key) {
-    if (by_cell)
-        encode_levels_by<MODE, G, R, BITS, MASKED, true>(v, code, mine, lo, inv_cells, lv, cells, near, coin, pivots,
-                                                         block_e0, l, key);
-    else
-        encode_levels_by<MODE, G, R, BITS, MASKED, false>(v, code, mine, lo, inv_cells, lv, cells, near, coin, pivots,
-                                                          block_e0, l, key);
-}
-
-// Every mode over the buckets first_bucket .. +num_buckets-1 (the last bucket of a tensor may
-// be short). BITS is the width of the codes that are stored (0: a step without code output, or
+// Every mode but the learned-level encoders (qsdp_levels_kernel.hpp) over the buckets first_bucket .. +num_buckets-1
+// (the last bucket of a tensor may be short). BITS is the width of the codes that are stored (0: a step without code output, or
 // MODE_SUM). W = waves per bucket (W > 1: the workgroup has exactly W waves and owns one bucket
 // per iteration). delta > 0 selects the explicit grid, p.flags the quantizer variants (both
 // wave-uniform branches).
 constexpr int mode_min_blocks(int mode) {
-    return mode_is_levels(mode) ? QSDP_LEVELS_MIN_BLOCKS
-           : mode == MODE_RECV_ADAMW ? QSDP_ADAMW_MIN_BLOCKS
+    return mode == MODE_RECV_ADAMW ? QSDP_ADAMW_MIN_BLOCKS
            : mode == MODE_RECV ? QSDP_RECV_MIN_BLOCKS
            : mode == MODE_FUSED ? QSDP_FUSED_MIN_BLOCKS : 1;
 }
@@ -459,105 +406,6 @@ __global__ void __launch_bounds__(256, mode_min_blocks(MODE)) wave_kernel(const 
     uint8_t* stage = reinterpret_cast<uint8_t*>(stage_all) + (kStaged ? wave_in_block * kTileBytes : 0);
     __shared__ float red_all[W > 1 ? 2 * 2 * 2 * W : 1];  // [parity][g or w][lo/hi][wave]
     uint32_t parity = 0;
-    // Which units this wave (workgroup) works on: unit0, unit0 + stride, ... (the one-pass modes normally have
-    // a wave per unit; the learned-level modes a resident grid, whose waves then sweep the buffer side by
-    // side); a contiguous run of units where every tensor has its own level tables, which a wave should
-    // have to set up as rarely as possible.
-    uint64_t q_begin = unit0, q_end = nunits, q_step = unit_stride;
-    if (mode_is_levels(MODE) && p.levels_per_tensor != 0 && segs != nullptr) {
-        const uint64_t run = (nunits + unit_stride - 1) / unit_stride;
-        q_begin = unit0 * run;
-        q_end = q_begin + run < nunits ? q_begin + run : nunits;
-        q_step = 1;
-    }
-    // The learned-level modes keep the values of the wave's next unit in flight while the current one is
-    // encoded, and those of its first unit while the level tables are set up (the tables' own loads, the
-    // barriers and the searches that fill them would otherwise all come before the first load of data).
-    // unit_tile: where unit q's tile of the data lies.
-    struct UnitTile {
-        bool active;         // the lane's bucket exists
-        uint64_t bucket;     // the lane's bucket (the unit's first one for a lane without a bucket)
-        uint32_t tensor;     // the tensor the bucket belongs to (multi-tensor calls)
-        uint32_t part0;      // first element of this wave's part of the bucket (W > 1)
-        uint64_t e0;         // first element of the wave's tile
-        int m;               // elements of the tile that exist
-        bool partial;        // wave-uniform: some lane's tile is short
-    };
-    auto unit_tile = [&](uint64_t q) -> UnitTile {
-        UnitTile t;
-        const uint64_t rel = q * BPW + sub;  // bucket within this launch
-        t.active = rel < p.num_buckets;
-        const uint64_t bucket0 = p.first_bucket + q * BPW;  // wave-uniform
-        t.bucket = t.active ? p.first_bucket + rel : bucket0;
-        const BucketRef ref = locate_bucket(p, segs, bucket0, t.bucket, B);
-        t.tensor = ref.tensor;
-        // this wave's tile of the bucket: all of it, or the wave's 1/W
-        t.part0 = W > 1 ? wave_in_block * (uint32_t)T : 0u;
-        t.e0 = ref.e0 + t.part0;
-        t.m = ref.m > t.part0 ? (int)(ref.m - t.part0 < (uint32_t)T ? ref.m - t.part0 : (uint32_t)T) : 0;
-        t.partial = __builtin_amdgcn_ballot_w64(t.m < T) != 0;
-        return t;
-    };
-    float next_w[mode_is_levels(MODE) ? R : 1][4];
-    if constexpr (mode_is_levels(MODE)) {
-        if (q_begin < q_end) {
-            const UnitTile t = unit_tile(q_begin);
-            load_rows<G, R>(p.xin + t.e0, l, t.m, t.partial, next_w);
-        }
-    }
-    // Learned levels (see the section of that name in qsdp_device.hpp): the level table in LDS, scaled
-    // to cell units, the cell table and the landing table of the mode's encoder, and the binary
-    // search's first pivots in scalar registers. One table for the whole call is set up once per
-    // workgroup; with one table per tensor every wave keeps the tables of the tensor it works on in
-    // slots of its own and sets them up again when its buckets move on to another tensor.
-    constexpr int kLevels = 1 << SB;
-    constexpr int kCellSlot = kLevelCells + 1;
-    __shared__ float level_tables[mode_is_levels(MODE) ? 4 * kLevels : 1];
-    __shared__ LevelCell level_cells_all[mode_is_levels(MODE) ? 4 * kCellSlot : 1];
-    __shared__ LevelNear level_nears[MODE == MODE_LEVELS ? 4 * kLevels : 1];
-    __shared__ LevelCoin level_coins[MODE == MODE_LEVELS_COIN ? 4 * kLevels : 1];
-    __shared__ int level_cells_crowded;
-    const bool levels_per_tensor = mode_is_levels(MODE) && p.levels_per_tensor != 0 && segs != nullptr;
-    const uint32_t level_slot = levels_per_tensor ? wave_in_block * (uint32_t)kLevels : 0u;
-    float* level_table = level_tables + level_slot;
-    LevelCell* level_cells = level_cells_all + (levels_per_tensor ? wave_in_block * (uint32_t)kCellSlot : 0u);
-    LevelNear* level_near = level_nears + (MODE == MODE_LEVELS ? level_slot : 0u);
-    LevelCoin* level_coin = level_coins + (MODE == MODE_LEVELS_COIN ? level_slot : 0u);
-    LevelPivots pivots = {0.0f, 0.0f, 0.0f, 0.0f};
-    bool count_by_cell = false;    // wave-uniform: no cell of the current table holds two levels
-    uint32_t loaded_tensor = ~0u;  // wave-uniform: whose tables the wave's slots hold
-    if constexpr (mode_is_levels(MODE)) {
-        if (!levels_per_tensor) {
-            if (threadIdx.x == 0) level_cells_crowded = 0;
-            constexpr int kThreads = W == 1 ? 256 : 64 * W;  // the launch's workgroup size
-            constexpr int kRounds = (kLevels + kThreads - 1) / kThreads;
-            float lv_mine[kRounds];  // this thread's levels
-#pragma unroll
-            for (int i = 0; i < kRounds; ++i) {
-                const int k = threadIdx.x + i * kThreads;
-                lv_mine[i] = k < kLevels ? p.levels[k] : 0.0f;
-            }
-#pragma unroll
-            for (int i = 0; i < kRounds; ++i) {
-                const int k = threadIdx.x + i * kThreads;
-                if (k < kLevels) level_tables[k] = lv_mine[i] * kLevelCellsF;
-            }
-            __syncthreads();
-            bool crowded;
-            if constexpr (MODE == MODE_LEVELS) {
-                fill_level_near(level_tables, level_nears, kLevels, threadIdx.x, blockDim.x);
-                crowded = fill_level_cells<false>(level_tables, level_cells_all, kLevels - 1, threadIdx.x, blockDim.x);
-            } else {
-                fill_level_coin(level_tables, level_coins, kLevels, threadIdx.x, blockDim.x);
-                crowded = fill_level_cells<true>(level_tables, level_cells_all, kLevels, threadIdx.x, blockDim.x);
-            }
-            if (crowded) level_cells_crowded = 1;
-            __syncthreads();
-            count_by_cell = __builtin_amdgcn_readfirstlane(level_cells_crowded) == 0;
-            pivots = load_level_pivots<SB>(level_tables);
-        }
-    }
-
     const float Lg = (float)((1 << p.gbits) - 1);
     const uint32_t top16_g = (uint32_t)((1 << p.gbits) - 1) << 16;  // L in units of 2^-16 of a cell
     const float Lw = (float)((1 << p.wbits) - 1);
@@ -568,20 +416,23 @@ __global__ void __launch_bounds__(256, mode_min_blocks(MODE)) wave_kernel(const 
     constexpr bool kWritesX = MODE == MODE_FUSED || MODE == MODE_ADAMW || mode_is_recv(MODE);
     const bool keep_master = kWritesX && (p.flags & FLAG_KEEP_MASTER) != 0;
     const PhiloxKey key = launch_key(p);
-    const Shifts shifts = draw_shifts(p, key, MODE != MODE_GRAD && !mode_is_levels(MODE) && MODE != MODE_SUM);
+    const Shifts shifts = draw_shifts(p, key, MODE != MODE_GRAD && MODE != MODE_SUM);
     const float xi = shifts.xi;
     uint32_t saturated = 0;
 
-    for (uint64_t q = q_begin; q < q_end; q += q_step, parity ^= 1u) {
-        const UnitTile tile = unit_tile(q);
-        const bool active = tile.active;
+    for (uint64_t q = unit0; q < nunits; q += unit_stride, parity ^= 1u) {
+        const uint64_t rel = q * BPW + sub;       // bucket within this launch
+        const bool active = rel < p.num_buckets;  // the lane's bucket exists
         const uint64_t left = p.num_buckets - q * BPW;
         const int active_buckets = left < (uint64_t)BPW ? (int)left : BPW;
-        const uint64_t bucket = tile.bucket;
-        const uint32_t part0 = tile.part0;
-        const uint64_t e0 = tile.e0;
-        const int m = tile.m;
-        const bool partial = tile.partial;
+        const uint64_t bucket0 = p.first_bucket + q * BPW;  // wave-uniform
+        const uint64_t bucket = active ? p.first_bucket + rel : bucket0;
+        const BucketRef ref = locate_bucket(p, segs, bucket0, bucket, B);
+        // this wave's tile of the bucket: all of it, or the wave's 1/W
+        const uint32_t part0 = W > 1 ? wave_in_block * (uint32_t)T : 0u;
+        const uint64_t e0 = ref.e0 + part0;
+        const int m = ref.m > part0 ? (int)(ref.m - part0 < (uint32_t)T ? ref.m - part0 : (uint32_t)T) : 0;
+        const bool partial = __builtin_amdgcn_ballot_w64(m < T) != 0;  // wave-uniform: some lane's tile is short
         // Philox block of the tile's first element; the tile's place in the code buffer (the
         // code stream is indexed by bucket number, every bucket padded to B slots)
         const uint64_t block_e0 = p.block0 + (e0 >> 3);
@@ -593,7 +444,6 @@ __global__ void __launch_bounds__(256, mode_min_blocks(MODE)) wave_kernel(const 
         const bool writes_meta = active && l == 0 && (W == 1 || wave_in_block == 0);
 
         float w[R][4];  // the values that get weight-quantized (x, or y = x - lr*ghat)
-        uint32_t lcode[mode_is_levels(MODE) ? R : 1][4] = {};  // the learned-level modes' codes
         float base = 0.0f, scale = 0.0f;
 
         if (mode_local_gradient(MODE)) {
@@ -705,73 +555,14 @@ __global__ void __launch_bounds__(256, mode_min_blocks(MODE)) wave_kernel(const 
                 }
             }
         } else {
-            if constexpr (mode_is_levels(MODE)) {
-#pragma unroll
-                for (int r = 0; r < R; ++r)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) w[r][i] = next_w[r][i];
-                if (q + q_step < q_end) {
-                    const UnitTile t = unit_tile(q + q_step);
-                    load_rows<G, R>(p.xin + t.e0, l, t.m, t.partial, next_w);
-                }
-            } else {
-                load_rows<G, R>(p.xin + e0, l, m, partial, w);
-            }
+            load_rows<G, R>(p.xin + e0, l, m, partial, w);
         }
 
         // the full-precision partition keeps the updated value itself (stored before w turns into codes)
         if (kWritesX && keep_master && active) store_rows<G, R>(p.x + e0, l, m, partial, w);
 
         // weight quantization of w
-        if constexpr (mode_is_levels(MODE)) {
-            float lo, hi;
-            rows_minmax<G, R>(w, l, m, partial, lo, hi);
-            block_combine_minmax<W>(lo, hi, red_w, wave_in_block);
-            const MinMaxGrid grid = make_minmax_grid(lo, hi, 1.0f, false);  // scale = hi - lo, inv = 1/(hi - lo)
-            base = grid.lo;
-            scale = grid.scale;
-            const float inv_cells = grid.inv * kLevelCellsF;  // normalised value in cell units: (v - lo) * inv_cells
-            if (!levels_per_tensor) {
-                encode_levels<MODE, G, R, SB, false>(w, lcode, true, grid.lo, inv_cells, level_table, level_cells, level_near,
-                                                     level_coin, pivots, count_by_cell, block_e0, l, key);
-            } else {
-                // One pass per distinct tensor among the wave's buckets (one pass, unless the buckets
-                // straddle tensors): every lane computes, the lanes of the pass's tensor keep the codes
-                // (a lane belongs to exactly one pass). All lanes stay converged (the uniforms are
-                // exchanged between lanes).
-                uint64_t pending = ~0ull;
-                do {
-                    const uint32_t cur = (uint32_t)__builtin_amdgcn_readlane((int)tile.tensor, __builtin_ctzll(pending));
-                    const bool mine = tile.tensor == cur;
-                    if (cur != loaded_tensor) {
-                        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // earlier reads of the slots are done
-                        __builtin_amdgcn_wave_barrier();
-                        for (int k = lane; k < kLevels; k += 64)
-                            level_table[k] = p.levels[(uint64_t)cur * kLevels + k] * kLevelCellsF;
-                        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                        __builtin_amdgcn_wave_barrier();
-                        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                        bool crowded;
-                        if constexpr (MODE == MODE_LEVELS) {
-                            fill_level_near(level_table, level_near, kLevels, lane, 64);
-                            crowded = fill_level_cells<false>(level_table, level_cells, kLevels - 1, lane, 64);
-                        } else {
-                            fill_level_coin(level_table, level_coin, kLevels, lane, 64);
-                            crowded = fill_level_cells<true>(level_table, level_cells, kLevels, lane, 64);
-                        }
-                        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                        __builtin_amdgcn_wave_barrier();
-                        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                        count_by_cell = __builtin_amdgcn_ballot_w64(crowded) == 0;
-                        pivots = load_level_pivots<SB>(level_table);
-                        loaded_tensor = cur;
-                    }
-                    encode_levels<MODE, G, R, SB, true>(w, lcode, mine, grid.lo, inv_cells, level_table, level_cells,
-                                                        level_near, level_coin, pivots, count_by_cell, block_e0, l, key);
-                    pending &= ~__builtin_amdgcn_ballot_w64(mine);
-                } while (pending != 0);
-            }
-        } else if (lattice) {
+        if (lattice) {
             float lo, unused_hi;
             rows_minmax<G, R>(w, l, m, partial, lo, unused_hi);
             block_combine_minmax<W>(lo, unused_hi, red_w, wave_in_block);
@@ -815,10 +606,7 @@ __global__ void __launch_bounds__(256, mode_min_blocks(MODE)) wave_kernel(const 
                     w[r][i] = kPackRounds ? weight_position_minmax(w[r][i], grid, xi)
                                           : weight_code_minmax(w[r][i], grid, Lw, xi);
         }
-        if constexpr (mode_is_levels(MODE)) {
-            if (__builtin_expect(partial, 0)) zero_slots_past_end<G, R>(lcode, l, m);
-            store_codes<G, R, SB>(stage, tile_out, lane, active_buckets, lcode);
-        } else if (BITS != 0) {
+        if (BITS != 0) {
             if (partial) zero_slots_past_end<G, R>(w, l, m);
             store_codes<G, R, SB>(stage, tile_out, lane, active_buckets, w);
         }
