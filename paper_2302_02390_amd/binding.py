@@ -136,16 +136,29 @@ def meta_bytes(n, bucket):
 
 
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
-
-
-def _stream(t):
-    return C.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
+    return None if t is None else t.data_ptr()
 
 
 def _check(status, what):
     if status != QSDP_OK:
         raise QsdpError(status, what)
+
+
+def _launch(t, name, *args):
+    """Calls entry point `name` with the current stream of t's device as its last argument, t's device being the
+    current one meanwhile. Small calls are bound by what happens here: a fused step over 2^20 parameters takes 4.3 us of GPU
+    time; with a device guard, a Stream object and a pointer object per tensor on every call a loop of them took 11-12 us
+    a call, without them 7-8 (3.4-4.1 of it the launch itself). So the device is switched only if it is another one, and
+    the stream is asked for its handle alone."""
+    device = t.get_device()
+    stream = torch._C._cuda_getCurrentRawStream(device)
+    if device == torch.cuda.current_device():
+        status = getattr(_lib or lib(), name)(*args, stream)
+    else:
+        with torch.cuda.device(device):
+            status = getattr(_lib or lib(), name)(*args, stream)
+    if status != QSDP_OK:
+        raise QsdpError(status, name)
 
 
 def _is(t, dtype):
@@ -175,6 +188,8 @@ def _need(t, numel, what):
 def _packed_ok(codes, meta, n, bits, bucket):
     """The packed buffers are large enough for n elements (the C ABI takes raw pointers and cannot
     check this itself). Invalid n / bits / bucket are left to the library to report."""
+    if codes is None and meta is None:
+        return
     cb, mb = codes_bytes(n, bits, bucket), meta_bytes(n, bucket)
     if cb and mb:
         if codes is not None:
@@ -206,17 +221,14 @@ def alloc_packed(n, bits, bucket, device):
 def qsdp_quantize_grad(g, bits, bucket, seed, index_offset, codes, meta):
     _is(g, torch.float32); _is(codes, torch.int32); _is(meta, torch.float32)
     _packed_ok(codes, meta, g.numel(), bits, bucket)
-    with torch.cuda.device(g.device):
-        _check(lib().qsdp_quantize_grad(_ptr(g), g.numel(), bits, bucket, seed, index_offset,
-                                        _ptr(codes), _ptr(meta), _stream(g)), "qsdp_quantize_grad")
+    _launch(g, "qsdp_quantize_grad", _ptr(g), g.numel(), bits, bucket, seed, index_offset, _ptr(codes), _ptr(meta))
 
 
 def qsdp_quantize_grad_ex(g, bits, bucket, seed, index_offset, flags, codes, meta):
     _is(g, torch.float32); _is(codes, torch.int32); _is(meta, torch.float32)
     _packed_ok(codes, meta, g.numel(), bits, bucket)
-    with torch.cuda.device(g.device):
-        _check(lib().qsdp_quantize_grad_ex(_ptr(g), g.numel(), bits, bucket, seed, index_offset, flags,
-                                           _ptr(codes), _ptr(meta), _stream(g)), "qsdp_quantize_grad_ex")
+    _launch(g, "qsdp_quantize_grad_ex", _ptr(g), g.numel(), bits, bucket, seed, index_offset, flags, _ptr(codes),
+            _ptr(meta))
 
 
 def qsdp_quantize_weight_ex(x, bits, bucket, delta, seed, flags, codes, meta, n_saturated=None):
@@ -224,10 +236,8 @@ def qsdp_quantize_weight_ex(x, bits, bucket, delta, seed, flags, codes, meta, n_
     _packed_ok(codes, meta, x.numel(), bits, bucket)
     if n_saturated is not None:
         _is(n_saturated, torch.int64)
-    with torch.cuda.device(x.device):
-        _check(lib().qsdp_quantize_weight_ex(_ptr(x), x.numel(), bits, bucket, delta, seed, flags, _ptr(codes),
-                                             _ptr(meta), _ptr(n_saturated), _stream(x)),
-               "qsdp_quantize_weight_ex")
+    _launch(x, "qsdp_quantize_weight_ex", _ptr(x), x.numel(), bits, bucket, delta, seed, flags, _ptr(codes), _ptr(meta),
+            _ptr(n_saturated))
 
 
 def qsdp_fused_step_ex(x, g, lr, wbits, gbits, bucket, delta, seed, index_offset, flags, wcodes=None,
@@ -239,10 +249,8 @@ def qsdp_fused_step_ex(x, g, lr, wbits, gbits, bucket, delta, seed, index_offset
         if t is not None:
             _is(t, dt)
     _packed_ok(wcodes, wmeta, x.numel(), wbits, bucket)
-    with torch.cuda.device(x.device):
-        _check(lib().qsdp_fused_step_ex(_ptr(x), _ptr(g), x.numel(), lr, wbits, gbits, bucket, delta, seed,
-                                        index_offset, flags, _ptr(wcodes), _ptr(wmeta), _ptr(n_saturated),
-                                        _stream(x)), "qsdp_fused_step_ex")
+    _launch(x, "qsdp_fused_step_ex", _ptr(x), _ptr(g), x.numel(), lr, wbits, gbits, bucket, delta, seed, index_offset,
+            flags, _ptr(wcodes), _ptr(wmeta), _ptr(n_saturated))
 
 
 def qsdp_quantize_weight(x, bits, bucket, delta, seed, codes, meta, n_saturated=None):
@@ -250,10 +258,8 @@ def qsdp_quantize_weight(x, bits, bucket, delta, seed, codes, meta, n_saturated=
     _packed_ok(codes, meta, x.numel(), bits, bucket)
     if n_saturated is not None:
         _is(n_saturated, torch.int64)
-    with torch.cuda.device(x.device):
-        _check(lib().qsdp_quantize_weight(_ptr(x), x.numel(), bits, bucket, delta, seed, _ptr(codes),
-                                          _ptr(meta), _ptr(n_saturated), _stream(x)),
-               "qsdp_quantize_weight")
+    _launch(x, "qsdp_quantize_weight", _ptr(x), x.numel(), bits, bucket, delta, seed, _ptr(codes), _ptr(meta),
+            _ptr(n_saturated))
 
 
 def qsdp_dequantize(codes, meta, n, bits, bucket, out):
@@ -263,9 +269,7 @@ def qsdp_dequantize(codes, meta, n, bits, bucket, out):
     if out.numel() < n:
         raise ValueError("out is too small")
     _packed_ok(codes, meta, n, bits, bucket)
-    with torch.cuda.device(out.device):
-        _check(lib().qsdp_dequantize(_ptr(codes), _ptr(meta), n, bits, bucket, dt, _ptr(out),
-                                     _stream(out)), "qsdp_dequantize")
+    _launch(out, "qsdp_dequantize", _ptr(codes), _ptr(meta), n, bits, bucket, dt, _ptr(out))
 
 
 def levels_uniform(bits, device):
@@ -281,9 +285,7 @@ def qsdp_quantize_levels(v, bits, bucket, levels, codes, meta):
     if levels.numel() != (1 << bits):
         raise ValueError("levels must hold 2^bits entries")
     _packed_ok(codes, meta, v.numel(), bits, bucket)
-    with torch.cuda.device(v.device):
-        _check(lib().qsdp_quantize_levels(_ptr(v), v.numel(), bits, bucket, _ptr(levels), _ptr(codes), _ptr(meta),
-                                          _stream(v)), "qsdp_quantize_levels")
+    _launch(v, "qsdp_quantize_levels", _ptr(v), v.numel(), bits, bucket, _ptr(levels), _ptr(codes), _ptr(meta))
 
 
 def qsdp_quantize_levels_stochastic(v, bits, bucket, levels, seed, index_offset, codes, meta):
@@ -291,10 +293,8 @@ def qsdp_quantize_levels_stochastic(v, bits, bucket, levels, seed, index_offset,
     if levels.numel() != (1 << bits):
         raise ValueError("levels must hold 2^bits entries")
     _packed_ok(codes, meta, v.numel(), bits, bucket)
-    with torch.cuda.device(v.device):
-        _check(lib().qsdp_quantize_levels_stochastic(_ptr(v), v.numel(), bits, bucket, _ptr(levels), seed,
-                                                     index_offset, _ptr(codes), _ptr(meta), _stream(v)),
-               "qsdp_quantize_levels_stochastic")
+    _launch(v, "qsdp_quantize_levels_stochastic", _ptr(v), v.numel(), bits, bucket, _ptr(levels), seed, index_offset,
+            _ptr(codes), _ptr(meta))
 
 
 def qsdp_dequantize_levels(codes, meta, n, bits, bucket, levels, out):
@@ -306,18 +306,14 @@ def qsdp_dequantize_levels(codes, meta, n, bits, bucket, levels, out):
     if out.numel() < n:
         raise ValueError("out is too small")
     _packed_ok(codes, meta, n, bits, bucket)
-    with torch.cuda.device(out.device):
-        _check(lib().qsdp_dequantize_levels(_ptr(codes), _ptr(meta), n, bits, bucket, _ptr(levels), dt, _ptr(out),
-                                            _stream(out)), "qsdp_dequantize_levels")
+    _launch(out, "qsdp_dequantize_levels", _ptr(codes), _ptr(meta), n, bits, bucket, _ptr(levels), dt, _ptr(out))
 
 
 def qsdp_fit_levels(v, bits, bucket, lr, levels, max_batches=0):
     _is(v, torch.float32); _is(levels, torch.float32)
     if levels.numel() != (1 << bits):
         raise ValueError("levels must hold 2^bits entries")
-    with torch.cuda.device(v.device):
-        _check(lib().qsdp_fit_levels(_ptr(v), v.numel(), bits, bucket, lr, max_batches, _ptr(levels), _stream(v)),
-               "qsdp_fit_levels")
+    _launch(v, "qsdp_fit_levels", _ptr(v), v.numel(), bits, bucket, lr, max_batches, _ptr(levels))
 
 
 def qsdp_dequantize_add(codes, meta, npeers, n, bits, bucket, alpha, out):
@@ -328,10 +324,8 @@ def qsdp_dequantize_add(codes, meta, npeers, n, bits, bucket, alpha, out):
     if out.numel() < n:
         raise ValueError("out is too small")
     _rows_ok(codes, meta, n, bits, bucket)
-    with torch.cuda.device(out.device):
-        _check(lib().qsdp_dequantize_add(_ptr(codes), codes.stride(0) * 4, _ptr(meta), meta.stride(0) * 4,
-                                         npeers, n, bits, bucket, alpha, _ptr(out), _stream(out)),
-               "qsdp_dequantize_add")
+    _launch(out, "qsdp_dequantize_add", _ptr(codes), codes.stride(0) * 4, _ptr(meta), meta.stride(0) * 4, npeers, n,
+            bits, bucket, alpha, _ptr(out))
 
 
 def qsdp_fused_step(x, g, lr, wbits, gbits, bucket, delta, seed, index_offset=0, wcodes=None,
@@ -346,10 +340,8 @@ def qsdp_fused_step(x, g, lr, wbits, gbits, bucket, delta, seed, index_offset=0,
     if n_saturated is not None:
         _is(n_saturated, torch.int64)
     _packed_ok(wcodes, wmeta, x.numel(), wbits, bucket)
-    with torch.cuda.device(x.device):
-        _check(lib().qsdp_fused_step(_ptr(x), _ptr(g), x.numel(), lr, wbits, gbits, bucket, delta, seed,
-                                     index_offset, _ptr(wcodes), _ptr(wmeta), _ptr(n_saturated),
-                                     _stream(x)), "qsdp_fused_step")
+    _launch(x, "qsdp_fused_step", _ptr(x), _ptr(g), x.numel(), lr, wbits, gbits, bucket, delta, seed, index_offset,
+            _ptr(wcodes), _ptr(wmeta), _ptr(n_saturated))
 
 
 def qsdp_fused_adamw_step(x, g, m, v, lr, beta1, beta2, eps, weight_decay, bias1, bias2, wbits, gbits, bucket,
@@ -362,11 +354,9 @@ def qsdp_fused_adamw_step(x, g, m, v, lr, beta1, beta2, eps, weight_decay, bias1
         if t is not None:
             _is(t, dt)
     _packed_ok(wcodes, wmeta, x.numel(), wbits, bucket)
-    with torch.cuda.device(x.device):
-        _check(lib().qsdp_fused_adamw_step(_ptr(x), _ptr(g), _ptr(m), _ptr(v), x.numel(), lr, beta1, beta2, eps,
-                                           weight_decay, bias1, bias2, wbits, gbits, bucket, delta, seed,
-                                           index_offset, flags, _ptr(wcodes), _ptr(wmeta), _ptr(n_saturated),
-                                           _stream(x)), "qsdp_fused_adamw_step")
+    _launch(x, "qsdp_fused_adamw_step", _ptr(x), _ptr(g), _ptr(m), _ptr(v), x.numel(), lr, beta1, beta2, eps,
+            weight_decay, bias1, bias2, wbits, gbits, bucket, delta, seed, index_offset, flags, _ptr(wcodes),
+            _ptr(wmeta), _ptr(n_saturated))
 
 
 def qsdp_fused_step_codes(wcodes, wmeta, g, lr, wbits, gbits, bucket, delta, seed, index_offset=0,
@@ -375,10 +365,8 @@ def qsdp_fused_step_codes(wcodes, wmeta, g, lr, wbits, gbits, bucket, delta, see
     if n_saturated is not None:
         _is(n_saturated, torch.int64)
     _packed_ok(wcodes, wmeta, g.numel(), wbits, bucket)
-    with torch.cuda.device(g.device):
-        _check(lib().qsdp_fused_step_codes(_ptr(wcodes), _ptr(wmeta), _ptr(g), g.numel(), lr, wbits, gbits,
-                                           bucket, delta, seed, index_offset, flags, _ptr(n_saturated),
-                                           _stream(g)), "qsdp_fused_step_codes")
+    _launch(g, "qsdp_fused_step_codes", _ptr(wcodes), _ptr(wmeta), _ptr(g), g.numel(), lr, wbits, gbits, bucket, delta,
+            seed, index_offset, flags, _ptr(n_saturated))
 
 
 class Segments:
@@ -420,10 +408,8 @@ def qsdp_quantize_grad_segmented(g, segs, bits, seed, index_offset, codes, meta)
     if g.numel() < segs.n:
         raise ValueError("g is smaller than the segments")
     segs.check_packed(codes, meta, bits)
-    with torch.cuda.device(g.device):
-        _check(lib().qsdp_quantize_grad_segmented(_ptr(g), _ptr(segs.device), segs.nseg, segs.total_buckets,
-                                                  bits, segs.bucket, seed, index_offset, _ptr(codes),
-                                                  _ptr(meta), _stream(g)), "qsdp_quantize_grad_segmented")
+    _launch(g, "qsdp_quantize_grad_segmented", _ptr(g), _ptr(segs.device), segs.nseg, segs.total_buckets, bits,
+            segs.bucket, seed, index_offset, _ptr(codes), _ptr(meta))
 
 
 def qsdp_quantize_weight_segmented(x, segs, bits, delta, seed, codes, meta, n_saturated=None):
@@ -433,11 +419,8 @@ def qsdp_quantize_weight_segmented(x, segs, bits, delta, seed, codes, meta, n_sa
     if n_saturated is not None:
         _is(n_saturated, torch.int64)
     segs.check_packed(codes, meta, bits)
-    with torch.cuda.device(x.device):
-        _check(lib().qsdp_quantize_weight_segmented(_ptr(x), _ptr(segs.device), segs.nseg,
-                                                    segs.total_buckets, bits, segs.bucket, delta, seed,
-                                                    _ptr(codes), _ptr(meta), _ptr(n_saturated), _stream(x)),
-               "qsdp_quantize_weight_segmented")
+    _launch(x, "qsdp_quantize_weight_segmented", _ptr(x), _ptr(segs.device), segs.nseg, segs.total_buckets, bits,
+            segs.bucket, delta, seed, _ptr(codes), _ptr(meta), _ptr(n_saturated))
 
 
 def qsdp_fused_step_segmented(x, g, segs, lr, wbits, gbits, delta, seed, index_offset=0, wcodes=None,
@@ -452,11 +435,8 @@ def qsdp_fused_step_segmented(x, g, segs, lr, wbits, gbits, delta, seed, index_o
     if n_saturated is not None:
         _is(n_saturated, torch.int64)
     segs.check_packed(wcodes, wmeta, wbits)
-    with torch.cuda.device(x.device):
-        _check(lib().qsdp_fused_step_segmented(_ptr(x), _ptr(g), _ptr(segs.device), segs.nseg,
-                                               segs.total_buckets, lr, wbits, gbits, segs.bucket, delta,
-                                               seed, index_offset, _ptr(wcodes), _ptr(wmeta),
-                                               _ptr(n_saturated), _stream(x)), "qsdp_fused_step_segmented")
+    _launch(x, "qsdp_fused_step_segmented", _ptr(x), _ptr(g), _ptr(segs.device), segs.nseg, segs.total_buckets, lr,
+            wbits, gbits, segs.bucket, delta, seed, index_offset, _ptr(wcodes), _ptr(wmeta), _ptr(n_saturated))
 
 
 def qsdp_dequantize_segmented(codes, meta, segs, bits, out):
@@ -467,10 +447,8 @@ def qsdp_dequantize_segmented(codes, meta, segs, bits, out):
         raise ValueError("out is smaller than the segments")
     if codes.numel() * 32 < segs.total_buckets * segs.bucket * bits or meta.numel() < 2 * segs.total_buckets:
         raise ValueError("codes or meta is smaller than the segments")
-    with torch.cuda.device(out.device):
-        _check(lib().qsdp_dequantize_segmented(_ptr(codes), _ptr(meta), _ptr(segs.device), segs.nseg,
-                                               segs.total_buckets, bits, segs.bucket, dt, _ptr(out),
-                                               _stream(out)), "qsdp_dequantize_segmented")
+    _launch(out, "qsdp_dequantize_segmented", _ptr(codes), _ptr(meta), _ptr(segs.device), segs.nseg, segs.total_buckets,
+            bits, segs.bucket, dt, _ptr(out))
 
 
 def qsdp_dequantize_gathered(codes, meta, npeers, n, shard, bits, bucket, out, levels=None):
@@ -485,19 +463,15 @@ def qsdp_dequantize_gathered(codes, meta, npeers, n, shard, bits, bucket, out, l
     if out.numel() < n:
         raise ValueError("out is too small")
     _rows_ok(codes, meta, min(n, shard) if shard > 0 else n, bits, bucket)
-    with torch.cuda.device(out.device):
-        if levels is not None:
-            _is(levels, torch.float32)
-            if levels.numel() != (1 << bits):
-                raise ValueError("levels must hold 2^bits entries")
-            _check(lib().qsdp_dequantize_levels_gathered(_ptr(codes), codes.stride(0) * 4, _ptr(meta),
-                                                         meta.stride(0) * 4, npeers, n, shard, bits, bucket,
-                                                         _ptr(levels), dt, _ptr(out), _stream(out)),
-                   "qsdp_dequantize_levels_gathered")
-            return
-        _check(lib().qsdp_dequantize_gathered(_ptr(codes), codes.stride(0) * 4, _ptr(meta), meta.stride(0) * 4,
-                                              npeers, n, shard, bits, bucket, dt, _ptr(out), _stream(out)),
-               "qsdp_dequantize_gathered")
+    if levels is not None:
+        _is(levels, torch.float32)
+        if levels.numel() != (1 << bits):
+            raise ValueError("levels must hold 2^bits entries")
+        _launch(out, "qsdp_dequantize_levels_gathered", _ptr(codes), codes.stride(0) * 4, _ptr(meta),
+                meta.stride(0) * 4, npeers, n, shard, bits, bucket, _ptr(levels), dt, _ptr(out))
+        return
+    _launch(out, "qsdp_dequantize_gathered", _ptr(codes), codes.stride(0) * 4, _ptr(meta), meta.stride(0) * 4, npeers,
+            n, shard, bits, bucket, dt, _ptr(out))
 
 
 def qsdp_recv_step(x, gcodes, gmeta, npeers, alpha, lr, wbits, gbits, bucket, delta, seed, flags=0, wcodes=None,
@@ -511,10 +485,9 @@ def qsdp_recv_step(x, gcodes, gmeta, npeers, alpha, lr, wbits, gbits, bucket, de
             _is(t, dt)
     _rows_ok(gcodes, gmeta, x.numel(), gbits, bucket)
     _packed_ok(wcodes, wmeta, x.numel(), wbits, bucket)
-    with torch.cuda.device(x.device):
-        _check(lib().qsdp_recv_step(_ptr(x), _ptr(gcodes), gcodes.stride(0) * 4, _ptr(gmeta), gmeta.stride(0) * 4,
-                                    npeers, x.numel(), alpha, lr, wbits, gbits, bucket, delta, seed, flags,
-                                    _ptr(wcodes), _ptr(wmeta), _ptr(n_saturated), _stream(x)), "qsdp_recv_step")
+    _launch(x, "qsdp_recv_step", _ptr(x), _ptr(gcodes), gcodes.stride(0) * 4, _ptr(gmeta), gmeta.stride(0) * 4, npeers,
+            x.numel(), alpha, lr, wbits, gbits, bucket, delta, seed, flags, _ptr(wcodes), _ptr(wmeta),
+            _ptr(n_saturated))
 
 
 def qsdp_recv_adamw_step(x, m, v, gcodes, gmeta, npeers, alpha, lr, beta1, beta2, eps, weight_decay, bias1, bias2,
@@ -532,12 +505,9 @@ def qsdp_recv_adamw_step(x, m, v, gcodes, gmeta, npeers, alpha, lr, beta1, beta2
             _is(t, dt)
     _rows_ok(gcodes, gmeta, x.numel(), gbits, bucket)
     _packed_ok(wcodes, wmeta, x.numel(), wbits, bucket)
-    with torch.cuda.device(x.device):
-        _check(lib().qsdp_recv_adamw_step(_ptr(x), _ptr(m), _ptr(v), _ptr(gcodes), gcodes.stride(0) * 4, _ptr(gmeta),
-                                          gmeta.stride(0) * 4, npeers, x.numel(), alpha, lr, beta1, beta2, eps,
-                                          weight_decay, bias1, bias2, wbits, gbits, bucket, delta, seed, flags,
-                                          _ptr(wcodes), _ptr(wmeta), _ptr(n_saturated), _stream(x)),
-               "qsdp_recv_adamw_step")
+    _launch(x, "qsdp_recv_adamw_step", _ptr(x), _ptr(m), _ptr(v), _ptr(gcodes), gcodes.stride(0) * 4, _ptr(gmeta),
+            gmeta.stride(0) * 4, npeers, x.numel(), alpha, lr, beta1, beta2, eps, weight_decay, bias1, bias2, wbits,
+            gbits, bucket, delta, seed, flags, _ptr(wcodes), _ptr(wmeta), _ptr(n_saturated))
 
 
 def qsdp_recv_step_segmented(x, segs, gcodes, gmeta, npeers, alpha, lr, wbits, gbits, delta, seed, flags=0,
@@ -554,24 +524,19 @@ def qsdp_recv_step_segmented(x, segs, gcodes, gmeta, npeers, alpha, lr, wbits, g
             _is(t, dt)
     segs.check_packed(gcodes, gmeta, gbits, rows=True)
     segs.check_packed(wcodes, wmeta, wbits)
-    with torch.cuda.device(x.device):
-        if adamw is None:
-            _check(lib().qsdp_recv_step_segmented(_ptr(x), _ptr(segs.device), segs.nseg, segs.total_buckets,
-                                                  _ptr(gcodes), gcodes.stride(0) * 4, _ptr(gmeta),
-                                                  gmeta.stride(0) * 4, npeers, alpha, lr, wbits, gbits, segs.bucket,
-                                                  delta, seed, flags, _ptr(wcodes), _ptr(wmeta), _ptr(n_saturated),
-                                                  _stream(x)), "qsdp_recv_step_segmented")
-        else:
-            m, v, b1, b2, eps, wd, c1, c2 = adamw
-            _is(m, torch.float32); _is(v, torch.float32)
-            if m.numel() < segs.n or v.numel() < segs.n:
-                raise ValueError("m or v is smaller than the segments")
-            _check(lib().qsdp_recv_adamw_step_segmented(_ptr(x), _ptr(m), _ptr(v), _ptr(segs.device), segs.nseg,
-                                                        segs.total_buckets, _ptr(gcodes), gcodes.stride(0) * 4,
-                                                        _ptr(gmeta), gmeta.stride(0) * 4, npeers, alpha, lr, b1, b2,
-                                                        eps, wd, c1, c2, wbits, gbits, segs.bucket, delta, seed, flags,
-                                                        _ptr(wcodes), _ptr(wmeta), _ptr(n_saturated), _stream(x)),
-                   "qsdp_recv_adamw_step_segmented")
+    if adamw is None:
+        _launch(x, "qsdp_recv_step_segmented", _ptr(x), _ptr(segs.device), segs.nseg, segs.total_buckets, _ptr(gcodes),
+                gcodes.stride(0) * 4, _ptr(gmeta), gmeta.stride(0) * 4, npeers, alpha, lr, wbits, gbits, segs.bucket,
+                delta, seed, flags, _ptr(wcodes), _ptr(wmeta), _ptr(n_saturated))
+    else:
+        m, v, b1, b2, eps, wd, c1, c2 = adamw
+        _is(m, torch.float32); _is(v, torch.float32)
+        if m.numel() < segs.n or v.numel() < segs.n:
+            raise ValueError("m or v is smaller than the segments")
+        _launch(x, "qsdp_recv_adamw_step_segmented", _ptr(x), _ptr(m), _ptr(v), _ptr(segs.device), segs.nseg,
+                segs.total_buckets, _ptr(gcodes), gcodes.stride(0) * 4, _ptr(gmeta), gmeta.stride(0) * 4, npeers, alpha,
+                lr, b1, b2, eps, wd, c1, c2, wbits, gbits, segs.bucket, delta, seed, flags, _ptr(wcodes), _ptr(wmeta),
+                _ptr(n_saturated))
 
 
 def qsdp_fused_adamw_step_segmented(x, g, m, v, segs, lr, beta1, beta2, eps, weight_decay, bias1, bias2, wbits, gbits,
@@ -584,12 +549,9 @@ def qsdp_fused_adamw_step_segmented(x, g, m, v, segs, lr, beta1, beta2, eps, wei
         if t is not None:
             _is(t, dt)
     segs.check_packed(wcodes, wmeta, wbits)
-    with torch.cuda.device(x.device):
-        _check(lib().qsdp_fused_adamw_step_segmented(_ptr(x), _ptr(g), _ptr(m), _ptr(v), _ptr(segs.device), segs.nseg,
-                                                     segs.total_buckets, lr, beta1, beta2, eps, weight_decay, bias1,
-                                                     bias2, wbits, gbits, segs.bucket, delta, seed, index_offset, flags,
-                                                     _ptr(wcodes), _ptr(wmeta), _ptr(n_saturated), _stream(x)),
-               "qsdp_fused_adamw_step_segmented")
+    _launch(x, "qsdp_fused_adamw_step_segmented", _ptr(x), _ptr(g), _ptr(m), _ptr(v), _ptr(segs.device), segs.nseg,
+            segs.total_buckets, lr, beta1, beta2, eps, weight_decay, bias1, bias2, wbits, gbits, segs.bucket, delta,
+            seed, index_offset, flags, _ptr(wcodes), _ptr(wmeta), _ptr(n_saturated))
 
 
 def qsdp_fused_step_codes_segmented(wcodes, wmeta, g, segs, lr, wbits, gbits, delta, seed, index_offset=0, flags=0,
@@ -600,11 +562,8 @@ def qsdp_fused_step_codes_segmented(wcodes, wmeta, g, segs, lr, wbits, gbits, de
     if n_saturated is not None:
         _is(n_saturated, torch.int64)
     segs.check_packed(wcodes, wmeta, wbits)
-    with torch.cuda.device(g.device):
-        _check(lib().qsdp_fused_step_codes_segmented(_ptr(wcodes), _ptr(wmeta), _ptr(g), _ptr(segs.device), segs.nseg,
-                                                     segs.total_buckets, lr, wbits, gbits, segs.bucket, delta, seed,
-                                                     index_offset, flags, _ptr(n_saturated), _stream(g)),
-               "qsdp_fused_step_codes_segmented")
+    _launch(g, "qsdp_fused_step_codes_segmented", _ptr(wcodes), _ptr(wmeta), _ptr(g), _ptr(segs.device), segs.nseg,
+            segs.total_buckets, lr, wbits, gbits, segs.bucket, delta, seed, index_offset, flags, _ptr(n_saturated))
 
 
 def qsdp_fit_levels_segmented(v, segs, bits, lr, levels, max_batches=0):
@@ -614,9 +573,8 @@ def qsdp_fit_levels_segmented(v, segs, bits, lr, levels, max_batches=0):
         raise ValueError("v is smaller than the segments")
     if levels.numel() != segs.nseg * (1 << bits):
         raise ValueError("levels must hold nseg * 2^bits entries")
-    with torch.cuda.device(v.device):
-        _check(lib().qsdp_fit_levels_segmented(_ptr(v), _ptr(segs.device), segs.nseg, bits, segs.bucket, lr,
-                                               max_batches, _ptr(levels), _stream(v)), "qsdp_fit_levels_segmented")
+    _launch(v, "qsdp_fit_levels_segmented", _ptr(v), _ptr(segs.device), segs.nseg, bits, segs.bucket, lr, max_batches,
+            _ptr(levels))
 
 
 def qsdp_fused_step_dseed(x, g, lr, wbits, gbits, bucket, delta, seed, seed_dev, index_offset=0, flags=0, wcodes=None,
@@ -630,10 +588,8 @@ def qsdp_fused_step_dseed(x, g, lr, wbits, gbits, bucket, delta, seed, seed_dev,
         if t is not None:
             _is(t, dt)
     _packed_ok(wcodes, wmeta, x.numel(), wbits, bucket)
-    with torch.cuda.device(x.device):
-        _check(lib().qsdp_fused_step_dseed(_ptr(x), _ptr(g), x.numel(), lr, wbits, gbits, bucket, delta, seed,
-                                           _ptr(seed_dev), index_offset, flags, _ptr(wcodes), _ptr(wmeta),
-                                           _ptr(n_saturated), _stream(x)), "qsdp_fused_step_dseed")
+    _launch(x, "qsdp_fused_step_dseed", _ptr(x), _ptr(g), x.numel(), lr, wbits, gbits, bucket, delta, seed,
+            _ptr(seed_dev), index_offset, flags, _ptr(wcodes), _ptr(wmeta), _ptr(n_saturated))
 
 
 def qsdp_quantize_levels_segmented(v, segs, bits, levels, codes, meta, stochastic=False, seed=0, index_offset=0):
@@ -644,11 +600,8 @@ def qsdp_quantize_levels_segmented(v, segs, bits, levels, codes, meta, stochasti
     if levels.numel() != segs.nseg * (1 << bits):
         raise ValueError("levels must hold nseg * 2^bits entries")
     segs.check_packed(codes, meta, bits)
-    with torch.cuda.device(v.device):
-        _check(lib().qsdp_quantize_levels_segmented(_ptr(v), _ptr(segs.device), segs.nseg, segs.total_buckets, bits,
-                                                    segs.bucket, _ptr(levels), int(bool(stochastic)), seed,
-                                                    index_offset, _ptr(codes), _ptr(meta), _stream(v)),
-               "qsdp_quantize_levels_segmented")
+    _launch(v, "qsdp_quantize_levels_segmented", _ptr(v), _ptr(segs.device), segs.nseg, segs.total_buckets, bits,
+            segs.bucket, _ptr(levels), int(bool(stochastic)), seed, index_offset, _ptr(codes), _ptr(meta))
 
 
 def qsdp_dequantize_levels_segmented(codes, meta, segs, bits, levels, out):
@@ -660,10 +613,8 @@ def qsdp_dequantize_levels_segmented(codes, meta, segs, bits, levels, out):
     if levels.numel() != segs.nseg * (1 << bits):
         raise ValueError("levels must hold nseg * 2^bits entries")
     segs.check_packed(codes, meta, bits)
-    with torch.cuda.device(out.device):
-        _check(lib().qsdp_dequantize_levels_segmented(_ptr(codes), _ptr(meta), _ptr(segs.device), segs.nseg,
-                                                      segs.total_buckets, bits, segs.bucket, _ptr(levels), dt,
-                                                      _ptr(out), _stream(out)), "qsdp_dequantize_levels_segmented")
+    _launch(out, "qsdp_dequantize_levels_segmented", _ptr(codes), _ptr(meta), _ptr(segs.device), segs.nseg,
+            segs.total_buckets, bits, segs.bucket, _ptr(levels), dt, _ptr(out))
 
 
 
@@ -676,9 +627,8 @@ def qsdp_quantize_grad_g16(g, bits, bucket, seed, index_offset, codes, meta, fla
         raise TypeError("g must be float16 or bfloat16")
     _is(g, g.dtype); _is(codes, torch.int32); _is(meta, torch.float32)
     _packed_ok(codes, meta, g.numel(), bits, bucket)
-    with torch.cuda.device(g.device):
-        _check(lib().qsdp_quantize_grad_g16(_ptr(g), _G16[g.dtype], g.numel(), bits, bucket, seed, index_offset, flags,
-                                            _ptr(codes), _ptr(meta), _stream(g)), "qsdp_quantize_grad_g16")
+    _launch(g, "qsdp_quantize_grad_g16", _ptr(g), _G16[g.dtype], g.numel(), bits, bucket, seed, index_offset, flags,
+            _ptr(codes), _ptr(meta))
 
 
 def qsdp_fused_step_g16(x, g, lr, wbits, gbits, bucket, delta, seed, index_offset=0, flags=0, wcodes=None, wmeta=None,
@@ -693,10 +643,8 @@ def qsdp_fused_step_g16(x, g, lr, wbits, gbits, bucket, delta, seed, index_offse
         if t is not None:
             _is(t, dt)
     _packed_ok(wcodes, wmeta, x.numel(), wbits, bucket)
-    with torch.cuda.device(x.device):
-        _check(lib().qsdp_fused_step_g16(_ptr(x), _ptr(g), _G16[g.dtype], x.numel(), lr, wbits, gbits, bucket, delta,
-                                         seed, index_offset, flags, _ptr(wcodes), _ptr(wmeta), _ptr(n_saturated),
-                                         _stream(x)), "qsdp_fused_step_g16")
+    _launch(x, "qsdp_fused_step_g16", _ptr(x), _ptr(g), _G16[g.dtype], x.numel(), lr, wbits, gbits, bucket, delta, seed,
+            index_offset, flags, _ptr(wcodes), _ptr(wmeta), _ptr(n_saturated))
 
 
 def qsdp_fused_adamw_step_codes(wcodes, wmeta, g, m, v, lr, beta1, beta2, eps, weight_decay, bias1, bias2, wbits, gbits,
@@ -710,11 +658,8 @@ def qsdp_fused_adamw_step_codes(wcodes, wmeta, g, m, v, lr, beta1, beta2, eps, w
     if n_saturated is not None:
         _is(n_saturated, torch.int64)
     _packed_ok(wcodes, wmeta, n, wbits, bucket)
-    with torch.cuda.device(g.device):
-        _check(lib().qsdp_fused_adamw_step_codes(_ptr(wcodes), _ptr(wmeta), _ptr(g), _ptr(m), _ptr(v), n, lr, beta1,
-                                                 beta2, eps, weight_decay, bias1, bias2, wbits, gbits, bucket, delta,
-                                                 seed, index_offset, flags, _ptr(n_saturated), _stream(g)),
-               "qsdp_fused_adamw_step_codes")
+    _launch(g, "qsdp_fused_adamw_step_codes", _ptr(wcodes), _ptr(wmeta), _ptr(g), _ptr(m), _ptr(v), n, lr, beta1, beta2,
+            eps, weight_decay, bias1, bias2, wbits, gbits, bucket, delta, seed, index_offset, flags, _ptr(n_saturated))
 
 
 def qsdp_fused_step_mp(x, g, lr, wbits, gbits, bucket, delta, seed, index_offset=0, flags=0, wcodes=None, wmeta=None,
@@ -738,10 +683,8 @@ def qsdp_fused_step_mp(x, g, lr, wbits, gbits, bucket, delta, seed, index_offset
         if t is not None:
             _is(t, dt)
     _packed_ok(wcodes, wmeta, x.numel(), wbits, bucket)
-    with torch.cuda.device(x.device):
-        _check(lib().qsdp_fused_step_mp(_ptr(x), _ptr(g), gdt, x.numel(), lr, wbits, gbits, bucket, delta, seed,
-                                        index_offset, flags, _ptr(wcodes), _ptr(wmeta), _ptr(x16), xdt,
-                                        _ptr(n_saturated), _stream(x)), "qsdp_fused_step_mp")
+    _launch(x, "qsdp_fused_step_mp", _ptr(x), _ptr(g), gdt, x.numel(), lr, wbits, gbits, bucket, delta, seed,
+            index_offset, flags, _ptr(wcodes), _ptr(wmeta), _ptr(x16), xdt, _ptr(n_saturated))
 
 
 def qsdp_fused_step_segmented_mp(x, g, segs, lr, wbits, gbits, delta, seed, index_offset=0, flags=0, wcodes=None,
@@ -763,11 +706,9 @@ def qsdp_fused_step_segmented_mp(x, g, segs, lr, wbits, gbits, delta, seed, inde
         if t is not None:
             _is(t, dt)
     segs.check_packed(wcodes, wmeta, wbits)
-    with torch.cuda.device(x.device):
-        _check(lib().qsdp_fused_step_segmented_mp(_ptr(x), _ptr(g), gdt, _ptr(segs.device), segs.nseg,
-                                                  segs.total_buckets, lr, wbits, gbits, segs.bucket, delta, seed,
-                                                  index_offset, flags, _ptr(wcodes), _ptr(wmeta), _ptr(x16), xdt,
-                                                  _ptr(n_saturated), _stream(x)), "qsdp_fused_step_segmented_mp")
+    _launch(x, "qsdp_fused_step_segmented_mp", _ptr(x), _ptr(g), gdt, _ptr(segs.device), segs.nseg, segs.total_buckets,
+            lr, wbits, gbits, segs.bucket, delta, seed, index_offset, flags, _ptr(wcodes), _ptr(wmeta), _ptr(x16), xdt,
+            _ptr(n_saturated))
 
 
 def qsdp_fused_adamw_step_mp(x, g, m, v, lr, beta1, beta2, eps, weight_decay, bias1, bias2, wbits, gbits, bucket, delta,
@@ -792,11 +733,9 @@ def qsdp_fused_adamw_step_mp(x, g, m, v, lr, beta1, beta2, eps, weight_decay, bi
         if t is not None:
             _is(t, dt)
     _packed_ok(wcodes, wmeta, n, wbits, bucket)
-    with torch.cuda.device(x.device):
-        _check(lib().qsdp_fused_adamw_step_mp(_ptr(x), _ptr(g), gdt, _ptr(m), _ptr(v), n, lr, beta1, beta2, eps,
-                                              weight_decay, bias1, bias2, wbits, gbits, bucket, delta, seed,
-                                              index_offset, flags, _ptr(wcodes), _ptr(wmeta), _ptr(x16), xdt,
-                                              _ptr(n_saturated), _stream(x)), "qsdp_fused_adamw_step_mp")
+    _launch(x, "qsdp_fused_adamw_step_mp", _ptr(x), _ptr(g), gdt, _ptr(m), _ptr(v), n, lr, beta1, beta2, eps,
+            weight_decay, bias1, bias2, wbits, gbits, bucket, delta, seed, index_offset, flags, _ptr(wcodes),
+            _ptr(wmeta), _ptr(x16), xdt, _ptr(n_saturated))
 
 
 class StepOptions(C.Structure):
@@ -848,9 +787,8 @@ def _step_opts(entry, x, g, lr, wbits, gbits, bucket, delta, seed, index_offset,
         _is(m, torch.float32); _is(v, torch.float32)
         _need(m, n, "m"); _need(v, n, "v")
         o.m, o.v = m.data_ptr(), v.data_ptr()
-    with torch.cuda.device(x.device):
-        _check(getattr(lib(), entry)(_ptr(x), _ptr(g), 0 if segs is not None else n, lr, wbits, gbits, bucket, delta,
-                                     seed, index_offset, C.byref(o), _stream(x)), entry)
+    _launch(x, entry, _ptr(x), _ptr(g), 0 if segs is not None else n, lr, wbits, gbits, bucket, delta, seed,
+            index_offset, C.byref(o))
 
 
 def qsdp_fused_step_opts(x, g, lr, wbits, gbits, bucket, delta, seed, index_offset=0, flags=0, segs=None, x16=None,
