@@ -23,17 +23,28 @@ typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------------------------------
 // Philox4x32-10 (Salmon et al., SC'11). The key is wave-uniform, so its schedule lives in
-// scalar registers; each round costs two 32x32->64 multiplies and three xors per lane.
+// scalar registers; each round costs two 32x32->64 multiplies and two three-operand xors per lane.
+// XOR3: an xor of three operands as one v_bitop3_b32 (the compiler makes two v_xor_b32 of it). For the kernels that
+// their instructions bind: 48.6M values, 3 bits from bf16, 34.2 -> 31.2 us; 100M, 2 bits from fp32, 71 -> 66.6;
+// coin flip onto levels 2 %. The kernels that memory binds got slower with it (fused step over the 1.3B vector 2.53
+// -> 2.56 ms, code-resident step over 350M 371 -> 382 us, 8-bit gradients 80.5 -> 83.4) and keep the two xors.
 // ---------------------------------------------------------------------------------------
+template <bool XOR3>
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+    if constexpr (XOR3) return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);  // truth table of a ^ b ^ c
+    return a ^ b ^ c;
+}
+
+template <bool XOR3 = false>
 __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                               uint32_t k0, uint32_t k1, uint32_t (&out)[4]) {
 #pragma unroll
     for (int round = 0; round < 10; ++round) {
         const uint64_t p0 = (uint64_t)0xD2511F53u * (uint64_t)c0;
         const uint64_t p1 = (uint64_t)0xCD9E8D57u * (uint64_t)c2;
-        const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0;
+        const uint32_t n0 = xor3<XOR3>((uint32_t)(p1 >> 32), c1, k0);
         const uint32_t n1 = (uint32_t)p1;
-        const uint32_t n2 = (uint32_t)(p0 >> 32) ^ c3 ^ k1;
+        const uint32_t n2 = xor3<XOR3>((uint32_t)(p0 >> 32), c3, k1);
         const uint32_t n3 = (uint32_t)p0;
         c0 = n0; c1 = n1; c2 = n2; c3 = n3;
         k0 += 0x9E3779B9u;
@@ -47,9 +58,10 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
 // row: the even lane computes the block of the pair's first row, the odd lane that of its second row
 // (`block` is the lane's own), and the pair swaps the halves the other needs.
 // h[0..1] serve the first row, h[2..3] the second.
+template <bool XOR3 = false>
 __device__ __forceinline__ void uniforms_of_pair(uint64_t block, int odd, uint32_t k0, uint32_t k1, uint32_t (&h)[4]) {
     uint32_t w[4];
-    philox4x32_10((uint32_t)block, (uint32_t)(block >> 32), 0u, 0u, k0, k1, w);
+    philox4x32_10<XOR3>((uint32_t)block, (uint32_t)(block >> 32), 0u, 0u, k0, k1, w);
     const uint32_t send0 = odd ? w[0] : w[2];
     const uint32_t send1 = odd ? w[1] : w[3];
     // every lane has a partner, so the destination's previous value never shows
@@ -61,11 +73,11 @@ __device__ __forceinline__ void uniforms_of_pair(uint64_t block, int odd, uint32
 
 // The same for rows 2c and 2c+1 of a bucket whose lane l holds elements (r*G + l)*4 .. +3 of every row r.
 // bucket_block = index of the bucket's first block.
-template <int G>
+template <int G, bool XOR3 = false>
 __device__ __forceinline__ void grad_uniforms_rows(uint64_t bucket_block, int c, int l, uint32_t k0,
                                                    uint32_t k1, uint32_t (&h)[4]) {
     const int odd = l & 1;
-    uniforms_of_pair(bucket_block + (uint64_t)(((2 * c + odd) * G + (l - odd)) >> 1), odd, k0, k1, h);
+    uniforms_of_pair<XOR3>(bucket_block + (uint64_t)(((2 * c + odd) * G + (l - odd)) >> 1), odd, k0, k1, h);
 }
 
 // The 16-bit uniform of element i (0..7) of a row pair out of the packed words above.

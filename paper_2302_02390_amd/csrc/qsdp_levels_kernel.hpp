@@ -140,7 +140,7 @@ __device__ __forceinline__ void encode_levels_by(const float (&v)[R][4], uint32_
 #pragma unroll
         for (int cp = 0; cp < R / 2; ++cp) {
             uint32_t h[4];
-            grad_uniforms_rows<G>(block_e0, cp, l, key.k0, key.k1, h);
+            grad_uniforms_rows<G, true>(block_e0, cp, l, key.k0, key.k1, h);
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 const int r = 2 * cp + (i >> 2);

@@ -271,7 +271,7 @@ __global__ void __launch_bounds__(256) tile_kernel(const Params p, const Segment
         auto uniforms = [&](int cp, uint32_t (&h)[4]) {
             const int slot = (2 * cp + odd) * TEAM + tid - odd;
             const uint32_t rel = __builtin_expect(whole, 1) ? (uint32_t)slot * 4u : place(slot).rel;
-            uniforms_of_pair(p.block0 + (e0 >> 3) + (rel >> 3), odd, key.k0, key.k1, h);
+            uniforms_of_pair<(MODE == MODE_GRAD || MODE == MODE_LEVELS_COIN)>(p.block0 + (e0 >> 3) + (rel >> 3), odd, key.k0, key.k1, h);
         };
         // Minimum and maximum of every bucket of the tile, then its grid: make(lo, hi, bucket in the tile) in the
         // lanes that combine that bucket, the result in lds.grid for all.

@@ -495,7 +495,7 @@ __global__ void __launch_bounds__(256, mode_min_blocks(MODE)) wave_kernel(const 
 #pragma unroll
                 for (int cp = 0; cp < R / 2; ++cp) {
                     uint32_t h[4];
-                    grad_uniforms_rows<G>(block_e0, cp, l, key.k0, key.k1, h);
+                    grad_uniforms_rows<G, (MODE == MODE_GRAD && BITS <= 4)>(block_e0, cp, l, key.k0, key.k1, h);
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
                         const int r = 2 * cp + (i >> 2);
