@@ -210,7 +210,8 @@ int run(int mode, Params p, int stored_bits, hipStream_t s) {
     } else {
         const TilePlan t = tile_plan(p.bucket);
         const uint64_t units = ceil_div(nb, (uint64_t)t.buckets);
-        const uint64_t blocks = t.waves == 1 ? ceil_div(units, 4) : units;
+        uint64_t blocks = t.waves == 1 ? ceil_div(units, 4) : units;
+        if (mode_is_levels(mode)) blocks = level_blocks(mode, blocks, 4);
         const TileArgs a = {units, t.buckets, t.lanes_log2, t.group_magic, word_magic(stored_bits > 0 ? stored_bits : 8)};
         if (tile_launcher(t)(mode, p, a, capped_grid(blocks), s) != hipSuccess) return QSDP_ELAUNCH;
     }

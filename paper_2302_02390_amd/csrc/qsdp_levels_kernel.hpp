@@ -62,18 +62,16 @@ __device__ __forceinline__ LevelCell level_cell(const float* bounds, int kb, int
     return e;
 }
 
-// Threshold k of the scaled levels lv; false if there is none to rely on: the comparison of the rounded distances is monotone
+// Threshold k of the K levels lv, scaled by `unit`; false if there is none to rely on: the comparison of the rounded distances is monotone
 // in z over the whole unit interval if the levels lie in it and the two are more than 2^-20 apart (the distances differ by the
 // gap outside the two levels, and each is rounded by less than 2^-24), and it flips within two steps of the midpoint (only
 // the distance to a level below z/2 is rounded at all, by half a step). In a run of equal levels every threshold is that
 // of the run's end, so that its first level is the only one that is ever chosen.
-template <int BITS>
-__device__ __forceinline__ bool level_threshold(const float* lv, int k, float* threshold) {
-    constexpr float unit = LevelShape<BITS>::kScale;
+__device__ __forceinline__ bool level_threshold(const float* lv, int k, int K, float unit, float* threshold) {
     const float lo = lv[k];
     int next = k + 1;
-    while (next < LevelShape<BITS>::K && lv[next] == lo) ++next;
-    if (next == LevelShape<BITS>::K) {
+    while (next < K && lv[next] == lo) ++next;
+    if (next == K) {
         *threshold = __builtin_inff();
         return lo >= 0.0f && lo <= unit;
     }
@@ -97,6 +95,9 @@ __device__ __forceinline__ bool level_threshold(const float* lv, int k, float* t
 struct LevelCoin {
     float q, rgap16;
 };
+__device__ __forceinline__ LevelCoin level_coin(const float* lv, int k, int K) {
+    return {lv[k], k + 1 < K ? (1.0f / (lv[k + 1] - lv[k])) * 65536.0f : 0.0f};
+}
 
 // The bounds' first pivots. All lanes read the same addresses, so the values are wave-uniform and can live in SGPRs.
 struct LevelPivots {
@@ -257,13 +258,10 @@ __global__ void __launch_bounds__(256, QSDP_LEVELS_MIN_BLOCKS) levels_kernel(con
         __syncthreads();
         int method = LEVELS_BY_CELL;  // workgroup-uniform
         if constexpr (kCoin) {
-            for (int k = threadIdx.x; k < K; k += kThreads) {
-                const LevelCoin e = {levels[k], k + 1 < K ? (1.0f / (levels[k + 1] - levels[k])) * 65536.0f : 0.0f};
-                coin[k] = e;
-            }
+            for (int k = threadIdx.x; k < K; k += kThreads) coin[k] = level_coin(levels, k, K);
         } else {
             bool unusable = false;
-            for (int k = threadIdx.x; k < K - 1; k += kThreads) unusable = !level_threshold<BITS>(levels, k, thresholds + k) || unusable;
+            for (int k = threadIdx.x; k < K - 1; k += kThreads) unusable = !level_threshold(levels, k, K, LevelShape<BITS>::kScale, thresholds + k) || unusable;
             if (__syncthreads_or(unusable)) method = LEVELS_PLAIN;
         }
         bool crowded = false, jumps = false;

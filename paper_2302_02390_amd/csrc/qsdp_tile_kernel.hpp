@@ -16,7 +16,7 @@
 #pragma once
 
 #include "qsdp_params.hpp"
-#include "qsdp_wave_kernel.hpp"  // widen16
+#include "qsdp_levels_kernel.hpp"  // the level tables; widen16
 
 namespace qsdp {
 
@@ -60,7 +60,7 @@ __device__ __forceinline__ void lanes_minmax(float& lo, float& hi, int log2) {
     }
 }
 
-// Code of z among the K = 2^bits levels lv (LDS or global memory), by the plain definitions: nearest level (ties and
+// Code of z among the K = 2^bits levels lv, by the plain definitions: nearest level (ties and
 // equal levels: the lowest index) ...
 __device__ __forceinline__ uint32_t nearest_level_any(float z, const float* lv, int K) {
     int j = 0;  // ends as the number of levels < z among the first K-1
@@ -86,6 +86,21 @@ __device__ __forceinline__ uint32_t stochastic_level_any(float z, float h, const
     return (uint32_t)i + ((65535.5f - h) < p * 65536.0f ? 1u : 0u);
 }
 
+// The tables of a learned-level encoder for the tensor that a team works on (see qsdp_levels_kernel.hpp), with the code width
+// a run-time value: levels and bounds in units of 1/256, a count by cell, by search where the cells are crowded. A team
+// takes a run of tiles and sets them up once per tensor. One table, us, against a search and two distances per value:
+// 113M values in buckets of 1472, 4 bits 204 -> 116; 27M, 1568, 2 bits 60 -> 29; 125M, 4128, 5 bits 325 -> 137; coin flip,
+// 125M, 608, 4 bits 229 -> 196. With a table per tensor the tiles that tensors share take a pass and a set-up for each
+// (113M 203 -> 120; 33M in 184 tensors, buckets of 96, 81 -> 69).
+template <bool COIN>
+struct TileLevels {
+    static constexpr int C = 256;
+    float levels[256];
+    float thresholds[COIN ? 1 : 256];
+    LevelCoin coin[COIN ? 256 : 1];
+    LevelCell cells[C + 1];
+};
+
 // What the launch adds to Params: the number of tiles (a 64-bit division in every wave's prologue otherwise), the
 // tile's shape (see TilePlan) and ceil(2^18 / width) of the stored codes.
 struct TileArgs {
@@ -102,12 +117,14 @@ __global__ void __launch_bounds__(256) tile_kernel(const Params p, const Segment
     constexpr bool kWritesX = MODE == MODE_FUSED || MODE == MODE_ADAMW || mode_is_recv(MODE);
     constexpr bool kLevels = mode_is_levels(MODE);
     __shared__ Lds lds_all[4 / W];
-    __shared__ float level_tables[kLevels ? 4 / W : 1][kLevels ? 256 : 1];
+    constexpr bool kCoin = MODE == MODE_LEVELS_COIN;
+    __shared__ char level_lds[kLevels ? 4 / W * sizeof(TileLevels<kCoin>) : 1] __attribute__((aligned(16)));
     const uint32_t wave_in_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int tid = W == 1 ? (int)(threadIdx.x & 63) : (int)threadIdx.x;
     Lds& lds = lds_all[W == 1 ? wave_in_block : 0];
-    float* level_table = level_tables[W == 1 ? (kLevels ? wave_in_block : 0) : 0];
+    TileLevels<kCoin>& lt = reinterpret_cast<TileLevels<kCoin>*>(level_lds)[W == 1 && kLevels ? wave_in_block : 0];
     uint32_t loaded_tensor = ~0u;  // whose level table the team holds
+    bool level_by_cell = false;    // ... and how it is used
 
     const int B = p.bucket;
     const int k = B >> 5;      // groups of a bucket
@@ -126,13 +143,20 @@ __global__ void __launch_bounds__(256) tile_kernel(const Params p, const Segment
     const float xi = shifts.xi;
     uint32_t saturated = 0;
 
-    const uint64_t unit0 = W == 1 ? (uint64_t)blockIdx.x * 4u + wave_in_block : blockIdx.x;
-    const uint64_t unit_stride = W == 1 ? (uint64_t)gridDim.x * 4u : gridDim.x;
+    uint64_t unit0 = W == 1 ? (uint64_t)blockIdx.x * 4u + wave_in_block : blockIdx.x;
+    uint64_t unit_stride = W == 1 ? (uint64_t)gridDim.x * 4u : gridDim.x;
+    uint64_t unit_end = a.tiles;
+    if constexpr (kLevels) {  // a run of tiles: the tables are set up once per tensor and run
+        const uint64_t run = (a.tiles + unit_stride - 1) / unit_stride;
+        unit0 *= run;
+        unit_end = unit0 + run < a.tiles ? unit0 + run : a.tiles;
+        unit_stride = 1;
+    }
     // row r of this lane: its slot; bucket of a slot in the tile
     auto slot_of = [&](int r) { return r * TEAM + tid; };
     auto bucket_of_slot = [&](int slot) { return (int)(((uint32_t)slot >> 3) * a.group_magic >> 16); };
 
-    for (uint64_t unit = unit0; unit < a.tiles; unit += unit_stride) {
+    for (uint64_t unit = unit0; unit < unit_end; unit += unit_stride) {
         // keeps what follows from the lane's number alone (slots, buckets, offsets of every row) out of registers that
         // live across the loop
         asm volatile("" : "+v"(tid));
@@ -501,49 +525,92 @@ __global__ void __launch_bounds__(256) tile_kernel(const Params p, const Segment
         // the full-precision partition keeps the updated value itself
         if (kWritesX && keep_master) store(p.x, w);
 
-        uint32_t code[R][4];
+        uint32_t code[R][4] = {};
         if constexpr (kLevels) {
             const int K = 1 << p.wbits;
-            const uint32_t tensor = p.levels_per_tensor != 0u ? first.tensor : 0u;
-            if (whole && tensor != loaded_tensor) {  // the tile lies in one tensor: its table comes into LDS
-                team_sync<W>();
-                for (int i = tid; i < K; i += TEAM) level_table[i] = p.levels[(uint64_t)tensor * K + i];
-                loaded_tensor = tensor;
-            }
-            bucket_grids(w, [&](float lo, float hi, int b) -> f4 {  // (its barriers publish the table too)
+            constexpr int C = TileLevels<kCoin>::C;
+            bucket_grids(w, [&](float lo, float hi, int b) -> f4 {
                 const MinMaxGrid g = make_minmax_grid(lo, hi, 1.0f, false);
                 write_meta(b, g.lo, g.scale);
-                return f4{g.lo, g.inv, 0.0f, 0.0f};
+                return f4{g.lo, g.inv * (float)C, 0.0f, 0.0f};
             });
-#pragma unroll
-            for (int cp = 0; cp < R / 2; ++cp) {
-                uint32_t h[4] = {0u, 0u, 0u, 0u};
-                if constexpr (MODE == MODE_LEVELS_COIN) uniforms(cp, h);
-#pragma unroll
-                for (int half = 0; half < 2; ++half) {
-                    const int r = 2 * cp + half;
-                    const int b = bucket_of_slot(slot_of(r));
-                    const f4 gr = lds.grid[b];
-                    if (__builtin_expect(whole, 1)) {
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const float z = (w[r][i] - gr[0]) * gr[1];
-                            code[r][i] = MODE == MODE_LEVELS_COIN
-                                             ? stochastic_level_any(z, (float)uniform16(h, 4 * half + i), level_table, K)
-                                             : nearest_level_any(z, level_table, K);
+            // One pass per tensor of the tile (one for nearly all): its tables come into LDS, its buckets keep their codes.
+            uint32_t tensor = p.levels_per_tensor != 0u ? first.tensor : 0u, last_tensor = tensor;
+            if (__builtin_expect(!whole, 0) && p.levels_per_tensor != 0u)
+                last_tensor = __builtin_amdgcn_readfirstlane(lds.where[here - 1][2]);
+            const bool single = tensor == last_tensor;
+            for (;; ++tensor) {
+                asm volatile("" : "+v"(tid));  // keeps values and uniforms of all rows from being held across the passes
+                if (tensor != loaded_tensor) {
+                    auto any = [](bool c) -> bool {
+                        if constexpr (W == 1) {
+                            team_sync<W>();
+                            return __builtin_amdgcn_ballot_w64(c) != 0;
+                        } else {
+                            return __syncthreads_or(c) != 0;
                         }
-                    } else {  // a tile over several tensors reads each one's table where it is
-                        const float* table = p.levels;
-                        if (p.levels_per_tensor != 0u) table += (uint64_t)(b < here ? lds.where[b][2] : 0u) * K;
+                    };
+                    team_sync<W>();
+                    for (int i = tid; i < K; i += TEAM) lt.levels[i] = p.levels[(uint64_t)tensor * K + i] * (float)C;
+                    team_sync<W>();
+                    bool unusable = false, crowded = false, jumps = false;
+                    if constexpr (kCoin) {
+                        for (int i = tid; i < K; i += TEAM) lt.coin[i] = level_coin(lt.levels, i, K);
+                    } else {
+                        for (int i = tid; i < K - 1; i += TEAM)
+                            unusable = !level_threshold(lt.levels, i, K, (float)C, lt.thresholds + i) || unusable;
+                    }
+                    unusable = any(unusable);
+                    const float* bounds = kCoin ? lt.levels + 1 : lt.thresholds;
+                    for (int c = tid; c <= C; c += TEAM) lt.cells[c] = level_cell(bounds, K - 1, c, crowded, jumps);
+                    level_by_cell = !any(crowded) && !unusable;
+                    loaded_tensor = tensor;
+                }
+                // by cell, by search and by search for some of the buckets are loops of their own, so that each is
+                // straight-line code over the rows
+                auto encode = [&](auto mine, auto code_of) {
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const float z = (w[r][i] - gr[0]) * gr[1];
-                            code[r][i] = MODE == MODE_LEVELS_COIN
-                                             ? stochastic_level_any(z, (float)uniform16(h, 4 * half + i), table, K)
-                                             : nearest_level_any(z, table, K);
+                    for (int cp = 0; cp < R / 2; ++cp) {
+                        uint32_t h[4] = {0u, 0u, 0u, 0u};
+                        if constexpr (kCoin) uniforms(cp, h);
+#pragma unroll
+                        for (int half = 0; half < 2; ++half) {
+                            const int r = 2 * cp + half;
+                            const int b = bucket_of_slot(slot_of(r));
+                            const f4 gr = lds.grid[b];
+                            if (mine(b)) {
+#pragma unroll
+                                for (int i = 0; i < 4; ++i)
+                                    code[r][i] = code_of((w[r][i] - gr[0]) * gr[1], (float)uniform16(h, 4 * half + i));
+                            }
                         }
                     }
+                };
+                auto every = [](int) { return true; };
+                auto search = [&](float z, float h) -> uint32_t {
+                    return kCoin ? stochastic_level_any(z, h, lt.levels, K) : nearest_level_any(z, lt.levels, K);
+                };
+                auto lookup = [&](float z, float h) -> uint32_t {
+                    const uint32_t c = (uint32_t)z;
+                    const LevelCell e = lt.cells[c < (uint32_t)C ? c : (uint32_t)C];
+                    const uint32_t n = (e.count & 0xFFFFu) + (e.next <= z ? (e.count >> 16) + 1u : 0u);
+                    if constexpr (!kCoin) return n;
+                    const LevelCoin l = lt.coin[n];
+                    return n + (65535.5f - h < (z - l.q) * l.rgap16 ? 1u : 0u);
+                };
+                if (__builtin_expect(single && level_by_cell, 1)) {
+                    encode(every, lookup);
+                    break;
                 }
+                if (single) {
+                    encode(every, search);
+                    break;
+                }
+                encode([&](int b) { return b < here && lds.where[b][2] == tensor; },
+                       [&](float z, float h) {  // the coin flip's lookup would cost this path too many registers
+                           return !kCoin && level_by_cell ? lookup(z, h) : search(z, h);
+                       });
+                if (tensor == last_tensor) break;
             }
             store_words(code, p.wbits);
             continue;

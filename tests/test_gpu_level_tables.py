@@ -37,7 +37,7 @@ def _values(n, B, table, rng):
     return x
 
 
-@pytest.mark.parametrize("B", [32, 128, 256, 512, 1024, 2048, 4096])
+@pytest.mark.parametrize("B", [32, 96, 128, 256, 512, 608, 1024, 2048, 2080, 4096, 8192])
 @pytest.mark.parametrize("bits", range(1, 9))
 def test_tables(bits, B):
     rng = np.random.default_rng(100 * bits + B)
@@ -56,7 +56,7 @@ def test_tables(bits, B):
 
 
 @pytest.mark.parametrize("grid", [None, "1", "7"])
-@pytest.mark.parametrize("B", [128, 512, 1024, 2048, 4096])
+@pytest.mark.parametrize("B", [96, 128, 512, 608, 1024, 2048, 2080, 4096])
 @pytest.mark.parametrize("bits", [3, 5, 7])
 def test_workgroups_that_cross_tensors(bits, B, grid, monkeypatch):
     """Runs of buckets with several tensors in them, each with another kind of table, also with few workgroups."""
