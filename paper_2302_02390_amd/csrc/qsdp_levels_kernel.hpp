@@ -19,7 +19,8 @@ namespace qsdp {
 //   * coin flip: the lower enclosing level i. Bound k is the level k+1. A second LDS read fetches level i and the
 //     reciprocal of its gap.
 // Bounds, levels and values are in "cell units", scaled by the number of cells C, a power of two, so all comparisons,
-// differences and products are the unscaled ones times an exact power of two and decide alike, bit for bit.
+// differences and products are the unscaled ones times an exact power of two and decide alike, bit for bit (but for
+// normalised values below 2^-126, which the scaling saves from being rounded to subnormals).
 //   * Counting by cell: for each of the C cells of the unit interval a table holds how many bounds lie at or below its
 //     start and the next bound. If no cell holds two different bounds, a count is one LDS read and one comparison. (Equal
 //     bounds, from equal levels, are passed all at once: the table also holds how many there are.)
@@ -89,14 +90,21 @@ __device__ __forceinline__ bool level_threshold(const float* lv, int k, int K, f
     return found && hi - lo > 0x1p-20f * unit && lo >= 0.0f && hi <= unit;
 }
 
-// What the coin flip needs at level i: the level (cell units) and 2^16 times the reciprocal of the gap to the next
-// one (per cell unit; 0 for the last level: nothing to round up to). The reciprocal of a scaled gap is the unscaled one
-// divided by C, exactly, so (z - q) * rgap16 is 2^16 times the unscaled product bit for bit.
+// What the coin flip needs at level i: the level (cell units) and the reciprocal of the gap to the next one (per cell
+// unit; 0 for the last level: nothing to round up to). The reciprocal is that of the unscaled gap, rounded (or infinite)
+// as the definition has it, then divided by `cells`, exactly: (z - q) * rgap is the unscaled product bit for bit.
 struct LevelCoin {
-    float q, rgap16;
+    float q, rgap;
 };
-__device__ __forceinline__ LevelCoin level_coin(const float* lv, int k, int K) {
-    return {lv[k], k + 1 < K ? (1.0f / (lv[k + 1] - lv[k])) * 65536.0f : 0.0f};
+__device__ __forceinline__ LevelCoin level_coin(const float* lv, int k, int K, float cells) {
+    const float per_cell = 1.0f / cells;
+    return {lv[k], k + 1 < K ? (1.0f / ((lv[k + 1] - lv[k]) * per_cell)) * per_cell : 0.0f};
+}
+
+// Whether the coin flip goes up: 2^16 - (h + 1/2) < 2^16 p for the 16-bit uniform h and p = (z - q) * rgap. Both sides are
+// taken at 2^-16 of that, where the left one is exact and the right one cannot overflow for small gaps.
+__device__ __forceinline__ bool coin_up(float z, float h, LevelCoin e) {
+    return fmaf(h, -0x1p-16f, 1.0f - 0x1p-17f) < (z - e.q) * e.rgap;
 }
 
 // The bounds' first pivots. All lanes read the same addresses, so the values are wave-uniform and can live in SGPRs.
@@ -151,7 +159,7 @@ __device__ __forceinline__ void encode_levels_by(const float (&v)[R][4], uint32_
                 // last K-1 (its reciprocal gap is 0).
                 const uint32_t at = count_bounds<BITS, METHOD>(z, bounds, cells, pivots);
                 const LevelCoin e = coin[at];
-                code[r][i & 3] = at + (65535.5f - (float)uniform16(h, i) < (z - e.q) * e.rgap16 ? 1u : 0u);
+                code[r][i & 3] = at + (coin_up(z, (float)uniform16(h, i), e) ? 1u : 0u);
             }
         }
     } else {
@@ -258,7 +266,7 @@ __global__ void __launch_bounds__(256, QSDP_LEVELS_MIN_BLOCKS) levels_kernel(con
         __syncthreads();
         int method = LEVELS_BY_CELL;  // workgroup-uniform
         if constexpr (kCoin) {
-            for (int k = threadIdx.x; k < K; k += kThreads) coin[k] = level_coin(levels, k, K);
+            for (int k = threadIdx.x; k < K; k += kThreads) coin[k] = level_coin(levels, k, K, LevelShape<BITS>::kScale);
         } else {
             bool unusable = false;
             for (int k = threadIdx.x; k < K - 1; k += kThreads) unusable = !level_threshold(levels, k, K, LevelShape<BITS>::kScale, thresholds + k) || unusable;

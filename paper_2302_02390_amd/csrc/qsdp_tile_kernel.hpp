@@ -72,8 +72,9 @@ __device__ __forceinline__ uint32_t nearest_level_any(float z, const float* lv, 
     return (uint32_t)c;
 }
 
-// ... or the coin flip between the two enclosing levels, h the element's 16-bit uniform.
-__device__ __forceinline__ uint32_t stochastic_level_any(float z, float h, const float* lv, int K) {
+// ... or the coin flip between the two enclosing levels, h the element's 16-bit uniform; z and the levels in units of
+// 1/cells.
+__device__ __forceinline__ uint32_t stochastic_level_any(float z, float h, const float* lv, int K, float cells) {
     int cnt = 0;  // levels <= z among the first K-1, then the last one
     for (int step = K >> 1; step >= 1; step >>= 1)
         if (lv[cnt + step - 1] <= z) cnt += step;
@@ -81,9 +82,7 @@ __device__ __forceinline__ uint32_t stochastic_level_any(float z, float h, const
     if (cnt == 0) return 0u;
     const int i = cnt - 1;
     if (i == K - 1) return (uint32_t)i;
-    const float q = lv[i];
-    const float p = (z - q) * (1.0f / (lv[i + 1] - q));
-    return (uint32_t)i + ((65535.5f - h) < p * 65536.0f ? 1u : 0u);
+    return (uint32_t)i + (coin_up(z, h, level_coin(lv, i, K, cells)) ? 1u : 0u);
 }
 
 // The tables of a learned-level encoder for the tensor that a team works on (see qsdp_levels_kernel.hpp), with the code width
@@ -555,7 +554,7 @@ __global__ void __launch_bounds__(256) tile_kernel(const Params p, const Segment
                     team_sync<W>();
                     bool unusable = false, crowded = false, jumps = false;
                     if constexpr (kCoin) {
-                        for (int i = tid; i < K; i += TEAM) lt.coin[i] = level_coin(lt.levels, i, K);
+                        for (int i = tid; i < K; i += TEAM) lt.coin[i] = level_coin(lt.levels, i, K, (float)C);
                     } else {
                         for (int i = tid; i < K - 1; i += TEAM)
                             unusable = !level_threshold(lt.levels, i, K, (float)C, lt.thresholds + i) || unusable;
@@ -588,15 +587,14 @@ __global__ void __launch_bounds__(256) tile_kernel(const Params p, const Segment
                 };
                 auto every = [](int) { return true; };
                 auto search = [&](float z, float h) -> uint32_t {
-                    return kCoin ? stochastic_level_any(z, h, lt.levels, K) : nearest_level_any(z, lt.levels, K);
+                    return kCoin ? stochastic_level_any(z, h, lt.levels, K, (float)C) : nearest_level_any(z, lt.levels, K);
                 };
                 auto lookup = [&](float z, float h) -> uint32_t {
                     const uint32_t c = (uint32_t)z;
                     const LevelCell e = lt.cells[c < (uint32_t)C ? c : (uint32_t)C];
                     const uint32_t n = (e.count & 0xFFFFu) + (e.next <= z ? (e.count >> 16) + 1u : 0u);
                     if constexpr (!kCoin) return n;
-                    const LevelCoin l = lt.coin[n];
-                    return n + (65535.5f - h < (z - l.q) * l.rgap16 ? 1u : 0u);
+                    return n + (coin_up(z, h, lt.coin[n]) ? 1u : 0u);
                 };
                 if (__builtin_expect(single && level_by_cell, 1)) {
                     encode(every, lookup);

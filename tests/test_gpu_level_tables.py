@@ -79,3 +79,22 @@ def test_workgroups_that_cross_tensors(bits, B, grid, monkeypatch):
             wm.append(m.view(np.uint32).reshape(-1))
             o += x.size
         assert np.array_equal(np_u32(codes), np.concatenate(wc)) and np.array_equal(np_u32(meta), np.concatenate(wm))
+
+
+@pytest.mark.parametrize("B", [96, 128, 608, 1024, 2048, 2080, 4096])
+@pytest.mark.parametrize("bits", [1, 2, 5, 6, 8])
+def test_coin_flip_in_gaps_next_to_zero(bits, B):
+    """The smallest gaps that binary32 has (only levels next to 0 can be that close): values all over such a gap."""
+    rng = np.random.default_rng(bits + B)
+    n = 4 * B
+    for exponent in (100, 119, 121, 123, 125, 127, 129, 134):
+        gap = np.float32(np.ldexp(1.0, -exponent))
+        table = ref.levels_uniform(bits)
+        table[1] = gap
+        x = rng.random(n).astype(np.float32) * gap
+        x[0::B], x[B - 1::B] = 0.0, 1.0
+        codes, meta = qb.alloc_packed(n, bits, B, DEV)
+        qb.qsdp_quantize_levels_stochastic(torch.from_numpy(x).to(DEV), bits, B, torch.from_numpy(table).to(DEV), 3, 8,
+                                           codes, meta.view(-1))
+        wc, wm = ref.quantize_levels_stochastic(x, bits, B, table, 3, index_offset=8)
+        assert np.array_equal(np_u32(codes), wc) and np.array_equal(np_u32(meta), wm.view(np.uint32).reshape(-1)), exponent
