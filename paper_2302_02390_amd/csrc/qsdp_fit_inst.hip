@@ -12,7 +12,7 @@
 namespace qsdp {
 
 hipError_t QSDP_CAT(launch_fit_, QSDP_FIT_V, _, QSDP_FIT_W)(const FitParams& p, unsigned grid, hipStream_t s) {
-    const dim3 block(FitShape<QSDP_FIT_V, QSDP_FIT_W>::kThreads);
+    const dim3 block(FitShape<1, QSDP_FIT_V, QSDP_FIT_W>::kThreads);
     switch (p.bits) {
         case 1: hipLaunchKernelGGL((fit_levels_kernel<1, QSDP_FIT_V, QSDP_FIT_W>), dim3(grid), block, 0, s, p); break;
         case 2: hipLaunchKernelGGL((fit_levels_kernel<2, QSDP_FIT_V, QSDP_FIT_W>), dim3(grid), block, 0, s, p); break;

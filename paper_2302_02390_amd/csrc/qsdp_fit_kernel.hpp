@@ -26,8 +26,12 @@ namespace qsdp {
 //
 // Measured (us per batch, 5-bit table, Gaussian values, buckets of 128 / 1024 / 4096 / 8192): 0.45 / 0.57 / 1.8 / 3.5,
 // against 1.27 / 2.6 / 10.7 / 21 for a workgroup that stages one batch in LDS and assigns value by value with a barrier
-// around each part; the 292 tables of the 350M model 2.85 -> 0.59 ms. The chain is latency: about 1,100 cycles of
+// around each part; the 292 tables of the 350M model 2.85 -> 0.57 ms. The chain is latency: about 1,100 cycles of
 // dependent LDS reads and binary64 steps per batch up to 1024 values, the sorting beyond.
+// Tensors of few batches are bound by what a workgroup does before its first one, the table of powers above all (one
+// batch of 1024, 4 bit: 32 us when the whole table was filled first, 10 us now, against 16 us for the workgroup that
+// staged its batches), and by one workgroup of this size to a compute unit: 2000 such tensors 240 -> 46 us (53 us then;
+// 2 bit, whose counts ask for more powers: 240 -> 103 us, 57 us then).
 //
 // The boundary search needs levels that ascend by more than 2^-20 within [0, 1] (then the comparison of the two
 // rounded distances is monotone in the value and flips within 2^-22 of the midpoint) and cells that are not
@@ -48,15 +52,17 @@ struct FitParams {
 template <int BMAX, int C>
 struct FitSlot;
 
-template <int VPT, int W>
+template <int BITS, int VPT, int W>
 struct FitShape {
     static constexpr int kBucketMax = 64 * W * VPT;
     static constexpr int kBatches = W == 1 ? 6 : 8 / W;          // P, batches per round
     static constexpr int kProducers = kBatches * W;              // producer waves; the consumer is one more
     static constexpr int kThreads = 64 * (kProducers + 1);
     static constexpr int kBarriers = W == 1 ? 1 : 4;             // per round
-    // about a cell per value, as far as the 2 P slots leave LDS to spare
-    static constexpr int kCells = kBucketMax <= 512 ? kBucketMax : kBucketMax <= 2048 ? 512 : 1024;
+    // About a cell per value, as far as the 2 P slots leave LDS to spare. Half of that for buckets of 512 and up to 16
+    // levels, where it lets two workgroups share a compute unit at no cost to the chain (2000 tensors of one batch, 4 bit:
+    // 33.7 -> 23.3 us; with more levels the chain loses: 5 bit 0.49 -> 0.53 us per batch, 6 bit 0.56 -> 0.65).
+    static constexpr int kCells = kBucketMax <= 256 ? kBucketMax : kBucketMax == 512 && BITS <= 4 ? 256 : kBucketMax <= 2048 ? 512 : 1024;
     using Slot = FitSlot<kBucketMax, kCells>;
 };
 
@@ -162,33 +168,66 @@ __device__ __forceinline__ void fit_wave_sync() {
 }
 
 // (1 - lr)^c by repeated multiplication, the order in which c single steps compound, for c up to the bucket size: every
-// power up to kFine with the reciprocal of the count, beyond that every kStep-th.
+// power up to kFine beside the reciprocal of the count, beyond that every kStep-th. The multiplications are a serial
+// chain (about 8 ns each), so the consumer extends it as the counts ask for it: most counts are a small share of a
+// bucket, and a tensor of few batches would wait for powers that it never reads. The reciprocals are the producers' work,
+// while their first loads are on the way.
+struct FitFilled {
+    int count;    // the powers of counts up to this one can be read
+    double keep;  // where the chain stands
+};
+template <int BMAX>
 struct FitPowers {
-    static constexpr int kFine = 1024, kStep = 16, kCoarse = (kMaxBucket - kFine) / kStep + 1;
+    static constexpr int kFine = BMAX < 1024 ? BMAX : 1024, kStep = 16, kCoarse = (BMAX - kFine) / kStep + 1;
+    static_assert(kFine % 64 == 0, "grows by 64");
     struct Entry {
         double moved, reciprocal;  // 1 - (1-lr)^c, 1 / c
     };
     Entry fine[kFine + 1];
     double coarse[kCoarse];
 
-    __device__ void fill(int top, double one_minus, int lane) {  // one wave
-        double keep = 1.0, mine = 1.0;
-        const int fine_top = top < kFine ? top : kFine;
-        for (int c0 = 0; c0 <= fine_top; c0 += 64) {
-            for (int i = 0; i < 64; ++i) {
-                mine = lane == i ? keep : mine;
-                if (c0 + i < fine_top) keep *= one_minus;  // ends as the power fine_top
+    __device__ void fill_reciprocals(int top, int thread, int threads) {
+        for (int c = thread; c <= kFine && c <= top; c += threads) fine[c].reciprocal = 1.0 / (double)(c > 0 ? c : 1);
+    }
+
+    __device__ FitFilled start(int lane) {
+        if (lane == 0) fine[0].moved = 0.0;
+        return {0, 1.0};
+    }
+
+    // The next 64 powers, or the next 16 of every kStep-th (one wave; the chain and its stores in one lane).
+    __device__ void extend(FitFilled& f, double one_minus, int lane) {
+        double keep = f.keep;
+        if (f.count < kFine) {
+            if (lane == 0) {
+                uint32_t first = (uint32_t)f.count + 1u;
+                asm volatile("" : "+v"(first));  // one address register, the stores' offsets in the instructions
+#pragma unroll 16
+                for (int i = 0; i < 64; ++i) {
+                    keep *= one_minus;
+                    fine[first + i].moved = keep;
+                }
             }
-            const int c = c0 + lane;
-            if (c <= fine_top) {
-                const Entry e = {1.0 - mine, 1.0 / (double)(c > 0 ? c : 1)};
-                fine[c] = e;
+            fit_wave_sync();
+            double& mine = fine[f.count + 1 + lane].moved;
+            mine = 1.0 - mine;
+            f.count += 64;
+        } else {
+            const int first = (f.count + 1 - kFine) / kStep;
+            if (lane == 0) {
+                for (int k = first; k < first + 16; ++k) {
+                    if (k < kCoarse) coarse[k] = keep;
+#pragma unroll
+                    for (int i = 0; i < kStep; ++i) keep *= one_minus;
+                }
             }
+            f.count = kFine + (first + 16) * kStep - 1;
         }
-        for (int k = 0; kFine + k * kStep <= top; ++k) {
-            if (lane == 0) coarse[k] = keep;
-            for (int i = 0; i < kStep; ++i) keep *= one_minus;
-        }
+        const uint64_t bits = __builtin_bit_cast(uint64_t, keep);
+        const uint64_t low = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)bits);
+        const uint64_t high = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(bits >> 32));
+        f.keep = __builtin_bit_cast(double, (high << 32) | low);
+        fit_wave_sync();
     }
 
     // Where the level q lands after the c values of fixed-point sum `total` that are its own (c = 0: it stays); c at
@@ -222,6 +261,7 @@ struct FitPowers {
 // another's banks (without it all 64 lanes meet in two banks: 0.15 us more per batch of 1024).
 template <int BMAX, int C>
 struct FitSlot {
+    static constexpr int kValues = BMAX;
     static constexpr int kOwn = C / 64;
     static __device__ __forceinline__ uint32_t at(uint32_t c) { return c + (kOwn > 1 ? c / kOwn : 0u); }
     uint64_t cell[C + 64 + 1];  // cell c at at(c)
@@ -239,8 +279,8 @@ struct FitLanes {
 
 // One batch of the chain. lv[i]: the lane's levels, updated. lv_shared, acc: K entries of LDS each, for batches that are
 // assigned value by value.
-template <int BITS, typename Slot, int C>
-__device__ __forceinline__ void fit_batch(const Slot& slot, int m, const FitPowers& powers, double one_minus,
+template <int BITS, typename Slot, typename Powers, int C>
+__device__ __forceinline__ void fit_batch(const Slot& slot, int m, Powers& powers, FitFilled& filled, double one_minus,
                                           FitCells cells, float (&lv)[FitLanes<BITS>::M], float* lv_shared,
                                           uint64_t* acc, int lane) {
     constexpr int K = FitLanes<BITS>::K, S = FitLanes<BITS>::S, M = FitLanes<BITS>::M;
@@ -340,16 +380,21 @@ __device__ __forceinline__ void fit_batch(const Slot& slot, int m, const FitPowe
         }
         fit_wave_sync();
     }
-    bool many = false;
+    uint32_t most = 0;
 #pragma unroll
-    for (int i = 0; i < M; ++i) many = many || (uint32_t)(own[i] >> kFitCountShift) > (uint32_t)FitPowers::kFine;
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64(many) == 0, 1)) {
-        FitPowers::Entry e[M];
+    for (int i = 0; i < M; ++i) {
+        const uint32_t c = (uint32_t)(own[i] >> kFitCountShift);
+        most = c > most ? c : most;
+    }
+    while (__builtin_expect(filled.count < m && __builtin_amdgcn_ballot_w64(most > (uint32_t)filled.count) != 0, 0))
+        powers.extend(filled, one_minus, lane);
+    if (Powers::kFine == Slot::kValues || __builtin_expect(__builtin_amdgcn_ballot_w64(most > (uint32_t)Powers::kFine) == 0, 1)) {
+        typename Powers::Entry e[M];
 #pragma unroll
         for (int i = 0; i < M; ++i) e[i] = powers.fine[own[i] >> kFitCountShift];
 #pragma unroll
         for (int i = 0; i < M; ++i)
-            lv[i] = FitPowers::step(lv[i], (uint32_t)(own[i] >> kFitCountShift), own[i] & kFitSumMask, e[i]);
+            lv[i] = Powers::step(lv[i], (uint32_t)(own[i] >> kFitCountShift), own[i] & kFitSumMask, e[i]);
     } else {
 #pragma unroll
         for (int i = 0; i < M; ++i)
@@ -358,13 +403,14 @@ __device__ __forceinline__ void fit_batch(const Slot& slot, int m, const FitPowe
 }
 
 template <int BITS, int VPT, int W>
-__global__ void __launch_bounds__((FitShape<VPT, W>::kThreads)) fit_levels_kernel(const FitParams p) {
-    using Shape = FitShape<VPT, W>;
+__global__ void __launch_bounds__((FitShape<BITS, VPT, W>::kThreads)) fit_levels_kernel(const FitParams p) {
+    using Shape = FitShape<BITS, VPT, W>;
     using Slot = typename Shape::Slot;
     constexpr int C = Shape::kCells, P = Shape::kBatches, K = 1 << BITS;
     constexpr int M = FitLanes<BITS>::M, S = FitLanes<BITS>::S;
     __shared__ Slot slots[2 * P];
-    __shared__ FitPowers powers;
+    typedef FitPowers<Shape::kBucketMax> Powers;
+    __shared__ Powers powers;
     __shared__ float lv_shared[K];
     __shared__ uint64_t acc[K];
     __shared__ float red[P][4][W];
@@ -400,7 +446,11 @@ __global__ void __launch_bounds__((FitShape<VPT, W>::kThreads)) fit_levels_kerne
             const int k = 64 * i + (S > 1 ? lane % (64 / S) : lane);
             lv[i] = k < K ? levels[k] : 0.0f;
         }
-        powers.fill(B, one_minus, lane);
+        FitFilled filled = powers.start(lane);
+        // while the producers sort the first round: up to three times the mean count, which the fullest level of a
+        // Gaussian batch on the uniform table does not reach; all of them for the smallest buckets
+        while (filled.count < Powers::kFine && (Powers::kFine <= 256 || filled.count * K < 3 * B))
+            powers.extend(filled, one_minus, lane);
         for (int i = 0; i < Shape::kBarriers; ++i) __syncthreads();  // the producers' first round
         for (uint64_t r = 0; r < rounds; ++r) {
             const int buffer = (int)(r & 1u) * P;
@@ -410,8 +460,8 @@ __global__ void __launch_bounds__((FitShape<VPT, W>::kThreads)) fit_levels_kerne
 #pragma unroll
             for (int i = 0; i < P; ++i) {
                 if (r * P + i < num_batches)
-                    fit_batch<BITS, Slot, C>(slots[buffer + i], batch_size(r * P + i), powers, one_minus, cells[i], lv,
-                                             lv_shared, acc, lane);
+                    fit_batch<BITS, Slot, Powers, C>(slots[buffer + i], batch_size(r * P + i), powers, filled, one_minus,
+                                                     cells[i], lv, lv_shared, acc, lane);
                 for (int b = 0; b < (W == 1 ? (i == P - 1 ? 1 : 0) : Shape::kBarriers / P); ++b) __syncthreads();
             }
         }
@@ -446,7 +496,12 @@ __global__ void __launch_bounds__((FitShape<VPT, W>::kThreads)) fit_levels_kerne
             }
         };
         fetch(batch(0));
+        powers.fill_reciprocals(B, threadIdx.x, 64 * Shape::kProducers);
         for (uint64_t r = 0; r <= rounds; ++r) {
+            if (r == rounds) {  // the consumer's last round: nothing left to sort
+                for (int i = 0; i < Shape::kBarriers; ++i) __syncthreads();
+                break;
+            }
             const int m = batch_size(batch(r));
             Slot& slot = slots[(int)(r & 1u) * P + team];
             float z[VPT];

@@ -59,3 +59,16 @@ def test_offset_data_and_tensors_that_start_anywhere():
             want = ref.fit_levels(v[o:o + s].copy(), bits, B, 0.01, ref.levels_uniform(bits), max_batches=30)
             assert np.array_equal(np_f32(levels[t]).view(np.uint32), want.view(np.uint32)), t
             o += s
+
+
+@pytest.mark.parametrize("m", [1, 63, 64, 65, 127, 128, 129, 192, 193, 1023, 1024, 1025, 1039, 1040, 1041, 1279, 1280,
+                               1296, 2047, 2048, 4095, 4096, 8191, 8192])
+def test_counts_where_the_table_of_powers_grows(m):
+    """All m values of a batch on one level, then fewer, then half of them: the table is extended, used as it is, and read
+    at its ends."""
+    B = -(-m // 32) * 32
+    v = np.full(3 * B, 0.5, np.float32)
+    v[m:B], v[2 * B: 2 * B + B // 2] = 3.0, -1.0
+    for bits in (1, 4, 8):
+        for n in (m, 3 * B, 2 * B - 1):
+            assert _same(v[:n].copy(), bits, B, 0.01, ref.levels_uniform(bits)), (bits, n)
