@@ -230,8 +230,8 @@ struct FitPowers {
         fit_wave_sync();
     }
 
-    // Where the level q lands after the c values of fixed-point sum `total` that are its own (c = 0: it stays); c at
-    // most kFine.
+    // Where the level q lands after the c values of fixed-point sum `total` that are its own; c at most kFine. Without
+    // values it stays, whatever it holds.
     static __device__ __forceinline__ float step(float level, uint32_t c, uint64_t total, Entry e) {
         // total / c rounded once: t * (1/c) is off by at most 2 ulp, the remainder is exact (c is below 2^11, so it has
         // at most 12 bits more than an ulp), and the corrected quotient is within 2^-50 ulp of t / c, which, t and c
@@ -240,7 +240,7 @@ struct FitPowers {
         const double q = (double)level, t = (double)total;
         const double a = t * e.reciprocal;
         const double mean = fma(fma(-a, (double)c, t), e.reciprocal, a) * (1.0 / 4294967296.0);
-        return (float)(q - e.moved * (q - mean));
+        return c == 0u ? level : (float)(q - e.moved * (q - mean));
     }
 
     // The same for any c.
@@ -251,7 +251,7 @@ struct FitPowers {
         for (int i = kFine + k * kStep; i < (int)c; ++i) keep *= one_minus;
         const double q = (double)level;
         const double mean = ((double)total / (double)c) * (1.0 / 4294967296.0);
-        return (float)(q - (1.0 - keep) * (q - mean));
+        return c == 0u ? level : (float)(q - (1.0 - keep) * (q - mean));
     }
 };
 

@@ -72,3 +72,22 @@ def test_counts_where_the_table_of_powers_grows(m):
     for bits in (1, 4, 8):
         for n in (m, 3 * B, 2 * B - 1):
             assert _same(v[:n].copy(), bits, B, 0.01, ref.levels_uniform(bits)), (bits, n)
+
+
+@pytest.mark.parametrize("bits", [1, 3, 5, 8])
+@pytest.mark.parametrize("B", [64, 1024, 4096])
+def test_levels_without_values_stay_as_they_are(B, bits):
+    """Bit for bit: a negative zero beside another one, and past [0, 1], where tables are not checked, padding."""
+    x, _ = synth(5 * B, B + bits)
+    K = 1 << bits
+    if K > 2:
+        levels = ref.levels_uniform(bits)
+        levels[:2] = -0.0  # the values at the minimum go to the first of the two
+        assert _same(x, bits, B, 0.01, levels, 1)
+    for fill in (np.inf, 3e38, 2.5):
+        levels = ref.levels_uniform(bits)
+        levels[K // 2:] = fill
+        lv = torch.from_numpy(levels).to(DEV)
+        qb.qsdp_fit_levels(torch.from_numpy(x).to(DEV), bits, B, 0.01, lv)
+        got = np_f32(lv)
+        assert np.array_equal(got[K // 2:], levels[K // 2:]) and (got[:K // 2] < 1.0).all(), fill
