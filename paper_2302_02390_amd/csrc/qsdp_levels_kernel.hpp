@@ -43,24 +43,54 @@ struct LevelCell {
     uint32_t count;  // bounds at or below the cell's start; upper half: bounds equal to `next`, less one
 };
 
-// Entry c of the cell table over `kb` bounds (cell c is [c, c+1) in cell units; the last entry serves a value of
-// exactly 1). crowded: the cell holds two different bounds; jumps: it holds equal ones.
-__device__ __forceinline__ LevelCell level_cell(const float* bounds, int kb, int c, bool& crowded, bool& jumps) {
-    const float start = (float)c;
-    int lo = 0, hi = kb;  // bounds[k] at or below start for k < lo, above for k >= hi
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (bounds[mid] <= start) lo = mid + 1; else hi = mid;
+// What is wrong with a table, collected over the threads that set it up.
+enum LevelFlags : uint32_t {
+    LEVELS_UNUSABLE = 1u,  // a threshold that cannot be relied on
+    LEVELS_CROWDED = 2u,   // a cell holds two different bounds
+    LEVELS_JUMPS = 4u      // a cell holds equal bounds
+};
+
+// Entries thread, thread + THREADS, ... of the cell table over K - 1 bounds, K a power of two (cell c is [c, c+1) in cell
+// units; the last entry, C, serves a value of exactly 1). All of a thread's entries are searched for side by side: the
+// set-up is a chain of LDS reads, and small calls and small tensors wait for it.
+template <int C, int THREADS>
+__device__ __forceinline__ uint32_t fill_level_cells(LevelCell* cells, const float* bounds, int K, int thread) {
+    constexpr int N = C / THREADS + 1;
+    const int kb = K - 1;
+    int at[N];  // ends as the number of bounds at or below the cell's start
+#pragma unroll
+    for (int i = 0; i < N; ++i) at[i] = 0;
+    auto cell = [&](int i) { return thread + i * THREADS < C ? thread + i * THREADS : C; };
+    for (int step = K >> 1; step >= 1; step >>= 1) {
+        float bound[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) bound[i] = bounds[at[i] + step - 1];
+#pragma unroll
+        for (int i = 0; i < N; ++i) at[i] += bound[i] <= (float)cell(i) ? step : 0;
     }
-    LevelCell e = {lo < kb ? bounds[lo] : __builtin_inff(), (uint32_t)lo};
-    int equal = 1;
-    while (lo + equal < kb && bounds[lo + equal] == e.next) ++equal;
-    crowded = crowded || (lo + equal < kb && bounds[lo + equal] < start + 1.0f);
-    if (equal > 1 && e.next < start + 1.0f) {
-        jumps = true;
-        e.count |= (uint32_t)(equal - 1) << 16;
+    float next[N], after[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        next[i] = at[i] < kb ? bounds[at[i]] : __builtin_inff();
+        after[i] = at[i] + 1 < kb ? bounds[at[i] + 1] : __builtin_inff();
     }
-    return e;
+    uint32_t flags = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const float end = (float)cell(i) + 1.0f;
+        uint32_t equal = 0;  // bounds equal to `next`, less one, if that lies in the cell
+        if (next[i] < end) {
+            while (after[i] == next[i]) {
+                ++equal;
+                const int k = at[i] + 1 + (int)equal;
+                after[i] = k < kb ? bounds[k] : __builtin_inff();
+            }
+            flags |= (after[i] < end ? LEVELS_CROWDED : 0u) | (equal != 0 ? LEVELS_JUMPS : 0u);
+        }
+        const LevelCell e = {next[i], (uint32_t)at[i] | (equal << 16)};
+        cells[cell(i)] = e;
+    }
+    return flags;
 }
 
 // Threshold k of the K levels lv, scaled by `unit`; false if there is none to rely on: the comparison of the rounded distances is monotone
@@ -195,6 +225,7 @@ __global__ void __launch_bounds__(256, QSDP_LEVELS_MIN_BLOCKS) levels_kernel(con
     __shared__ float thresholds[kCoin ? 1 : K];
     __shared__ LevelCoin coin[kCoin ? K : 1];
     __shared__ LevelCell cells[C + 1];
+    __shared__ uint32_t table_flags;
     const float* bounds = kCoin ? levels + 1 : thresholds;
     const int lane = threadIdx.x & 63;
     const int sub = lane / G;
@@ -258,24 +289,29 @@ __global__ void __launch_bounds__(256, QSDP_LEVELS_MIN_BLOCKS) levels_kernel(con
             mine[i] = k < K ? table[k] : 0.0f;
         }
         __syncthreads();  // the tables of the piece before are no longer read
+        if (threadIdx.x == 0) table_flags = 0;
 #pragma unroll
         for (int i = 0; i * kThreads < K; ++i) {
             const int k = threadIdx.x + i * kThreads;
             if (k < K) levels[k] = mine[i] * LevelShape<BITS>::kScale;
         }
         __syncthreads();
-        int method = LEVELS_BY_CELL;  // workgroup-uniform
+        uint32_t found = 0;
         if constexpr (kCoin) {
             for (int k = threadIdx.x; k < K; k += kThreads) coin[k] = level_coin(levels, k, K, LevelShape<BITS>::kScale);
         } else {
-            bool unusable = false;
-            for (int k = threadIdx.x; k < K - 1; k += kThreads) unusable = !level_threshold(levels, k, K, LevelShape<BITS>::kScale, thresholds + k) || unusable;
-            if (__syncthreads_or(unusable)) method = LEVELS_PLAIN;
+            for (int k = threadIdx.x; k < K - 1; k += kThreads)
+                if (!level_threshold(levels, k, K, LevelShape<BITS>::kScale, thresholds + k)) found |= LEVELS_UNUSABLE;
+            __syncthreads();
         }
-        bool crowded = false, jumps = false;
-        for (int c = threadIdx.x; c <= C; c += kThreads) cells[c] = level_cell(bounds, K - 1, c, crowded, jumps);
-        const bool any_crowded = __syncthreads_or(crowded) != 0, any_jumps = __syncthreads_or(jumps) != 0;
-        if (method != LEVELS_PLAIN) method = any_crowded ? LEVELS_BY_SEARCH : any_jumps ? LEVELS_BY_CELL_JUMPS : LEVELS_BY_CELL;
+        found |= fill_level_cells<C, kThreads>(cells, bounds, K, threadIdx.x);
+        if (found != 0) atomicOr(&table_flags, found);
+        __syncthreads();
+        const uint32_t flags = __builtin_amdgcn_readfirstlane(table_flags);
+        const int method = flags & LEVELS_UNUSABLE ? LEVELS_PLAIN  // workgroup-uniform
+                         : flags & LEVELS_CROWDED  ? LEVELS_BY_SEARCH
+                         : flags & LEVELS_JUMPS    ? LEVELS_BY_CELL_JUMPS
+                                                   : LEVELS_BY_CELL;
         const LevelPivots pivots = load_level_pivots<BITS>(bounds);
 
         for (uint64_t q = q0; q < nunits; q += q_step, parity ^= 1u) {

@@ -552,17 +552,16 @@ __global__ void __launch_bounds__(256) tile_kernel(const Params p, const Segment
                     team_sync<W>();
                     for (int i = tid; i < K; i += TEAM) lt.levels[i] = p.levels[(uint64_t)tensor * K + i] * (float)C;
                     team_sync<W>();
-                    bool unusable = false, crowded = false, jumps = false;
+                    uint32_t found = 0;
                     if constexpr (kCoin) {
                         for (int i = tid; i < K; i += TEAM) lt.coin[i] = level_coin(lt.levels, i, K, (float)C);
                     } else {
                         for (int i = tid; i < K - 1; i += TEAM)
-                            unusable = !level_threshold(lt.levels, i, K, (float)C, lt.thresholds + i) || unusable;
+                            if (!level_threshold(lt.levels, i, K, (float)C, lt.thresholds + i)) found |= LEVELS_UNUSABLE;
+                        team_sync<W>();
                     }
-                    unusable = any(unusable);
-                    const float* bounds = kCoin ? lt.levels + 1 : lt.thresholds;
-                    for (int c = tid; c <= C; c += TEAM) lt.cells[c] = level_cell(bounds, K - 1, c, crowded, jumps);
-                    level_by_cell = !any(crowded) && !unusable;
+                    found |= fill_level_cells<C, TEAM>(lt.cells, kCoin ? lt.levels + 1 : lt.thresholds, K, tid);
+                    level_by_cell = !any((found & (LEVELS_UNUSABLE | LEVELS_CROWDED)) != 0);
                     loaded_tensor = tensor;
                 }
                 // by cell, by search and by search for some of the buckets are loops of their own, so that each is
