@@ -93,11 +93,13 @@ __device__ __forceinline__ uint32_t fill_level_cells(LevelCell* cells, const flo
     return flags;
 }
 
-// Threshold k of the K levels lv, scaled by `unit`; false if there is none to rely on: the comparison of the rounded distances is monotone
-// in z over the whole unit interval if the levels lie in it and the two are more than 2^-20 apart (the distances differ by the
-// gap outside the two levels, and each is rounded by less than 2^-24), and it flips within two steps of the midpoint (only
-// the distance to a level below z/2 is rounded at all, by half a step). In a run of equal levels every threshold is that
-// of the run's end, so that its first level is the only one that is ever chosen.
+// Threshold k of the K levels lv, scaled by `unit`; false if there is none to rely on. A value between the levels k and
+// k+1 is compared with these two alone: one rounded distance rises with the value and the other falls, so the comparison
+// flips once, and it does so within two steps of the midpoint (only the distance to a level below z/2 is rounded at all, by
+// half a step). Values past the last level are compared with the last two: that goes to the last one if these are more
+// than 2^-20 apart (the distances differ by the gap, and each is rounded by less than 2^-24), or equal, or if the last
+// level is 1. In a run of equal levels every threshold is that of the run's end, so that its first level is the only
+// one that is ever chosen.
 __device__ __forceinline__ bool level_threshold(const float* lv, int k, int K, float unit, float* threshold) {
     const float lo = lv[k];
     int next = k + 1;
@@ -117,7 +119,8 @@ __device__ __forceinline__ bool level_threshold(const float* lv, int k, int K, f
         else found = true;
     }
     *threshold = t;
-    return found && hi - lo > 0x1p-20f * unit && lo >= 0.0f && hi <= unit;
+    const bool apart = hi - lo > 0x1p-20f * unit || hi == unit || lv[K - 1] != hi;
+    return found && apart && lo >= 0.0f && hi <= unit;
 }
 
 // What the coin flip needs at level i: the level (cell units) and the reciprocal of the gap to the next one (per cell

@@ -98,3 +98,26 @@ def test_coin_flip_in_gaps_next_to_zero(bits, B):
                                            codes, meta.view(-1))
         wc, wm = ref.quantize_levels_stochastic(x, bits, B, table, 3, index_offset=8)
         assert np.array_equal(np_u32(codes), wc) and np.array_equal(np_u32(meta), wm.view(np.uint32).reshape(-1)), exponent
+
+
+@pytest.mark.parametrize("B", [96, 128, 608, 1024, 2080, 4096])
+@pytest.mark.parametrize("bits", [2, 4, 6, 8])
+def test_nearest_level_among_close_levels(bits, B):
+    """Two neighbours a few steps apart, anywhere in the table: values all over the interval, on the pair and between."""
+    K, n = 1 << bits, 6 * B
+    for k, top in ((0, 1.0), (K // 2 - 1, 1.0), (K // 3, 1.0), (K - 2, 1.0), (K - 2, 0.5), (K - 2, 0.999)):
+        for gap in (2.0 ** -19, 2.0 ** -21, 2.0 ** -23):
+            rng = np.random.default_rng(bits + B + k)
+            table = (ref.levels_uniform(bits) * np.float32(top)).astype(np.float32)
+            if k == K - 2:
+                table[k] = table[k + 1] - np.float32(gap)
+            else:
+                table[k + 1] = table[k] + np.float32(gap)
+            x = rng.random(n).astype(np.float32)
+            near = np.arange(n) % 3 == 0
+            x[near] = np.clip(table[k] + (rng.integers(-6, 7, near.sum()) * gap / 4), 0, 1).astype(np.float32)
+            x[0::B], x[B - 1::B] = 0.0, 1.0
+            codes, meta = qb.alloc_packed(n, bits, B, DEV)
+            qb.qsdp_quantize_levels(torch.from_numpy(x).to(DEV), bits, B, torch.from_numpy(table).to(DEV), codes, meta.view(-1))
+            wc, wm = ref.quantize_levels(x, bits, B, table)
+            assert np.array_equal(np_u32(codes), wc) and np.array_equal(np_u32(meta), wm.view(np.uint32).reshape(-1)), (k, gap)
