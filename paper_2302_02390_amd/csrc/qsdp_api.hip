@@ -126,14 +126,19 @@ namespace {
 
 constexpr unsigned kMaxGrid = 1u << 20;
 
-// Workgroups to launch for `blocks` units of work: all of them up to kMaxGrid, the kernels stride
-// beyond that. QSDP_DEBUG_MAXGRID (the library's one debug switch) lowers the cap so that the
-// striding paths can be exercised on small inputs.
-unsigned capped_grid(uint64_t blocks, unsigned cap = kMaxGrid) {
+// Most workgroups of a launch; the kernels stride beyond that. QSDP_DEBUG_MAXGRID (the library's one debug switch) lowers it,
+// and the size from which the chip counts as busy with it, so that the striding paths and the tiles of large calls
+// can be exercised on small inputs.
+unsigned grid_cap() {
     if (const char* e = std::getenv("QSDP_DEBUG_MAXGRID")) {
         const long v = std::atol(e);
-        if (v >= 1 && v < (long)cap) cap = (unsigned)v;
+        if (v >= 1 && v < (long)kMaxGrid) return (unsigned)v;
     }
+    return kMaxGrid;
+}
+
+unsigned capped_grid(uint64_t blocks) {
+    const unsigned cap = grid_cap();
     return (unsigned)(blocks < cap ? blocks : cap);
 }
 
@@ -170,6 +175,7 @@ WaveLauncher wave_launcher(int bucket, int* buckets_per_wave) {
 typedef hipError_t (*TileLauncher)(int, const Params&, const TileArgs&, unsigned, hipStream_t);
 
 TileLauncher tile_launcher(const TilePlan& t) {
+    if (t.rows == 2) return t.waves == 1 ? launch_tile_1_2 : launch_tile_4_2;
     if (t.waves == 1) return t.rows == 4 ? launch_tile_1_4 : t.rows == 6 ? launch_tile_1_6 : launch_tile_1_8;
     return t.rows == 4 ? launch_tile_4_4 : t.rows == 6 ? launch_tile_4_6 : launch_tile_4_8;
 }
@@ -208,7 +214,7 @@ int run(int mode, Params p, int stored_bits, hipStream_t s) {
         if (mode_is_levels(mode)) blocks = level_blocks(mode, blocks, bpw > 0 ? 4 : p.bucket / 1024);
         if (wl(mode, stored_bits, p, capped_grid(blocks), s) != hipSuccess) return QSDP_ELAUNCH;
     } else {
-        const TilePlan t = tile_plan(p.bucket);
+        const TilePlan t = choose_tile(p.bucket, nb, 4 * (uint64_t)grid_cap());
         const uint64_t units = ceil_div(nb, (uint64_t)t.buckets);
         uint64_t blocks = t.waves == 1 ? ceil_div(units, 4) : units;
         if (mode_is_levels(mode)) blocks = level_blocks(mode, blocks, 4);

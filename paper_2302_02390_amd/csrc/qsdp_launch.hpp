@@ -24,6 +24,8 @@ QSDP_DECLARE_WAVE(1024w2)  // weight quantizer only: two waves per 1024-bucket
 // One launcher per tile shape (waves, rows), see tile_plan.
 #define QSDP_DECLARE_TILE(W, R) \
     hipError_t launch_tile_##W##_##R(int mode, const Params& p, const TileArgs& a, unsigned grid, hipStream_t s);
+QSDP_DECLARE_TILE(1, 2)
+QSDP_DECLARE_TILE(4, 2)
 QSDP_DECLARE_TILE(1, 4)
 QSDP_DECLARE_TILE(1, 6)
 QSDP_DECLARE_TILE(1, 8)

@@ -169,6 +169,8 @@ __global__ void __launch_bounds__(256) tile_kernel(const Params p, const Segment
         const bool whole = here == P && first.left >= (uint64_t)P * (uint64_t)B;
         const uint64_t word0 = bucket0 * (uint64_t)(B >> 5);  // times the code width: the tile's first code word
         const int used = here * S;                            // slots of these buckets
+        // whether the row is computed: the smallest teams leave an unused second one out
+        auto computed = [&](int r) { return R > 2 || r == 0 || used > TEAM; };
         if (W > 1) team_sync<W>();  // the previous tile's LDS reads are done
         if (__builtin_expect(!whole, 0)) {
             if (tid < P) {
@@ -430,7 +432,7 @@ __global__ void __launch_bounds__(256) tile_kernel(const Params p, const Segment
                 if constexpr (MODE == MODE_GRAD) write_meta(b, base, g.scale);
                 return f4{g.lo, g.inv, g.scale, base};
             });
-            uint32_t code[MODE == MODE_GRAD ? R : 1][4];
+            uint32_t code[MODE == MODE_GRAD ? R : 1][4] = {};
 #pragma unroll
             for (int cp = 0; cp < R / 2; ++cp) {
                 uint32_t h[4] = {0u, 0u, 0u, 0u};
@@ -438,6 +440,7 @@ __global__ void __launch_bounds__(256) tile_kernel(const Params p, const Segment
 #pragma unroll
                 for (int half = 0; half < 2; ++half) {
                     const int r = 2 * cp + half;
+                    if (!computed(r)) continue;
                     const f4 gr = lds.grid[bucket_of_slot(slot_of(r))];
                     const MinMaxGrid grid = {gr[0], gr[2], gr[1]};
 #pragma unroll
@@ -512,7 +515,7 @@ __global__ void __launch_bounds__(256) tile_kernel(const Params p, const Segment
             for (int r = 0; r < R; ++r)
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    w[r][i] = step_value<MODE>(p, w[r][i], p.alpha * sum[r][i], mom[r][i], var[r][i]);
+                    if (computed(r)) w[r][i] = step_value<MODE>(p, w[r][i], p.alpha * sum[r][i], mom[r][i], var[r][i]);
             if constexpr (MODE == MODE_RECV_ADAMW) {
                 store(p.mom, mom);
                 store(p.var, var);
@@ -574,6 +577,7 @@ __global__ void __launch_bounds__(256) tile_kernel(const Params p, const Segment
 #pragma unroll
                         for (int half = 0; half < 2; ++half) {
                             const int r = 2 * cp + half;
+                            if (!computed(r)) continue;
                             const int b = bucket_of_slot(slot_of(r));
                             const f4 gr = lds.grid[b];
                             if (mine(b)) {
@@ -634,6 +638,7 @@ __global__ void __launch_bounds__(256) tile_kernel(const Params p, const Segment
         const bool want16 = (MODE == MODE_FUSED || MODE == MODE_ADAMW) && p.x16 != nullptr;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
+            if (!computed(r)) continue;
             const f4 gr = lds.grid[bucket_of_slot(slot_of(r))];
             const MinMaxGrid grid = {gr[0], gr[2], gr[1]};
             if (lattice) {

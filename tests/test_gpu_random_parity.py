@@ -4,6 +4,8 @@ not powers of two, variant flags, seeds, offsets; Gaussian, heavy-tailed, huge a
 nearly constant data; 16-bit gradients; per-tensor level tables). Longer runs of the same generator
 (144,000 cases, 101,000 more after the last two families were added, 148,000 more with binary16 decoding and the
 code-resident AdamW step) found no mismatch."""
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -15,6 +17,7 @@ from gpu_util import DEV, np_f32, np_u32
 pytestmark = pytest.mark.gpu
 
 BUCKETS = [32, 64, 96, 128, 160, 256, 384, 512, 1024, 1536, 2048, 4096, 8192]
+TILE_BUCKETS = [32, 96, 224, 288, 544, 608, 1056, 2016, 2080, 3072, 4064, 4128, 6176]  # every shape of a tile
 KEEP = qb.QSDP_FLAG_KEEP_MASTER
 
 
@@ -216,5 +219,17 @@ def one_case(rng):
 @pytest.mark.parametrize("chunk", range(8))
 def test_random_cases_match_the_oracle(chunk):
     rng = np.random.default_rng(1000 + chunk)
+    for _ in range(150):
+        one_case(rng)
+
+
+@pytest.mark.parametrize("grid", ["", "2", "16"])
+@pytest.mark.parametrize("chunk", range(4))
+def test_random_cases_on_every_tile_shape(chunk, grid, monkeypatch):
+    """... with the tiles of small calls, and of large ones where few workgroups are allowed."""
+    monkeypatch.setattr(sys.modules[__name__], "BUCKETS", TILE_BUCKETS)
+    if grid:
+        monkeypatch.setenv("QSDP_DEBUG_MAXGRID", grid)
+    rng = np.random.default_rng(2000 + chunk + 10 * len(grid))
     for _ in range(150):
         one_case(rng)

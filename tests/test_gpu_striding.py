@@ -1,5 +1,5 @@
 """The kernels launch one wave (or workgroup) per unit of work up to 2^20 workgroups and stride
-beyond that. QSDP_DEBUG_MAXGRID lowers that cap, so the striding loops (and the double-buffered
+beyond that (608 and 2080: tiles that four waves share). QSDP_DEBUG_MAXGRID lowers that cap, so the striding loops (and the double-buffered
 LDS reductions of the multi-wave buckets) are checked for parity on small inputs."""
 import os
 
@@ -21,7 +21,7 @@ def tiny_grid(request):
     del os.environ["QSDP_DEBUG_MAXGRID"]
 
 
-@pytest.mark.parametrize("bucket", [96, 128, 1024, 2048, 4096])
+@pytest.mark.parametrize("bucket", [96, 128, 608, 1024, 2048, 2080, 4096])
 def test_all_entry_points_with_a_tiny_grid(tiny_grid, bucket):
     n = 41 * bucket + bucket // 3 + 1
     x, g = synth(n, 1300 + bucket)

@@ -12,7 +12,15 @@ from gpu_util import DEV, bits_equal, np_f32, np_u32, synth
 
 pytestmark = pytest.mark.gpu
 
-BUCKETS = [32, 64, 224, 288, 768, 1056, 1504, 1536, 2016, 2080, 2720, 4064, 4128, 6144, 6176, 8160, 8192]
+# every shape of a tile, in small calls and in large ones (see test_tile_plan.py)
+RECEIVE_BUCKETS = [32, 224, 288, 608, 768, 2016, 2080, 4064, 4128]
+BUCKETS = [32, 64, 224, 288, 608, 768, 1056, 1504, 1536, 2016, 2080, 2720, 4064, 4128, 6144, 6176, 8160, 8192]
+
+
+@pytest.fixture
+def large(monkeypatch):
+    """Few workgroups, so that the tiles of large calls are taken and every team works on several of them."""
+    monkeypatch.setenv("QSDP_DEBUG_MAXGRID", "2")
 
 
 def _dev(a):
@@ -41,7 +49,7 @@ def test_single_tensor(B, buckets, cut):
         assert np.array_equal(np_u32(c), wc) and np.array_equal(np_u32(m), wm.view(np.uint32).reshape(-1))
 
 
-@pytest.mark.parametrize("B", [32, 288, 768, 2080, 4128])
+@pytest.mark.parametrize("B", RECEIVE_BUCKETS)
 def test_receive_side(B):
     n, P, gbits = 41 * B - 9, 3, 5
     x, _ = synth(n, 3 * B)
@@ -61,7 +69,7 @@ def test_receive_side(B):
     assert np.array_equal(np_u32(c), want[3]) and np.array_equal(np_u32(m), want[4].view(np.uint32).reshape(-1))
 
 
-@pytest.mark.parametrize("B", [32, 224, 768, 2080, 4128])
+@pytest.mark.parametrize("B", [32, 224, 608, 768, 2016, 2080, 4064, 4128])
 def test_tensors_inside_a_tile(B):
     sizes = [B, 8, 3 * B + 16, 24 * B, 40, 97 * B + 8, 2 * B, 5 * B + 3]
     segs, n = qb.Segments(sizes, B, DEV), sum(sizes)
@@ -88,3 +96,32 @@ def test_tensors_inside_a_tile(B):
         o += s
     for got, w in zip((c, m, lc, lm, sc, sm, xd), want):
         assert np.array_equal(np_u32(got), np.concatenate(w))
+
+
+@pytest.mark.parametrize("B", BUCKETS)
+def test_large_tiles_single_tensor(B, large):
+    test_single_tensor(B, 97, 0)
+    test_single_tensor(B, 131, 13)
+
+
+@pytest.mark.parametrize("B", RECEIVE_BUCKETS)
+def test_large_tiles_receive_side(B, large):
+    test_receive_side(B)
+
+
+@pytest.mark.parametrize("B", [32, 224, 608, 768, 2016, 2080, 4064, 4128])
+def test_large_tiles_tensors(B, large):
+    test_tensors_inside_a_tile(B)
+
+
+@pytest.mark.parametrize("B", [96, 224, 608, 768, 2016, 2080, 4064, 8192])
+def test_more_tiles_than_a_small_call_has(B):
+    n = 9 * 2 ** 20 - 27
+    x, g = synth(n, B)
+    c, m = qb.alloc_packed(n, 5, B, DEV)
+    qb.qsdp_quantize_grad(_dev(g), 5, B, 5, 24, c, m.view(-1))
+    wc, wm = ref.quantize_grad(g, 5, B, 5, index_offset=24)
+    assert np.array_equal(np_u32(c), wc) and np.array_equal(np_u32(m), wm.view(np.uint32).reshape(-1))
+    xd = _dev(x)
+    qb.qsdp_fused_step(xd, _dev(g), 1e-2, 8, 4, B, 0.0, 9)
+    assert bits_equal(np_f32(xd), ref.fused_step(x, g, 1e-2, 8, 4, B, 0.0, 9)[0])

@@ -1,6 +1,6 @@
 """The tile kernels' launch shapes (csrc/qsdp_tile_plan.hpp, plain C++) for every bucket size, compiled and checked
 without a GPU: whole buckets fit the team, every bucket has lanes of its own, and the two multiplications that stand
-for divisions are exact over the ranges the kernel uses them on."""
+for divisions are exact over the ranges the kernel uses them on; small calls get small tiles; the buckets of the GPU tests see every shape."""
 import subprocess
 
 from paper_2302_02390_amd import build as lib_build
@@ -8,30 +8,57 @@ from paper_2302_02390_amd import build as lib_build
 SOURCE = r"""
 #include "qsdp_tile_plan.hpp"
 #include <cstdio>
+#include <initializer_list>
 using namespace qsdp;
-int main() {
-    int bad = 0;
+static int bad = 0;
+static void check(const TilePlan& t, int k, bool as_many_as_fit) {
+    const int groups = tile_groups(t.waves, t.rows), lanes = 1 << t.lanes_log2;
+    const bool shape = (t.waves == 1 || t.waves == 4) && t.rows % 2 == 0 && t.rows >= 2 && t.rows <= kTileMaxRows;
+    if (!shape || t.buckets < 1 || t.buckets * k > groups) ++bad;
+    if (as_many_as_fit && (t.buckets + 1) * k <= groups) ++bad;
+    if (t.buckets * lanes > 64 * t.waves || lanes > 64 || t.buckets > 64 * t.waves) ++bad;
+    for (int i = 0; i < groups; ++i)
+        if ((int)((uint32_t)i * t.group_magic >> 16) != i / k) ++bad;
+}
+int main(int argc, char** argv) {
+    const uint64_t any = ~0ull;
     for (int k = 1; k <= 256; ++k) {
-        const TilePlan t = tile_plan(32 * k);
-        const int groups = tile_groups(t.waves, t.rows), lanes = 1 << t.lanes_log2;
-        const bool shape = (t.waves == 1 || t.waves == 4) && t.rows % 2 == 0 && t.rows >= 2 && t.rows <= kTileMaxRows;
-        if (!shape || t.buckets < 1 || t.buckets * k > groups || (t.buckets + 1) * k <= groups) ++bad;
-        if (t.buckets * lanes > 64 * t.waves || lanes > 64 || t.buckets > 64 * t.waves) ++bad;
-        for (int i = 0; i < groups; ++i)
-            if ((int)((uint32_t)i * t.group_magic >> 16) != i / k) ++bad;
+        check(tile_plan(32 * k), k, true);
+        const TilePlan s = tile_plan_small(32 * k);
+        check(s, k, false);
+        if (s.buckets > 1 && s.buckets * k > tile_groups(s.waves, 1)) ++bad;  // one row, or one bucket ...
+        if (tile_groups(s.waves, 1) < k && (s.buckets + 1) * k <= tile_groups(s.waves, s.rows)) ++bad;  // ... or all that fit
+        // the line between small and large calls, and a launch that is capped
+        const uint64_t most = 4095 / s.waves * (uint64_t)s.buckets;
+        if (choose_tile(32 * k, most, any).rows != s.rows || choose_tile(32 * k, most, any).buckets != s.buckets) ++bad;
+        const TilePlan f = tile_plan(32 * k), l = choose_tile(32 * k, most + 4 * (uint64_t)s.buckets, any);
+        if (l.rows != f.rows || l.waves != f.waves || l.buckets != f.buckets) ++bad;
+        const TilePlan c = choose_tile(32 * k, 8 * (uint64_t)s.buckets, 8);
+        if (c.rows != f.rows || c.waves != f.waves || c.buckets != f.buckets) ++bad;
     }
     for (int bits = 1; bits <= 8; ++bits)
         for (uint32_t w = 0; w < 2048u * bits / 8; ++w)
             if ((8 * w * word_magic(bits)) >> 18 != 8 * w / bits) ++bad;
-    std::printf("%d\n", bad);
+    std::printf("%d", bad);
+    for (int i = 1; i < argc; ++i) {  // shapes of some buckets: large calls, small ones
+        int b;
+        std::sscanf(argv[i], "%d", &b);
+        for (const TilePlan& t : {tile_plan(b), tile_plan_small(b)})
+            std::printf(" %d,%d", t.waves, t.rows);
+    }
     return bad != 0;
 }
 """
 
 
 def test_every_bucket_size_has_an_exact_plan(tmp_path):
+    from test_gpu_tile import BUCKETS, RECEIVE_BUCKETS
+    from test_gpu_random_parity import TILE_BUCKETS
     src, exe = tmp_path / "plan.cpp", tmp_path / "plan"
     src.write_text(SOURCE)
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", lib_build.CSRC, str(src), "-o", str(exe)], check=True)
-    run = subprocess.run([str(exe)], capture_output=True, text=True)
-    assert run.returncode == 0 and run.stdout.strip() == "0"
+    for buckets in (BUCKETS, RECEIVE_BUCKETS, TILE_BUCKETS):
+        run = subprocess.run([str(exe)] + [str(b) for b in buckets], capture_output=True, text=True)
+        bad, *shapes = run.stdout.split()
+        assert run.returncode == 0 and bad == "0"
+        assert set(shapes) == {f"{w},{r}" for w, r in lib_build.TILE_SHAPES}
