@@ -240,8 +240,8 @@ __global__ void __launch_bounds__(256, QSDP_LEVELS_MIN_BLOCKS) levels_kernel(con
     const bool per_tensor = segs != nullptr;
 
     // the buckets of this workgroup; within a piece of them its waves (W > 1: the workgroup) take the units in turn
-    const uint64_t units = (p.num_buckets + BPW - 1) / BPW;
-    const uint64_t run = (units + gridDim.x - 1) / gridDim.x * BPW;
+    uint64_t run = (p.num_buckets + gridDim.x - 1) / gridDim.x;
+    if (run > BPW) run = (run + BPW - 1) / BPW * BPW;  // whole units, unless that would leave workgroups without work
     uint64_t begin = blockIdx.x * run;
     const uint64_t end = begin + run < p.num_buckets ? begin + run : p.num_buckets;
     const uint32_t q0 = W == 1 ? wave : 0u, q_step = W == 1 ? 4u : 1u;

@@ -72,13 +72,26 @@ inline TilePlan tile_plan_small(int bucket) {
     return t;
 }
 
+// ... for tensors of `mean` buckets with a level table each, where a tile of many buckets would give one team table after
+// table: the smallest team that holds a bucket, of one wave if that can be, and no more buckets than a tensor has.
+inline TilePlan tile_plan_tensors(int bucket, uint64_t mean) {
+    static const int shapes[7][2] = {{1, 2}, {1, 4}, {1, 6}, {1, 8}, {4, 4}, {4, 6}, {4, 8}};
+    int i = 0;
+    while (tile_groups(shapes[i][0], shapes[i][1]) < bucket / 32) ++i;
+    TilePlan t = tile_plan_for(bucket, shapes[i][0], shapes[i][1]);
+    if (mean < (uint64_t)t.buckets) tile_take(t, bucket, mean > 0 ? (int)mean : 1);
+    return t;
+}
+
 // The tile of a call of `num_buckets` buckets. Fewer than four waves to each of the chip's 1024 SIMDs leave it idle.
 // Measured (us, buckets of 224 and 608, the fuller tile against the small one): 2^18 elements AdamW step 19.4 / 7.6 and
 // 16.4 / 7.9, encoder 7.2 / 3.9 and 6.7 / 4.1, receive side from 8 peers 24 / 10 and 21 / 11; 2^20 elements in buckets of 416
 // 1.04-1.3 times faster, in buckets of 32 and 96, which are past the line, 0.9-1.1 times.
-// most_waves: of a launch.
-inline TilePlan choose_tile(int bucket, uint64_t num_buckets, uint64_t most_waves) {
+// tensors: how many level tables the call has (0: not one per tensor). most_waves: of a launch.
+inline TilePlan choose_tile(int bucket, uint64_t num_buckets, uint64_t tensors, uint64_t most_waves) {
     const TilePlan full = tile_plan(bucket);
+    if (tensors > 0 && num_buckets / tensors < (uint64_t)full.buckets)
+        return tile_plan_tensors(bucket, num_buckets / tensors);
     const TilePlan small = tile_plan_small(bucket);
     const uint64_t waves = (num_buckets + (uint64_t)small.buckets - 1) / (uint64_t)small.buckets * (uint64_t)small.waves;
     return waves < 4096 && waves < most_waves ? small : full;

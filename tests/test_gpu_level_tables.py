@@ -121,3 +121,26 @@ def test_nearest_level_among_close_levels(bits, B):
             qb.qsdp_quantize_levels(torch.from_numpy(x).to(DEV), bits, B, torch.from_numpy(table).to(DEV), codes, meta.view(-1))
             wc, wm = ref.quantize_levels(x, bits, B, table)
             assert np.array_equal(np_u32(codes), wc) and np.array_equal(np_u32(meta), wm.view(np.uint32).reshape(-1)), (k, gap)
+
+
+@pytest.mark.parametrize("stochastic", [False, True])
+@pytest.mark.parametrize("B,tensors", [(32, 1500), (128, 40), (128, 1400), (512, 1400), (608, 300), (1024, 1300), (2080, 50), (4096, 20)])
+def test_tensors_of_a_bucket_or_two(B, tensors, stochastic):
+    """A table each: as many workgroups as tensors, small tiles, and past 1280 small tensors the tile kernel for all buckets."""
+    rng = np.random.default_rng(B + tensors)
+    for most, bits in ((1, 4), (2, 7)):
+        sizes = [8 * int(v) for v in rng.integers(1, most * B // 8 + 1, tensors)]
+        tables = np.sort(rng.random((tensors, 1 << bits)), axis=1).astype(np.float32)
+        x = rng.standard_normal(sum(sizes)).astype(np.float32)
+        segs = qb.Segments(sizes, B, DEV)
+        codes, meta = segs.alloc_packed(bits)
+        qb.qsdp_quantize_levels_segmented(torch.from_numpy(x).to(DEV), segs, bits, torch.from_numpy(tables).to(DEV), codes,
+                                          meta.view(-1), stochastic, 3, 16)
+        want, o = [[], []], 0
+        for t, s in enumerate(sizes):
+            v = x[o:o + s].copy()
+            wc, wm = (ref.quantize_levels_stochastic(v, bits, B, tables[t], 3, 16 + o) if stochastic
+                      else ref.quantize_levels(v, bits, B, tables[t]))
+            want[0].append(wc); want[1].append(wm.view(np.uint32).reshape(-1))
+            o += s
+        assert np.array_equal(np_u32(codes), np.concatenate(want[0])) and np.array_equal(np_u32(meta), np.concatenate(want[1]))
