@@ -180,19 +180,24 @@ TileLauncher tile_launcher(const TilePlan& t) {
     return t.rows == 4 ? launch_tile_4_4 : t.rows == 6 ? launch_tile_4_6 : launch_tile_4_8;
 }
 
-// Workgroups of a learned-level encoder, given the number that would take one tile per wave (`waves` to a workgroup). A workgroup
-// sets up tables before its first tile, so it takes several: 16 for the nearest level, 32 for the coin flip with its
-// larger share of instructions, fewer where that would leave compute units without work (five workgroups each).
+constexpr uint64_t kComputeUnits = 256;
+
+// Workgroups of a learned-level encoder, given the number that would take one tile per wave (`waves` to a workgroup), how
+// many a compute unit holds at once and the number of tensors with a table of their own (0: one table). A workgroup sets up
+// tables before its first tile, so it takes several: 16 for the nearest level, 32 for the coin flip with its larger share of
+// instructions, fewer where that would leave compute units without work.
 // Measured (us, tiles per workgroup 12-20 / 16-32 / 24-48 / 32-64; nearest level, coin flip): 350M model in 292
 // tensors 317, 362 / 292, 346 / 302, 347 / 312, 331; 104M in buckets of 256, 128: 86, 136 / 89, 132 / 94, 132 / 101, 141;
 // 125M in buckets of 2048, 4096: 111, 143 / 113, 145 / 117, 143 / 118, 149.
-// And every tensor with a table of its own gets a workgroup, however small: with fewer, one workgroup sets up table after table
-// (300 tensors of one bucket of 128: 126 us against 8.6).
-uint64_t level_blocks(int mode, uint64_t blocks, int waves, uint64_t tensors) {
+// At least a round of the chip's resident ones, and no second round that would be less than half full (33M in 862 tensors,
+// buckets of 608, nearest level: 58.6 us in 1380 workgroups of which 1280 are resident, 47.6 in 1280; but 33M in buckets of
+// 1024 are faster in 1.6 rounds, 29.0 us, than in two, 31.3). And every tensor gets a workgroup, however small: with fewer, one
+// workgroup sets up table after table (300 tensors of one bucket of 128: 126 us against 8.6).
+uint64_t level_blocks(int mode, uint64_t blocks, int waves, int resident, uint64_t tensors) {
     const uint64_t tiles = mode == MODE_LEVELS_COIN ? 32 : 16;
     const uint64_t want = ceil_div(blocks * (uint64_t)waves, tiles);
-    const uint64_t resident = 5u * 256u;
-    const uint64_t most = want > resident ? want : resident;
+    const uint64_t round = (uint64_t)resident * kComputeUnits;
+    const uint64_t most = 2 * want < 3 * round ? round : want;
     const uint64_t few = blocks < most ? blocks : most;
     return few > tensors ? few : tensors;
 }
@@ -216,20 +221,21 @@ int run(int mode, Params p, int stored_bits, hipStream_t s) {
     // Tensors smaller than a wave's tile, more of them than the wave kernels' resident workgroups: the tile kernel has
     // four waves with tables of their own in a workgroup (8000 tensors of 512 or 1024 elements: 16-20 us against 31-32; 300
     // of them 8.6-8.9 us either way, 8 bit 10-20 against 9-11).
-    const bool many_small = tensors > 5u * 256u && p.bucket <= 1024 &&
+    const bool many_small = tensors > kLevelsResident * kComputeUnits && p.bucket <= 1024 &&
                             nb / tensors * (uint64_t)p.bucket <= 1024;
     if (wl != nullptr && !many_small) {
         // 4 waves per workgroup, each on bpw buckets; or one workgroup per bucket
         uint64_t blocks = bpw > 0 ? ceil_div(ceil_div(nb, (uint64_t)bpw), 4) : nb;
         if (mode_is_levels(mode))
-            blocks = level_blocks(mode, blocks, bpw > 0 ? 4 : p.bucket / 1024, tensors);
+            blocks = level_blocks(mode, blocks, bpw > 0 ? 4 : p.bucket / 1024, kLevelsResident, tensors);
         if (wl(mode, stored_bits, p, capped_grid(blocks), s) != hipSuccess) return QSDP_ELAUNCH;
     } else {
         const TilePlan t = choose_tile(p.bucket, nb, tensors, 4 * (uint64_t)grid_cap());
         const uint64_t units = ceil_div(nb, (uint64_t)t.buckets);
         uint64_t blocks = t.waves == 1 ? ceil_div(units, 4) : units;
         if (mode_is_levels(mode))
-            blocks = level_blocks(mode, blocks, 4, t.waves == 1 ? ceil_div(tensors, 4) : tensors);
+            blocks = level_blocks(mode, blocks, 4, tile_resident(mode == MODE_LEVELS_COIN, t.waves, t.rows),
+                                  t.waves == 1 ? ceil_div(tensors, 4) : tensors);
         const TileArgs a = {units, t.buckets, t.lanes_log2, t.group_magic, word_magic(stored_bits > 0 ? stored_bits : 8)};
         if (tile_launcher(t)(mode, p, a, capped_grid(blocks), s) != hipSuccess) return QSDP_ELAUNCH;
     }

@@ -4,12 +4,10 @@
 
 #include "qsdp_wave_kernel.hpp"
 
-// Workgroups (of 4 waves) per compute unit the compiler has to leave room for in registers.
-#ifndef QSDP_LEVELS_MIN_BLOCKS
-#define QSDP_LEVELS_MIN_BLOCKS 5
-#endif
-
 namespace qsdp {
+
+// Workgroups (of 4 waves) that a compute unit holds at once; the compiler has to leave room for them in registers.
+constexpr int kLevelsResident = 5;
 
 // ---------------------------------------------------------------------------------------
 // Both encoders count bounds. The K-1 ascending BOUNDS of a table split the unit interval so that the number of bounds
@@ -213,7 +211,7 @@ __device__ __forceinline__ void encode_levels_by(const float (&v)[R][4], uint32_
 // 6.2 TB/s 265 / 258): 5 bit nearest 292, 4 bit coin flip 346, against 519 and 485 with tables of its own for every wave, set
 // up for three buckets, and a second lookup (two levels and their distances) for the nearest level.
 template <int MODE, int G, int R, int BITS, int W>
-__global__ void __launch_bounds__(256, QSDP_LEVELS_MIN_BLOCKS) levels_kernel(const Params p, const Segment* __restrict__ segs) {
+__global__ void __launch_bounds__(256, kLevelsResident) levels_kernel(const Params p, const Segment* __restrict__ segs) {
     static_assert(mode_is_levels(MODE), "mode");
     constexpr int T = 4 * G * R;  // elements of a bucket one wave holds
     constexpr int B = T * W;

@@ -17,6 +17,7 @@
 
 #include "qsdp_params.hpp"
 #include "qsdp_levels_kernel.hpp"  // the level tables; widen16
+#include "qsdp_tile_plan.hpp"
 
 namespace qsdp {
 
@@ -109,7 +110,7 @@ struct TileArgs {
 };
 
 template <int MODE, int R, int W>
-__global__ void __launch_bounds__(256) tile_kernel(const Params p, const Segment* __restrict__ segs, const TileArgs a) {
+__global__ void __launch_bounds__(256, mode_is_levels(MODE) ? tile_resident(MODE == MODE_LEVELS_COIN, W, R) : 1) tile_kernel(const Params p, const Segment* __restrict__ segs, const TileArgs a) {
     static_assert(R % 2 == 0 && R <= kTileMaxRows && (W == 1 || W == 4), "shape");
     typedef TileLds<R, W> Lds;
     constexpr int TEAM = Lds::kTeam;

@@ -97,6 +97,12 @@ inline TilePlan choose_tile(int bucket, uint64_t num_buckets, uint64_t tensors, 
     return waves < 4096 && waves < most_waves ? small : full;
 }
 
+// Workgroups of a learned-level encoder that a compute unit holds at once: by registers (the kernels' launch bounds ask
+// for as many) and, for teams of one wave with their tables for each, by LDS.
+constexpr int tile_resident(bool coin, int waves, int rows) {
+    return rows <= 4 ? 5 : rows == 6 ? (coin ? 4 : waves == 1 ? 5 : 6) : coin ? (waves == 1 ? 3 : 2) : (waves == 1 ? 4 : 5);
+}
+
 // ceil(2^18 / bits): slot of the first bit of word w of a tile's code stream = (8 * w * magic) >> 18. A tile has at
 // most 2^11 slots, so 8 * w < 2^11 * bits and the product stays below 2^30.
 inline uint32_t word_magic(int bits) { return (262144u + (uint32_t)bits - 1u) / (uint32_t)bits; }
