@@ -296,13 +296,14 @@ __global__ void __launch_bounds__(256) dequant_seg_kernel(const DequantSegParams
                     }
                 }
             } else {
+                uint32_t t = tensor;  // the lane's tensor; its rows ascend, so the walk goes on from row to row
                 for (int u = 0; u < U; ++u) {
                     const uint64_t s = s0 + (uint64_t)(u * 64 * E + lane * E);
                     if (s < p.n) {
                         const uint64_t bucket = bucket_of<BK>(s, p);
-                        Segment mine = seg;
-                        uint32_t t = tensor;
-                        while (t + 1 < q.nseg && segs[t + 1].first_bucket <= bucket) mine = segs[++t];
+                        if (BK != BK_TILE_UNIFORM)
+                            while (t + 1 < q.nseg && segs[t + 1].first_bucket <= bucket) ++t;
+                        const Segment mine = t == tensor ? seg : segs[t];
                         const uint64_t e = mine.offset + (s - mine.first_bucket * B);
                         const uint64_t end = mine.offset + mine.n;
                         if (e < end) {
