@@ -73,8 +73,8 @@ void dequant_seg_launch(int bk, const DequantSegParams& q, unsigned grid, hipStr
 
 template <int BITS>
 hipError_t dequant_seg_go(bool bf16, const DequantSegParams& q, unsigned grid, hipStream_t s) {
-    const int bk = bucket_indexing(q.d, bf16, seg_rows(bf16));
     const bool lut = q.d.levels != nullptr;  // one table per tensor
+    const int bk = bucket_indexing(q.d, bf16, seg_rows(bf16, lut));
     if (bf16 && lut) dequant_seg_launch<BITS, true, true>(bk, q, grid, s);
     else if (bf16) dequant_seg_launch<BITS, true, false>(bk, q, grid, s);
     else if (lut) dequant_seg_launch<BITS, false, true>(bk, q, grid, s);
@@ -899,7 +899,7 @@ static int dequantize_segmented_common(const float* levels, const uint32_t* code
     q.segs = reinterpret_cast<const Segment*>(table);
     q.nseg = nseg;
     const bool half = out_dtype != QSDP_F32;
-    q.d.ntiles = ceil_div(q.d.n, (uint64_t)seg_rows(half) * 64u * (half ? 8u : 4u));
+    q.d.ntiles = ceil_div(q.d.n, (uint64_t)seg_rows(half, levels != nullptr) * 64u * (half ? 8u : 4u));
     q.run = seg_run(half, levels != nullptr, q.d.ntiles);
     grid = capped_grid(ceil_div(q.d.ntiles, 4u * (uint64_t)q.run));
     if (launch_dequant_seg(bits, out_dtype != QSDP_F32, q, grid, static_cast<hipStream_t>(stream)) != hipSuccess)

@@ -194,17 +194,21 @@ __global__ void __launch_bounds__(256) dequant_kernel(const DequantParams p) {
 // bank conflicts); wider tables go to an LDS slot of the wave. The lane-by-lane path reads them
 // through global memory.
 // What bounds it: the tables, segment search and codes of a wave that decodes one tile are a chain of round trips to
-// memory before its first store. Rows and run below were measured on the 350M model in 292 tensors, inputs not in
-// cache (us, 5 bit -> bf16 / 4 bit -> fp32 / 8 bit -> fp32 of 177M elements; one tile of 2 rows a wave, tables in LDS:
-// 235 / 353 / 265, uniform levels 192 / 328 / 180): 2 rows, run 2: 193 / 316 / 195, uniform 177 / 304 / 170; 4 rows, run
-// 1: 204 / 280 / 178, uniform 172 / 300 / 193; 4 rows, run 2: 197 / 307 / 194, uniform 175 / 295 / 172.
+// memory before its first store. With tables, rows and run were measured on the 350M model in 292 tensors, inputs not
+// in cache (us, 5 bit -> bf16 / 4 bit -> fp32 / 8 bit -> fp32 of 177M elements; one tile of 2 rows a wave, tables in LDS:
+// 235 / 353 / 265): 2 rows, run 2: 193 / 316 / 195; 4 rows, run 1: 204 / 280 / 178; 4 rows, run 2: 197 / 307 / 194.
+// Uniform levels have a shorter chain, and more in flight costs the stores (us, 4 bit / 8 bit -> fp32; 2 rows, run 1
+// against 4 rows, run 2): 131M elements in 400 tensors 97 / 107 against 120 / 122, codes in cache, and 112 / 107 against 124 / 122
+// not in cache; 60M in 400 47 / 52 against 57 / 58; the 350M model 249 / 281 against 262 / 310 and 298 / 282 against 272 / 309;
+// 8 bit -> bf16 165 against 166-170 with run 2. The search before the codes, as it once was: 98 / 113, 122 / 113; 45 / 54; 218 /
+// 291, 311 / 288.
 // ---------------------------------------------------------------------------------------
-constexpr int seg_rows(bool bf16) { return bf16 ? 2 : 4; }
+constexpr int seg_rows(bool bf16, bool lut) { return lut && !bf16 ? 4 : 2; }
 
-// Consecutive tiles of a wave: two, so that a search and a table serve both and the second tile's codes are under way while
-// the first is decoded; one for tables with fp32 output (280 against 307 us above: four rows in flight are enough there) and
-// where a buffer has too few tiles to give every resident wave of the chip (256 compute units x 32) two.
-inline uint32_t seg_run(bool bf16, bool lut, uint64_t ntiles) { return ntiles < 2 * 8192u || (!bf16 && lut) ? 1u : 2u; }
+// Consecutive tiles of a wave: two for tables with 2-byte output, so that a search and a table serve both and the second
+// tile's codes are under way while the first is decoded; one otherwise (see above) and where a buffer has too few tiles to give
+// every resident wave of the chip (256 compute units x 32) two.
+inline uint32_t seg_run(bool bf16, bool lut, uint64_t ntiles) { return lut && bf16 && ntiles >= 2 * 8192u ? 2u : 1u; }
 
 struct DequantSegParams {
     DequantParams d;  // d.n: slots (total buckets * bucket); d.out: the flat output
@@ -221,7 +225,7 @@ __global__ void __launch_bounds__(256) dequant_seg_kernel(const DequantSegParams
     constexpr bool kLanes = LUT && BITS <= 6, kShared = LUT && !kLanes;
     __shared__ float lut_all[kShared ? 4 * K : 1];
     constexpr int E = BF16 ? 8 : 4;
-    constexpr int U = seg_rows(BF16);
+    constexpr int U = seg_rows(BF16, LUT);
     constexpr uint64_t T = (uint64_t)U * 64 * E;
     const int lane = threadIdx.x & 63;
     const uint32_t wave_in_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
