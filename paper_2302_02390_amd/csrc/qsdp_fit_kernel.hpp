@@ -380,25 +380,31 @@ __device__ __forceinline__ void fit_batch(const Slot& slot, int m, Powers& power
         }
         fit_wave_sync();
     }
-    uint32_t most = 0;
+    // the powers are requested before it is known whether the table holds them: the answer comes while they are on the way
+    uint32_t c[M], most = 0;
+    typename Powers::Entry e[M];
+    auto request = [&] {
+#pragma unroll
+        for (int i = 0; i < M; ++i) e[i] = powers.fine[c[i] < (uint32_t)Powers::kFine ? c[i] : (uint32_t)Powers::kFine];
+    };
 #pragma unroll
     for (int i = 0; i < M; ++i) {
-        const uint32_t c = (uint32_t)(own[i] >> kFitCountShift);
-        most = c > most ? c : most;
+        c[i] = (uint32_t)(own[i] >> kFitCountShift);
+        most = c[i] > most ? c[i] : most;
     }
-    while (__builtin_expect(filled.count < m && __builtin_amdgcn_ballot_w64(most > (uint32_t)filled.count) != 0, 0))
-        powers.extend(filled, one_minus, lane);
+    request();
+    if (filled.count < m) {
+        while (__builtin_expect(__builtin_amdgcn_ballot_w64(most > (uint32_t)filled.count) != 0, 0)) {
+            powers.extend(filled, one_minus, lane);
+            request();
+        }
+    }
     if (Powers::kFine == Slot::kValues || __builtin_expect(__builtin_amdgcn_ballot_w64(most > (uint32_t)Powers::kFine) == 0, 1)) {
-        typename Powers::Entry e[M];
 #pragma unroll
-        for (int i = 0; i < M; ++i) e[i] = powers.fine[own[i] >> kFitCountShift];
-#pragma unroll
-        for (int i = 0; i < M; ++i)
-            lv[i] = Powers::step(lv[i], (uint32_t)(own[i] >> kFitCountShift), own[i] & kFitSumMask, e[i]);
+        for (int i = 0; i < M; ++i) lv[i] = Powers::step(lv[i], c[i], own[i] & kFitSumMask, e[i]);
     } else {
 #pragma unroll
-        for (int i = 0; i < M; ++i)
-            lv[i] = powers.step_any(lv[i], (uint32_t)(own[i] >> kFitCountShift), own[i] & kFitSumMask, one_minus);
+        for (int i = 0; i < M; ++i) lv[i] = powers.step_any(lv[i], c[i], own[i] & kFitSumMask, one_minus);
     }
 }
 
