@@ -206,7 +206,6 @@ uint64_t level_blocks(int mode, uint64_t blocks, int waves, int resident, uint64
 // p.num_buckets must be set.
 int run(int mode, Params p, int stored_bits, hipStream_t s) {
     const uint64_t nb = p.num_buckets;
-    p.first_bucket = 0;
     int bpw = 1;
     WaveLauncher wl = wave_launcher(p.bucket, &bpw);
     if (mode == MODE_WEIGHT && p.bucket == 1024 && p.segs == nullptr) {

@@ -87,10 +87,9 @@ struct Params {
     int npeers;
     float alpha;
     // problem
-    uint64_t n;             // elements (single tensor)
-    uint64_t first_bucket;  // first bucket this launch handles
-    uint64_t num_buckets;   // buckets this launch handles
-    uint64_t block0;        // index_offset / 8
+    uint64_t n;  // elements (single tensor)
+    uint64_t num_buckets;
+    uint64_t block0;  // index_offset / 8
     uint32_t nseg;
     uint32_t x16_f16;  // x16 holds IEEE binary16 instead of bf16
     uint32_t g_half;  // 0: binary32 gradient; 1: bf16, 2: binary16, widened to binary32 (exactly) on load

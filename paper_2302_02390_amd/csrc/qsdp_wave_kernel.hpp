@@ -368,7 +368,7 @@ __device__ __forceinline__ void sum_peer_slices(const Params& p, uint8_t* stage,
     }
 }
 
-// Every mode but the learned-level encoders (qsdp_levels_kernel.hpp) over the buckets first_bucket .. +num_buckets-1
+// Every mode but the learned-level encoders (qsdp_levels_kernel.hpp) over the buckets 0 .. num_buckets-1
 // (the last bucket of a tensor may be short). BITS is the width of the codes that are stored (0: a step without code output, or
 // MODE_SUM). W = waves per bucket (W > 1: the workgroup has exactly W waves and owns one bucket
 // per iteration). delta > 0 selects the explicit grid, p.flags the quantizer variants (both
@@ -421,12 +421,11 @@ __global__ void __launch_bounds__(256, mode_min_blocks(MODE)) wave_kernel(const 
     uint32_t saturated = 0;
 
     for (uint64_t q = unit0; q < nunits; q += unit_stride, parity ^= 1u) {
-        const uint64_t rel = q * BPW + sub;       // bucket within this launch
-        const bool active = rel < p.num_buckets;  // the lane's bucket exists
-        const uint64_t left = p.num_buckets - q * BPW;
+        const uint64_t bucket0 = q * BPW;                   // wave-uniform
+        const bool active = bucket0 + sub < p.num_buckets;  // the lane's bucket exists
+        const uint64_t left = p.num_buckets - bucket0;
         const int active_buckets = left < (uint64_t)BPW ? (int)left : BPW;
-        const uint64_t bucket0 = p.first_bucket + q * BPW;  // wave-uniform
-        const uint64_t bucket = active ? p.first_bucket + rel : bucket0;
+        const uint64_t bucket = active ? bucket0 + sub : bucket0;
         const BucketRef ref = locate_bucket(p, segs, bucket0, bucket, B);
         // this wave's tile of the bucket: all of it, or the wave's 1/W
         const uint32_t part0 = W > 1 ? wave_in_block * (uint32_t)T : 0u;
@@ -436,8 +435,7 @@ __global__ void __launch_bounds__(256, mode_min_blocks(MODE)) wave_kernel(const 
         // Philox block of the tile's first element; the tile's place in the code buffer (the
         // code stream is indexed by bucket number, every bucket padded to B slots)
         const uint64_t block_e0 = p.block0 + (e0 >> 3);
-        const uint64_t tile_slot0 = (W == 1 ? (p.first_bucket + q * BPW) * (uint64_t)B
-                                            : bucket * (uint64_t)B + part0);
+        const uint64_t tile_slot0 = (W == 1 ? bucket0 * (uint64_t)B : bucket * (uint64_t)B + part0);
         u4* tile_out = reinterpret_cast<u4*>(reinterpret_cast<uint8_t*>(p.codes) + (tile_slot0 >> 3) * SB);
         float* red_g = red_all + (W > 1 ? parity * 4 * W : 0);
         float* red_w = red_g + (W > 1 ? 2 * W : 0);
