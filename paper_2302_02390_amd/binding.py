@@ -139,9 +139,17 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+def _stream_handle(device):
+    return torch.cuda.current_stream(device).cuda_stream
+
+
 def _check(status, what):
     if status != QSDP_OK:
         raise QsdpError(status, what)
+
+
+# The handle alone, where torch offers it (a private name): a Stream object costs a small call as much as its kernel.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or _stream_handle
 
 
 def _launch(t, name, *args):
@@ -151,7 +159,7 @@ def _launch(t, name, *args):
     11-12 us a call, without them 7-8 (3.4-4.1 of it the launch itself). So the device is switched only if it is
     another one, and the stream is asked for its handle alone."""
     device = t.get_device()
-    stream = torch._C._cuda_getCurrentRawStream(device)
+    stream = _raw_stream(device)
     if device == torch.cuda.current_device():
         status = getattr(_lib or lib(), name)(*args, stream)
     else:

@@ -37,3 +37,20 @@ def test_two_streams_at_once_equal_sequential_calls():
     for k in range(2):
         assert torch.equal(got[k][0], want[k][0])
         assert torch.equal(got[k][1], want[k][1]) and torch.equal(got[k][2], want[k][2])
+
+
+def test_stream_handle_by_either_name(monkeypatch):
+    """The binding asks torch for the bare handle of the current stream, or for a Stream object where torch has no such name."""
+    n, B = 64 * 1024, 1024
+    x, g = wl.weights(n, 5, DEV), wl.grads_student_t3(n, 6, DEV)
+    want = x.clone()
+    qb.qsdp_fused_step(want, g, 1e-3, 8, 4, B, 0.0, 1)
+    torch.cuda.synchronize()
+    stream = torch.cuda.Stream(device=DEV)
+    with torch.cuda.stream(stream):
+        assert qb._raw_stream(torch.cuda.current_device()) == qb._stream_handle(torch.cuda.current_device())
+        monkeypatch.setattr(qb, "_raw_stream", qb._stream_handle)
+        got = x.clone()
+        qb.qsdp_fused_step(got, g, 1e-3, 8, 4, B, 0.0, 1)
+    stream.synchronize()
+    assert torch.equal(got, want)
