@@ -126,9 +126,9 @@ namespace {
 
 constexpr unsigned kMaxGrid = 1u << 20;
 
-// Most workgroups of a launch; the kernels stride beyond that. QSDP_DEBUG_MAXGRID (the library's one debug switch) lowers it,
-// and the size from which the chip counts as busy with it, so that the striding paths and the tiles of large calls
-// can be exercised on small inputs.
+// Most workgroups of a launch; the kernels stride beyond that. QSDP_DEBUG_MAXGRID (the library's one debug switch)
+// lowers it, and the size from which the chip counts as busy with it, so that the striding paths and the tiles of
+// large calls can be exercised on small inputs.
 unsigned grid_cap() {
     if (const char* e = std::getenv("QSDP_DEBUG_MAXGRID")) {
         const long v = std::atol(e);
@@ -182,17 +182,18 @@ TileLauncher tile_launcher(const TilePlan& t) {
 
 constexpr uint64_t kComputeUnits = 256;
 
-// Workgroups of a learned-level encoder, given the number that would take one tile per wave (`waves` to a workgroup), how
-// many a compute unit holds at once and the number of tensors with a table of their own (0: one table). A workgroup sets up
-// tables before its first tile, so it takes several: 16 for the nearest level, 32 for the coin flip with its larger share of
-// instructions, fewer where that would leave compute units without work.
+// Workgroups of a learned-level encoder, given the number that would take one tile per wave (`waves` to a workgroup),
+// how many a compute unit holds at once and the number of tensors with a table of their own (0: one table). A
+// workgroup sets up tables before its first tile, so it takes several: 16 for the nearest level, 32 for the coin flip
+// with its larger share of instructions, fewer where that would leave compute units without work.
 // Measured (us, tiles per workgroup 12-20 / 16-32 / 24-48 / 32-64; nearest level, coin flip): 350M model in 292
-// tensors 317, 362 / 292, 346 / 302, 347 / 312, 331; 104M in buckets of 256, 128: 86, 136 / 89, 132 / 94, 132 / 101, 141;
-// 125M in buckets of 2048, 4096: 111, 143 / 113, 145 / 117, 143 / 118, 149.
-// At least a round of the chip's resident ones, and no second round that would be less than half full (33M in 862 tensors,
-// buckets of 608, nearest level: 58.6 us in 1380 workgroups of which 1280 are resident, 47.6 in 1280; but 33M in buckets of
-// 1024 are faster in 1.6 rounds, 29.0 us, than in two, 31.3). And every tensor gets a workgroup, however small: with fewer, one
-// workgroup sets up table after table (300 tensors of one bucket of 128: 126 us against 8.6).
+// tensors 317, 362 / 292, 346 / 302, 347 / 312, 331; 104M in buckets of 256, 128: 86, 136 / 89, 132 / 94, 132 / 101,
+// 141; 125M in buckets of 2048, 4096: 111, 143 / 113, 145 / 117, 143 / 118, 149.
+// At least a round of the chip's resident ones, and no second round that would be less than half full (33M in 862
+// tensors, buckets of 608, nearest level: 58.6 us in 1380 workgroups of which 1280 are resident, 47.6 in 1280; but
+// 33M in buckets of 1024 are faster in 1.6 rounds, 29.0 us, than in two, 31.3). And every tensor gets a workgroup,
+// however small: with fewer, one workgroup sets up table after table (300 tensors of one bucket of 128: 126 us
+// against 8.6).
 uint64_t level_blocks(int mode, uint64_t blocks, int waves, int resident, uint64_t tensors) {
     const uint64_t tiles = mode == MODE_LEVELS_COIN ? 32 : 16;
     const uint64_t want = ceil_div(blocks * (uint64_t)waves, tiles);
@@ -217,9 +218,9 @@ int run(int mode, Params p, int stored_bits, hipStream_t s) {
     }
     // learned levels with a table per tensor: how many there are
     const uint64_t tensors = mode_is_levels(mode) && p.levels_per_tensor != 0 ? (p.nseg < nb ? p.nseg : nb) : 0;
-    // Tensors smaller than a wave's tile, more of them than the wave kernels' resident workgroups: the tile kernel has
-    // four waves with tables of their own in a workgroup (8000 tensors of 512 or 1024 elements: 16-20 us against 31-32; 300
-    // of them 8.6-8.9 us either way, 8 bit 10-20 against 9-11).
+    // Tensors smaller than a wave's tile, more of them than the wave kernels' resident workgroups: the tile kernel
+    // has four waves with tables of their own in a workgroup (8000 tensors of 512 or 1024 elements: 16-20 us against
+    // 31-32; 300 of them 8.6-8.9 us either way, 8 bit 10-20 against 9-11).
     const bool many_small = tensors > kLevelsResident * kComputeUnits && p.bucket <= 1024 &&
                             nb / tensors * (uint64_t)p.bucket <= 1024;
     if (wl != nullptr && !many_small) {

@@ -179,35 +179,33 @@ __global__ void __launch_bounds__(256) dequant_kernel(const DequantParams p) {
 }
 
 // ---------------------------------------------------------------------------------------
-// Decoder for a multi-tensor code buffer: slot s of the padded code stream (bucket s / B of the
-// whole buffer) belongs to the tensor whose bucket range holds that bucket and lands at element
-// seg.offset + (s - seg.first_bucket * B) of the flat output, if the tensor has that element.
-// Same tiling as dequant_kernel over SLOTS (p.n = number of slots). A wave takes `run` consecutive
-// tiles: the tensor of the first tile's first slot is found by a wave-uniform search (scalar loads,
-// see find_segment), from there it walks on. The codes and meta of a tile are addressed by slot alone,
-// so those of the first tile are requested before the search and those of the next one before a tile
-// is decoded. A tile that lies inside its tensor's elements (the common case) is decoded without
-// per-lane control flow; a tile that reaches a tensor's padding or the next tensor goes lane by lane,
-// each lane walking on from the tile's tensor to its own. LUT: learned levels, one table of 2^BITS floats
-// per tensor at d.levels (tensor t's at d.levels + t * 2^BITS). Up to 6 bits the lanes of a wave hold
-// the table of its tensor, one level each, and look it up by lane permutation (no LDS to fill, no
-// bank conflicts); wider tables go to an LDS slot of the wave. The lane-by-lane path reads them
-// through global memory.
+// Decoder for a multi-tensor code buffer: slot s of the padded code stream (bucket s / B of the whole buffer) belongs
+// to the tensor whose bucket range holds that bucket and lands at element seg.offset + (s - seg.first_bucket * B) of
+// the flat output, if the tensor has that element.
+// Same tiling as dequant_kernel over SLOTS (p.n = number of slots). A wave takes `run` consecutive tiles: the tensor
+// of the first tile's first slot is found by a wave-uniform search (scalar loads, see find_segment), from there it
+// walks on. The codes and meta of a tile are addressed by slot alone, so those of the first tile are requested before
+// the search and those of the next one before a tile is decoded. A tile that lies inside its tensor's elements (the
+// common case) is decoded without per-lane control flow; a tile that reaches a tensor's padding or the next tensor
+// goes lane by lane, each lane walking on from the tile's tensor to its own. LUT: learned levels, one table of 2^BITS
+// floats per tensor at d.levels (tensor t's at d.levels + t * 2^BITS). Up to 6 bits the lanes of a wave hold the
+// table of its tensor, one level each, and look it up by lane permutation (no LDS to fill, no bank conflicts); wider
+// tables go to an LDS slot of the wave. The lane-by-lane path reads them through global memory.
 // What bounds it: the tables, segment search and codes of a wave that decodes one tile are a chain of round trips to
 // memory before its first store. With tables, rows and run were measured on the 350M model in 292 tensors, inputs not
-// in cache (us, 5 bit -> bf16 / 4 bit -> fp32 / 8 bit -> fp32 of 177M elements; one tile of 2 rows a wave, tables in LDS:
-// 235 / 353 / 265): 2 rows, run 2: 193 / 316 / 195; 4 rows, run 1: 204 / 280 / 178; 4 rows, run 2: 197 / 307 / 194.
-// Uniform levels have a shorter chain, and more in flight costs the stores (us, 4 bit / 8 bit -> fp32; 2 rows, run 1
-// against 4 rows, run 2): 131M elements in 400 tensors 97 / 107 against 120 / 122, codes in cache, and 112 / 107 against 124 / 122
-// not in cache; 60M in 400 47 / 52 against 57 / 58; the 350M model 249 / 281 against 262 / 310 and 298 / 282 against 272 / 309;
-// 8 bit -> bf16 165 against 166-170 with run 2. The search before the codes, as it once was: 98 / 113, 122 / 113; 45 / 54; 218 /
-// 291, 311 / 288.
+// in cache (us, 5 bit -> bf16 / 4 bit -> fp32 / 8 bit -> fp32 of 177M elements; one tile of 2 rows a wave, tables in
+// LDS: 235 / 353 / 265): 2 rows, run 2: 193 / 316 / 195; 4 rows, run 1: 204 / 280 / 178; 4 rows, run 2: 197 / 307 /
+// 194. Uniform levels have a shorter chain, and more in flight costs the stores (us, 4 bit / 8 bit -> fp32; 2 rows,
+// run 1 against 4 rows, run 2): 131M elements in 400 tensors 97 / 107 against 120 / 122, codes in cache, and 112 /
+// 107 against 124 / 122 not in cache; 60M in 400 47 / 52 against 57 / 58; the 350M model 249 / 281 against 262 / 310
+// and 298 / 282 against 272 / 309; 8 bit -> bf16 165 against 166-170 with run 2. The search before the codes, as it
+// once was: 98 / 113, 122 / 113; 45 / 54; 218 / 291, 311 / 288.
 // ---------------------------------------------------------------------------------------
 constexpr int seg_rows(bool bf16, bool lut) { return lut && !bf16 ? 4 : 2; }
 
-// Consecutive tiles of a wave: two for tables with 2-byte output, so that a search and a table serve both and the second
-// tile's codes are under way while the first is decoded; one otherwise (see above) and where a buffer has too few tiles to give
-// every resident wave of the chip (256 compute units x 32) two.
+// Consecutive tiles of a wave: two for tables with 2-byte output, so that a search and a table serve both and the
+// second tile's codes are under way while the first is decoded; one otherwise (see above) and where a buffer has too
+// few tiles to give every resident wave of the chip (256 compute units x 32) two.
 inline uint32_t seg_run(bool bf16, bool lut, uint64_t ntiles) { return lut && bf16 && ntiles >= 2 * 8192u ? 2u : 1u; }
 
 struct DequantSegParams {

@@ -25,9 +25,11 @@ typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 // Philox4x32-10 (Salmon et al., SC'11). The key is wave-uniform, so its schedule lives in
 // scalar registers; each round costs two 32x32->64 multiplies and two three-operand xors per lane.
 // XOR3: an xor of three operands as one v_bitop3_b32 (the compiler makes two v_xor_b32 of it). For the kernels that
-// their instructions bind: 48.6M values, 3 bits from bf16, 34.2 -> 31.2 us; 100M, 2 bits from fp32, 71 -> 66.6;
-// coin flip onto levels 2 %. The kernels that memory binds got slower with it (fused step over the 1.3B vector 2.53
-// -> 2.56 ms, code-resident step over 350M 371 -> 382 us, 8-bit gradients 80.5 -> 83.4) and keep the two xors.
+// their instructions bind: coin flip onto levels 2 %; the tile kernel's gradient encoder 1-7 % at every width of 2-8
+// bits, from fp32 and 16-bit gradients (100M and 60M values, buckets of 96 to 8192; fp32, 8 bits, 8192: 2 % slower);
+// the wave kernels' up to 4 bits (128, 1024, 4096: fp32 0-8 %, 16 bits 6-11 %). Above 4 bits these keep the two xors:
+// from fp32 the gain is 0-3 % (8 bits 0), from 16-bit gradients it would be 4-9 %. The kernels that memory binds got
+// slower with it (fused step over the 1.3B vector 2.53 -> 2.56 ms, code-resident step over 350M 371 -> 382 us).
 // ---------------------------------------------------------------------------------------
 template <bool XOR3>
 __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {

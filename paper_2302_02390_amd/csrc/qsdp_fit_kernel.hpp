@@ -11,18 +11,19 @@ namespace qsdp {
 // steps of rate lr towards the mean of its values at once, in binary64: q <- q - (1 - (1-lr)^c)(q - mean), with the
 // mean of exact 32.32 fixed-point sums.
 //
-// The serial chain of batches bounds this, so the chain holds as little as possible. What a batch needs from the levels
-// is, for each pair of neighbours, how many values lie on the lower one's side and their sum; the normalised values
-// themselves do not depend on the levels. Producer waves therefore sort the coming batches into cells of the unit interval
-// (a counting sort: one LDS atomic per value returns the place within the cell and adds up count and sum, packed
-// into one word; a prefix sum over the cells follows), and one consumer wave walks the chain: a lane per pair of
-// neighbours reads the prefix at the cell of the midpoint, compares the few values of that cell with the two levels, and
-// has count and sum below the boundary; differences between lanes are the levels' own. No barrier and no atomic is left
-// in the chain; two LDS round trips for the boundary, one for the powers of 1 - lr and the reciprocals of the counts.
-// A team of W producer waves sorts a batch (the values stay in registers, at most 16 to a lane) and P teams make a round:
-// W = 1, P = 6 for buckets of up to 1024 values (one wave needs no barrier between its passes, and six of them sort as
-// fast as the consumer walks), W = 2, 4, 8 and P = 8 / W up to 2048, 4096, 8192 with a barrier after each of the four
-// passes. The consumer meanwhile walks the P batches of the round before; the slots are double-buffered.
+// The serial chain of batches bounds this, so the chain holds as little as possible. What a batch needs from the
+// levels is, for each pair of neighbours, how many values lie on the lower one's side and their sum; the normalised
+// values themselves do not depend on the levels. Producer waves therefore sort the coming batches into cells of the
+// unit interval (a counting sort: one LDS atomic per value returns the place within the cell and adds up count and
+// sum, packed into one word; a prefix sum over the cells follows), and one consumer wave walks the chain: a lane per
+// pair of neighbours reads the prefix at the cell of the midpoint, compares the few values of that cell with the two
+// levels, and has count and sum below the boundary; differences between lanes are the levels' own. No barrier and no
+// atomic is left in the chain; two LDS round trips for the boundary, one for the powers of 1 - lr and the reciprocals
+// of the counts. A team of W producer waves sorts a batch (the values stay in registers, at most 16 to a lane) and P
+// teams make a round: W = 1, P = 6 for buckets of up to 1024 values (one wave needs no barrier between its passes,
+// and six of them sort as fast as the consumer walks), W = 2, 4, 8 and P = 8 / W up to 2048, 4096, 8192 with a
+// barrier after each of the four passes. The consumer meanwhile walks the P batches of the round before; the slots
+// are double-buffered.
 //
 // Measured (us per batch, 5-bit table, Gaussian values, buckets of 128 / 1024 / 4096 / 8192): 0.45 / 0.57 / 1.8 / 3.5,
 // against 1.27 / 2.6 / 10.7 / 21 for a workgroup that stages one batch in LDS and assigns value by value with a barrier
@@ -59,14 +60,19 @@ struct FitShape {
     static constexpr int kProducers = kBatches * W;              // producer waves; the consumer is one more
     static constexpr int kThreads = 64 * (kProducers + 1);
     static constexpr int kBarriers = W == 1 ? 1 : 4;             // per round
-    // About a cell per value, as far as the 2 P slots leave LDS to spare. Half of that for buckets of 512 and up to 16
-    // levels, where it lets two workgroups share a compute unit at no cost to the chain (2000 tensors of one batch, 4 bit:
-    // 33.7 -> 23.3 us; with more levels the chain loses: 5 bit 0.49 -> 0.53 us per batch, 6 bit 0.56 -> 0.65).
-    static constexpr int kCells = kBucketMax <= 256 ? kBucketMax : kBucketMax == 512 && BITS <= 4 ? 256 : kBucketMax <= 2048 ? 512 : 1024;
+    // About a cell per value, as far as the 2 P slots leave LDS to spare. Half of that for buckets of 512 and up to
+    // 16 levels, where it lets two workgroups share a compute unit at no cost to the chain (2000 tensors of one
+    // batch, 4 bit: 33.7 -> 23.3 us; with more levels the chain loses: 5 bit 0.49 -> 0.53 us per batch, 6 bit 0.56 ->
+    // 0.65).
+    static constexpr int kCells = kBucketMax <= 256                ? kBucketMax
+                                  : kBucketMax == 512 && BITS <= 4 ? 256
+                                  : kBucketMax <= 2048             ? 512
+                                                                   : 1024;
     using Slot = FitSlot<kBucketMax, kCells>;
 };
 
-// Count and sum of a set of normalised values in one word: sum of at most 2^13 values of at most 2^32 below, count above.
+// Count and sum of a set of normalised values in one word: sum of at most 2^13 values of at most 2^32 below, count
+// above.
 constexpr int kFitCountShift = 46;
 constexpr uint64_t kFitSumMask = (1ull << kFitCountShift) - 1;
 
@@ -76,8 +82,8 @@ __device__ __forceinline__ uint64_t fit_fixed(float z) {
     return ((uint64_t)whole << 32) | (uint32_t)((z - (float)whole) * 4294967296.0f);
 }
 
-// The cell of a value (or of a boundary): C cells of equal width from `from` on, what lies outside them in the first and
-// the last. Monotone, and in range whatever the argument (the conversion saturates).
+// The cell of a value (or of a boundary): C cells of equal width from `from` on, what lies outside them in the first
+// and the last. Monotone, and in range whatever the argument (the conversion saturates).
 struct FitCells {
     float from, per_unit;
 };
@@ -154,8 +160,8 @@ __device__ __forceinline__ uint64_t fit_sum_subs(uint64_t v) {
     return v;
 }
 
-// Adds to a word in LDS and returns what it held. Relaxed: the callers put their own fences, and an ordered atomic would
-// wait for each one before the next.
+// Adds to a word in LDS and returns what it held. Relaxed: the callers put their own fences, and an ordered atomic
+// would wait for each one before the next.
 __device__ __forceinline__ uint64_t fit_add(uint64_t* word, uint64_t v) {
     return __hip_atomic_fetch_add(word, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
@@ -167,11 +173,11 @@ __device__ __forceinline__ void fit_wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// (1 - lr)^c by repeated multiplication, the order in which c single steps compound, for c up to the bucket size: every
-// power up to kFine beside the reciprocal of the count, beyond that every kStep-th. The multiplications are a serial
-// chain (about 8 ns each), so the consumer extends it as the counts ask for it: most counts are a small share of a
-// bucket, and a tensor of few batches would wait for powers that it never reads. The reciprocals are the producers' work,
-// while their first loads are on the way.
+// (1 - lr)^c by repeated multiplication, the order in which c single steps compound, for c up to the bucket size:
+// every power up to kFine beside the reciprocal of the count, beyond that every kStep-th. The multiplications are a
+// serial chain (about 8 ns each), so the consumer extends it as the counts ask for it: most counts are a small share
+// of a bucket, and a tensor of few batches would wait for powers that it never reads. The reciprocals are the
+// producers' work, while their first loads are on the way.
 struct FitFilled {
     int count;    // the powers of counts up to this one can be read
     double keep;  // where the chain stands
@@ -255,10 +261,10 @@ struct FitPowers {
     }
 };
 
-// A batch as the consumer reads it: the values grouped by cell (ascending cells, any order within one), and for every cell
-// count and sum of the values in the cells before it; cell C: of all values.
-// The prefix sum gives a lane kOwn cells in a row; one word of padding after each of these runs keeps the lanes off one
-// another's banks (without it all 64 lanes meet in two banks: 0.15 us more per batch of 1024).
+// A batch as the consumer reads it: the values grouped by cell (ascending cells, any order within one), and for every
+// cell count and sum of the values in the cells before it; cell C: of all values.
+// The prefix sum gives a lane kOwn cells in a row; one word of padding after each of these runs keeps the lanes off
+// one another's banks (without it all 64 lanes meet in two banks: 0.15 us more per batch of 1024).
 template <int BMAX, int C>
 struct FitSlot {
     static constexpr int kValues = BMAX;
@@ -277,8 +283,8 @@ struct FitLanes {
     static constexpr int M = K <= 64 ? 1 : K / 64;
 };
 
-// One batch of the chain. lv[i]: the lane's levels, updated. lv_shared, acc: K entries of LDS each, for batches that are
-// assigned value by value.
+// One batch of the chain. lv[i]: the lane's levels, updated. lv_shared, acc: K entries of LDS each, for batches that
+// are assigned value by value.
 template <int BITS, typename Slot, typename Powers, int C>
 __device__ __forceinline__ void fit_batch(const Slot& slot, int m, Powers& powers, FitFilled& filled, double one_minus,
                                           FitCells cells, float (&lv)[FitLanes<BITS>::M], float* lv_shared,
@@ -380,7 +386,8 @@ __device__ __forceinline__ void fit_batch(const Slot& slot, int m, Powers& power
         }
         fit_wave_sync();
     }
-    // the powers are requested before it is known whether the table holds them: the answer comes while they are on the way
+    // the powers are requested before it is known whether the table holds them: the answer comes while they are on
+    // the way
     uint32_t c[M], most = 0;
     typename Powers::Entry e[M];
     auto request = [&] {
@@ -399,7 +406,8 @@ __device__ __forceinline__ void fit_batch(const Slot& slot, int m, Powers& power
             request();
         }
     }
-    if (Powers::kFine == Slot::kValues || __builtin_expect(__builtin_amdgcn_ballot_w64(most > (uint32_t)Powers::kFine) == 0, 1)) {
+    if (Powers::kFine == Slot::kValues ||
+        __builtin_expect(__builtin_amdgcn_ballot_w64(most > (uint32_t)Powers::kFine) == 0, 1)) {
 #pragma unroll
         for (int i = 0; i < M; ++i) lv[i] = Powers::step(lv[i], c[i], own[i] & kFitSumMask, e[i]);
     } else {
@@ -466,8 +474,8 @@ __global__ void __launch_bounds__((FitShape<BITS, VPT, W>::kThreads)) fit_levels
 #pragma unroll
             for (int i = 0; i < P; ++i) {
                 if (r * P + i < num_batches)
-                    fit_batch<BITS, Slot, Powers, C>(slots[buffer + i], batch_size(r * P + i), powers, filled, one_minus,
-                                                     cells[i], lv, lv_shared, acc, lane);
+                    fit_batch<BITS, Slot, Powers, C>(slots[buffer + i], batch_size(r * P + i), powers, filled,
+                                                     one_minus, cells[i], lv, lv_shared, acc, lane);
                 for (int b = 0; b < (W == 1 ? (i == P - 1 ? 1 : 0) : Shape::kBarriers / P); ++b) __syncthreads();
             }
         }
@@ -481,9 +489,9 @@ __global__ void __launch_bounds__((FitShape<BITS, VPT, W>::kThreads)) fit_levels
         auto team_sync = [] {
             if constexpr (W > 1) __syncthreads(); else fit_wave_sync();
         };
-        // a producer: batch r * P + team in round r, this wave's 1/W of it; past the last batch the last one again (nobody
-        // reads it). Lanes past the end of a batch carry its last value: it changes no minimum or maximum, it counts
-        // nothing and lands in the spare place.
+        // a producer: batch r * P + team in round r, this wave's 1/W of it; past the last batch the last one again
+        // (nobody reads it). Lanes past the end of a batch carry its last value: it changes no minimum or maximum, it
+        // counts nothing and lands in the spare place.
         const int team = wave / W, part = wave % W;
         const int scanner = W == 2 ? team / 2 : W == 4 ? team : 0;  // of the team's waves: on another SIMD for every team
         const int first = part * 64 + lane;  // value q of the lane: first + q * 64 * W

@@ -1,6 +1,8 @@
-// The learned-level encoders: a bucket is owned as in the wave kernels (qsdp_wave_kernel.hpp, whose loads, reductions and
-// packing they share), its values are encoded against a table of K = 2^BITS ascending levels in [0, 1].
+// The learned-level encoders: a bucket is owned as in the wave kernels (qsdp_wave_kernel.hpp, whose loads, reductions
+// and packing they share), its values are encoded against a table of K = 2^BITS ascending levels in [0, 1].
 #pragma once
+
+#include <type_traits>
 
 #include "qsdp_wave_kernel.hpp"
 
@@ -20,8 +22,8 @@ constexpr int kLevelsResident = 5;
 // differences and products are the unscaled ones times an exact power of two and decide alike, bit for bit (but for
 // normalised values below 2^-126, which the scaling saves from being rounded to subnormals).
 //   * Counting by cell: for each of the C cells of the unit interval a table holds how many bounds lie at or below its
-//     start and the next bound. If no cell holds two different bounds, a count is one LDS read and one comparison. (Equal
-//     bounds, from equal levels, are passed all at once: the table also holds how many there are.)
+//     start and the next bound. If no cell holds two different bounds, a count is one LDS read and one comparison.
+//     (Equal bounds, from equal levels, are passed all at once: the table also holds how many there are.)
 //   * Counting by search, where a cell holds two: branch-free binary search whose first two pivots are
 //     wave-uniform and held in scalar registers.
 // Nearest-level tables whose thresholds cannot be relied on (see level_threshold) are searched by the plain definition.
@@ -31,7 +33,8 @@ enum LevelMethod { LEVELS_PLAIN = 0, LEVELS_BY_SEARCH = 1, LEVELS_BY_CELL = 2, L
 template <int BITS>
 struct LevelShape {
     static constexpr int K = 1 << BITS;
-    // about eight cells to a bound: tables denser in the middle by a factor of four still have their cells to themselves
+    // about eight cells to a bound: tables denser in the middle by a factor of four still have their cells to
+    // themselves
     static constexpr int C = BITS <= 5 ? 256 : BITS == 6 ? 512 : 1024;
     static constexpr float kScale = (float)C;
 };
@@ -48,9 +51,9 @@ enum LevelFlags : uint32_t {
     LEVELS_JUMPS = 4u      // a cell holds equal bounds
 };
 
-// Entries thread, thread + THREADS, ... of the cell table over K - 1 bounds, K a power of two (cell c is [c, c+1) in cell
-// units; the last entry, C, serves a value of exactly 1). All of a thread's entries are searched for side by side: the
-// set-up is a chain of LDS reads, and small calls and small tensors wait for it.
+// Entries thread, thread + THREADS, ... of the cell table over K - 1 bounds, K a power of two (cell c is [c, c+1) in
+// cell units; the last entry, C, serves a value of exactly 1). All of a thread's entries are searched for side by
+// side: the set-up is a chain of LDS reads, and small calls and small tensors wait for it.
 template <int C, int THREADS>
 __device__ __forceinline__ uint32_t fill_level_cells(LevelCell* cells, const float* bounds, int K, int thread) {
     constexpr int N = C / THREADS + 1;
@@ -91,13 +94,13 @@ __device__ __forceinline__ uint32_t fill_level_cells(LevelCell* cells, const flo
     return flags;
 }
 
-// Threshold k of the K levels lv, scaled by `unit`; false if there is none to rely on. A value between the levels k and
-// k+1 is compared with these two alone: one rounded distance rises with the value and the other falls, so the comparison
-// flips once, and it does so within two steps of the midpoint (only the distance to a level below z/2 is rounded at all, by
-// half a step). Values past the last level are compared with the last two: that goes to the last one if these are more
-// than 2^-20 apart (the distances differ by the gap, and each is rounded by less than 2^-24), or equal, or if the last
-// level is 1. In a run of equal levels every threshold is that of the run's end, so that its first level is the only
-// one that is ever chosen.
+// Threshold k of the K levels lv, scaled by `unit`; false if there is none to rely on. A value between the levels k
+// and k+1 is compared with these two alone: one rounded distance rises with the value and the other falls, so the
+// comparison flips once, and it does so within two steps of the midpoint (only the distance to a level below z/2 is
+// rounded at all, by half a step). Values past the last level are compared with the last two: that goes to the last
+// one if these are more than 2^-20 apart (the distances differ by the gap, and each is rounded by less than 2^-24),
+// or equal, or if the last level is 1. In a run of equal levels every threshold is that of the run's end, so that its
+// first level is the only one that is ever chosen.
 __device__ __forceinline__ bool level_threshold(const float* lv, int k, int K, float unit, float* threshold) {
     const float lo = lv[k];
     int next = k + 1;
@@ -122,8 +125,9 @@ __device__ __forceinline__ bool level_threshold(const float* lv, int k, int K, f
 }
 
 // What the coin flip needs at level i: the level (cell units) and the reciprocal of the gap to the next one (per cell
-// unit; 0 for the last level: nothing to round up to). The reciprocal is that of the unscaled gap, rounded (or infinite)
-// as the definition has it, then divided by `cells`, exactly: (z - q) * rgap is the unscaled product bit for bit.
+// unit; 0 for the last level: nothing to round up to). The reciprocal is that of the unscaled gap, rounded (or
+// infinite) as the definition has it, then divided by `cells`, exactly: (z - q) * rgap is the unscaled product bit
+// for bit.
 struct LevelCoin {
     float q, rgap;
 };
@@ -132,8 +136,8 @@ __device__ __forceinline__ LevelCoin level_coin(const float* lv, int k, int K, f
     return {lv[k], k + 1 < K ? (1.0f / ((lv[k + 1] - lv[k]) * per_cell)) * per_cell : 0.0f};
 }
 
-// Whether the coin flip goes up: 2^16 - (h + 1/2) < 2^16 p for the 16-bit uniform h and p = (z - q) * rgap. Both sides are
-// taken at 2^-16 of that, where the left one is exact and the right one cannot overflow for small gaps.
+// Whether the coin flip goes up: 2^16 - (h + 1/2) < 2^16 p for the 16-bit uniform h and p = (z - q) * rgap. Both
+// sides are taken at 2^-16 of that, where the left one is exact and the right one cannot overflow for small gaps.
 __device__ __forceinline__ bool coin_up(float z, float h, LevelCoin e) {
     return fmaf(h, -0x1p-16f, 1.0f - 0x1p-17f) < (z - e.q) * e.rgap;
 }
@@ -150,10 +154,11 @@ __device__ __forceinline__ LevelPivots load_level_pivots(const float* bounds) {
             uniform(bounds[BITS >= 2 ? 3 * K / 4 - 1 : 0])};
 }
 
-// How many bounds are at or below z (cell units). By cell the conversion saturates and the index is clamped, so a non-finite
-// value cannot read outside the table.
+// How many bounds are at or below z (cell units). By cell the conversion saturates and the index is clamped, so a
+// non-finite value cannot read outside the table.
 template <int BITS, int METHOD>
-__device__ __forceinline__ uint32_t count_bounds(float z, const float* bounds, const LevelCell* cells, const LevelPivots& pv) {
+__device__ __forceinline__ uint32_t count_bounds(float z, const float* bounds, const LevelCell* cells,
+                                                 const LevelPivots& pv) {
     constexpr int K = 1 << BITS, C = LevelShape<BITS>::C;
     if constexpr (METHOD == LEVELS_BY_CELL || METHOD == LEVELS_BY_CELL_JUMPS) {
         const uint32_t c = (uint32_t)z;
@@ -172,10 +177,10 @@ __device__ __forceinline__ uint32_t count_bounds(float z, const float* bounds, c
 
 // A lane's rows: v -> codes.
 template <int MODE, int G, int R, int BITS, int METHOD>
-__device__ __forceinline__ void encode_levels_by(const float (&v)[R][4], uint32_t (&code)[R][4], float lo, float inv_cells,
-                                                 const float* lv, const float* bounds, const LevelCell* cells,
-                                                 const LevelCoin* coin, const LevelPivots& pivots, uint64_t block_e0, int l,
-                                                 PhiloxKey key) {
+__device__ __forceinline__ void encode_levels_by(const float (&v)[R][4], uint32_t (&code)[R][4], float lo,
+                                                 float inv_cells, const float* lv, const float* bounds,
+                                                 const LevelCell* cells, const LevelCoin* coin,
+                                                 const LevelPivots& pivots, uint64_t block_e0, int l, PhiloxKey key) {
     if constexpr (MODE == MODE_LEVELS_COIN) {
 #pragma unroll
         for (int cp = 0; cp < R / 2; ++cp) {
@@ -186,8 +191,8 @@ __device__ __forceinline__ void encode_levels_by(const float (&v)[R][4], uint32_
                 const int r = 2 * cp + (i >> 2);
                 const float z = (v[r][i & 3] - lo) * inv_cells;
                 // Unbiased rounding onto the enclosing levels: with p = (z - level) / gap, up for the round(p * 2^16)
-                // largest of the 2^16 values of the uniform h. z below the first level gives 0 (p < 0 there), at or above the
-                // last K-1 (its reciprocal gap is 0).
+                // largest of the 2^16 values of the uniform h. z below the first level gives 0 (p < 0 there), at or
+                // above the last K-1 (its reciprocal gap is 0).
                 const uint32_t at = count_bounds<BITS, METHOD>(z, bounds, cells, pivots);
                 const LevelCoin e = coin[at];
                 code[r][i & 3] = at + (coin_up(z, (float)uniform16(h, i), e) ? 1u : 0u);
@@ -205,13 +210,15 @@ __device__ __forceinline__ void encode_levels_by(const float (&v)[R][4], uint32_
     }
 }
 
-// A workgroup takes a contiguous run of buckets (see level_blocks for how many), piece by piece of its tensors where every
-// tensor has its own table (segs != nullptr), and its waves share the tables of the piece. What bounds the encoders: the
-// instructions first, then the time a workgroup spends on its tables. Measured, 350M model in 292 tensors (us; floor at
-// 6.2 TB/s 265 / 258): 5 bit nearest 292, 4 bit coin flip 346, against 519 and 485 with tables of its own for every wave, set
-// up for three buckets, and a second lookup (two levels and their distances) for the nearest level.
+// A workgroup takes a contiguous run of buckets (see level_blocks for how many), piece by piece of its tensors where
+// every tensor has its own table (segs != nullptr), and its waves share the tables of the piece. What bounds the
+// encoders: the instructions first, then the time a workgroup spends on its tables. Measured, 350M model in 292
+// tensors (us; floor at 6.2 TB/s 265 / 258): 5 bit nearest 292, 4 bit coin flip 346, against 519 and 485 with tables
+// of its own for every wave, set up for three buckets, and a second lookup (two levels and their distances) for the
+// nearest level.
 template <int MODE, int G, int R, int BITS, int W>
-__global__ void __launch_bounds__(256, kLevelsResident) levels_kernel(const Params p, const Segment* __restrict__ segs) {
+__global__ void __launch_bounds__(256, kLevelsResident) levels_kernel(const Params p,
+                                                                       const Segment* __restrict__ segs) {
     static_assert(mode_is_levels(MODE), "mode");
     constexpr int T = 4 * G * R;  // elements of a bucket one wave holds
     constexpr int B = T * W;
@@ -299,7 +306,8 @@ __global__ void __launch_bounds__(256, kLevelsResident) levels_kernel(const Para
         __syncthreads();
         uint32_t found = 0;
         if constexpr (kCoin) {
-            for (int k = threadIdx.x; k < K; k += kThreads) coin[k] = level_coin(levels, k, K, LevelShape<BITS>::kScale);
+            for (int k = threadIdx.x; k < K; k += kThreads)
+                coin[k] = level_coin(levels, k, K, LevelShape<BITS>::kScale);
         } else {
             for (int k = threadIdx.x; k < K - 1; k += kThreads)
                 if (!level_threshold(levels, k, K, LevelShape<BITS>::kScale, thresholds + k)) found |= LEVELS_UNUSABLE;
@@ -334,23 +342,20 @@ __global__ void __launch_bounds__(256, kLevelsResident) levels_kernel(const Para
             rows_minmax<G, R>(v, l, tile.m, tile.partial, lo, hi);
             block_combine_minmax<W>(lo, hi, red_all + (W > 1 ? parity * 2 * W : 0), wave);
             const MinMaxGrid grid = make_minmax_grid(lo, hi, 1.0f, false);  // scale = hi - lo, inv = 1/(hi - lo)
-            const float inv_cells = grid.inv * LevelShape<BITS>::kScale;  // normalised value in cell units: (v - lo) * inv_cells
+            // normalised value in cell units: (v - lo) * inv_cells
+            const float inv_cells = grid.inv * LevelShape<BITS>::kScale;
             const uint64_t block_e0 = p.block0 + (tile.e0 >> 3);  // Philox block of the tile's first element
             uint32_t code[R][4];
-            // the method is chosen once for all of the lane's elements, so that each is straight-line code over the rows
-            // and the LDS reads of different elements overlap
-            if (__builtin_expect(method == LEVELS_BY_CELL, 1))
-                encode_levels_by<MODE, G, R, BITS, LEVELS_BY_CELL>(v, code, grid.lo, inv_cells, levels, bounds, cells, coin, pivots,
-                                                                   block_e0, l, key);
-            else if (method == LEVELS_BY_CELL_JUMPS)
-                encode_levels_by<MODE, G, R, BITS, LEVELS_BY_CELL_JUMPS>(v, code, grid.lo, inv_cells, levels, bounds, cells, coin,
-                                                                         pivots, block_e0, l, key);
-            else if (kCoin || method == LEVELS_BY_SEARCH)
-                encode_levels_by<MODE, G, R, BITS, LEVELS_BY_SEARCH>(v, code, grid.lo, inv_cells, levels, bounds, cells, coin,
-                                                                     pivots, block_e0, l, key);
-            else
-                encode_levels_by<MODE, G, R, BITS, LEVELS_PLAIN>(v, code, grid.lo, inv_cells, levels, bounds, cells, coin, pivots,
-                                                                 block_e0, l, key);
+            // the method is chosen once for all of the lane's elements, so that each is straight-line code over the
+            // rows and the LDS reads of different elements overlap
+            auto encode = [&](auto by) {
+                encode_levels_by<MODE, G, R, BITS, decltype(by)::value>(v, code, grid.lo, inv_cells, levels, bounds,
+                                                                        cells, coin, pivots, block_e0, l, key);
+            };
+            if (__builtin_expect(method == LEVELS_BY_CELL, 1)) encode(std::integral_constant<int, LEVELS_BY_CELL>{});
+            else if (method == LEVELS_BY_CELL_JUMPS) encode(std::integral_constant<int, LEVELS_BY_CELL_JUMPS>{});
+            else if (kCoin || method == LEVELS_BY_SEARCH) encode(std::integral_constant<int, LEVELS_BY_SEARCH>{});
+            else encode(std::integral_constant<int, LEVELS_PLAIN>{});
             if (__builtin_expect(tile.partial, 0)) zero_slots_past_end<G, R>(code, l, tile.m);
             store_codes<G, R, BITS>(stage, tile_out, lane, active_buckets, code);
             if (tile.active && l == 0 && (W == 1 || wave == 0)) {

@@ -1,5 +1,6 @@
 // Tile kernel: the encoders and steps for any bucket size (a multiple of 32 up to kMaxBucket) and any code width, both
-// run-time values. Serves the bucket sizes the wave kernels are not instantiated for.
+// run-time values. Serves the bucket sizes the wave kernels are not instantiated for, and tensors too small for them
+// with a level table each.
 //
 // A team of W waves works on a tile of P whole consecutive buckets, i.e. on one contiguous piece of the vector and of
 // the code stream: slot s of the tile is its elements 4s .. 4s+3, lane t of the team holds slots r*64W + t of every
@@ -11,8 +12,9 @@
 // Bound by HBM where a tile is well filled: the step with code output on 125 million parameters in buckets of 768 (W8
 // G8) takes 0.268 ms = 6.1 TB/s, against 1.33 ms for a workgroup per bucket that stages its values in LDS and packs
 // its codes bit by bit; buckets of 96 on 8 million parameters 0.022 against 0.353 ms. P is the largest count that fits
-// (qsdp_tile_plan.hpp), so few slots idle; leaving out the arithmetic of a wave's idle rows by branches cost the full
-// tiles 3-10 % (the rows no longer overlap) and won 4 % at the worst fill, so it is not done.
+// (qsdp_tile_plan.hpp, which also says when a tile is smaller), so few slots idle; leaving out the arithmetic of a
+// wave's idle rows by branches cost the full tiles 3-10 % (the rows no longer overlap) and won 4 % at the worst fill,
+// so it is not done there.
 #pragma once
 
 #include "qsdp_params.hpp"
@@ -86,12 +88,12 @@ __device__ __forceinline__ uint32_t stochastic_level_any(float z, float h, const
     return (uint32_t)i + (coin_up(z, h, level_coin(lv, i, K, cells)) ? 1u : 0u);
 }
 
-// The tables of a learned-level encoder for the tensor that a team works on (see qsdp_levels_kernel.hpp), with the code width
-// a run-time value: levels and bounds in units of 1/256, a count by cell, by search where the cells are crowded. A team
-// takes a run of tiles and sets them up once per tensor. One table, us, against a search and two distances per value:
-// 113M values in buckets of 1472, 4 bits 204 -> 116; 27M, 1568, 2 bits 60 -> 29; 125M, 4128, 5 bits 325 -> 137; coin flip,
-// 125M, 608, 4 bits 229 -> 196. With a table per tensor the tiles that tensors share take a pass and a set-up for each
-// (113M 203 -> 120; 33M in 184 tensors, buckets of 96, 81 -> 69).
+// The tables of a learned-level encoder for the tensor that a team works on (see qsdp_levels_kernel.hpp), with the
+// code width a run-time value: levels and bounds in units of 1/256, a count by cell, by search where the cells are
+// crowded. A team takes a run of tiles and sets them up once per tensor. One table, us, against a search and two
+// distances per value: 113M values in buckets of 1472, 4 bits 204 -> 116; 27M, 1568, 2 bits 60 -> 29; 125M, 4128, 5
+// bits 325 -> 137; coin flip, 125M, 608, 4 bits 229 -> 196. With a table per tensor the tiles that tensors share take
+// a pass and a set-up for each (113M 203 -> 120; 33M in 184 tensors, buckets of 96, 81 -> 69).
 template <bool COIN>
 struct TileLevels {
     static constexpr int C = 256;
@@ -110,7 +112,8 @@ struct TileArgs {
 };
 
 template <int MODE, int R, int W>
-__global__ void __launch_bounds__(256, mode_is_levels(MODE) ? tile_resident(MODE == MODE_LEVELS_COIN, W, R) : 1) tile_kernel(const Params p, const Segment* __restrict__ segs, const TileArgs a) {
+__global__ void __launch_bounds__(256, mode_is_levels(MODE) ? tile_resident(MODE == MODE_LEVELS_COIN, W, R) : 1)
+    tile_kernel(const Params p, const Segment* __restrict__ segs, const TileArgs a) {
     static_assert(R % 2 == 0 && R <= kTileMaxRows && (W == 1 || W == 4), "shape");
     typedef TileLds<R, W> Lds;
     constexpr int TEAM = Lds::kTeam;
@@ -245,12 +248,14 @@ __global__ void __launch_bounds__(256, mode_is_levels(MODE) ? tile_resident(MODE
 #pragma unroll
                 for (int r = 0; r < R; ++r)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) v[r][i] = widen16<true>(i & 1 ? h[r][i >> 1] >> 16 : h[r][i >> 1] & 0xFFFFu);
+                    for (int i = 0; i < 4; ++i)
+                        v[r][i] = widen16<true>(i & 1 ? h[r][i >> 1] >> 16 : h[r][i >> 1] & 0xFFFFu);
             } else {
 #pragma unroll
                 for (int r = 0; r < R; ++r)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) v[r][i] = widen16<false>(i & 1 ? h[r][i >> 1] >> 16 : h[r][i >> 1] & 0xFFFFu);
+                    for (int i = 0; i < 4; ++i)
+                        v[r][i] = widen16<false>(i & 1 ? h[r][i >> 1] >> 16 : h[r][i >> 1] & 0xFFFFu);
             }
         };
         auto store = [&](float* base, const float (&v)[R][4]) {
@@ -259,7 +264,8 @@ __global__ void __launch_bounds__(256, mode_is_levels(MODE) ? tile_resident(MODE
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
                     const f4 x = {v[r][0], v[r][1], v[r][2], v[r][3]};
-                    if (slot_of(r) < used) __builtin_nontemporal_store(x, reinterpret_cast<f4*>(at + (uint32_t)slot_of(r) * 16u));
+                    if (slot_of(r) < used)
+                        __builtin_nontemporal_store(x, reinterpret_cast<f4*>(at + (uint32_t)slot_of(r) * 16u));
                 }
             } else {
 #pragma unroll
@@ -297,7 +303,8 @@ __global__ void __launch_bounds__(256, mode_is_levels(MODE) ? tile_resident(MODE
         auto uniforms = [&](int cp, uint32_t (&h)[4]) {
             const int slot = (2 * cp + odd) * TEAM + tid - odd;
             const uint32_t rel = __builtin_expect(whole, 1) ? (uint32_t)slot * 4u : place(slot).rel;
-            uniforms_of_pair<(MODE == MODE_GRAD || MODE == MODE_LEVELS_COIN)>(p.block0 + (e0 >> 3) + (rel >> 3), odd, key.k0, key.k1, h);
+            uniforms_of_pair<(MODE == MODE_GRAD || MODE == MODE_LEVELS_COIN)>(p.block0 + (e0 >> 3) + (rel >> 3), odd,
+                                                                              key.k0, key.k1, h);
         };
         // Minimum and maximum of every bucket of the tile, then its grid: make(lo, hi, bucket in the tile) in the
         // lanes that combine that bucket, the result in lds.grid for all.
@@ -382,7 +389,8 @@ __global__ void __launch_bounds__(256, mode_is_levels(MODE) ? tile_resident(MODE
             if (bits != 8) team_sync<W>();
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                uint32_t q = code[r][0] | (code[r][1] << bits) | (code[r][2] << (2 * bits)) | (code[r][3] << (3 * bits));
+                uint32_t q = code[r][0] | (code[r][1] << bits);
+                q |= (code[r][2] << (2 * bits)) | (code[r][3] << (3 * bits));
                 if (__builtin_expect(!whole, 0)) {
                     const int c = place(slot_of(r)).count;
                     if (c < 4) q &= (1u << (c * bits)) - 1u;
@@ -483,8 +491,9 @@ __global__ void __launch_bounds__(256, mode_is_levels(MODE) ? tile_resident(MODE
                 fetch_words(words + next * p.peer_codes_stride_words, p.gbits, words_b);
                 f4 meta = {0.0f, 0.0f, 0.0f, 0.0f};
                 if (tid < here) {
-                    const float* m = p.peer_meta + (uint64_t)peer0 * p.peer_meta_stride_floats + 2 * (bucket0 + (uint64_t)tid);
-                    const float* m2 = p.peer_meta + next * p.peer_meta_stride_floats + 2 * (bucket0 + (uint64_t)tid);
+                    const float* meta0 = p.peer_meta + 2 * (bucket0 + (uint64_t)tid);
+                    const float* m = meta0 + (uint64_t)peer0 * p.peer_meta_stride_floats;
+                    const float* m2 = meta0 + next * p.peer_meta_stride_floats;
                     meta = f4{m[0], m[1], m2[0], m2[1]};
                 }
                 team_sync<W>();  // the previous pair's meta has been read
@@ -537,13 +546,15 @@ __global__ void __launch_bounds__(256, mode_is_levels(MODE) ? tile_resident(MODE
                 write_meta(b, g.lo, g.scale);
                 return f4{g.lo, g.inv * (float)C, 0.0f, 0.0f};
             });
-            // One pass per tensor of the tile (one for nearly all): its tables come into LDS, its buckets keep their codes.
+            // One pass per tensor of the tile (one for nearly all): its tables come into LDS, its buckets keep their
+            // codes.
             uint32_t tensor = p.levels_per_tensor != 0u ? first.tensor : 0u, last_tensor = tensor;
             if (__builtin_expect(!whole, 0) && p.levels_per_tensor != 0u)
                 last_tensor = __builtin_amdgcn_readfirstlane(lds.where[here - 1][2]);
             const bool single = tensor == last_tensor;
             for (;; ++tensor) {
-                asm volatile("" : "+v"(tid));  // keeps values and uniforms of all rows from being held across the passes
+                // keeps values and uniforms of all rows from being held across the passes
+                asm volatile("" : "+v"(tid));
                 if (tensor != loaded_tensor) {
                     auto any = [](bool c) -> bool {
                         if constexpr (W == 1) {
@@ -591,7 +602,8 @@ __global__ void __launch_bounds__(256, mode_is_levels(MODE) ? tile_resident(MODE
                 };
                 auto every = [](int) { return true; };
                 auto search = [&](float z, float h) -> uint32_t {
-                    return kCoin ? stochastic_level_any(z, h, lt.levels, K, (float)C) : nearest_level_any(z, lt.levels, K);
+                    return kCoin ? stochastic_level_any(z, h, lt.levels, K, (float)C)
+                                 : nearest_level_any(z, lt.levels, K);
                 };
                 auto lookup = [&](float z, float h) -> uint32_t {
                     const uint32_t c = (uint32_t)z;

@@ -58,9 +58,9 @@ inline TilePlan tile_plan(int bucket) {
     return best;
 }
 
-// ... for a call that leaves most of the chip idle: the smallest team that holds a bucket, and no more buckets than fill
-// its first row if that holds one (the arithmetic of an unused second row is left out). What bounds such a call is the
-// instructions of a single wave.
+// ... for a call that leaves most of the chip idle: the smallest team that holds a bucket, and no more buckets than
+// fill its first row if that holds one (the arithmetic of an unused second row is left out). What bounds such a call
+// is the instructions of a single wave.
 inline TilePlan tile_plan_small(int bucket) {
     static const int shapes[5][2] = {{1, 2}, {4, 2}, {4, 4}, {4, 6}, {4, 8}};
     const int k = bucket / 32;
@@ -72,8 +72,9 @@ inline TilePlan tile_plan_small(int bucket) {
     return t;
 }
 
-// ... for tensors of `mean` buckets with a level table each, where a tile of many buckets would give one team table after
-// table: the smallest team that holds a bucket, of one wave if that can be, and no more buckets than a tensor has.
+// ... for tensors of `mean` buckets with a level table each, where a tile of many buckets would give one team table
+// after table: the smallest team that holds a bucket, of one wave if that can be, and no more buckets than a tensor
+// has.
 inline TilePlan tile_plan_tensors(int bucket, uint64_t mean) {
     static const int shapes[7][2] = {{1, 2}, {1, 4}, {1, 6}, {1, 8}, {4, 4}, {4, 6}, {4, 8}};
     int i = 0;
@@ -84,23 +85,27 @@ inline TilePlan tile_plan_tensors(int bucket, uint64_t mean) {
 }
 
 // The tile of a call of `num_buckets` buckets. Fewer than four waves to each of the chip's 1024 SIMDs leave it idle.
-// Measured (us, buckets of 224 and 608, the fuller tile against the small one): 2^18 elements AdamW step 19.4 / 7.6 and
-// 16.4 / 7.9, encoder 7.2 / 3.9 and 6.7 / 4.1, receive side from 8 peers 24 / 10 and 21 / 11; 2^20 elements in buckets of 416
-// 1.04-1.3 times faster, in buckets of 32 and 96, which are past the line, 0.9-1.1 times.
+// Measured (us, buckets of 224 and 608, the fuller tile against the small one): 2^18 elements AdamW step 19.4 / 7.6
+// and 16.4 / 7.9, encoder 7.2 / 3.9 and 6.7 / 4.1, receive side from 8 peers 24 / 10 and 21 / 11; 2^20 elements in
+// buckets of 416 1.04-1.3 times faster, in buckets of 32 and 96, which are past the line, 0.9-1.1 times.
 // tensors: how many level tables the call has (0: not one per tensor). most_waves: of a launch.
 inline TilePlan choose_tile(int bucket, uint64_t num_buckets, uint64_t tensors, uint64_t most_waves) {
     const TilePlan full = tile_plan(bucket);
     if (tensors > 0 && num_buckets / tensors < (uint64_t)full.buckets)
         return tile_plan_tensors(bucket, num_buckets / tensors);
     const TilePlan small = tile_plan_small(bucket);
-    const uint64_t waves = (num_buckets + (uint64_t)small.buckets - 1) / (uint64_t)small.buckets * (uint64_t)small.waves;
+    const uint64_t tiles = (num_buckets + (uint64_t)small.buckets - 1) / (uint64_t)small.buckets;
+    const uint64_t waves = tiles * (uint64_t)small.waves;
     return waves < 4096 && waves < most_waves ? small : full;
 }
 
 // Workgroups of a learned-level encoder that a compute unit holds at once: by registers (the kernels' launch bounds ask
-// for as many) and, for teams of one wave with their tables for each, by LDS.
+// for as many) and, for teams of one wave with their tables for each, by LDS. Against five for every shape (us, 4 bit
+// coin flip): 134M values in buckets of 608 188 -> 169, 33M in buckets of 2080 93 -> 77.
 constexpr int tile_resident(bool coin, int waves, int rows) {
-    return rows <= 4 ? 5 : rows == 6 ? (coin ? 4 : waves == 1 ? 5 : 6) : coin ? (waves == 1 ? 3 : 2) : (waves == 1 ? 4 : 5);
+    if (rows <= 4) return 5;
+    if (rows == 6) return coin ? 4 : waves == 1 ? 5 : 6;
+    return coin ? (waves == 1 ? 3 : 2) : (waves == 1 ? 4 : 5);
 }
 
 // ceil(2^18 / bits): slot of the first bit of word w of a tile's code stream = (8 * w * magic) >> 18. A tile has at

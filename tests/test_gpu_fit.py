@@ -64,8 +64,8 @@ def test_offset_data_and_tensors_that_start_anywhere():
 @pytest.mark.parametrize("m", [1, 63, 64, 65, 127, 128, 129, 192, 193, 1023, 1024, 1025, 1039, 1040, 1041, 1279, 1280,
                                1296, 2047, 2048, 4095, 4096, 8191, 8192])
 def test_counts_where_the_table_of_powers_grows(m):
-    """All m values of a batch on one level, then fewer, then half of them: the table is extended, used as it is, and read
-    at its ends."""
+    """All m values of a batch on one level, then fewer, then half of them: the table is extended, used as it is, and
+    read at its ends."""
     B = -(-m // 32) * 32
     v = np.full(3 * B, 0.5, np.float32)
     v[m:B], v[2 * B: 2 * B + B // 2] = 3.0, -1.0

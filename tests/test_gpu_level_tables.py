@@ -81,6 +81,11 @@ def test_workgroups_that_cross_tensors(bits, B, grid, monkeypatch):
         assert np.array_equal(np_u32(codes), np.concatenate(wc)) and np.array_equal(np_u32(meta), np.concatenate(wm))
 
 
+def _same_bits(codes, want_codes, meta, want_meta):
+    return (np.array_equal(np_u32(codes), want_codes)
+            and np.array_equal(np_u32(meta), want_meta.view(np.uint32).reshape(-1)))
+
+
 @pytest.mark.parametrize("B", [96, 128, 608, 1024, 2048, 2080, 4096])
 @pytest.mark.parametrize("bits", [1, 2, 5, 6, 8])
 def test_coin_flip_in_gaps_next_to_zero(bits, B):
@@ -97,13 +102,13 @@ def test_coin_flip_in_gaps_next_to_zero(bits, B):
         qb.qsdp_quantize_levels_stochastic(torch.from_numpy(x).to(DEV), bits, B, torch.from_numpy(table).to(DEV), 3, 8,
                                            codes, meta.view(-1))
         wc, wm = ref.quantize_levels_stochastic(x, bits, B, table, 3, index_offset=8)
-        assert np.array_equal(np_u32(codes), wc) and np.array_equal(np_u32(meta), wm.view(np.uint32).reshape(-1)), exponent
+        assert _same_bits(codes, wc, meta, wm), exponent
 
 
 @pytest.mark.parametrize("B", [96, 128, 608, 1024, 2080, 4096])
 @pytest.mark.parametrize("bits", [2, 4, 6, 8])
 def test_nearest_level_among_close_levels(bits, B):
-    """Two neighbours a few steps apart, anywhere in the table: values all over the interval, on the pair and between."""
+    """Two neighbours a few steps apart, anywhere in the table: values all over, on the pair and between."""
     K, n = 1 << bits, 6 * B
     for k, top in ((0, 1.0), (K // 2 - 1, 1.0), (K // 3, 1.0), (K - 2, 1.0), (K - 2, 0.5), (K - 2, 0.999)):
         for gap in (2.0 ** -19, 2.0 ** -21, 2.0 ** -23):
@@ -118,15 +123,17 @@ def test_nearest_level_among_close_levels(bits, B):
             x[near] = np.clip(table[k] + (rng.integers(-6, 7, near.sum()) * gap / 4), 0, 1).astype(np.float32)
             x[0::B], x[B - 1::B] = 0.0, 1.0
             codes, meta = qb.alloc_packed(n, bits, B, DEV)
-            qb.qsdp_quantize_levels(torch.from_numpy(x).to(DEV), bits, B, torch.from_numpy(table).to(DEV), codes, meta.view(-1))
+            qb.qsdp_quantize_levels(torch.from_numpy(x).to(DEV), bits, B, torch.from_numpy(table).to(DEV), codes,
+                                    meta.view(-1))
             wc, wm = ref.quantize_levels(x, bits, B, table)
-            assert np.array_equal(np_u32(codes), wc) and np.array_equal(np_u32(meta), wm.view(np.uint32).reshape(-1)), (k, gap)
+            assert _same_bits(codes, wc, meta, wm), (k, gap)
 
 
 @pytest.mark.parametrize("stochastic", [False, True])
-@pytest.mark.parametrize("B,tensors", [(32, 1500), (128, 40), (128, 1400), (512, 1400), (608, 300), (1024, 1300), (2080, 50), (4096, 20)])
+@pytest.mark.parametrize("B,tensors", [(32, 1500), (128, 40), (128, 1400), (512, 1400), (608, 300), (1024, 1300),
+                                       (2080, 50), (4096, 20)])
 def test_tensors_of_a_bucket_or_two(B, tensors, stochastic):
-    """A table each: as many workgroups as tensors, small tiles, and past 1280 small tensors the tile kernel for all buckets."""
+    """A table each: as many workgroups as tensors, small tiles, past 1280 small tensors the tile kernel for all."""
     rng = np.random.default_rng(B + tensors)
     for most, bits in ((1, 4), (2, 7)):
         sizes = [8 * int(v) for v in rng.integers(1, most * B // 8 + 1, tensors)]
@@ -134,8 +141,8 @@ def test_tensors_of_a_bucket_or_two(B, tensors, stochastic):
         x = rng.standard_normal(sum(sizes)).astype(np.float32)
         segs = qb.Segments(sizes, B, DEV)
         codes, meta = segs.alloc_packed(bits)
-        qb.qsdp_quantize_levels_segmented(torch.from_numpy(x).to(DEV), segs, bits, torch.from_numpy(tables).to(DEV), codes,
-                                          meta.view(-1), stochastic, 3, 16)
+        qb.qsdp_quantize_levels_segmented(torch.from_numpy(x).to(DEV), segs, bits, torch.from_numpy(tables).to(DEV),
+                                          codes, meta.view(-1), stochastic, 3, 16)
         want, o = [[], []], 0
         for t, s in enumerate(sizes):
             v = x[o:o + s].copy()
@@ -143,4 +150,5 @@ def test_tensors_of_a_bucket_or_two(B, tensors, stochastic):
                       else ref.quantize_levels(v, bits, B, tables[t]))
             want[0].append(wc); want[1].append(wm.view(np.uint32).reshape(-1))
             o += s
-        assert np.array_equal(np_u32(codes), np.concatenate(want[0])) and np.array_equal(np_u32(meta), np.concatenate(want[1]))
+        assert np.array_equal(np_u32(codes), np.concatenate(want[0]))
+        assert np.array_equal(np_u32(meta), np.concatenate(want[1]))

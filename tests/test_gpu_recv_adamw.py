@@ -20,7 +20,7 @@ CASES = [
     (7 * 2048 + 1000, 9, 8, 4, 2048, 0.0, qb.QSDP_FLAG_KEEP_MASTER),
     (5 * 4096 + 4095, 2, 7, 8, 4096, 0.0, qb.QSDP_FLAG_NO_SHIFT),
     (20 * 1024 + 300, 6, 4, 4, 1024, 2.0 ** -10, qb.QSDP_FLAG_KEEP_MASTER),   # saturating lattice
-    (11 * 96 + 40, 4, 5, 7, 96, 0.0, qb.QSDP_FLAG_KEEP_MASTER),               # generic bucket size: block kernel
+    (11 * 96 + 40, 4, 5, 7, 96, 0.0, qb.QSDP_FLAG_KEEP_MASTER),               # generic bucket size: tile kernel
     (100, 2, 8, 1, 1024, 0.0, 0),
 ]
 

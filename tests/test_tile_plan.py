@@ -1,7 +1,7 @@
 """The tile kernels' launch shapes (csrc/qsdp_tile_plan.hpp, plain C++) for every bucket size, compiled and checked
 without a GPU: whole buckets fit the team, every bucket has lanes of its own, and the two multiplications that stand
-for divisions are exact over the ranges the kernel uses them on; small calls and tensors with tables of their own get small
-tiles; the buckets of the GPU tests see every shape."""
+for divisions are exact over the ranges the kernel uses them on; small calls and tensors with tables of their own get
+small tiles; the buckets of the GPU tests see every shape."""
 import subprocess
 
 from paper_2302_02390_amd import build as lib_build
@@ -28,7 +28,8 @@ int main(int argc, char** argv) {
         const TilePlan s = tile_plan_small(32 * k);
         check(s, k, false);
         if (s.buckets > 1 && s.buckets * k > tile_groups(s.waves, 1)) ++bad;  // one row, or one bucket ...
-        if (tile_groups(s.waves, 1) < k && (s.buckets + 1) * k <= tile_groups(s.waves, s.rows)) ++bad;  // ... or all that fit
+        // ... or all that fit
+        if (tile_groups(s.waves, 1) < k && (s.buckets + 1) * k <= tile_groups(s.waves, s.rows)) ++bad;
         for (const uint64_t mean : {0ull, 1ull, 2ull, 3ull, 7ull, 40ull, 1000ull}) {
             const TilePlan t = tile_plan_tensors(32 * k, mean);
             check(t, k, false);
@@ -36,14 +37,15 @@ int main(int argc, char** argv) {
         }
         // the line between small and large calls, and a launch that is capped
         const uint64_t most = 4095 / s.waves * (uint64_t)s.buckets;
-        if (choose_tile(32 * k, most, 0, any).rows != s.rows || choose_tile(32 * k, most, 0, any).buckets != s.buckets) ++bad;
+        const TilePlan below = choose_tile(32 * k, most, 0, any);
+        if (below.rows != s.rows || below.waves != s.waves || below.buckets != s.buckets) ++bad;
         const TilePlan f = tile_plan(32 * k), l = choose_tile(32 * k, most + 4 * (uint64_t)s.buckets, 0, any);
         if (l.rows != f.rows || l.waves != f.waves || l.buckets != f.buckets) ++bad;
         const TilePlan c = choose_tile(32 * k, 8 * (uint64_t)s.buckets, 0, 8);
         if (c.rows != f.rows || c.waves != f.waves || c.buckets != f.buckets) ++bad;
         // tables per tensor: never more buckets to a tile than to the mean tensor
         for (const uint64_t tensors : {1ull, 10ull, 999ull})
-            if (const uint64_t mean = 1000 / tensors; (uint64_t)choose_tile(32 * k, 1000, tensors, any).buckets > mean) ++bad;
+            if ((uint64_t)choose_tile(32 * k, 1000, tensors, any).buckets > 1000 / tensors) ++bad;
     }
     for (int bits = 1; bits <= 8; ++bits)
         for (uint32_t w = 0; w < 2048u * bits / 8; ++w)
