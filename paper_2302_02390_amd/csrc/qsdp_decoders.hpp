@@ -298,14 +298,19 @@ __global__ void __launch_bounds__(256) dequant_seg_kernel(const DequantSegParams
                     }
                 }
             } else {
-                uint32_t t = tensor;  // the lane's tensor; its rows ascend, so the walk goes on from row to row
+                // The lane's tensor. Its rows ascend, so the walk goes on from row to row. A tile in one bucket has
+                // nothing to walk; with tables and four rows the step stays all the same, as the compiler's order of
+                // the common path is the better one with it (350M model, 4 bit -> fp32 263 us, without 268), while
+                // the others are as fast or faster without (8000 tensors of 1024: 8 bit tables 13.2, without 12.2).
+                uint32_t t = tensor;
                 for (int u = 0; u < U; ++u) {
                     const uint64_t s = s0 + (uint64_t)(u * 64 * E + lane * E);
                     if (s < p.n) {
                         const uint64_t bucket = bucket_of<BK>(s, p);
-                        if (BK != BK_TILE_UNIFORM)
-                            while (t + 1 < q.nseg && segs[t + 1].first_bucket <= bucket) ++t;
-                        const Segment mine = t == tensor ? seg : segs[t];
+                        if (BK == BK_TILE_UNIFORM) t = tensor;
+                        Segment mine = t == tensor ? seg : segs[t];
+                        if (BK != BK_TILE_UNIFORM || (kLanes && !BF16))
+                            while (t + 1 < q.nseg && segs[t + 1].first_bucket <= bucket) mine = segs[++t];
                         const uint64_t e = mine.offset + (s - mine.first_bucket * B);
                         const uint64_t end = mine.offset + mine.n;
                         if (e < end) {
