@@ -25,9 +25,9 @@ namespace qsdp {
 // barrier after each of the four passes. The consumer meanwhile walks the P batches of the round before; the slots
 // are double-buffered.
 //
-// Measured (us per batch, 5-bit table, Gaussian values, buckets of 128 / 1024 / 4096 / 8192): 0.45 / 0.57 / 1.8 / 3.5,
+// Measured (us per batch, 5-bit table, Gaussian values, buckets of 128 / 1024 / 4096 / 8192): 0.44 / 0.51 / 1.8 / 3.5,
 // against 1.27 / 2.6 / 10.7 / 21 for a workgroup that stages one batch in LDS and assigns value by value with a barrier
-// around each part; the 292 tables of the 350M model 2.85 -> 0.57 ms. The chain is latency: about 1,100 cycles of
+// around each part; the 292 tables of the 350M model 2.85 -> 0.54 ms. The chain is latency: about 1,100 cycles of
 // dependent LDS reads and binary64 steps per batch up to 1024 values, the sorting beyond.
 // Tensors of few batches are bound by what a workgroup does before its first one, the table of powers above all (one
 // batch of 1024, 4 bit: 32 us when the whole table was filled first, 10 us now, against 16 us for the workgroup that
