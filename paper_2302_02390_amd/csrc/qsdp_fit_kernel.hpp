@@ -20,19 +20,24 @@ namespace qsdp {
 // levels, and has count and sum below the boundary; differences between lanes are the levels' own. No barrier and no
 // atomic is left in the chain; two LDS round trips for the boundary, one for the powers of 1 - lr and the reciprocals
 // of the counts. A team of W producer waves sorts a batch (the values stay in registers, at most 16 to a lane) and P
-// teams make a round: W = 1, P = 6 for buckets of up to 1024 values (one wave needs no barrier between its passes,
-// and six of them sort as fast as the consumer walks), W = 2, 4, 8 and P = 8 / W up to 2048, 4096, 8192 with a
-// barrier after each of the four passes. The consumer meanwhile walks the P batches of the round before; the slots
-// are double-buffered.
+// teams make a round: W = 1, P = 7 for buckets of up to 1024 values (one wave needs no barrier between its passes;
+// six sort more slowly than the consumer walks, 0.51 us per batch of 1024 where seven take 0.46, and eight are no
+// faster), W = 2, 4, 8 and P = 8 / W up to 2048, 4096, 8192 with a barrier after each of the four passes. The
+// consumer meanwhile walks the P batches of the round before; the slots are double-buffered.
 //
-// Measured (us per batch, 5-bit table, Gaussian values, buckets of 128 / 1024 / 4096 / 8192): 0.44 / 0.51 / 1.8 / 3.5,
-// against 1.27 / 2.6 / 10.7 / 21 for a workgroup that stages one batch in LDS and assigns value by value with a barrier
-// around each part; the 292 tables of the 350M model 2.85 -> 0.54 ms. The chain is latency: about 1,100 cycles of
-// dependent LDS reads and binary64 steps per batch up to 1024 values, the sorting beyond.
+// Measured (us per batch, 5-bit table, Gaussian values, buckets of 128 / 352 / 1024 / 4096 / 8192): 0.40 / 0.43 / 0.49
+// / 1.74 / 3.3, against 1.27 / - / 2.6 / 10.7 / 21 for a workgroup that stages one batch in LDS and assigns value by
+// value with a barrier around each part; the 292 tables of the 350M model 2.85 -> 0.51 ms. The chain is latency: about
+// 950 cycles of dependent LDS reads, comparisons and binary64 steps per batch. The sorting is bound by LDS, about a
+// value per cycle and compute unit: an atomic, a read and a write to random places take 15 + 16 + 11 cycles for the 64
+// lanes of a wave. Lanes without a value therefore make none of them: on one place, as they did when they added zero to
+// their neighbour's cell, they meet in turn (buckets of 352 / 736, 5 bit: 0.56 / 0.69 -> 0.43 / 0.50 us per batch, 3040,
+// 4 bit: 2.4 -> 1.8).
 // Tensors of few batches are bound by what a workgroup does before its first one, the table of powers above all (one
 // batch of 1024, 4 bit: 32 us when the whole table was filled first, 10 us now, against 16 us for the workgroup that
 // staged its batches), and by one workgroup of this size to a compute unit: 2000 such tensors 240 -> 46 us (53 us then;
-// 2 bit, whose counts ask for more powers: 240 -> 103 us, 57 us then).
+// 2 bit, whose counts ask for more powers: 240 -> 103 us, 57 us then). Producers without a batch sort nothing (they
+// sorted the last one again: 2000 tensors of one batch of 512, 4 bit, 25.8 -> 20.2 us).
 //
 // The boundary search needs levels that ascend by more than 2^-20 within [0, 1] (then the comparison of the two
 // rounded distances is monotone in the value and flips within 2^-22 of the midpoint) and cells that are not
@@ -56,7 +61,7 @@ struct FitSlot;
 template <int BITS, int VPT, int W>
 struct FitShape {
     static constexpr int kBucketMax = 64 * W * VPT;
-    static constexpr int kBatches = W == 1 ? 6 : 8 / W;          // P, batches per round
+    static constexpr int kBatches = W == 1 ? 7 : 8 / W;          // P, batches per round
     static constexpr int kProducers = kBatches * W;              // producer waves; the consumer is one more
     static constexpr int kThreads = 64 * (kProducers + 1);
     static constexpr int kBarriers = W == 1 ? 1 : 4;             // per round
@@ -75,6 +80,10 @@ struct FitShape {
 // above.
 constexpr int kFitCountShift = 46;
 constexpr uint64_t kFitSumMask = (1ull << kFitCountShift) - 1;
+
+// What follows the values of a batch: above every boundary, as many as the consumer reads at once.
+constexpr float kFitFiller = 2.0f;
+constexpr int kFitSpare = 16;
 
 // z (in [0, 1]) in 32.32 fixed point, truncated: exact scaling, the integer and the fraction converted apart.
 __device__ __forceinline__ uint64_t fit_fixed(float z) {
@@ -271,7 +280,7 @@ struct FitSlot {
     static constexpr int kOwn = C / 64;
     static __device__ __forceinline__ uint32_t at(uint32_t c) { return c + (kOwn > 1 ? c / kOwn : 0u); }
     uint64_t cell[C + 64 + 1];  // cell c at at(c)
-    float z[BMAX + 1];          // one to spare, where lanes without a value write
+    float z[BMAX + kFitSpare];  // grouped by cell, kFitSpare fillers past the last one
     FitCells cells;
 };
 
@@ -290,7 +299,11 @@ __device__ __forceinline__ void fit_batch(const Slot& slot, int m, Powers& power
                                           FitCells cells, float (&lv)[FitLanes<BITS>::M], float* lv_shared,
                                           uint64_t* acc, int lane) {
     constexpr int K = FitLanes<BITS>::K, S = FitLanes<BITS>::S, M = FitLanes<BITS>::M;
-    constexpr int U = M == 4 ? 2 : 4;  // values a lane reads at once
+    // Values a lane reads at once, one after the other in the slot: one address, no question of range (below), half the
+    // instructions of a read, test and sum for each on its own (6 bits 0.66 -> 0.59 us per batch of 1024, 5 bits 0.43 ->
+    // 0.40 per batch of 128). Eight of them where two lanes share a level are slower (0.46).
+    constexpr int U = M == 4 ? 2 : 4;
+    static_assert(S * U <= kFitSpare, "reads past the last value");
     // values in a boundary's cells from which the plain assignment of the batch is faster
     const uint32_t crowded = (uint32_t)(m * S * U / (48 * M)) + 64u;
     const int sub = S > 1 ? lane / (64 / S) : 0;
@@ -322,23 +335,26 @@ __device__ __forceinline__ void fit_batch(const Slot& slot, int m, Powers& power
     if (__builtin_expect(__builtin_amdgcn_ballot_w64(plain) == 0, 1)) {
 #pragma unroll
         for (int i = 0; i < M; ++i) {
+            // The values at `end` and beyond are those of higher cells, or the fillers past the last one: above the
+            // boundary, so they may be read with the others. A lane past the last boundary compares with levels that
+            // have nothing on the lower one's side.
+            const bool inner = 64 * i + k0 < K - 1;
+            const float below_level = inner ? lv[i] : -4.0f, above_level = inner ? hi[i] : kFitFiller;
             uint64_t below = 0;
-            uint32_t p = pos[i] + sub;
+            uint32_t p = pos[i];
             do {
+                const float* at = &slot.z[p + sub * U];
                 float z[U];
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const uint32_t at = p + u * S;
-                    z[u] = slot.z[at < end[i] ? at : 0u];
-                }
+                for (int u = 0; u < U; ++u) z[u] = at[u];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     // on the lower level's side: below 1 (the upper level is at most 1 and closer), so 32 bits hold it
-                    const bool lower = p + u * S < end[i] && !(fabsf(z[u] - hi[i]) < fabsf(z[u] - lv[i]));
+                    const bool lower = !(fabsf(z[u] - above_level) < fabsf(z[u] - below_level));
                     const uint32_t fixed = (uint32_t)(z[u] * 4294967296.0f);
                     below += ((uint64_t)(lower ? 1u << (kFitCountShift - 32) : 0u) << 32) | (lower ? fixed : 0u);
                 }
-                p += S * U;
+                p = p + S * U < end[i] ? p + S * U : end[i];  // the lanes that are done: nothing below any more
             } while (__builtin_amdgcn_ballot_w64(p < end[i]) != 0);
             upto[i] += fit_sum_subs<S>(below);
         }
@@ -489,17 +505,13 @@ __global__ void __launch_bounds__((FitShape<BITS, VPT, W>::kThreads)) fit_levels
         auto team_sync = [] {
             if constexpr (W > 1) __syncthreads(); else fit_wave_sync();
         };
-        // a producer: batch r * P + team in round r, this wave's 1/W of it; past the last batch the last one again
-        // (nobody reads it). Lanes past the end of a batch carry its last value: it changes no minimum or maximum, it
-        // counts nothing and lands in the spare place.
+        // a producer: batch r * P + team in round r, this wave's 1/W of it; nothing but the barriers past the last one.
+        // Lanes past the end of a batch fetch its last value, which changes no minimum or maximum, and enter nothing.
         const int team = wave / W, part = wave % W;
         const int scanner = W == 2 ? team / 2 : W == 4 ? team : 0;  // of the team's waves: on another SIMD for every team
         const int first = part * 64 + lane;  // value q of the lane: first + q * 64 * W
         float next[VPT];
-        auto batch = [&](uint64_t r) -> uint64_t {
-            const uint64_t j = r * P + team;
-            return j < num_batches ? j : num_batches - 1;
-        };
+        auto batch = [&](uint64_t r) -> uint64_t { return r * P + team; };
         auto fetch = [&](uint64_t j) {
             const int m = batch_size(j);
             const float* src = v + j * (uint64_t)B;
@@ -509,12 +521,12 @@ __global__ void __launch_bounds__((FitShape<BITS, VPT, W>::kThreads)) fit_levels
                 next[q] = src[i < m ? i : m - 1];
             }
         };
-        fetch(batch(0));
+        fetch(batch(0) < num_batches ? batch(0) : num_batches - 1);
         powers.fill_reciprocals(B, threadIdx.x, 64 * Shape::kProducers);
         for (uint64_t r = 0; r <= rounds; ++r) {
-            if (r == rounds) {  // the consumer's last round: nothing left to sort
+            if (batch(r) >= num_batches) {  // the consumer's last round among them
                 for (int i = 0; i < Shape::kBarriers; ++i) __syncthreads();
-                break;
+                continue;
             }
             const int m = batch_size(batch(r));
             Slot& slot = slots[(int)(r & 1u) * P + team];
@@ -528,7 +540,7 @@ __global__ void __launch_bounds__((FitShape<BITS, VPT, W>::kThreads)) fit_levels
                 sum += z[q];
                 absolute += fabsf(z[q]);
             }
-            fetch(batch(r + 1));  // in flight while this batch is sorted
+            fetch(batch(r + 1) < num_batches ? batch(r + 1) : num_batches - 1);  // in flight while this batch is sorted
             for (int c = first; c < C + 64; c += 64 * W) slot.cell[c] = 0;  // all but the last, written below
             lo = group_min<64>(lo);
             hi = group_max<64>(hi);
@@ -557,13 +569,19 @@ __global__ void __launch_bounds__((FitShape<BITS, VPT, W>::kThreads)) fit_levels
             const FitCells cells = fit_cells<C>(grid, hi, sum * (1.0f / (64 * W * VPT)), absolute * (1.0f / (64 * W * VPT)));
             uint32_t cell[VPT];
             uint64_t held[VPT];  // the cell's word before this value came (both halves used: half of one dropped costs a wait)
-#pragma unroll
-            for (int q = 0; q < VPT; ++q) {
+            auto enter = [&](int q) {
                 z[q] = (z[q] - grid.lo) * grid.inv;
                 cell[q] = Slot::at(fit_cell<C>(z[q], cells));
-                const uint64_t one = (1ull << kFitCountShift) | fit_fixed(z[q]);
-                const uint64_t there = first + q * 64 * W < m ? ~0ull : 0ull;
-                held[q] = fit_add(&slot.cell[cell[q]], one & there);
+                held[q] = fit_add(&slot.cell[cell[q]], (1ull << kFitCountShift) | fit_fixed(z[q]));
+            };
+            const bool full = m == Shape::kBucketMax;
+            if (full) {
+#pragma unroll
+                for (int q = 0; q < VPT; ++q) enter(q);
+            } else {
+#pragma unroll
+                for (int q = 0; q < VPT; ++q)
+                    if (first + q * 64 * W < m) enter(q);
             }
             team_sync();
             if (part == scanner) {
@@ -582,11 +600,18 @@ __global__ void __launch_bounds__((FitShape<BITS, VPT, W>::kThreads)) fit_levels
                 if (lane == 0) slot.cells = cells;
             }
             team_sync();
+            auto place = [&](int q) {
+                slot.z[(uint32_t)((slot.cell[cell[q]] + held[q]) >> kFitCountShift)] = z[q];
+            };
+            if (full) {
 #pragma unroll
-            for (int q = 0; q < VPT; ++q) {
-                const uint32_t to = (uint32_t)((slot.cell[cell[q]] + held[q]) >> kFitCountShift);
-                slot.z[first + q * 64 * W < m ? to : (uint32_t)Shape::kBucketMax] = z[q];
+                for (int q = 0; q < VPT; ++q) place(q);
+            } else {
+#pragma unroll
+                for (int q = 0; q < VPT; ++q)
+                    if (first + q * 64 * W < m) place(q);
             }
+            if (part == 0 && lane < kFitSpare) slot.z[m + lane] = kFitFiller;
             __syncthreads();
         }
     }

@@ -47,6 +47,20 @@ def test_batches_without_a_boundary_search(B, bits):
             assert _same(v, bits, B, 0.02, levels), (B, bits)
 
 
+@pytest.mark.parametrize("B", [96, 128, 512, 1024, 4096])
+@pytest.mark.parametrize("bits", [1, 3, 5, 6, 8])
+def test_boundaries_among_the_last_values_of_a_batch(B, bits):
+    """The consumer reads on past the cells of a boundary and past the batch: boundaries in the last cell, batches that
+    end at, before and after a multiple of what it reads at once, seven to a round and one more."""
+    rng = np.random.default_rng(B + bits)
+    for cut in (0, 1, 3, 4, 8, 15, 16, 17):
+        x = rng.beta(8.0, 1.0, 8 * B - cut).astype(np.float32)  # most of a bucket next to its maximum
+        x[B - 1 - cut::B] = 1.0
+        assert _same(x, bits, B, 0.05, ref.levels_uniform(bits)), cut
+        high = np.sort(rng.uniform(0.9, 1.0, 1 << bits)).astype(np.float32)
+        assert _same(x, bits, B, 0.05, high), cut
+
+
 def test_offset_data_and_tensors_that_start_anywhere():
     B, bits, sizes = 1024, 5, [8, 40 * 1024 + 8, 1024, 24, 13 * 1024 + 40]
     x, g = synth(sum(sizes), 5)
