@@ -8,6 +8,7 @@ the symbols raises.
 import ctypes as C
 import functools
 import os
+import threading
 
 import torch
 
@@ -96,6 +97,9 @@ _SIGNATURES = {
 EXPORTS = tuple(_SIGNATURES)
 
 _lib = None
+_lib_lock = threading.Lock()
+# The functions of this file that lib() replaces by native ones of the same name, which call them for the uncommon cases.
+_IN_PYTHON = dict.fromkeys(("_is", "_is_rows", "_packed_ok", "_rows_ok", "_step_outputs", "_launch"))
 
 
 class QsdpError(RuntimeError):
@@ -108,15 +112,30 @@ def lib():
     """Load libqsdp.so (built by ``python -m paper_2302_02390_amd.build``)."""
     global _lib
     if _lib is None:
-        if not os.path.exists(LIB_PATH):
-            raise ImportError(f"{LIB_PATH} is missing: run `python -m paper_2302_02390_amd.build`")
-        L = C.CDLL(LIB_PATH)
-        for name, (restype, argtypes) in _SIGNATURES.items():
-            fn = getattr(L, name)
-            fn.restype = restype
-            fn.argtypes = argtypes
-        _lib = L
+        with _lib_lock:
+            if _lib is None:
+                _lib = _load()
     return _lib
+
+
+def _load():
+    if not os.path.exists(LIB_PATH):
+        raise ImportError(f"{LIB_PATH} is missing: run `python -m paper_2302_02390_amd.build`")
+    L = C.CDLL(LIB_PATH)
+    for name, (restype, argtypes) in _SIGNATURES.items():
+        fn = getattr(L, name)
+        fn.restype = restype
+        fn.argtypes = argtypes
+    # From here on in native code (csrc/qsdp_marshal.cpp), with the functions of this file for whatever that does not
+    # take: a call costs about 2.5 us less of host time.
+    from . import _marshal
+    own = globals()
+    for name in _IN_PYTHON:
+        _IN_PYTHON[name] = own[name]
+    _marshal.attach(own, *_IN_PYTHON.values())
+    for name in _IN_PYTHON:
+        own[name] = getattr(_marshal, name[1:])
+    return L
 
 
 def status_string(status):
@@ -154,12 +173,13 @@ _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or _stream_ha
 
 def _launch(t, name, *args):
     """Calls entry point `name` with the current stream of t's device as its last argument, t's device being the
-    current one meanwhile. Small calls are bound by what happens here: a fused step over 2^20 parameters takes 4.3 us
-    of GPU time; with a device guard, a Stream object and a pointer object per tensor on every call a loop of them took
-    11-12 us a call, without them 7-8 (3.4-4.1 of it the launch itself). So the device is switched only if it is
-    another one, and the stream is asked for its handle alone."""
+    current one meanwhile; a tensor in the place of a pointer stands for its address. This is the general form; plain
+    tensors on the current device go through csrc/qsdp_marshal.cpp."""
     device = t.get_device()
     stream = _raw_stream(device)
+    kinds = _SIGNATURES[name][1]
+    args = [a.data_ptr() if hasattr(a, "data_ptr") and i < len(kinds) and kinds[i] is _vp else a
+            for i, a in enumerate(args)]
     if device == torch.cuda.current_device():
         status = getattr(_lib or lib(), name)(*args, stream)
     else:
@@ -174,9 +194,12 @@ def _is(t, dtype):
         raise TypeError(f"expected a contiguous {dtype} tensor on the GPU")
 
 
+_DTYPES = {torch.float32: QSDP_F32, torch.bfloat16: QSDP_BF16, torch.float16: QSDP_F16}
+
+
 def _out_dtype(out):
     """The decoders' output formats: float32, bfloat16 or float16 (IEEE binary16)."""
-    dt = {torch.float32: QSDP_F32, torch.bfloat16: QSDP_BF16, torch.float16: QSDP_F16}.get(out.dtype)
+    dt = _DTYPES.get(out.dtype)
     if dt is None:
         raise TypeError("out must be float32, bfloat16 or float16")
     return dt
@@ -186,6 +209,13 @@ def _is_rows(t, dtype):
     """A 2-D tensor whose rows are contiguous (the rows themselves may be strided apart)."""
     if not (t.is_cuda and t.dtype == dtype and t.dim() == 2 and (t.shape[1] == 1 or t.stride(1) == 1)):
         raise TypeError(f"expected a {dtype} GPU tensor [rows, row length] with contiguous rows")
+
+
+def _step_outputs(wcodes, wmeta, n_saturated):
+    """The optional outputs of a step."""
+    for t, dt in ((wcodes, torch.int32), (wmeta, torch.float32), (n_saturated, torch.int64)):
+        if t is not None:
+            _is(t, dt)
 
 
 def _need(t, numel, what):
@@ -228,46 +258,49 @@ def alloc_packed(n, bits, bucket, device):
 
 def qsdp_quantize_grad(g, bits, bucket, seed, index_offset, codes, meta):
     _is(g, torch.float32); _is(codes, torch.int32); _is(meta, torch.float32)
-    _packed_ok(codes, meta, g.numel(), bits, bucket)
-    _launch(g, "qsdp_quantize_grad", _ptr(g), g.numel(), bits, bucket, seed, index_offset, _ptr(codes), _ptr(meta))
+    n = g.numel()
+    _packed_ok(codes, meta, n, bits, bucket)
+    _launch(g, "qsdp_quantize_grad", g, n, bits, bucket, seed, index_offset, codes, meta)
 
 
 def qsdp_quantize_grad_ex(g, bits, bucket, seed, index_offset, flags, codes, meta):
     _is(g, torch.float32); _is(codes, torch.int32); _is(meta, torch.float32)
-    _packed_ok(codes, meta, g.numel(), bits, bucket)
-    _launch(g, "qsdp_quantize_grad_ex", _ptr(g), g.numel(), bits, bucket, seed, index_offset, flags, _ptr(codes),
-            _ptr(meta))
+    n = g.numel()
+    _packed_ok(codes, meta, n, bits, bucket)
+    _launch(g, "qsdp_quantize_grad_ex", g, n, bits, bucket, seed, index_offset, flags, codes,
+            meta)
 
 
 def qsdp_quantize_weight_ex(x, bits, bucket, delta, seed, flags, codes, meta, n_saturated=None):
     _is(x, torch.float32); _is(codes, torch.int32); _is(meta, torch.float32)
-    _packed_ok(codes, meta, x.numel(), bits, bucket)
+    n = x.numel()
+    _packed_ok(codes, meta, n, bits, bucket)
     if n_saturated is not None:
         _is(n_saturated, torch.int64)
-    _launch(x, "qsdp_quantize_weight_ex", _ptr(x), x.numel(), bits, bucket, delta, seed, flags, _ptr(codes), _ptr(meta),
-            _ptr(n_saturated))
+    _launch(x, "qsdp_quantize_weight_ex", x, n, bits, bucket, delta, seed, flags, codes, meta,
+            n_saturated)
 
 
 def qsdp_fused_step_ex(x, g, lr, wbits, gbits, bucket, delta, seed, index_offset, flags, wcodes=None,
                        wmeta=None, n_saturated=None):
     _is(x, torch.float32); _is(g, torch.float32)
-    if g.numel() != x.numel():
+    n = x.numel()
+    if g.numel() != n:
         raise ValueError("x and g differ in size")
-    for t, dt in ((wcodes, torch.int32), (wmeta, torch.float32), (n_saturated, torch.int64)):
-        if t is not None:
-            _is(t, dt)
-    _packed_ok(wcodes, wmeta, x.numel(), wbits, bucket)
-    _launch(x, "qsdp_fused_step_ex", _ptr(x), _ptr(g), x.numel(), lr, wbits, gbits, bucket, delta, seed, index_offset,
-            flags, _ptr(wcodes), _ptr(wmeta), _ptr(n_saturated))
+    _step_outputs(wcodes, wmeta, n_saturated)
+    _packed_ok(wcodes, wmeta, n, wbits, bucket)
+    _launch(x, "qsdp_fused_step_ex", x, g, n, lr, wbits, gbits, bucket, delta, seed, index_offset,
+            flags, wcodes, wmeta, n_saturated)
 
 
 def qsdp_quantize_weight(x, bits, bucket, delta, seed, codes, meta, n_saturated=None):
     _is(x, torch.float32); _is(codes, torch.int32); _is(meta, torch.float32)
-    _packed_ok(codes, meta, x.numel(), bits, bucket)
+    n = x.numel()
+    _packed_ok(codes, meta, n, bits, bucket)
     if n_saturated is not None:
         _is(n_saturated, torch.int64)
-    _launch(x, "qsdp_quantize_weight", _ptr(x), x.numel(), bits, bucket, delta, seed, _ptr(codes), _ptr(meta),
-            _ptr(n_saturated))
+    _launch(x, "qsdp_quantize_weight", x, n, bits, bucket, delta, seed, codes, meta,
+            n_saturated)
 
 
 def qsdp_dequantize(codes, meta, n, bits, bucket, out):
@@ -277,7 +310,7 @@ def qsdp_dequantize(codes, meta, n, bits, bucket, out):
     if out.numel() < n:
         raise ValueError("out is too small")
     _packed_ok(codes, meta, n, bits, bucket)
-    _launch(out, "qsdp_dequantize", _ptr(codes), _ptr(meta), n, bits, bucket, dt, _ptr(out))
+    _launch(out, "qsdp_dequantize", codes, meta, n, bits, bucket, dt, out)
 
 
 def levels_uniform(bits, device):
@@ -290,19 +323,21 @@ def levels_uniform(bits, device):
 
 def qsdp_quantize_levels(v, bits, bucket, levels, codes, meta):
     _is(v, torch.float32); _is(levels, torch.float32); _is(codes, torch.int32); _is(meta, torch.float32)
+    n = v.numel()
     if levels.numel() != (1 << bits):
         raise ValueError("levels must hold 2^bits entries")
-    _packed_ok(codes, meta, v.numel(), bits, bucket)
-    _launch(v, "qsdp_quantize_levels", _ptr(v), v.numel(), bits, bucket, _ptr(levels), _ptr(codes), _ptr(meta))
+    _packed_ok(codes, meta, n, bits, bucket)
+    _launch(v, "qsdp_quantize_levels", v, n, bits, bucket, levels, codes, meta)
 
 
 def qsdp_quantize_levels_stochastic(v, bits, bucket, levels, seed, index_offset, codes, meta):
     _is(v, torch.float32); _is(levels, torch.float32); _is(codes, torch.int32); _is(meta, torch.float32)
+    n = v.numel()
     if levels.numel() != (1 << bits):
         raise ValueError("levels must hold 2^bits entries")
-    _packed_ok(codes, meta, v.numel(), bits, bucket)
-    _launch(v, "qsdp_quantize_levels_stochastic", _ptr(v), v.numel(), bits, bucket, _ptr(levels), seed, index_offset,
-            _ptr(codes), _ptr(meta))
+    _packed_ok(codes, meta, n, bits, bucket)
+    _launch(v, "qsdp_quantize_levels_stochastic", v, n, bits, bucket, levels, seed, index_offset,
+            codes, meta)
 
 
 def qsdp_dequantize_levels(codes, meta, n, bits, bucket, levels, out):
@@ -314,14 +349,14 @@ def qsdp_dequantize_levels(codes, meta, n, bits, bucket, levels, out):
     if out.numel() < n:
         raise ValueError("out is too small")
     _packed_ok(codes, meta, n, bits, bucket)
-    _launch(out, "qsdp_dequantize_levels", _ptr(codes), _ptr(meta), n, bits, bucket, _ptr(levels), dt, _ptr(out))
+    _launch(out, "qsdp_dequantize_levels", codes, meta, n, bits, bucket, levels, dt, out)
 
 
 def qsdp_fit_levels(v, bits, bucket, lr, levels, max_batches=0):
     _is(v, torch.float32); _is(levels, torch.float32)
     if levels.numel() != (1 << bits):
         raise ValueError("levels must hold 2^bits entries")
-    _launch(v, "qsdp_fit_levels", _ptr(v), v.numel(), bits, bucket, lr, max_batches, _ptr(levels))
+    _launch(v, "qsdp_fit_levels", v, v.numel(), bits, bucket, lr, max_batches, levels)
 
 
 def qsdp_dequantize_add(codes, meta, npeers, n, bits, bucket, alpha, out):
@@ -332,24 +367,20 @@ def qsdp_dequantize_add(codes, meta, npeers, n, bits, bucket, alpha, out):
     if out.numel() < n:
         raise ValueError("out is too small")
     _rows_ok(codes, meta, n, bits, bucket)
-    _launch(out, "qsdp_dequantize_add", _ptr(codes), codes.stride(0) * 4, _ptr(meta), meta.stride(0) * 4, npeers, n,
-            bits, bucket, alpha, _ptr(out))
+    _launch(out, "qsdp_dequantize_add", codes, codes.stride(0) * 4, meta, meta.stride(0) * 4, npeers, n,
+            bits, bucket, alpha, out)
 
 
 def qsdp_fused_step(x, g, lr, wbits, gbits, bucket, delta, seed, index_offset=0, wcodes=None,
                     wmeta=None, n_saturated=None):
     _is(x, torch.float32); _is(g, torch.float32)
-    if g.numel() != x.numel():
+    n = x.numel()
+    if g.numel() != n:
         raise ValueError("x and g differ in size")
-    if wcodes is not None:
-        _is(wcodes, torch.int32)
-    if wmeta is not None:
-        _is(wmeta, torch.float32)
-    if n_saturated is not None:
-        _is(n_saturated, torch.int64)
-    _packed_ok(wcodes, wmeta, x.numel(), wbits, bucket)
-    _launch(x, "qsdp_fused_step", _ptr(x), _ptr(g), x.numel(), lr, wbits, gbits, bucket, delta, seed, index_offset,
-            _ptr(wcodes), _ptr(wmeta), _ptr(n_saturated))
+    _step_outputs(wcodes, wmeta, n_saturated)
+    _packed_ok(wcodes, wmeta, n, wbits, bucket)
+    _launch(x, "qsdp_fused_step", x, g, n, lr, wbits, gbits, bucket, delta, seed, index_offset,
+            wcodes, wmeta, n_saturated)
 
 
 def qsdp_fused_adamw_step(x, g, m, v, lr, beta1, beta2, eps, weight_decay, bias1, bias2, wbits, gbits, bucket,
@@ -358,23 +389,22 @@ def qsdp_fused_adamw_step(x, g, m, v, lr, beta1, beta2, eps, weight_decay, bias1
         _is(t, torch.float32)
     if not (g.numel() == x.numel() == m.numel() == v.numel()):
         raise ValueError("x, g, m, v differ in size")
-    for t, dt in ((wcodes, torch.int32), (wmeta, torch.float32), (n_saturated, torch.int64)):
-        if t is not None:
-            _is(t, dt)
+    _step_outputs(wcodes, wmeta, n_saturated)
     _packed_ok(wcodes, wmeta, x.numel(), wbits, bucket)
-    _launch(x, "qsdp_fused_adamw_step", _ptr(x), _ptr(g), _ptr(m), _ptr(v), x.numel(), lr, beta1, beta2, eps,
-            weight_decay, bias1, bias2, wbits, gbits, bucket, delta, seed, index_offset, flags, _ptr(wcodes),
-            _ptr(wmeta), _ptr(n_saturated))
+    _launch(x, "qsdp_fused_adamw_step", x, g, m, v, x.numel(), lr, beta1, beta2, eps,
+            weight_decay, bias1, bias2, wbits, gbits, bucket, delta, seed, index_offset, flags, wcodes,
+            wmeta, n_saturated)
 
 
 def qsdp_fused_step_codes(wcodes, wmeta, g, lr, wbits, gbits, bucket, delta, seed, index_offset=0,
                           n_saturated=None, flags=0):
     _is(wcodes, torch.int32); _is(wmeta, torch.float32); _is(g, torch.float32)
+    n = g.numel()
     if n_saturated is not None:
         _is(n_saturated, torch.int64)
-    _packed_ok(wcodes, wmeta, g.numel(), wbits, bucket)
-    _launch(g, "qsdp_fused_step_codes", _ptr(wcodes), _ptr(wmeta), _ptr(g), g.numel(), lr, wbits, gbits, bucket, delta,
-            seed, index_offset, flags, _ptr(n_saturated))
+    _packed_ok(wcodes, wmeta, n, wbits, bucket)
+    _launch(g, "qsdp_fused_step_codes", wcodes, wmeta, g, n, lr, wbits, gbits, bucket, delta,
+            seed, index_offset, flags, n_saturated)
 
 
 class Segments:
@@ -416,8 +446,8 @@ def qsdp_quantize_grad_segmented(g, segs, bits, seed, index_offset, codes, meta)
     if g.numel() < segs.n:
         raise ValueError("g is smaller than the segments")
     segs.check_packed(codes, meta, bits)
-    _launch(g, "qsdp_quantize_grad_segmented", _ptr(g), _ptr(segs.device), segs.nseg, segs.total_buckets, bits,
-            segs.bucket, seed, index_offset, _ptr(codes), _ptr(meta))
+    _launch(g, "qsdp_quantize_grad_segmented", g, segs.device, segs.nseg, segs.total_buckets, bits,
+            segs.bucket, seed, index_offset, codes, meta)
 
 
 def qsdp_quantize_weight_segmented(x, segs, bits, delta, seed, codes, meta, n_saturated=None):
@@ -427,8 +457,8 @@ def qsdp_quantize_weight_segmented(x, segs, bits, delta, seed, codes, meta, n_sa
     if n_saturated is not None:
         _is(n_saturated, torch.int64)
     segs.check_packed(codes, meta, bits)
-    _launch(x, "qsdp_quantize_weight_segmented", _ptr(x), _ptr(segs.device), segs.nseg, segs.total_buckets, bits,
-            segs.bucket, delta, seed, _ptr(codes), _ptr(meta), _ptr(n_saturated))
+    _launch(x, "qsdp_quantize_weight_segmented", x, segs.device, segs.nseg, segs.total_buckets, bits,
+            segs.bucket, delta, seed, codes, meta, n_saturated)
 
 
 def qsdp_fused_step_segmented(x, g, segs, lr, wbits, gbits, delta, seed, index_offset=0, wcodes=None,
@@ -436,15 +466,10 @@ def qsdp_fused_step_segmented(x, g, segs, lr, wbits, gbits, delta, seed, index_o
     _is(x, torch.float32); _is(g, torch.float32)
     if x.numel() < segs.n or g.numel() < segs.n:
         raise ValueError("x or g is smaller than the segments")
-    if wcodes is not None:
-        _is(wcodes, torch.int32)
-    if wmeta is not None:
-        _is(wmeta, torch.float32)
-    if n_saturated is not None:
-        _is(n_saturated, torch.int64)
+    _step_outputs(wcodes, wmeta, n_saturated)
     segs.check_packed(wcodes, wmeta, wbits)
-    _launch(x, "qsdp_fused_step_segmented", _ptr(x), _ptr(g), _ptr(segs.device), segs.nseg, segs.total_buckets, lr,
-            wbits, gbits, segs.bucket, delta, seed, index_offset, _ptr(wcodes), _ptr(wmeta), _ptr(n_saturated))
+    _launch(x, "qsdp_fused_step_segmented", x, g, segs.device, segs.nseg, segs.total_buckets, lr,
+            wbits, gbits, segs.bucket, delta, seed, index_offset, wcodes, wmeta, n_saturated)
 
 
 def qsdp_dequantize_segmented(codes, meta, segs, bits, out):
@@ -455,8 +480,8 @@ def qsdp_dequantize_segmented(codes, meta, segs, bits, out):
         raise ValueError("out is smaller than the segments")
     if codes.numel() * 32 < segs.total_buckets * segs.bucket * bits or meta.numel() < 2 * segs.total_buckets:
         raise ValueError("codes or meta is smaller than the segments")
-    _launch(out, "qsdp_dequantize_segmented", _ptr(codes), _ptr(meta), _ptr(segs.device), segs.nseg, segs.total_buckets,
-            bits, segs.bucket, dt, _ptr(out))
+    _launch(out, "qsdp_dequantize_segmented", codes, meta, segs.device, segs.nseg, segs.total_buckets,
+            bits, segs.bucket, dt, out)
 
 
 def qsdp_dequantize_gathered(codes, meta, npeers, n, shard, bits, bucket, out, levels=None):
@@ -475,27 +500,26 @@ def qsdp_dequantize_gathered(codes, meta, npeers, n, shard, bits, bucket, out, l
         _is(levels, torch.float32)
         if levels.numel() != (1 << bits):
             raise ValueError("levels must hold 2^bits entries")
-        _launch(out, "qsdp_dequantize_levels_gathered", _ptr(codes), codes.stride(0) * 4, _ptr(meta),
-                meta.stride(0) * 4, npeers, n, shard, bits, bucket, _ptr(levels), dt, _ptr(out))
+        _launch(out, "qsdp_dequantize_levels_gathered", codes, codes.stride(0) * 4, meta,
+                meta.stride(0) * 4, npeers, n, shard, bits, bucket, levels, dt, out)
         return
-    _launch(out, "qsdp_dequantize_gathered", _ptr(codes), codes.stride(0) * 4, _ptr(meta), meta.stride(0) * 4, npeers,
-            n, shard, bits, bucket, dt, _ptr(out))
+    _launch(out, "qsdp_dequantize_gathered", codes, codes.stride(0) * 4, meta, meta.stride(0) * 4, npeers,
+            n, shard, bits, bucket, dt, out)
 
 
 def qsdp_recv_step(x, gcodes, gmeta, npeers, alpha, lr, wbits, gbits, bucket, delta, seed, flags=0, wcodes=None,
                    wmeta=None, n_saturated=None):
     """gcodes int32[npeers, words], gmeta float32[npeers, nb*2] (row k = peer k's slice)."""
     _is(x, torch.float32); _is_rows(gcodes, torch.int32); _is_rows(gmeta, torch.float32)
+    n = x.numel()
     if gcodes.shape[0] != npeers or gmeta.shape[0] != npeers:
         raise ValueError("gcodes and gmeta must be [npeers, ...]")
-    for t, dt in ((wcodes, torch.int32), (wmeta, torch.float32), (n_saturated, torch.int64)):
-        if t is not None:
-            _is(t, dt)
-    _rows_ok(gcodes, gmeta, x.numel(), gbits, bucket)
-    _packed_ok(wcodes, wmeta, x.numel(), wbits, bucket)
-    _launch(x, "qsdp_recv_step", _ptr(x), _ptr(gcodes), gcodes.stride(0) * 4, _ptr(gmeta), gmeta.stride(0) * 4, npeers,
-            x.numel(), alpha, lr, wbits, gbits, bucket, delta, seed, flags, _ptr(wcodes), _ptr(wmeta),
-            _ptr(n_saturated))
+    _step_outputs(wcodes, wmeta, n_saturated)
+    _rows_ok(gcodes, gmeta, n, gbits, bucket)
+    _packed_ok(wcodes, wmeta, n, wbits, bucket)
+    _launch(x, "qsdp_recv_step", x, gcodes, gcodes.stride(0) * 4, gmeta, gmeta.stride(0) * 4, npeers,
+            n, alpha, lr, wbits, gbits, bucket, delta, seed, flags, wcodes, wmeta,
+            n_saturated)
 
 
 def qsdp_recv_adamw_step(x, m, v, gcodes, gmeta, npeers, alpha, lr, beta1, beta2, eps, weight_decay, bias1, bias2,
@@ -508,14 +532,12 @@ def qsdp_recv_adamw_step(x, m, v, gcodes, gmeta, npeers, alpha, lr, beta1, beta2
     _is_rows(gcodes, torch.int32); _is_rows(gmeta, torch.float32)
     if gcodes.shape[0] != npeers or gmeta.shape[0] != npeers:
         raise ValueError("gcodes and gmeta must be [npeers, ...]")
-    for t, dt in ((wcodes, torch.int32), (wmeta, torch.float32), (n_saturated, torch.int64)):
-        if t is not None:
-            _is(t, dt)
+    _step_outputs(wcodes, wmeta, n_saturated)
     _rows_ok(gcodes, gmeta, x.numel(), gbits, bucket)
     _packed_ok(wcodes, wmeta, x.numel(), wbits, bucket)
-    _launch(x, "qsdp_recv_adamw_step", _ptr(x), _ptr(m), _ptr(v), _ptr(gcodes), gcodes.stride(0) * 4, _ptr(gmeta),
+    _launch(x, "qsdp_recv_adamw_step", x, m, v, gcodes, gcodes.stride(0) * 4, gmeta,
             gmeta.stride(0) * 4, npeers, x.numel(), alpha, lr, beta1, beta2, eps, weight_decay, bias1, bias2, wbits,
-            gbits, bucket, delta, seed, flags, _ptr(wcodes), _ptr(wmeta), _ptr(n_saturated))
+            gbits, bucket, delta, seed, flags, wcodes, wmeta, n_saturated)
 
 
 def qsdp_recv_step_segmented(x, segs, gcodes, gmeta, npeers, alpha, lr, wbits, gbits, delta, seed, flags=0,
@@ -527,24 +549,22 @@ def qsdp_recv_step_segmented(x, segs, gcodes, gmeta, npeers, alpha, lr, wbits, g
         raise ValueError("x is smaller than the segments")
     if gcodes.shape[0] != npeers or gmeta.shape[0] != npeers:
         raise ValueError("gcodes and gmeta must be [npeers, ...]")
-    for t, dt in ((wcodes, torch.int32), (wmeta, torch.float32), (n_saturated, torch.int64)):
-        if t is not None:
-            _is(t, dt)
+    _step_outputs(wcodes, wmeta, n_saturated)
     segs.check_packed(gcodes, gmeta, gbits, rows=True)
     segs.check_packed(wcodes, wmeta, wbits)
     if adamw is None:
-        _launch(x, "qsdp_recv_step_segmented", _ptr(x), _ptr(segs.device), segs.nseg, segs.total_buckets, _ptr(gcodes),
-                gcodes.stride(0) * 4, _ptr(gmeta), gmeta.stride(0) * 4, npeers, alpha, lr, wbits, gbits, segs.bucket,
-                delta, seed, flags, _ptr(wcodes), _ptr(wmeta), _ptr(n_saturated))
+        _launch(x, "qsdp_recv_step_segmented", x, segs.device, segs.nseg, segs.total_buckets, gcodes,
+                gcodes.stride(0) * 4, gmeta, gmeta.stride(0) * 4, npeers, alpha, lr, wbits, gbits, segs.bucket,
+                delta, seed, flags, wcodes, wmeta, n_saturated)
     else:
         m, v, b1, b2, eps, wd, c1, c2 = adamw
         _is(m, torch.float32); _is(v, torch.float32)
         if m.numel() < segs.n or v.numel() < segs.n:
             raise ValueError("m or v is smaller than the segments")
-        _launch(x, "qsdp_recv_adamw_step_segmented", _ptr(x), _ptr(m), _ptr(v), _ptr(segs.device), segs.nseg,
-                segs.total_buckets, _ptr(gcodes), gcodes.stride(0) * 4, _ptr(gmeta), gmeta.stride(0) * 4, npeers, alpha,
-                lr, b1, b2, eps, wd, c1, c2, wbits, gbits, segs.bucket, delta, seed, flags, _ptr(wcodes), _ptr(wmeta),
-                _ptr(n_saturated))
+        _launch(x, "qsdp_recv_adamw_step_segmented", x, m, v, segs.device, segs.nseg,
+                segs.total_buckets, gcodes, gcodes.stride(0) * 4, gmeta, gmeta.stride(0) * 4, npeers, alpha,
+                lr, b1, b2, eps, wd, c1, c2, wbits, gbits, segs.bucket, delta, seed, flags, wcodes, wmeta,
+                n_saturated)
 
 
 def qsdp_fused_adamw_step_segmented(x, g, m, v, segs, lr, beta1, beta2, eps, weight_decay, bias1, bias2, wbits, gbits,
@@ -553,13 +573,11 @@ def qsdp_fused_adamw_step_segmented(x, g, m, v, segs, lr, beta1, beta2, eps, wei
         _is(t, torch.float32)
         if t.numel() < segs.n:
             raise ValueError("a tensor is smaller than the segments")
-    for t, dt in ((wcodes, torch.int32), (wmeta, torch.float32), (n_saturated, torch.int64)):
-        if t is not None:
-            _is(t, dt)
+    _step_outputs(wcodes, wmeta, n_saturated)
     segs.check_packed(wcodes, wmeta, wbits)
-    _launch(x, "qsdp_fused_adamw_step_segmented", _ptr(x), _ptr(g), _ptr(m), _ptr(v), _ptr(segs.device), segs.nseg,
+    _launch(x, "qsdp_fused_adamw_step_segmented", x, g, m, v, segs.device, segs.nseg,
             segs.total_buckets, lr, beta1, beta2, eps, weight_decay, bias1, bias2, wbits, gbits, segs.bucket, delta,
-            seed, index_offset, flags, _ptr(wcodes), _ptr(wmeta), _ptr(n_saturated))
+            seed, index_offset, flags, wcodes, wmeta, n_saturated)
 
 
 def qsdp_fused_step_codes_segmented(wcodes, wmeta, g, segs, lr, wbits, gbits, delta, seed, index_offset=0, flags=0,
@@ -570,8 +588,8 @@ def qsdp_fused_step_codes_segmented(wcodes, wmeta, g, segs, lr, wbits, gbits, de
     if n_saturated is not None:
         _is(n_saturated, torch.int64)
     segs.check_packed(wcodes, wmeta, wbits)
-    _launch(g, "qsdp_fused_step_codes_segmented", _ptr(wcodes), _ptr(wmeta), _ptr(g), _ptr(segs.device), segs.nseg,
-            segs.total_buckets, lr, wbits, gbits, segs.bucket, delta, seed, index_offset, flags, _ptr(n_saturated))
+    _launch(g, "qsdp_fused_step_codes_segmented", wcodes, wmeta, g, segs.device, segs.nseg,
+            segs.total_buckets, lr, wbits, gbits, segs.bucket, delta, seed, index_offset, flags, n_saturated)
 
 
 def qsdp_fit_levels_segmented(v, segs, bits, lr, levels, max_batches=0):
@@ -581,8 +599,8 @@ def qsdp_fit_levels_segmented(v, segs, bits, lr, levels, max_batches=0):
         raise ValueError("v is smaller than the segments")
     if levels.numel() != segs.nseg * (1 << bits):
         raise ValueError("levels must hold nseg * 2^bits entries")
-    _launch(v, "qsdp_fit_levels_segmented", _ptr(v), _ptr(segs.device), segs.nseg, bits, segs.bucket, lr, max_batches,
-            _ptr(levels))
+    _launch(v, "qsdp_fit_levels_segmented", v, segs.device, segs.nseg, bits, segs.bucket, lr, max_batches,
+            levels)
 
 
 def qsdp_fused_step_dseed(x, g, lr, wbits, gbits, bucket, delta, seed, seed_dev, index_offset=0, flags=0, wcodes=None,
@@ -590,14 +608,13 @@ def qsdp_fused_step_dseed(x, g, lr, wbits, gbits, bucket, delta, seed, seed_dev,
     """qsdp_fused_step_ex with the seed in force = seed + seed_dev[0] (an int64 GPU tensor read by the
     kernel), so that a step captured in a graph can be replayed with an advancing seed."""
     _is(x, torch.float32); _is(g, torch.float32); _is(seed_dev, torch.int64)
-    if g.numel() != x.numel():
+    n = x.numel()
+    if g.numel() != n:
         raise ValueError("x and g differ in size")
-    for t, dt in ((wcodes, torch.int32), (wmeta, torch.float32), (n_saturated, torch.int64)):
-        if t is not None:
-            _is(t, dt)
-    _packed_ok(wcodes, wmeta, x.numel(), wbits, bucket)
-    _launch(x, "qsdp_fused_step_dseed", _ptr(x), _ptr(g), x.numel(), lr, wbits, gbits, bucket, delta, seed,
-            _ptr(seed_dev), index_offset, flags, _ptr(wcodes), _ptr(wmeta), _ptr(n_saturated))
+    _step_outputs(wcodes, wmeta, n_saturated)
+    _packed_ok(wcodes, wmeta, n, wbits, bucket)
+    _launch(x, "qsdp_fused_step_dseed", x, g, n, lr, wbits, gbits, bucket, delta, seed,
+            seed_dev, index_offset, flags, wcodes, wmeta, n_saturated)
 
 
 def qsdp_quantize_levels_segmented(v, segs, bits, levels, codes, meta, stochastic=False, seed=0, index_offset=0):
@@ -608,8 +625,8 @@ def qsdp_quantize_levels_segmented(v, segs, bits, levels, codes, meta, stochasti
     if levels.numel() != segs.nseg * (1 << bits):
         raise ValueError("levels must hold nseg * 2^bits entries")
     segs.check_packed(codes, meta, bits)
-    _launch(v, "qsdp_quantize_levels_segmented", _ptr(v), _ptr(segs.device), segs.nseg, segs.total_buckets, bits,
-            segs.bucket, _ptr(levels), int(bool(stochastic)), seed, index_offset, _ptr(codes), _ptr(meta))
+    _launch(v, "qsdp_quantize_levels_segmented", v, segs.device, segs.nseg, segs.total_buckets, bits,
+            segs.bucket, levels, int(bool(stochastic)), seed, index_offset, codes, meta)
 
 
 def qsdp_dequantize_levels_segmented(codes, meta, segs, bits, levels, out):
@@ -621,8 +638,8 @@ def qsdp_dequantize_levels_segmented(codes, meta, segs, bits, levels, out):
     if levels.numel() != segs.nseg * (1 << bits):
         raise ValueError("levels must hold nseg * 2^bits entries")
     segs.check_packed(codes, meta, bits)
-    _launch(out, "qsdp_dequantize_levels_segmented", _ptr(codes), _ptr(meta), _ptr(segs.device), segs.nseg,
-            segs.total_buckets, bits, segs.bucket, _ptr(levels), dt, _ptr(out))
+    _launch(out, "qsdp_dequantize_levels_segmented", codes, meta, segs.device, segs.nseg,
+            segs.total_buckets, bits, segs.bucket, levels, dt, out)
 
 
 
@@ -634,9 +651,10 @@ def qsdp_quantize_grad_g16(g, bits, bucket, seed, index_offset, codes, meta, fla
     if g.dtype not in _G16:
         raise TypeError("g must be float16 or bfloat16")
     _is(g, g.dtype); _is(codes, torch.int32); _is(meta, torch.float32)
-    _packed_ok(codes, meta, g.numel(), bits, bucket)
-    _launch(g, "qsdp_quantize_grad_g16", _ptr(g), _G16[g.dtype], g.numel(), bits, bucket, seed, index_offset, flags,
-            _ptr(codes), _ptr(meta))
+    n = g.numel()
+    _packed_ok(codes, meta, n, bits, bucket)
+    _launch(g, "qsdp_quantize_grad_g16", g, _G16[g.dtype], n, bits, bucket, seed, index_offset, flags,
+            codes, meta)
 
 
 def qsdp_fused_step_g16(x, g, lr, wbits, gbits, bucket, delta, seed, index_offset=0, flags=0, wcodes=None, wmeta=None,
@@ -645,14 +663,13 @@ def qsdp_fused_step_g16(x, g, lr, wbits, gbits, bucket, delta, seed, index_offse
     if g.dtype not in _G16:
         raise TypeError("g must be float16 or bfloat16")
     _is(x, torch.float32); _is(g, g.dtype)
-    if g.numel() != x.numel():
+    n = x.numel()
+    if g.numel() != n:
         raise ValueError("x and g differ in size")
-    for t, dt in ((wcodes, torch.int32), (wmeta, torch.float32), (n_saturated, torch.int64)):
-        if t is not None:
-            _is(t, dt)
-    _packed_ok(wcodes, wmeta, x.numel(), wbits, bucket)
-    _launch(x, "qsdp_fused_step_g16", _ptr(x), _ptr(g), _G16[g.dtype], x.numel(), lr, wbits, gbits, bucket, delta, seed,
-            index_offset, flags, _ptr(wcodes), _ptr(wmeta), _ptr(n_saturated))
+    _step_outputs(wcodes, wmeta, n_saturated)
+    _packed_ok(wcodes, wmeta, n, wbits, bucket)
+    _launch(x, "qsdp_fused_step_g16", x, g, _G16[g.dtype], n, lr, wbits, gbits, bucket, delta, seed,
+            index_offset, flags, wcodes, wmeta, n_saturated)
 
 
 def qsdp_fused_adamw_step_codes(wcodes, wmeta, g, m, v, lr, beta1, beta2, eps, weight_decay, bias1, bias2, wbits, gbits,
@@ -666,39 +683,38 @@ def qsdp_fused_adamw_step_codes(wcodes, wmeta, g, m, v, lr, beta1, beta2, eps, w
     if n_saturated is not None:
         _is(n_saturated, torch.int64)
     _packed_ok(wcodes, wmeta, n, wbits, bucket)
-    _launch(g, "qsdp_fused_adamw_step_codes", _ptr(wcodes), _ptr(wmeta), _ptr(g), _ptr(m), _ptr(v), n, lr, beta1, beta2,
-            eps, weight_decay, bias1, bias2, wbits, gbits, bucket, delta, seed, index_offset, flags, _ptr(n_saturated))
+    _launch(g, "qsdp_fused_adamw_step_codes", wcodes, wmeta, g, m, v, n, lr, beta1, beta2,
+            eps, weight_decay, bias1, bias2, wbits, gbits, bucket, delta, seed, index_offset, flags, n_saturated)
 
 
 def qsdp_fused_step_mp(x, g, lr, wbits, gbits, bucket, delta, seed, index_offset=0, flags=0, wcodes=None, wmeta=None,
                        x16=None, n_saturated=None):
     """The fused step with a float32 / float16 / bfloat16 gradient and, optionally, the new quantized weights
     written once more as float16 / bfloat16 into x16."""
-    gdt = {torch.float32: QSDP_F32, torch.bfloat16: QSDP_BF16, torch.float16: QSDP_F16}.get(g.dtype)
+    gdt = _DTYPES.get(g.dtype)
     if gdt is None:
         raise TypeError("g must be float32, float16 or bfloat16")
     _is(x, torch.float32); _is(g, g.dtype)
-    if g.numel() != x.numel():
+    n = x.numel()
+    if g.numel() != n:
         raise ValueError("x and g differ in size")
     xdt = QSDP_BF16
     if x16 is not None:
         if x16.dtype not in _G16:
             raise TypeError("x16 must be float16 or bfloat16")
         _is(x16, x16.dtype)
-        _need(x16, x.numel(), "x16")
+        _need(x16, n, "x16")
         xdt = _G16[x16.dtype]
-    for t, dt in ((wcodes, torch.int32), (wmeta, torch.float32), (n_saturated, torch.int64)):
-        if t is not None:
-            _is(t, dt)
-    _packed_ok(wcodes, wmeta, x.numel(), wbits, bucket)
-    _launch(x, "qsdp_fused_step_mp", _ptr(x), _ptr(g), gdt, x.numel(), lr, wbits, gbits, bucket, delta, seed,
-            index_offset, flags, _ptr(wcodes), _ptr(wmeta), _ptr(x16), xdt, _ptr(n_saturated))
+    _step_outputs(wcodes, wmeta, n_saturated)
+    _packed_ok(wcodes, wmeta, n, wbits, bucket)
+    _launch(x, "qsdp_fused_step_mp", x, g, gdt, n, lr, wbits, gbits, bucket, delta, seed,
+            index_offset, flags, wcodes, wmeta, x16, xdt, n_saturated)
 
 
 def qsdp_fused_step_segmented_mp(x, g, segs, lr, wbits, gbits, delta, seed, index_offset=0, flags=0, wcodes=None,
                                  wmeta=None, x16=None, n_saturated=None):
     """qsdp_fused_step_mp over the tensors of a segment table, one launch."""
-    gdt = {torch.float32: QSDP_F32, torch.bfloat16: QSDP_BF16, torch.float16: QSDP_F16}.get(g.dtype)
+    gdt = _DTYPES.get(g.dtype)
     if gdt is None:
         raise TypeError("g must be float32, float16 or bfloat16")
     _is(x, torch.float32); _is(g, g.dtype)
@@ -710,20 +726,18 @@ def qsdp_fused_step_segmented_mp(x, g, segs, lr, wbits, gbits, delta, seed, inde
         _is(x16, x16.dtype)
         _need(x16, segs.n, "x16")
         xdt = _G16[x16.dtype]
-    for t, dt in ((wcodes, torch.int32), (wmeta, torch.float32), (n_saturated, torch.int64)):
-        if t is not None:
-            _is(t, dt)
+    _step_outputs(wcodes, wmeta, n_saturated)
     segs.check_packed(wcodes, wmeta, wbits)
-    _launch(x, "qsdp_fused_step_segmented_mp", _ptr(x), _ptr(g), gdt, _ptr(segs.device), segs.nseg, segs.total_buckets,
-            lr, wbits, gbits, segs.bucket, delta, seed, index_offset, flags, _ptr(wcodes), _ptr(wmeta), _ptr(x16), xdt,
-            _ptr(n_saturated))
+    _launch(x, "qsdp_fused_step_segmented_mp", x, g, gdt, segs.device, segs.nseg, segs.total_buckets,
+            lr, wbits, gbits, segs.bucket, delta, seed, index_offset, flags, wcodes, wmeta, x16, xdt,
+            n_saturated)
 
 
 def qsdp_fused_adamw_step_mp(x, g, m, v, lr, beta1, beta2, eps, weight_decay, bias1, bias2, wbits, gbits, bucket, delta,
                              seed, index_offset=0, flags=0, wcodes=None, wmeta=None, x16=None, n_saturated=None):
     """qsdp_fused_adamw_step with a float32 / float16 / bfloat16 gradient and an optional float16 / bfloat16
     copy x16 of the new quantized weights."""
-    gdt = {torch.float32: QSDP_F32, torch.bfloat16: QSDP_BF16, torch.float16: QSDP_F16}.get(g.dtype)
+    gdt = _DTYPES.get(g.dtype)
     if gdt is None:
         raise TypeError("g must be float32, float16 or bfloat16")
     _is(x, torch.float32); _is(g, g.dtype); _is(m, torch.float32); _is(v, torch.float32)
@@ -737,13 +751,11 @@ def qsdp_fused_adamw_step_mp(x, g, m, v, lr, beta1, beta2, eps, weight_decay, bi
         _is(x16, x16.dtype)
         _need(x16, n, "x16")
         xdt = _G16[x16.dtype]
-    for t, dt in ((wcodes, torch.int32), (wmeta, torch.float32), (n_saturated, torch.int64)):
-        if t is not None:
-            _is(t, dt)
+    _step_outputs(wcodes, wmeta, n_saturated)
     _packed_ok(wcodes, wmeta, n, wbits, bucket)
-    _launch(x, "qsdp_fused_adamw_step_mp", _ptr(x), _ptr(g), gdt, _ptr(m), _ptr(v), n, lr, beta1, beta2, eps,
-            weight_decay, bias1, bias2, wbits, gbits, bucket, delta, seed, index_offset, flags, _ptr(wcodes),
-            _ptr(wmeta), _ptr(x16), xdt, _ptr(n_saturated))
+    _launch(x, "qsdp_fused_adamw_step_mp", x, g, gdt, m, v, n, lr, beta1, beta2, eps,
+            weight_decay, bias1, bias2, wbits, gbits, bucket, delta, seed, index_offset, flags, wcodes,
+            wmeta, x16, xdt, n_saturated)
 
 
 class StepOptions(C.Structure):
@@ -758,7 +770,7 @@ class StepOptions(C.Structure):
 
 def _step_opts(entry, x, g, lr, wbits, gbits, bucket, delta, seed, index_offset, flags, segs, x16, seed_increment,
                wcodes, wmeta, n_saturated, adamw):
-    gdt = {torch.float32: QSDP_F32, torch.bfloat16: QSDP_BF16, torch.float16: QSDP_F16}.get(g.dtype)
+    gdt = _DTYPES.get(g.dtype)
     if gdt is None:
         raise TypeError("g must be float32, float16 or bfloat16")
     _is(x, torch.float32); _is(g, g.dtype)
@@ -795,7 +807,7 @@ def _step_opts(entry, x, g, lr, wbits, gbits, bucket, delta, seed, index_offset,
         _is(m, torch.float32); _is(v, torch.float32)
         _need(m, n, "m"); _need(v, n, "v")
         o.m, o.v = m.data_ptr(), v.data_ptr()
-    _launch(x, entry, _ptr(x), _ptr(g), 0 if segs is not None else n, lr, wbits, gbits, bucket, delta, seed,
+    _launch(x, entry, x, g, 0 if segs is not None else n, lr, wbits, gbits, bucket, delta, seed,
             index_offset, C.byref(o))
 
 

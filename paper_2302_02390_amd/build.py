@@ -20,6 +20,8 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libqsdp.so")
 BENCH_LIB = os.path.join(HERE, "libqsdp_bench.so")  # streaming kernels for bench.py, not part of the codec
 
+MARSHAL = os.path.join(HERE, "_marshal.so")  # the binding's argument marshalling
+
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-fno-fast-math", "-fno-honor-nans", "-Wall", "-Wno-unused-result",
@@ -70,8 +72,31 @@ def build(jobs=None, verbose=False):
         raise RuntimeError(f"{' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
     if verbose:
         print(LIB)
+    build_marshal(verbose)
     build_bench_support(verbose)
     return LIB
+
+
+def build_marshal(verbose=False):
+    """_marshal.so: the binding's argument marshalling (csrc/qsdp_marshal.cpp, host code against torch's headers)."""
+    import sysconfig
+    import torch
+    from torch.utils import cpp_extension
+    includes = [sysconfig.get_paths()["include"]] + cpp_extension.include_paths("cuda")
+    cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden", "-Wall", "-D__HIP_PLATFORM_AMD__",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+    for d in includes:
+        cmd += ["-isystem", d]
+    cmd += [os.path.join(CSRC, "qsdp_marshal.cpp"), "-o", MARSHAL, "-L", HERE, "-lqsdp"]
+    for d in cpp_extension.library_paths("cuda"):
+        cmd += ["-L", d]
+    cmd += ["-ltorch_python", "-ltorch_cpu", "-lc10", "-lamdhip64", "-Wl,-rpath,$ORIGIN"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"{' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
+    if verbose:
+        print(MARSHAL)
+    return MARSHAL
 
 
 def build_bench_support(verbose=False):
