@@ -10,11 +10,16 @@
 // combine those of one bucket, and the bucket's grid comes back with one 16-byte LDS read per row.
 //
 // Bound by HBM where a tile is well filled: the step with code output on 125 million parameters in buckets of 768 (W8
-// G8) takes 0.268 ms = 6.1 TB/s, against 1.33 ms for a workgroup per bucket that stages its values in LDS and packs
+// G8) takes 0.265 ms = 6.2 TB/s, against 1.33 ms for a workgroup per bucket that stages its values in LDS and packs
 // its codes bit by bit; buckets of 96 on 8 million parameters 0.022 against 0.353 ms. P is the largest count that fits
 // (qsdp_tile_plan.hpp, which also says when a tile is smaller), so few slots idle; leaving out the arithmetic of a
 // wave's idle rows by branches cost the full tiles 3-10 % (the rows no longer overlap) and won 4 % at the worst fill,
 // so it is not done there.
+//
+// A question that is the same for all rows (whether the tile is contiguous, which grid, eight bits or not) is asked once
+// around them: asked in every row or element, as it was, each row was a block of its own that waited for itself.
+// us, before / after: eight peers with AdamW 2^26 elements in buckets of 160 / 1504 414 / 371, 454 / 423, four peers 156
+// / 140, 162 / 139, gradient encoder 4 bits, 160, 66.7 / 62.3, code-resident step 1504 / 3040 99 / 96, 106 / 92.
 #pragma once
 
 #include "qsdp_params.hpp"
@@ -111,8 +116,14 @@ struct TileArgs {
     uint32_t group_magic, word_magic;
 };
 
+constexpr int tile_min_blocks(int mode, int waves, int rows) {
+    if (mode_is_levels(mode)) return tile_resident(mode == MODE_LEVELS_COIN, waves, rows);
+    if (mode == MODE_RECV_ADAMW && rows <= 4) return 4;
+    return 1;
+}
+
 template <int MODE, int R, int W>
-__global__ void __launch_bounds__(256, mode_is_levels(MODE) ? tile_resident(MODE == MODE_LEVELS_COIN, W, R) : 1)
+__global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
     tile_kernel(const Params p, const Segment* __restrict__ segs, const TileArgs a) {
     static_assert(R % 2 == 0 && R <= kTileMaxRows && (W == 1 || W == 4), "shape");
     typedef TileLds<R, W> Lds;
@@ -300,33 +311,50 @@ __global__ void __launch_bounds__(256, mode_is_levels(MODE) ? tile_resident(MODE
         };
         // Rounding uniforms of rows 2cp and 2cp + 1: the pair's even lane draws the block of the first, its odd lane
         // that of the second.
+        uint32_t block_rel[R / 2];
+        auto locate_blocks = [&]() {
+#pragma unroll
+            for (int cp = 0; cp < R / 2; ++cp) block_rel[cp] = (uint32_t)((2 * cp + odd) * TEAM + tid - odd) >> 1;
+            if (__builtin_expect(!whole, 0)) {
+#pragma unroll
+                for (int cp = 0; cp < R / 2; ++cp) block_rel[cp] = place((2 * cp + odd) * TEAM + tid - odd).rel >> 3;
+            }
+        };
         auto uniforms = [&](int cp, uint32_t (&h)[4]) {
-            const int slot = (2 * cp + odd) * TEAM + tid - odd;
-            const uint32_t rel = __builtin_expect(whole, 1) ? (uint32_t)slot * 4u : place(slot).rel;
-            uniforms_of_pair<(MODE == MODE_GRAD || MODE == MODE_LEVELS_COIN)>(p.block0 + (e0 >> 3) + (rel >> 3), odd,
+            uniforms_of_pair<(MODE == MODE_GRAD || MODE == MODE_LEVELS_COIN)>(p.block0 + (e0 >> 3) + block_rel[cp], odd,
                                                                               key.k0, key.k1, h);
         };
         // Minimum and maximum of every bucket of the tile, then its grid: make(lo, hi, bucket in the tile) in the
         // lanes that combine that bucket, the result in lds.grid for all.
         auto bucket_grids = [&](const float (&v)[R][4], auto make) {
+            float row_lo[R], row_hi[R];
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                float lo = fminf(fminf(v[r][0], v[r][1]), fminf(v[r][2], v[r][3]));
-                float hi = fmaxf(fmaxf(v[r][0], v[r][1]), fmaxf(v[r][2], v[r][3]));
-                if (__builtin_expect(!whole, 0)) {
+                row_lo[r] = fminf(fminf(v[r][0], v[r][1]), fminf(v[r][2], v[r][3]));
+                row_hi[r] = fmaxf(fmaxf(v[r][0], v[r][1]), fmaxf(v[r][2], v[r][3]));
+            }
+            if (__builtin_expect(!whole, 0)) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
                     const int c = place(slot_of(r)).count;
-                    lo = __builtin_inff();
-                    hi = -__builtin_inff();
+                    row_lo[r] = __builtin_inff();
+                    row_hi[r] = -__builtin_inff();
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        lo = i < c ? fminf(lo, v[r][i]) : lo;
-                        hi = i < c ? fmaxf(hi, v[r][i]) : hi;
+                        row_lo[r] = i < c ? fminf(row_lo[r], v[r][i]) : row_lo[r];
+                        row_hi[r] = i < c ? fmaxf(row_hi[r], v[r][i]) : row_hi[r];
                     }
                 }
-                lo = group_min<8>(lo);
-                hi = group_max<8>(hi);
-                if ((tid & 7) == 0) {
-                    const u2 e = {__float_as_uint(lo), __float_as_uint(hi)};
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                row_lo[r] = group_min<8>(row_lo[r]);
+                row_hi[r] = group_max<8>(row_hi[r]);
+            }
+            if ((tid & 7) == 0) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const u2 e = {__float_as_uint(row_lo[r]), __float_as_uint(row_hi[r])};
                     lds.part[slot_of(r) >> 3] = e;
                 }
             }
@@ -369,36 +397,42 @@ __global__ void __launch_bounds__(256, mode_is_levels(MODE) ? tile_resident(MODE
                     if (r * 8 < R * bits) lds.stage[slot_of(r)] = w[r];
                 team_sync<W>();
             }
-            const uint32_t mask = (1u << bits) - 1u;
+            uint32_t q[R];
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                uint32_t q = w[r];
-                if (bits != 8) {
+            for (int r = 0; r < R; ++r) q[r] = w[r];
+            if (bits != 8) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
                     const uint32_t bit = (uint32_t)(slot_of(r) * 4 * bits);
                     const uint64_t two = (uint64_t)lds.stage[bit >> 5] | ((uint64_t)lds.stage[(bit >> 5) + 1] << 32);
-                    q = (uint32_t)(two >> (bit & 31u));
+                    q[r] = (uint32_t)(two >> (bit & 31u));
                 }
-#pragma unroll
-                for (int i = 0; i < 4; ++i) c[r][i] = (float)((q >> (i * bits)) & mask);
             }
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) c[r][i] = (float)__builtin_amdgcn_ubfe(q[r], (uint32_t)(i * bits), (uint32_t)bits);
         };
         // The reverse: pack the codes and write the tile's part of the code stream. Slots past a short bucket's end
         // carry zeros.
-        auto store_words = [&](const uint32_t (&code)[R][4], int bits) {
+        auto store_packed = [&](uint32_t (&q)[R], int bits) {
             uint32_t* out = p.codes + word0 * (uint64_t)bits;
-            if (bits != 8) team_sync<W>();
+            if (__builtin_expect(!whole, 0)) {
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                uint32_t q = code[r][0] | (code[r][1] << bits);
-                q |= (code[r][2] << (2 * bits)) | (code[r][3] << (3 * bits));
-                if (__builtin_expect(!whole, 0)) {
+                for (int r = 0; r < R; ++r) {
                     const int c = place(slot_of(r)).count;
-                    if (c < 4) q &= (1u << (c * bits)) - 1u;
+                    if (c < 4) q[r] &= (1u << (c * bits)) - 1u;
                 }
-                if (bits != 8) lds.stage[slot_of(r)] = q;
-                else if (slot_of(r) < used) __builtin_nontemporal_store(q, out + slot_of(r));
             }
-            if (bits == 8) return;
+            if (bits == 8) {
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    if (slot_of(r) < used) __builtin_nontemporal_store(q[r], out + slot_of(r));
+                return;
+            }
+            team_sync<W>();
+#pragma unroll
+            for (int r = 0; r < R; ++r) lds.stage[slot_of(r)] = q[r];
             team_sync<W>();
             const int total = used * bits >> 3;
             for (int w = tid; w < total; w += TEAM) {
@@ -408,6 +442,15 @@ __global__ void __launch_bounds__(256, mode_is_levels(MODE) ? tile_resident(MODE
                 for (at += 4 * bits; at < 32; at += 4 * bits) word |= lds.stage[++s] << at;
                 __builtin_nontemporal_store(word, out + w);
             }
+        };
+        auto store_words = [&](const uint32_t (&code)[R][4], int bits) {
+            uint32_t q[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                q[r] = code[r][0] | (code[r][1] << bits);
+                q[r] |= (code[r][2] << (2 * bits)) | (code[r][3] << (3 * bits));
+            }
+            store_packed(q, bits);
         };
 
         float w[R][4];  // the values that get weight-quantized
@@ -442,25 +485,47 @@ __global__ void __launch_bounds__(256, mode_is_levels(MODE) ? tile_resident(MODE
                 return f4{g.lo, g.inv, g.scale, base};
             });
             uint32_t code[MODE == MODE_GRAD ? R : 1][4] = {};
+            auto grid_of_row = [&](int r) -> f4 { return lds.grid[bucket_of_slot(slot_of(r))]; };
+            // The question outside the rows, so that these are straight-line code (gradient encoder, 2^26 elements from
+            // bf16, 3 bits, buckets of 160: 68.7 -> 65.7 us). The steps on resident weights ask it for every element: with the rows of their divisions side by side AdamW's take 40 more registers (2^26 elements,
+            // buckets of 1504, 333 against 351 us), and the plain step is bound by memory and 1-2 % slower.
+            constexpr bool kAskInside = MODE == MODE_FUSED || mode_local_adamw(MODE);
+            if (!kAskInside && grad_shift) {
 #pragma unroll
-            for (int cp = 0; cp < R / 2; ++cp) {
-                uint32_t h[4] = {0u, 0u, 0u, 0u};
-                if (!grad_shift) uniforms(cp, h);
-#pragma unroll
-                for (int half = 0; half < 2; ++half) {
-                    const int r = 2 * cp + half;
+                for (int r = 0; r < R; ++r) {
                     if (!computed(r)) continue;
-                    const f4 gr = lds.grid[bucket_of_slot(slot_of(r))];
+                    const f4 gr = grid_of_row(r);
                     const MinMaxGrid grid = {gr[0], gr[2], gr[1]};
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        if constexpr (MODE == MODE_GRAD) {
-                            code[r][i] = grad_shift ? (uint32_t)weight_code_minmax(gv[r][i], grid, Lg, shifts.xi_g)
-                                                    : grad_code_int(gv[r][i], grid, top16_g, uniform16(h, 4 * half + i));
-                        } else {
-                            const float c = grad_shift ? weight_code_minmax(gv[r][i], grid, Lg, shifts.xi_g)
-                                                       : grad_code(gv[r][i], grid, top16_g, uniform16(h, 4 * half + i));
-                            w[r][i] = step_value<MODE>(p, w[r][i], fmaf(c, grid.scale, gr[3]), mom[r][i], var[r][i]);
+                        const float c = weight_code_minmax(gv[r][i], grid, Lg, shifts.xi_g);
+                        if constexpr (MODE == MODE_GRAD) code[r][i] = (uint32_t)c;
+                        else w[r][i] = step_value<MODE>(p, w[r][i], fmaf(c, grid.scale, gr[3]), mom[r][i], var[r][i]);
+                    }
+                }
+            } else {
+                locate_blocks();
+#pragma unroll
+                for (int cp = 0; cp < R / 2; ++cp) {
+                    uint32_t h[4] = {0u, 0u, 0u, 0u};
+                    if (!kAskInside || !grad_shift) uniforms(cp, h);
+#pragma unroll
+                    for (int half = 0; half < 2; ++half) {
+                        const int r = 2 * cp + half;
+                        if (!computed(r)) continue;
+                        const f4 gr = grid_of_row(r);
+                        const MinMaxGrid grid = {gr[0], gr[2], gr[1]};
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const uint32_t u = uniform16(h, 4 * half + i);
+                            if constexpr (MODE == MODE_GRAD) {
+                                code[r][i] = grad_code_int(gv[r][i], grid, top16_g, u);
+                            } else {
+                                const float c = kAskInside && grad_shift
+                                                    ? weight_code_minmax(gv[r][i], grid, Lg, shifts.xi_g)
+                                                    : grad_code(gv[r][i], grid, top16_g, u);
+                                w[r][i] = step_value<MODE>(p, w[r][i], fmaf(c, grid.scale, gr[3]), mom[r][i], var[r][i]);
+                            }
                         }
                     }
                 }
@@ -581,6 +646,7 @@ __global__ void __launch_bounds__(256, mode_is_levels(MODE) ? tile_resident(MODE
                 }
                 // by cell, by search and by search for some of the buckets are loops of their own, so that each is
                 // straight-line code over the rows
+                if constexpr (kCoin) locate_blocks();
                 auto encode = [&](auto mine, auto code_of) {
 #pragma unroll
                     for (int cp = 0; cp < R / 2; ++cp) {
@@ -649,12 +715,11 @@ __global__ void __launch_bounds__(256, mode_is_levels(MODE) ? tile_resident(MODE
             return f4{origin, inv, scale, base};
         });
         const bool want16 = (MODE == MODE_FUSED || MODE == MODE_ADAMW) && p.x16 != nullptr;
+        if (lattice) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            if (!computed(r)) continue;
-            const f4 gr = lds.grid[bucket_of_slot(slot_of(r))];
-            const MinMaxGrid grid = {gr[0], gr[2], gr[1]};
-            if (lattice) {
+            for (int r = 0; r < R; ++r) {
+                if (!computed(r)) continue;
+                const f4 gr = lds.grid[bucket_of_slot(slot_of(r))];
                 const int n = __builtin_expect(whole, 1) ? (slot_of(r) < used ? 4 : 0) : place(slot_of(r)).count;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
@@ -664,7 +729,28 @@ __global__ void __launch_bounds__(256, mode_is_levels(MODE) ? tile_resident(MODE
                     code[r][i] = (uint32_t)c;
                     w[r][i] = fmaf(c, gr[2], gr[3]);
                 }
-            } else {
+            }
+        } else if ((MODE == MODE_WEIGHT || mode_codes_resident(MODE)) && p.wbits == 8) {
+            // only stored: the packing instruction rounds and clamps (see pack4)
+            uint32_t q[R] = {};
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if (!computed(r)) continue;
+                const f4 gr = lds.grid[bucket_of_slot(slot_of(r))];
+                const MinMaxGrid grid = {gr[0], gr[2], gr[1]};
+                float at[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) at[i] = weight_position_minmax(w[r][i], grid, xi);
+                q[r] = pack4<8>(at);
+            }
+            store_packed(q, 8);
+            continue;
+        } else {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if (!computed(r)) continue;
+                const f4 gr = lds.grid[bucket_of_slot(slot_of(r))];
+                const MinMaxGrid grid = {gr[0], gr[2], gr[1]};
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const float c = weight_code_minmax(w[r][i], grid, Lw, xi);
@@ -673,9 +759,9 @@ __global__ void __launch_bounds__(256, mode_is_levels(MODE) ? tile_resident(MODE
                 }
             }
         }
+        if (emit) store_words(code, p.wbits);
         if (kWritesX && !keep_master) store(p.x, w);
         if (want16) store_half(p.x16, p.x16_f16 != 0u, w);
-        if (emit) store_words(code, p.wbits);
     }
 
     if (MODE != MODE_GRAD && !kLevels && p.n_saturated != nullptr) {

@@ -99,6 +99,46 @@ inline TilePlan choose_tile(int bucket, uint64_t num_buckets, uint64_t tensors, 
     return waves < 4096 && waves < most_waves ? small : full;
 }
 
+// What a mode is bound by in a full tile.
+enum TileWork {
+    TILE_MEMORY,        // the steps, the weight encoder
+    TILE_INSTRUCTIONS,  // gradient encoder, code-resident step, receive side
+    TILE_ADAMW,         // long chains of divisions: more waves in flight for longer
+};
+
+// ... for a call of middling size: two rows of a team of four, all buckets that fit (buckets of at most 2048).
+inline TilePlan tile_plan_half(int bucket) { return tile_plan_for(bucket, 4, 2); }
+
+// The tile of a call without learned levels. Between the two plans above lies a range in which the small tile would be
+// too many half-empty waves and the full one too few waves: from one to six waves of the half tile to a SIMD, or
+// twelve with AdamW. Measured (us, the plan of choose_tile / half; buckets of 96, 416, 544, 1504): step, 2^19 elements
+// 7.2 / 6.6, 6.9 / 6.6, 8.2 / 6.9, 7.5 / 7.2, 2^20 9.1 / 7.5, 8.1 / 7.7, 9.6 / 8.4, 8.3 / 8.2, 2^21 10.5 / 9.6, 10.6 /
+// 9.3, 11.4 / 10.5, 12.1 / 10.8, 2^22 13.4 / 14.3, 13.6 / 15.1, 14.1 / 16.1, 14.3 / 16.2; AdamW step, 2^20 15.8 / 11.8,
+// 12.5 / 11.8, 16.9 / 12.9, 13.1 / 12.9, 2^22 27.3 / 25.7, 27.3 / 26.6, 28.1 / 27.6, 28.0 / 28.2. Below, at 2^16, the
+// small tile is 0-6 % faster (eight peers with AdamW 9.2 against 11.1).
+// The modes that instructions bind share what a tile costs among six rows rather than four where these are as full
+// (2^25 elements, buckets of 96, 416, 544: gradient encoder 31.8 / 28.7, 31.6 / 29.8, 31.6 / 29.5, code-resident step
+// 55.0 / 49.3, 55.4 / 49.5, 54.7 / 48.6; steps bound by memory 74.0 / 75.1, 74.3 / 75.4, 76.1 / 75.5), from four waves
+// of theirs to a SIMD on (2^22, bucket 160: gradient encoder from 16 bits 8.7 / 9.2, code-resident step, 5 bits, 13.5 /
+// 14.4).
+inline TilePlan choose_step_tile(int bucket, uint64_t num_buckets, uint64_t most_waves, TileWork work) {
+    if (bucket <= 32 * tile_groups(4, 2)) {
+        const TilePlan half = tile_plan_half(bucket);
+        const uint64_t waves = (num_buckets + (uint64_t)half.buckets - 1) / (uint64_t)half.buckets * 4;
+        if (waves >= 1024 && waves < (work == TILE_ADAMW ? 12288u : 6144u) && waves < most_waves) return half;
+    }
+    const TilePlan t = choose_tile(bucket, num_buckets, 0, most_waves), full = tile_plan(bucket);
+    if (work == TILE_INSTRUCTIONS && t.rows == full.rows && t.waves == full.waves && t.buckets == full.buckets &&
+        t.rows == 4) {
+        const TilePlan six = tile_plan_for(bucket, 4, 6);
+        const uint64_t waves = (num_buckets + (uint64_t)six.buckets - 1) / (uint64_t)six.buckets * 4;
+        // as full: buckets a row, six rows against four
+        const bool as_full = 100 * six.buckets * tile_groups(full.waves, 4) >= 95 * full.buckets * tile_groups(4, 6);
+        if (as_full && waves >= 4096) return six;
+    }
+    return t;
+}
+
 // Workgroups of a learned-level encoder that a compute unit holds at once: by registers (the kernels' launch bounds ask
 // for as many) and, for teams of one wave with their tables for each, by LDS. Against five for every shape (us, 4 bit
 // coin flip): 134M values in buckets of 608 188 -> 169, 33M in buckets of 2080 93 -> 77.

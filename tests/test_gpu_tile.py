@@ -125,3 +125,32 @@ def test_more_tiles_than_a_small_call_has(B):
     xd = _dev(x)
     qb.qsdp_fused_step(xd, _dev(g), 1e-2, 8, 4, B, 0.0, 9)
     assert bits_equal(np_f32(xd), ref.fused_step(x, g, 1e-2, 8, 4, B, 0.0, 9)[0])
+
+
+@pytest.mark.parametrize("B", [32, 96, 416, 544, 1024 + 480, 2016])
+def test_tiles_of_middling_and_large_calls(B):
+    """Sizes at which a call takes tiles of two rows of four waves, and of six rows in the modes that instructions bind
+    (test_tile_plan_of_a_call says which)."""
+    for buckets, cut in (((1 << 19) // B, 5), ((7 << 20) // B + 7, 31)):
+        n = buckets * B - cut
+        x, g = synth(n, B)
+        c, m = qb.alloc_packed(n, 3, B, DEV)
+        qb.qsdp_quantize_grad(_dev(g), 3, B, 5, 24, c, m.view(-1))
+        gc, gm = ref.quantize_grad(g, 3, B, 5, index_offset=24)
+        assert np.array_equal(np_u32(c), gc) and np.array_equal(np_u32(m), gm.view(np.uint32).reshape(-1))
+        for wbits, delta in ((8, 0.0), (5, 2.0 ** -8)):
+            xd = _dev(x)
+            c, m = qb.alloc_packed(n, wbits, B, DEV)
+            qb.qsdp_quantize_weight(xd, wbits, B, delta, 9, c, m.view(-1))
+            wc, wm, _ = ref.quantize_weight(x, wbits, B, delta, 9)
+            assert np.array_equal(np_u32(c), wc) and np.array_equal(np_u32(m), wm.view(np.uint32).reshape(-1))
+            qb.qsdp_fused_step_codes(c, m.view(-1), _dev(g), 1e-2, wbits, 4, B, delta, 10)
+            wc, wm, _ = ref.fused_step_codes(wc, wm, g, 1e-2, wbits, 4, B, delta, 10)
+            assert np.array_equal(np_u32(c), wc) and np.array_equal(np_u32(m), wm.view(np.uint32).reshape(-1))
+        rows = torch.zeros((1, -(-gc.size // 4) * 4), dtype=torch.int32, device=DEV)  # 16-byte rows
+        rows[0, :gc.size] = _dev(gc.view(np.int32))
+        floats = torch.zeros((1, -(-gm.size // 4) * 4), dtype=torch.float32, device=DEV)
+        floats[0, :gm.size] = _dev(gm.reshape(-1))
+        qb.qsdp_recv_step(xd, rows, floats, 1, 0.5, 1e-2, 8, 3, B, 0.0, 11)
+        want = ref.recv_step(x, gc[None], gm.reshape(1, -1), 1, 0.5, 1e-2, 8, 3, B, 0.0, 11)[0]
+        assert bits_equal(np_f32(xd), want)

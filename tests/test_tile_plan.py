@@ -73,3 +73,39 @@ def test_every_bucket_size_has_an_exact_plan(tmp_path):
         bad, *shapes = run.stdout.split()
         assert run.returncode == 0 and bad == "0"
         assert set(shapes) == {f"{w},{r}" for w, r in lib_build.TILE_SHAPES}
+
+
+CALL_SOURCE = r"""
+#include "qsdp_tile_plan.hpp"
+#include <cstdio>
+using namespace qsdp;
+int main() {
+    int bad = 0, half = 0, six = 0;
+    for (int k = 1; k <= 256; ++k)
+        for (int work = 0; work < 3; ++work)
+            for (uint64_t nb = 1; nb * k < (1u << 20); nb = nb * 5 / 4 + 1) {
+                const TilePlan t = choose_step_tile(32 * k, nb, ~0ull, (TileWork)work), f = tile_plan(32 * k);
+                const int groups = tile_groups(t.waves, t.rows);
+                if (t.buckets < 1 || t.buckets * k > groups || (t.buckets << t.lanes_log2) > 64 * t.waves) ++bad;
+                for (int i = 0; i < groups; ++i)
+                    if ((int)((uint32_t)i * t.group_magic >> 16) != i / k) ++bad;
+                if (t.waves == 4 && t.rows == 2 && t.buckets == groups / k) ++half;
+                if (work == TILE_INSTRUCTIONS && f.rows == 4 && t.rows == 6 && t.waves == 4) ++six;
+                // few workgroups: the tiles of large calls
+                const TilePlan c = choose_step_tile(32 * k, 1000000, 8, (TileWork)work);
+                if (work != TILE_INSTRUCTIONS && (c.rows != f.rows || c.waves != f.waves)) ++bad;
+            }
+    std::printf("%d %d", half, six);
+    return bad != 0;
+}
+"""
+
+
+def test_tile_plan_of_a_call(tmp_path):
+    """Every tile of a call is a valid plan, and calls of the sizes in test_gpu_tile.py see the two that only they take."""
+    src, exe = tmp_path / "call.cpp", tmp_path / "call"
+    src.write_text(CALL_SOURCE)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", lib_build.CSRC, str(src), "-o", str(exe)], check=True)
+    run = subprocess.run([str(exe)], capture_output=True, text=True)
+    half, six = map(int, run.stdout.split())
+    assert run.returncode == 0 and half > 100 and six > 100
