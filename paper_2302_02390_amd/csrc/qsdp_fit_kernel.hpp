@@ -299,9 +299,9 @@ __device__ __forceinline__ void fit_batch(const Slot& slot, int m, Powers& power
                                           FitCells cells, float (&lv)[FitLanes<BITS>::M], float* lv_shared,
                                           uint64_t* acc, int lane) {
     constexpr int K = FitLanes<BITS>::K, S = FitLanes<BITS>::S, M = FitLanes<BITS>::M;
-    // Values a lane reads at once, one after the other in the slot: one address, no question of range (below), half the
-    // instructions of a read, test and sum for each on its own (6 bits 0.66 -> 0.59 us per batch of 1024, 5 bits 0.43 ->
-    // 0.40 per batch of 128). Eight of them where two lanes share a level are slower (0.46).
+    // Values a lane reads at once, one after the other in the slot: one address, no question of range (below), half
+    // the instructions of a read, test and sum for each on its own (6 bits 0.66 -> 0.59 us per batch of 1024, 5 bits
+    // 0.43 -> 0.40 per batch of 128). Eight of them where two lanes share a level are slower (0.46).
     constexpr int U = M == 4 ? 2 : 4;
     static_assert(S * U <= kFitSpare, "reads past the last value");
     // values in a boundary's cells from which the plain assignment of the batch is faster

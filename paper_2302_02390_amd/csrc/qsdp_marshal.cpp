@@ -1,7 +1,7 @@
 // Argument marshalling of the Python binding in native code: a CPython module beside libqsdp.so that turns tensors and
-// numbers into a call of the C ABI. A call over a few 100,000 elements is bound by what happens on the host. In a loop,
-// with the checks and the conversions in Python and ctypes / here: fused step over 2^16 parameters 7.5 / 5.3 us, encoder
-// 7.9 / 4.7, decoder 7.8 / 4.5, receive side 12.1 / 6.6; about 2.7 us of each is the launch.
+// numbers into a call of the C ABI. A call over a few 100,000 elements is bound by what happens on the host. In a
+// loop, with the checks and the conversions in Python and ctypes / here: fused step over 2^16 parameters 7.5 / 5.3 us,
+// encoder 7.9 / 4.7, decoder 7.8 / 4.5, receive side 12.1 / 6.6; about 2.7 us of each is the launch.
 //
 // Only what is common is done here: plain tensors, arguments of the expected kinds, the tensor's device the current
 // one. For anything else the caller's Python function of the same purpose is called with the same arguments, and its

@@ -16,10 +16,10 @@
 // wave's idle rows by branches cost the full tiles 3-10 % (the rows no longer overlap) and won 4 % at the worst fill,
 // so it is not done there.
 //
-// A question that is the same for all rows (whether the tile is contiguous, which grid, eight bits or not) is asked once
-// around them: asked in every row or element, as it was, each row was a block of its own that waited for itself.
-// us, before / after: eight peers with AdamW 2^26 elements in buckets of 160 / 1504 414 / 371, 454 / 423, four peers 156
-// / 140, 162 / 139, gradient encoder 4 bits, 160, 66.7 / 62.3, code-resident step 1504 / 3040 99 / 96, 106 / 92.
+// A question that is the same for all rows (whether the tile is contiguous, which grid, eight bits or not) is asked
+// once around them: asked in every row or element, as it was, each row was a block of its own that waited for itself.
+// us, before / after: eight peers with AdamW 2^26 elements in buckets of 160 / 1504 414 / 371, 454 / 423, four peers
+// 156 / 140, 162 / 139, gradient encoder 4 bits, 160, 66.7 / 62.3, code-resident step 1504 / 3040 99 / 96, 106 / 92.
 #pragma once
 
 #include "qsdp_params.hpp"
@@ -411,7 +411,8 @@ __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
 #pragma unroll
             for (int r = 0; r < R; ++r)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) c[r][i] = (float)__builtin_amdgcn_ubfe(q[r], (uint32_t)(i * bits), (uint32_t)bits);
+                for (int i = 0; i < 4; ++i)
+                    c[r][i] = (float)__builtin_amdgcn_ubfe(q[r], (uint32_t)(i * bits), (uint32_t)bits);
         };
         // The reverse: pack the codes and write the tile's part of the code stream. Slots past a short bucket's end
         // carry zeros.
@@ -486,8 +487,9 @@ __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
             });
             uint32_t code[MODE == MODE_GRAD ? R : 1][4] = {};
             auto grid_of_row = [&](int r) -> f4 { return lds.grid[bucket_of_slot(slot_of(r))]; };
-            // The question outside the rows, so that these are straight-line code (gradient encoder, 2^26 elements from
-            // bf16, 3 bits, buckets of 160: 68.7 -> 65.7 us). The steps on resident weights ask it for every element: with the rows of their divisions side by side AdamW's take 40 more registers (2^26 elements,
+            // The question outside the rows, so that these are straight-line code (gradient encoder, 2^26 elements
+            // from bf16, 3 bits, buckets of 160: 68.7 -> 65.7 us). The steps on resident weights ask it for every
+            // element: with the rows of their divisions side by side AdamW's take 40 more registers (2^26 elements,
             // buckets of 1504, 333 against 351 us), and the plain step is bound by memory and 1-2 % slower.
             constexpr bool kAskInside = MODE == MODE_FUSED || mode_local_adamw(MODE);
             if (!kAskInside && grad_shift) {
@@ -500,7 +502,8 @@ __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
                     for (int i = 0; i < 4; ++i) {
                         const float c = weight_code_minmax(gv[r][i], grid, Lg, shifts.xi_g);
                         if constexpr (MODE == MODE_GRAD) code[r][i] = (uint32_t)c;
-                        else w[r][i] = step_value<MODE>(p, w[r][i], fmaf(c, grid.scale, gr[3]), mom[r][i], var[r][i]);
+                        else
+                            w[r][i] = step_value<MODE>(p, w[r][i], fmaf(c, grid.scale, gr[3]), mom[r][i], var[r][i]);
                     }
                 }
             } else {
