@@ -286,7 +286,7 @@ __global__ void __launch_bounds__(256, kLevelsResident) levels_kernel(const Para
         float next[R][4];
         if (q0 < nunits) {
             const UnitTile t = unit_tile(q0);
-            load_rows<G, R>(p.xin + t.e0, l, t.m, t.partial, next);
+            load_rows<G, R, false>(p.xin + t.e0, l, t.m, t.partial, next);
         }
         // tables of the piece
         const float* table = p.levels + (per_tensor ? (uint64_t)tensor * K : 0u);
@@ -336,10 +336,10 @@ __global__ void __launch_bounds__(256, kLevelsResident) levels_kernel(const Para
                 for (int i = 0; i < 4; ++i) v[r][i] = next[r][i];
             if (q + q_step < nunits) {
                 const UnitTile t = unit_tile(q + q_step);
-                load_rows<G, R>(p.xin + t.e0, l, t.m, t.partial, next);
+                load_rows<G, R, false>(p.xin + t.e0, l, t.m, t.partial, next);
             }
             float lo, hi;
-            rows_minmax<G, R>(v, l, tile.m, tile.partial, lo, hi);
+            rows_minmax<G, R, false>(v, l, tile.m, tile.partial, lo, hi);
             block_combine_minmax<W>(lo, hi, red_all + (W > 1 ? parity * 2 * W : 0), wave);
             const MinMaxGrid grid = make_minmax_grid(lo, hi, 1.0f, false);  // scale = hi - lo, inv = 1/(hi - lo)
             // normalised value in cell units: (v - lo) * inv_cells
@@ -356,7 +356,7 @@ __global__ void __launch_bounds__(256, kLevelsResident) levels_kernel(const Para
             else if (method == LEVELS_BY_CELL_JUMPS) encode(std::integral_constant<int, LEVELS_BY_CELL_JUMPS>{});
             else if (kCoin || method == LEVELS_BY_SEARCH) encode(std::integral_constant<int, LEVELS_BY_SEARCH>{});
             else encode(std::integral_constant<int, LEVELS_PLAIN>{});
-            if (__builtin_expect(tile.partial, 0)) zero_slots_past_end<G, R>(code, l, tile.m);
+            if (__builtin_expect(tile.partial, 0)) zero_slots_past_end<G, R, false>(code, l, tile.m);
             store_codes<G, R, BITS>(stage, tile_out, lane, active_buckets, code);
             if (tile.active && l == 0 && (W == 1 || wave == 0)) {
                 p.meta[2 * tile.bucket] = grid.lo;
