@@ -98,7 +98,8 @@ EXPORTS = tuple(_SIGNATURES)
 
 _lib = None
 _lib_lock = threading.Lock()
-# The functions of this file that lib() replaces by native ones of the same name, which call them for the uncommon cases.
+# The functions of this file that lib() replaces by native ones of the same name, where these are built for the running
+# torch. The native ones call them for the uncommon cases.
 _IN_PYTHON = dict.fromkeys(("_is", "_is_rows", "_packed_ok", "_rows_ok", "_step_outputs", "_launch"))
 
 
@@ -126,16 +127,27 @@ def _load():
         fn = getattr(L, name)
         fn.restype = restype
         fn.argtypes = argtypes
-    # From here on in native code (csrc/qsdp_marshal.cpp), with the functions of this file for whatever that does not
-    # take: a call costs about 2.5 us less of host time.
-    from . import _marshal
     own = globals()
     for name in _IN_PYTHON:
         _IN_PYTHON[name] = own[name]
-    _marshal.attach(own, *_IN_PYTHON.values())
-    for name in _IN_PYTHON:
-        own[name] = getattr(_marshal, name[1:])
+    native = _native_marshalling()
+    if native is not None:
+        native.attach(own, *_IN_PYTHON.values())
+        for name in _IN_PYTHON:
+            own[name] = getattr(native, name[1:])
     return L
+
+
+def _native_marshalling():
+    """The module of csrc/qsdp_marshal.cpp, which takes about 2.5 us of host time off a call, or None if it is not built
+    or was compiled against another torch: it reads tensors through torch's C++ headers, and the functions of this file
+    do the same without."""
+    try:
+        from . import _marshal
+    except ImportError:
+        return None
+    built_for = getattr(_marshal, "torch_version", None)
+    return _marshal if built_for == f"{torch.__version__} {torch.version.git_version}" else None
 
 
 def status_string(status):

@@ -9,9 +9,11 @@ vector: quantize_grad 0.97 ms with the flag, 1.05 ms without; the code-resident 
 1.55 ms). The flag changes no result for finite inputs. Packed-fp32 instruction selection is
 switched off.
 """
+import glob
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -20,7 +22,8 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libqsdp.so")
 BENCH_LIB = os.path.join(HERE, "libqsdp_bench.so")  # streaming kernels for bench.py, not part of the codec
 
-MARSHAL = os.path.join(HERE, "_marshal.so")  # the binding's argument marshalling
+# The binding's argument marshalling: a Python extension module, so its name says which interpreter it is for.
+MARSHAL = os.path.join(HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
@@ -78,13 +81,15 @@ def build(jobs=None, verbose=False):
 
 
 def build_marshal(verbose=False):
-    """_marshal.so: the binding's argument marshalling (csrc/qsdp_marshal.cpp, host code against torch's headers)."""
-    import sysconfig
+    """The binding's argument marshalling (csrc/qsdp_marshal.cpp, host code against torch's headers)."""
+    for old in glob.glob(os.path.join(HERE, "_marshal*.so")):  # nothing stale is left if what follows fails
+        os.remove(old)
     import torch
     from torch.utils import cpp_extension
     includes = [sysconfig.get_paths()["include"]] + cpp_extension.include_paths("cuda")
     cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden", "-Wall", "-D__HIP_PLATFORM_AMD__",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f'-DQSDP_TORCH_VERSION="{torch.__version__} {torch.version.git_version}"']
     for d in includes:
         cmd += ["-isystem", d]
     cmd += [os.path.join(CSRC, "qsdp_marshal.cpp"), "-o", MARSHAL, "-L", HERE, "-lqsdp"]

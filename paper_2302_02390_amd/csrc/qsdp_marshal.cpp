@@ -281,5 +281,11 @@ PyMODINIT_FUNC PyInit__marshal(void) {
         entry_names[i] = PyUnicode_InternFromString(entries[i].name);
         if (entry_names[i] == nullptr) return nullptr;
     }
-    return PyModule_Create(&module_def);
+    PyObject* module = PyModule_Create(&module_def);
+    // The layouts compiled in are those of this torch; the binding compares before it uses anything else.
+    if (module != nullptr && PyModule_AddStringConstant(module, "torch_version", QSDP_TORCH_VERSION) != 0) {
+        Py_DECREF(module);
+        return nullptr;
+    }
+    return module;
 }

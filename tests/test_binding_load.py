@@ -1,0 +1,48 @@
+"""The binding with and without its native argument marshalling: the library loads and answers either way (no GPU)."""
+import os
+import shutil
+import subprocess
+import sys
+import sysconfig
+
+import pytest
+
+from paper_2302_02390_amd import binding as qb
+from paper_2302_02390_amd import build as lib_build
+
+SUFFIX = sysconfig.get_config_var("EXT_SUFFIX")
+# another torch's module: whoever attaches it has not looked at its version
+OTHER_TORCH = "torch_version = '0.0.0 elsewhere'\ndef attach(*args):\n    raise AssertionError('attached')\n"
+PROGRAM = """
+from paper_2302_02390_amd import binding as qb
+assert qb.spec_version() == 3 and qb.codes_bytes(1025, 4, 1024) == 1024 and qb.meta_bytes(1025, 1024) == 16
+assert qb.status_string(-1) == "invalid argument"
+assert all(getattr(qb, name) is f and f.__module__ == qb.__name__ for name, f in qb._IN_PYTHON.items())
+try:
+    import torch
+    qb.qsdp_quantize_grad(torch.zeros(64), 4, 32, 1, 0, None, None)
+except TypeError as e:
+    assert "contiguous" in str(e)
+else:
+    raise AssertionError("a tensor on the CPU was accepted")
+"""
+
+
+def test_the_built_tree_uses_the_native_functions():
+    qb.lib()
+    assert os.path.exists(lib_build.MARSHAL) and lib_build.MARSHAL.endswith(SUFFIX)
+    assert all(getattr(qb, name) is not f for name, f in qb._IN_PYTHON.items())
+
+
+@pytest.mark.parametrize("module", [None, ("_marshal" + SUFFIX, b"no shared object"),
+                                    ("_marshal.py", OTHER_TORCH.encode()), ("_marshal.py", b"")])
+def test_a_library_without_a_module_for_this_torch(tmp_path, module):
+    package = tmp_path / "paper_2302_02390_amd"
+    package.mkdir()
+    for name in ("__init__.py", "binding.py"):
+        shutil.copy(os.path.join(lib_build.HERE, name), package)
+    os.symlink(os.path.join(lib_build.HERE, "libqsdp.so"), package / "libqsdp.so")
+    if module is not None:
+        (package / module[0]).write_bytes(module[1])
+    run = subprocess.run([sys.executable, "-c", PROGRAM], cwd=tmp_path, capture_output=True, text=True)
+    assert run.returncode == 0, run.stderr
