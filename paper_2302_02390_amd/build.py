@@ -75,14 +75,18 @@ def build(jobs=None, verbose=False):
         raise RuntimeError(f"{' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
     if verbose:
         print(LIB)
-    build_marshal(verbose)
+    try:
+        build_marshal(verbose)
+    except (ImportError, OSError, RuntimeError) as e:  # no torch, no g++, no headers, or others than it was written for
+        print(f"the binding's argument marshalling is not built, its Python functions do that work: {e}", file=sys.stderr)
     build_bench_support(verbose)
     return LIB
 
 
 def build_marshal(verbose=False):
-    """The binding's argument marshalling (csrc/qsdp_marshal.cpp, host code against torch's headers)."""
-    for old in glob.glob(os.path.join(HERE, "_marshal*.so")):  # nothing stale is left if what follows fails
+    """The binding's argument marshalling (csrc/qsdp_marshal.cpp, host code against torch's headers). The library and
+    programs in C need neither it nor torch."""
+    for old in glob.glob(os.path.join(HERE, "_marshal*.so")):  # none of another library or torch stays behind
         os.remove(old)
     import torch
     from torch.utils import cpp_extension

@@ -46,3 +46,26 @@ def test_a_library_without_a_module_for_this_torch(tmp_path, module):
         (package / module[0]).write_bytes(module[1])
     run = subprocess.run([sys.executable, "-c", PROGRAM], cwd=tmp_path, capture_output=True, text=True)
     assert run.returncode == 0, run.stderr
+
+
+@pytest.mark.parametrize("why", ["torch", "compiler", "headers"])
+def test_a_build_without_what_the_module_needs(tmp_path, monkeypatch, capsys, why):
+    """The library and the bench's kernels are built all the same, and no module of an earlier build stays."""
+    commands = []
+
+    def run(cmd, **kwargs):
+        if cmd[0] == "g++" and why == "compiler":
+            raise FileNotFoundError("g++")
+        commands.append(cmd)
+        return subprocess.CompletedProcess(cmd, int(cmd[0] == "g++" and why == "headers"), "", "Python.h: no such file")
+
+    for name, value in (("HERE", str(tmp_path)), ("OBJ", str(tmp_path / "ob")), ("LIB", str(tmp_path / "libqsdp.so")),
+                        ("MARSHAL", str(tmp_path / ("_marshal" + SUFFIX))), ("_compile", lambda unit: unit[0])):
+        monkeypatch.setattr(lib_build, name, value)
+    monkeypatch.setattr(lib_build.subprocess, "run", run)
+    if why == "torch":
+        monkeypatch.setitem(sys.modules, "torch", None)
+    (tmp_path / ("_marshal" + SUFFIX)).write_bytes(b"")
+    assert lib_build.build() == str(tmp_path / "libqsdp.so")
+    assert any(lib_build.BENCH_LIB in c for c in commands) and not list(tmp_path.glob("_marshal*"))
+    assert "not built" in capsys.readouterr().err
