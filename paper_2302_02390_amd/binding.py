@@ -95,6 +95,8 @@ _SIGNATURES = {
     "qsdp_dequantize_levels_segmented": (_i32, [_vp, _vp, _vp, _u32, _u64, _i32, _i32, _vp, _i32, _vp, _vp]),
 }
 EXPORTS = tuple(_SIGNATURES)
+# Where the entry points take pointers, the stream left out.
+_POINTERS = {name: tuple(i for i, kind in enumerate(kinds[:-1]) if kind is _vp) for name, (_, kinds) in _SIGNATURES.items()}
 
 _lib = None
 _lib_lock = threading.Lock()
@@ -166,10 +168,6 @@ def meta_bytes(n, bucket):
     return int(lib().qsdp_meta_bytes(int(n), int(bucket)))
 
 
-def _ptr(t):
-    return None if t is None else t.data_ptr()
-
-
 def _stream_handle(device):
     return torch.cuda.current_stream(device).cuda_stream
 
@@ -187,11 +185,20 @@ def _launch(t, name, *args):
     """Calls entry point `name` with the current stream of t's device as its last argument, t's device being the
     current one meanwhile; a tensor in the place of a pointer stands for its address. This is the general form; plain
     tensors on the current device go through csrc/qsdp_marshal.cpp."""
+    args = list(args)
+    for i in _POINTERS[name][:len(args)]:
+        a = args[i]
+        if a is not None:
+            address = getattr(a, "data_ptr", None)
+            if address is not None:
+                args[i] = address()
+    _call(t, name, *args)
+
+
+def _call(t, name, *args):
+    """_launch with addresses in the place of tensors."""
     device = t.get_device()
     stream = _raw_stream(device)
-    kinds = _SIGNATURES[name][1]
-    args = [a.data_ptr() if hasattr(a, "data_ptr") and i < len(kinds) and kinds[i] is _vp else a
-            for i, a in enumerate(args)]
     if device == torch.cuda.current_device():
         status = getattr(_lib or lib(), name)(*args, stream)
     else:
@@ -819,8 +826,8 @@ def _step_opts(entry, x, g, lr, wbits, gbits, bucket, delta, seed, index_offset,
         _is(m, torch.float32); _is(v, torch.float32)
         _need(m, n, "m"); _need(v, n, "v")
         o.m, o.v = m.data_ptr(), v.data_ptr()
-    _launch(x, entry, x, g, 0 if segs is not None else n, lr, wbits, gbits, bucket, delta, seed,
-            index_offset, C.byref(o))
+    _call(x, entry, x.data_ptr(), g.data_ptr(), 0 if segs is not None else n, lr, wbits, gbits, bucket, delta, seed,
+          index_offset, C.byref(o))
 
 
 def qsdp_fused_step_opts(x, g, lr, wbits, gbits, bucket, delta, seed, index_offset=0, flags=0, segs=None, x16=None,

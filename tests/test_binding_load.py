@@ -69,3 +69,41 @@ def test_a_build_without_what_the_module_needs(tmp_path, monkeypatch, capsys, wh
     assert lib_build.build() == str(tmp_path / "libqsdp.so")
     assert any(lib_build.BENCH_LIB in c for c in commands) and not list(tmp_path.glob("_marshal*"))
     assert "not built" in capsys.readouterr().err
+
+
+class _Argument(int):
+    """A number that notices when it is asked for an address, and a tensor's stand-in that has one."""
+    asked = 0
+
+    @property
+    def data_ptr(self):
+        _Argument.asked += 1
+        raise AttributeError("data_ptr")
+
+
+class _OnDevice:
+    def __init__(self, address):
+        self.address = address
+
+    def data_ptr(self):
+        return self.address
+
+    def get_device(self):
+        return 0
+
+
+def test_the_general_launch_asks_pointers_alone_for_their_address(monkeypatch):
+    qb.lib()
+    calls = []
+    library = type("L", (), {name: staticmethod(lambda *args: calls.append(args) or 0) for name in qb.EXPORTS})
+    monkeypatch.setattr(qb, "_lib", library)
+    monkeypatch.setattr(qb, "_raw_stream", lambda device: 77)
+    monkeypatch.setattr(qb.torch.cuda, "current_device", lambda: 0)
+    for name, (_, kinds) in qb._SIGNATURES.items():
+        if kinds and kinds[-1] is qb._vp:
+            pointer = [kind is qb._vp for kind in kinds[:-1]]
+            for absent in (False, True):
+                args = [(None if absent else _OnDevice(i)) if p else _Argument(i) for i, p in enumerate(pointer)]
+                qb._IN_PYTHON["_launch"](_OnDevice(5), name, *args)
+                assert calls[-1] == tuple(None if p and absent else i for i, p in enumerate(pointer)) + (77,)
+    assert len(calls) > 70 and _Argument.asked == 0
