@@ -235,8 +235,9 @@ int run(int mode, Params p, int stored_bits, hipStream_t s) {
                                   ? TILE_INSTRUCTIONS
                                   : TILE_MEMORY;
         const uint64_t most_waves = 4 * (uint64_t)grid_cap();
-        const TilePlan t = mode_is_levels(mode) ? choose_tile(p.bucket, nb, tensors, most_waves)
-                                                : choose_step_tile(p.bucket, nb, most_waves, work);
+        const TilePlan t = mode_is_levels(mode)
+                               ? choose_tile(p.bucket, nb, tensors, most_waves)
+                               : choose_step_tile(p.bucket, nb, most_waves, work, p.segs != nullptr);
         const uint64_t units = ceil_div(nb, (uint64_t)t.buckets);
         uint64_t blocks = t.waves == 1 ? ceil_div(units, 4) : units;
         if (mode_is_levels(mode))

@@ -121,15 +121,24 @@ inline TilePlan tile_plan_half(int bucket) { return tile_plan_for(bucket, 4, 2);
 // 55.0 / 49.3, 55.4 / 49.5, 54.7 / 48.6; steps bound by memory 74.0 / 75.1, 74.3 / 75.4, 76.1 / 75.5), from four waves
 // of theirs to a SIMD on (2^22, bucket 160: gradient encoder from 16 bits 8.7 / 9.2, code-resident step, 5 bits, 13.5 /
 // 14.4).
-inline TilePlan choose_step_tile(int bucket, uint64_t num_buckets, uint64_t most_waves, TileWork work) {
+// A multi-tensor call takes neither unless its tiles hold fewer buckets than those of choose_tile: a tile that meets a
+// tensor's end is not contiguous and goes element by element, all of it, so small tensors make a larger tile slower
+// throughout, and large ones end such a call late (us, the plan of choose_tile / the larger tile: 2^19 elements in
+// tensors of one bucket of 32 / forty of 96, steps 9.1 / 13.4, 6.3 / 8.8, AdamW steps 12.0 / 16.5, 8.3 / 13.2; 2^23 in
+// buckets of 32, gradient encoder 35.0 / 49.2, code-resident step 41.5 / 84.8; 2^25 in tensors of forty buckets of 160,
+// the last one short, receive side 84 / 112). Two rows with 4 buckets of 416 in place of four with 9 are 1.1-1.8 times
+// faster at 2^21 elements, in tensors of 1 to 500 buckets.
+inline TilePlan choose_step_tile(int bucket, uint64_t num_buckets, uint64_t most_waves, TileWork work, bool tensors) {
+    const TilePlan t = choose_tile(bucket, num_buckets, 0, most_waves), full = tile_plan(bucket);
     if (bucket <= 32 * tile_groups(4, 2)) {
         const TilePlan half = tile_plan_half(bucket);
         const uint64_t waves = (num_buckets + (uint64_t)half.buckets - 1) / (uint64_t)half.buckets * 4;
-        if (waves >= 1024 && waves < (work == TILE_ADAMW ? 12288u : 6144u) && waves < most_waves) return half;
+        if (waves >= 1024 && waves < (work == TILE_ADAMW ? 12288u : 6144u) && waves < most_waves &&
+            (!tensors || half.buckets < t.buckets))
+            return half;
     }
-    const TilePlan t = choose_tile(bucket, num_buckets, 0, most_waves), full = tile_plan(bucket);
-    if (work == TILE_INSTRUCTIONS && t.rows == full.rows && t.waves == full.waves && t.buckets == full.buckets &&
-        t.rows == 4) {
+    if (work == TILE_INSTRUCTIONS && !tensors && t.rows == full.rows && t.waves == full.waves &&
+        t.buckets == full.buckets && t.rows == 4) {
         const TilePlan six = tile_plan_for(bucket, 4, 6);
         const uint64_t waves = (num_buckets + (uint64_t)six.buckets - 1) / (uint64_t)six.buckets * 4;
         // as full: buckets a row, six rows against four

@@ -84,7 +84,7 @@ int main() {
     for (int k = 1; k <= 256; ++k)
         for (int work = 0; work < 3; ++work)
             for (uint64_t nb = 1; nb * k < (1u << 20); nb = nb * 5 / 4 + 1) {
-                const TilePlan t = choose_step_tile(32 * k, nb, ~0ull, (TileWork)work), f = tile_plan(32 * k);
+                const TilePlan t = choose_step_tile(32 * k, nb, ~0ull, (TileWork)work, false), f = tile_plan(32 * k);
                 const int groups = tile_groups(t.waves, t.rows);
                 if (t.buckets < 1 || t.buckets * k > groups || (t.buckets << t.lanes_log2) > 64 * t.waves) ++bad;
                 for (int i = 0; i < groups; ++i)
@@ -92,7 +92,7 @@ int main() {
                 if (t.waves == 4 && t.rows == 2 && t.buckets == groups / k) ++half;
                 if (work == TILE_INSTRUCTIONS && f.rows == 4 && t.rows == 6 && t.waves == 4) ++six;
                 // few workgroups: the tiles of large calls
-                const TilePlan c = choose_step_tile(32 * k, 1000000, 8, (TileWork)work);
+                const TilePlan c = choose_step_tile(32 * k, 1000000, 8, (TileWork)work, false);
                 if (work != TILE_INSTRUCTIONS && (c.rows != f.rows || c.waves != f.waves)) ++bad;
             }
     std::printf("%d %d", half, six);
@@ -109,3 +109,33 @@ def test_tile_plan_of_a_call(tmp_path):
     run = subprocess.run([str(exe)], capture_output=True, text=True)
     half, six = map(int, run.stdout.split())
     assert run.returncode == 0 and half > 100 and six > 100
+
+
+TENSORS_SOURCE = r"""
+#include "qsdp_tile_plan.hpp"
+#include <cstdio>
+using namespace qsdp;
+int main() {
+    int bad = 0, fewer = 0;
+    for (int k = 1; k <= 256; ++k)
+        for (int work = 0; work < 3; ++work)
+            for (uint64_t nb = 1; nb * k < (1u << 21); nb = nb * 5 / 4 + 1) {
+                const TilePlan t = choose_step_tile(32 * k, nb, ~0ull, (TileWork)work, true);
+                const TilePlan plain = choose_tile(32 * k, nb, 0, ~0ull);
+                const bool same = t.waves == plain.waves && t.rows == plain.rows && t.buckets == plain.buckets;
+                if (!same && t.buckets >= plain.buckets) ++bad;
+                fewer += !same;
+            }
+    std::printf("%d", fewer);
+    return bad != 0;
+}
+"""
+
+
+def test_tile_plan_of_a_multi_tensor_call(tmp_path):
+    """Tiles that meet tensors' ends are slow: no call over tensors takes tiles of more buckets than the general rule."""
+    src, exe = tmp_path / "tensors.cpp", tmp_path / "tensors"
+    src.write_text(TENSORS_SOURCE)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", lib_build.CSRC, str(src), "-o", str(exe)], check=True)
+    run = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert run.returncode == 0 and int(run.stdout) > 100
