@@ -230,10 +230,9 @@ int run(int mode, Params p, int stored_bits, hipStream_t s) {
             blocks = level_blocks(mode, blocks, bpw > 0 ? 4 : p.bucket / 1024, kLevelsResident, tensors);
         if (wl(mode, stored_bits, p, capped_grid(blocks), s) != hipSuccess) return QSDP_ELAUNCH;
     } else {
-        const TileWork work = mode_is_adamw(mode) ? TILE_ADAMW
-                              : mode == MODE_GRAD || mode == MODE_FUSED_CODES || mode == MODE_RECV
-                                  ? TILE_INSTRUCTIONS
-                                  : TILE_MEMORY;
+        const TileWork work = mode_is_adamw(mode)                         ? TILE_ADAMW
+                              : mode == MODE_GRAD || mode == MODE_RECV ? TILE_INSTRUCTIONS
+                                                                       : TILE_MEMORY;
         const uint64_t most_waves = 4 * (uint64_t)grid_cap();
         const TilePlan t = mode_is_levels(mode)
                                ? choose_tile(p.bucket, nb, tensors, most_waves)

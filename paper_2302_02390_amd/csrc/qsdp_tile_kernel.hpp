@@ -19,7 +19,8 @@
 // A question that is the same for all rows (whether the tile is contiguous, which grid, eight bits or not) is asked
 // once around them: asked in every row or element, as it was, each row was a block of its own that waited for itself.
 // us, before / after: eight peers with AdamW 2^26 elements in buckets of 160 / 1504 414 / 371, 454 / 423, four peers
-// 156 / 140, 162 / 139, gradient encoder 4 bits, 160, 66.7 / 62.3, code-resident step 1504 / 3040 99 / 96, 106 / 92.
+// 156 / 140, 162 / 139, gradient encoder 4 bits, 160, 66.7 / 62.3. Side by side the rows take more registers, so where
+// that costs waves which the mode needs, the question stays inside (kAskInside, kAskGridInside, kRowByRow below).
 #pragma once
 
 #include "qsdp_params.hpp"
@@ -130,6 +131,11 @@ __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
     constexpr int TEAM = Lds::kTeam;
     constexpr bool kWritesX = MODE == MODE_FUSED || MODE == MODE_ADAMW || mode_is_recv(MODE);
     constexpr bool kLevels = mode_is_levels(MODE);
+    // Eight rows of the weight encoder one after the other: side by side they take 105 registers instead of 64, four
+    // waves to a SIMD instead of seven (us, 2^26 elements in buckets of 2080 / 7200: 4 bits 54.7 / 53.6 and side by
+    // side 60.4 / 58.1, on a lattice 59.4 / 55.8 and 70.7 / 66.1; 8 bits 58.5 / 58.3 and, packed by the converting
+    // instruction, 56.6 / 56.5, which does not make up for the others).
+    constexpr bool kRowByRow = MODE == MODE_WEIGHT && R == 8;
     __shared__ Lds lds_all[4 / W];
     constexpr bool kCoin = MODE == MODE_LEVELS_COIN;
     __shared__ char level_lds[kLevels ? 4 / W * sizeof(TileLevels<kCoin>) : 1] __attribute__((aligned(16)));
@@ -328,34 +334,48 @@ __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
         // lanes that combine that bucket, the result in lds.grid for all.
         auto bucket_grids = [&](const float (&v)[R][4], auto make) {
             float row_lo[R], row_hi[R];
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
+            auto range = [&](int r) {
                 row_lo[r] = fminf(fminf(v[r][0], v[r][1]), fminf(v[r][2], v[r][3]));
                 row_hi[r] = fmaxf(fmaxf(v[r][0], v[r][1]), fmaxf(v[r][2], v[r][3]));
-            }
-            if (__builtin_expect(!whole, 0)) {
+            };
+            auto range_of_existing = [&](int r) {
+                const int c = place(slot_of(r)).count;
+                row_lo[r] = __builtin_inff();
+                row_hi[r] = -__builtin_inff();
 #pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const int c = place(slot_of(r)).count;
-                    row_lo[r] = __builtin_inff();
-                    row_hi[r] = -__builtin_inff();
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        row_lo[r] = i < c ? fminf(row_lo[r], v[r][i]) : row_lo[r];
-                        row_hi[r] = i < c ? fmaxf(row_hi[r], v[r][i]) : row_hi[r];
-                    }
+                for (int i = 0; i < 4; ++i) {
+                    row_lo[r] = i < c ? fminf(row_lo[r], v[r][i]) : row_lo[r];
+                    row_hi[r] = i < c ? fmaxf(row_hi[r], v[r][i]) : row_hi[r];
                 }
-            }
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
+            };
+            auto over_group = [&](int r) {
                 row_lo[r] = group_min<8>(row_lo[r]);
                 row_hi[r] = group_max<8>(row_hi[r]);
-            }
-            if ((tid & 7) == 0) {
+            };
+            auto keep = [&](int r) {
+                const u2 e = {__float_as_uint(row_lo[r]), __float_as_uint(row_hi[r])};
+                lds.part[slot_of(r) >> 3] = e;
+            };
+            if constexpr (kRowByRow) {
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
-                    const u2 e = {__float_as_uint(row_lo[r]), __float_as_uint(row_hi[r])};
-                    lds.part[slot_of(r) >> 3] = e;
+                    range(r);
+                    if (__builtin_expect(!whole, 0)) range_of_existing(r);
+                    over_group(r);
+                    if ((tid & 7) == 0) keep(r);
+                }
+            } else {
+#pragma unroll
+                for (int r = 0; r < R; ++r) range(r);
+                if (__builtin_expect(!whole, 0)) {
+#pragma unroll
+                    for (int r = 0; r < R; ++r) range_of_existing(r);
+                }
+#pragma unroll
+                for (int r = 0; r < R; ++r) over_group(r);
+                if ((tid & 7) == 0) {
+#pragma unroll
+                    for (int r = 0; r < R; ++r) keep(r);
                 }
             }
             team_sync<W>();
@@ -490,8 +510,11 @@ __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
             // The question outside the rows, so that these are straight-line code (gradient encoder, 2^26 elements
             // from bf16, 3 bits, buckets of 160: 68.7 -> 65.7 us). The steps on resident weights ask it for every
             // element: with the rows of their divisions side by side AdamW's take 40 more registers (2^26 elements,
-            // buckets of 1504, 333 against 351 us), and the plain step is bound by memory and 1-2 % slower.
-            constexpr bool kAskInside = MODE == MODE_FUSED || mode_local_adamw(MODE);
+            // buckets of 1504, 333 against 351 us), the code-resident step's 20-30 (four rows: 92 for 73, five waves to
+            // a SIMD instead of six; us, 125M in buckets of 608 / 800 / 2080 / 3488, 8 bits 157 / 167 / 190 / 181
+            // against 164 / 182 / 208 / 194, 5 bits 176 / 186 / 226 / 208 against 189 / 202 / 242 / 225), and the plain
+            // step is bound by memory and 1-2 % slower.
+            constexpr bool kAskInside = MODE == MODE_FUSED || mode_codes_resident(MODE) || mode_local_adamw(MODE);
             if (!kAskInside && grad_shift) {
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
@@ -527,7 +550,8 @@ __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
                                 const float c = kAskInside && grad_shift
                                                     ? weight_code_minmax(gv[r][i], grid, Lg, shifts.xi_g)
                                                     : grad_code(gv[r][i], grid, top16_g, u);
-                                w[r][i] = step_value<MODE>(p, w[r][i], fmaf(c, grid.scale, gr[3]), mom[r][i], var[r][i]);
+                                w[r][i] =
+                                    step_value<MODE>(p, w[r][i], fmaf(c, grid.scale, gr[3]), mom[r][i], var[r][i]);
                             }
                         }
                     }
@@ -718,28 +742,39 @@ __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
             return f4{origin, inv, scale, base};
         });
         const bool want16 = (MODE == MODE_FUSED || MODE == MODE_ADAMW) && p.x16 != nullptr;
-        if (lattice) {
+        auto weight_grid = [&](int r) -> f4 { return lds.grid[bucket_of_slot(slot_of(r))]; };
+        auto onto_lattice = [&](int r) {
+            const f4 gr = weight_grid(r);
+            const int n = __builtin_expect(whole, 1) ? (slot_of(r) < used ? 4 : 0) : place(slot_of(r)).count;
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                if (!computed(r)) continue;
-                const f4 gr = lds.grid[bucket_of_slot(slot_of(r))];
-                const int n = __builtin_expect(whole, 1) ? (slot_of(r) < used ? 4 : 0) : place(slot_of(r)).count;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    uint32_t over = 0;
-                    const float c = weight_code_lattice(w[r][i], div, xi, gr[0], Lw, over);
-                    saturated += i < n ? over : 0u;
-                    code[r][i] = (uint32_t)c;
-                    w[r][i] = fmaf(c, gr[2], gr[3]);
-                }
+            for (int i = 0; i < 4; ++i) {
+                uint32_t over = 0;
+                const float c = weight_code_lattice(w[r][i], div, xi, gr[0], Lw, over);
+                saturated += i < n ? over : 0u;
+                code[r][i] = (uint32_t)c;
+                w[r][i] = fmaf(c, gr[2], gr[3]);
             }
-        } else if ((MODE == MODE_WEIGHT || mode_codes_resident(MODE)) && p.wbits == 8) {
+        };
+        auto onto_minmax = [&](int r) {
+            const f4 gr = weight_grid(r);
+            const MinMaxGrid grid = {gr[0], gr[2], gr[1]};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float c = weight_code_minmax(w[r][i], grid, Lw, xi);
+                code[r][i] = (uint32_t)c;
+                w[r][i] = fmaf(c, gr[2], gr[3]);
+            }
+        };
+        // Which grid is a question for every row in the weight encoder's large tiles, whose divisions by delta would
+        // cost waves side by side (4 bits, 2^26 elements in buckets of 288 / 1504, 54.9 / 54.1 against 57.9 / 56.6 us).
+        constexpr bool kAskGridInside = MODE == MODE_WEIGHT && R >= 6;
+        if (!kRowByRow && !lattice && (MODE == MODE_WEIGHT || mode_codes_resident(MODE)) && p.wbits == 8) {
             // only stored: the packing instruction rounds and clamps (see pack4)
             uint32_t q[R] = {};
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 if (!computed(r)) continue;
-                const f4 gr = lds.grid[bucket_of_slot(slot_of(r))];
+                const f4 gr = weight_grid(r);
                 const MinMaxGrid grid = {gr[0], gr[2], gr[1]};
                 float at[4];
 #pragma unroll
@@ -748,18 +783,17 @@ __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
             }
             store_packed(q, 8);
             continue;
+        }
+        if (!kAskGridInside && lattice) {
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (computed(r)) onto_lattice(r);
         } else {
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 if (!computed(r)) continue;
-                const f4 gr = lds.grid[bucket_of_slot(slot_of(r))];
-                const MinMaxGrid grid = {gr[0], gr[2], gr[1]};
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float c = weight_code_minmax(w[r][i], grid, Lw, xi);
-                    code[r][i] = (uint32_t)c;
-                    w[r][i] = fmaf(c, gr[2], gr[3]);
-                }
+                if (kAskGridInside && lattice) onto_lattice(r);
+                else onto_minmax(r);
             }
         }
         if (emit) store_words(code, p.wbits);

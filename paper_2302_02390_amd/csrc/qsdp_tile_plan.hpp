@@ -101,8 +101,8 @@ inline TilePlan choose_tile(int bucket, uint64_t num_buckets, uint64_t tensors, 
 
 // What a mode is bound by in a full tile.
 enum TileWork {
-    TILE_MEMORY,        // the steps, the weight encoder
-    TILE_INSTRUCTIONS,  // gradient encoder, code-resident step, receive side
+    TILE_MEMORY,        // the weight encoder, the steps; the code-resident one is bound by both
+    TILE_INSTRUCTIONS,  // gradient encoder, receive side
     TILE_ADAMW,         // long chains of divisions: more waves in flight for longer
 };
 
@@ -117,10 +117,10 @@ inline TilePlan tile_plan_half(int bucket) { return tile_plan_for(bucket, 4, 2);
 // 12.5 / 11.8, 16.9 / 12.9, 13.1 / 12.9, 2^22 27.3 / 25.7, 27.3 / 26.6, 28.1 / 27.6, 28.0 / 28.2. Below, at 2^16, the
 // small tile is 0-6 % faster (eight peers with AdamW 9.2 against 11.1).
 // The modes that instructions bind share what a tile costs among six rows rather than four where these are as full
-// (2^25 elements, buckets of 96, 416, 544: gradient encoder 31.8 / 28.7, 31.6 / 29.8, 31.6 / 29.5, code-resident step
-// 55.0 / 49.3, 55.4 / 49.5, 54.7 / 48.6; steps bound by memory 74.0 / 75.1, 74.3 / 75.4, 76.1 / 75.5), from four waves
-// of theirs to a SIMD on (2^22, bucket 160: gradient encoder from 16 bits 8.7 / 9.2, code-resident step, 5 bits, 13.5 /
-// 14.4).
+// (2^25 elements, buckets of 96, 416, 544: gradient encoder 31.8 / 28.7, 31.6 / 29.8, 31.6 / 29.5; steps bound by
+// memory 74.0 / 75.1, 74.3 / 75.4, 76.1 / 75.5), from four waves of theirs to a SIMD on (2^22, bucket 160, gradient
+// encoder from 16 bits 8.7 / 9.2). The code-resident step gains 3-5 % where codes are of 8 bits, and loses up to 8 % at
+// 5 bits (2^22.7 elements, buckets of 416, 544).
 // A multi-tensor call takes neither unless its tiles hold fewer buckets than those of choose_tile: a tile that meets a
 // tensor's end is not contiguous and goes element by element, all of it, so small tensors make a larger tile slower
 // throughout, and large ones end such a call late (us, the plan of choose_tile / the larger tile: 2^19 elements in
