@@ -13,13 +13,10 @@ namespace {
 
 template <int MODE>
 hipError_t go(const Params& p, const TileArgs& a, unsigned grid, hipStream_t s) {
-    // Six rows of two fp32 operands in, weights and codes out: three workgroups to a compute unit stream faster than
-    // the four that its registers allow, where the vector is large (us, four / three: 125M in buckets of 768 270 /
-    // 264, of 3040 273 / 266, 300M in buckets of 768 668 / 634; 30M in buckets of 768 68 / 71; without codes 125M 241
-    // / 245).
-    const bool capped = MODE == MODE_FUSED && QSDP_TILE_R == 6 && p.codes != nullptr && p.g_half == 0u &&
-                        p.num_buckets * (uint64_t)p.bucket >= (1ull << 26);
-    const unsigned unused_lds = capped ? 32000u : 0u;
+    const bool three = MODE == MODE_FUSED &&
+                       three_workgroups_stream(p.bucket, a.buckets, QSDP_TILE_W, QSDP_TILE_R, p.n, p.segs != nullptr,
+                                               p.g_half != 0u, p.codes != nullptr ? p.wbits : 0, p.delta > 0.0f);
+    const unsigned unused_lds = three ? 32000u : 0u;
     hipLaunchKernelGGL((tile_kernel<MODE, QSDP_TILE_R, QSDP_TILE_W>), dim3(grid), dim3(256), unused_lds, s, p,
                        p.segs, a);
     return hipGetLastError();

@@ -139,3 +139,33 @@ def test_tile_plan_of_a_multi_tensor_call(tmp_path):
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", lib_build.CSRC, str(src), "-o", str(exe)], check=True)
     run = subprocess.run([str(exe)], capture_output=True, text=True)
     assert run.returncode == 0 and int(run.stdout) > 100
+
+
+STREAM_SOURCE = r"""
+#include "qsdp_tile_plan.hpp"
+#include <initializer_list>
+using namespace qsdp;
+static bool three(int bucket, uint64_t n, bool tensors = false, bool half = false, int bits = 8, bool lattice = false) {
+    const TilePlan t = tile_plan(bucket);
+    return three_workgroups_stream(bucket, t.buckets, t.waves, t.rows, n, tensors, half, bits, lattice);
+}
+int main() {
+    const uint64_t large = 3ull << 25;
+    int bad = 0;
+    for (int bucket : {384, 608, 768, 864, 1536, 3040, 6048, 6144}) {
+        bad += !three(bucket, large) + three(bucket, large - 1) + three(bucket, large, true);
+        bad += three(bucket, large, false, true) + three(bucket, large, false, false, 0);
+        bad += three(bucket, large, false, false, 4) + three(bucket, large, false, false, 8, true);
+    }
+    for (int bucket : {32, 160, 224, 288, 704, 736, 800, 1472, 2016, 2080, 4128, 4992, 8192}) bad += three(bucket, large);
+    return bad != 0;
+}
+"""
+
+
+def test_large_steps_in_full_tiles_run_three_workgroups(tmp_path):
+    """... and no others: not over tensors, in tiles that are less full, on smaller vectors or with other outputs."""
+    src, exe = tmp_path / "stream.cpp", tmp_path / "stream"
+    src.write_text(STREAM_SOURCE)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", lib_build.CSRC, str(src), "-o", str(exe)], check=True)
+    assert subprocess.run([str(exe)]).returncode == 0
