@@ -11,20 +11,29 @@
 
 namespace qsdp {
 
+namespace {
+
+template <int BITS>
+hipError_t go(const FitParams& p, unsigned grid, hipStream_t s) {
+    hipLaunchKernelGGL((fit_levels_kernel<BITS, QSDP_FIT_V, QSDP_FIT_W>), dim3(grid),
+                       dim3(FitShape<BITS, QSDP_FIT_V, QSDP_FIT_W>::kThreads), 0, s, p);
+    return hipGetLastError();
+}
+
+}  // namespace
+
 hipError_t QSDP_CAT(launch_fit_, QSDP_FIT_V, _, QSDP_FIT_W)(const FitParams& p, unsigned grid, hipStream_t s) {
-    const dim3 block(FitShape<1, QSDP_FIT_V, QSDP_FIT_W>::kThreads);
     switch (p.bits) {
-        case 1: hipLaunchKernelGGL((fit_levels_kernel<1, QSDP_FIT_V, QSDP_FIT_W>), dim3(grid), block, 0, s, p); break;
-        case 2: hipLaunchKernelGGL((fit_levels_kernel<2, QSDP_FIT_V, QSDP_FIT_W>), dim3(grid), block, 0, s, p); break;
-        case 3: hipLaunchKernelGGL((fit_levels_kernel<3, QSDP_FIT_V, QSDP_FIT_W>), dim3(grid), block, 0, s, p); break;
-        case 4: hipLaunchKernelGGL((fit_levels_kernel<4, QSDP_FIT_V, QSDP_FIT_W>), dim3(grid), block, 0, s, p); break;
-        case 5: hipLaunchKernelGGL((fit_levels_kernel<5, QSDP_FIT_V, QSDP_FIT_W>), dim3(grid), block, 0, s, p); break;
-        case 6: hipLaunchKernelGGL((fit_levels_kernel<6, QSDP_FIT_V, QSDP_FIT_W>), dim3(grid), block, 0, s, p); break;
-        case 7: hipLaunchKernelGGL((fit_levels_kernel<7, QSDP_FIT_V, QSDP_FIT_W>), dim3(grid), block, 0, s, p); break;
-        case 8: hipLaunchKernelGGL((fit_levels_kernel<8, QSDP_FIT_V, QSDP_FIT_W>), dim3(grid), block, 0, s, p); break;
+        case 1: return go<1>(p, grid, s);
+        case 2: return go<2>(p, grid, s);
+        case 3: return go<3>(p, grid, s);
+        case 4: return go<4>(p, grid, s);
+        case 5: return go<5>(p, grid, s);
+        case 6: return go<6>(p, grid, s);
+        case 7: return go<7>(p, grid, s);
+        case 8: return go<8>(p, grid, s);
         default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 }  // namespace qsdp

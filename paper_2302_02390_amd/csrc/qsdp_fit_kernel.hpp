@@ -20,7 +20,7 @@ namespace qsdp {
 // levels, and has count and sum below the boundary; differences between lanes are the levels' own. No barrier and no
 // atomic is left in the chain; two LDS round trips for the boundary, one for the powers of 1 - lr and the reciprocals
 // of the counts. A team of W producer waves sorts a batch (the values stay in registers, at most 16 to a lane) and P
-// teams make a round: W = 1, P = 7 for buckets of up to 1024 values (one wave needs no barrier between its passes;
+// teams make a round: W = 1, P = 6 or 7 for buckets of up to 1024 values (one wave needs no barrier between its passes;
 // six sort more slowly than the consumer walks, 0.51 us per batch of 1024 where seven take 0.46, and eight are no
 // faster), W = 2, 4, 8 and P = 8 / W up to 2048, 4096, 8192 with a barrier after each of the four passes. The
 // consumer meanwhile walks the P batches of the round before; the slots are double-buffered.
@@ -61,7 +61,14 @@ struct FitSlot;
 template <int BITS, int VPT, int W>
 struct FitShape {
     static constexpr int kBucketMax = 64 * W * VPT;
-    static constexpr int kBatches = W == 1 ? 7 : 8 / W;          // P, batches per round
+    // Buckets of 129-256 keep six producers: seven ask for more than a third of a compute unit's LDS, and the chain is
+    // no faster with them (us, six / seven, 5 bits, buckets of 160 and 256: one tensor 163 / 163, 164 / 163 per 400
+    // batches, 700 tensors of two 8.6 / 11.5, 8.7 / 11.6; 2000 of three at 8 bits 30 / 37, 32 / 40). So do tables of up to
+    // 8 levels with buckets of 257-512: 200 tensors of one bucket of 512, 1 / 2 / 3 bits, 9.6 / 11.8, 8.3 / 10.0, 6.5 /
+    // 7.3, 400 batches of one tensor 173 / 173, 178 / 180, 177 / 178 (at 4 bits seven are as fast or faster: 2000
+    // tensors 17.1 for 18.8).
+    static constexpr bool kSixProducers = VPT == 4 || (VPT == 8 && BITS <= 3);
+    static constexpr int kBatches = W > 1 ? 8 / W : kSixProducers ? 6 : 7;  // P, batches per round
     static constexpr int kProducers = kBatches * W;              // producer waves; the consumer is one more
     static constexpr int kThreads = 64 * (kProducers + 1);
     static constexpr int kBarriers = W == 1 ? 1 : 4;             // per round
