@@ -1,0 +1,172 @@
+"""The tile kernel against the oracle, bit for bit, in calls large enough for the tiles that only such calls take: two
+rows of four waves with several buckets (from about 2^19 elements, AdamW up to 2^23), six rows in the gradient encoder
+and the receive side (from about 2^22.5), three workgroups to a compute unit (large steps with codes). Every mode that
+is served, from 16-bit gradients, with 16-bit weights out, several peers, and over tensors that end inside tiles."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ref
+from paper_2302_02390_amd import binding as qb
+from paper_2302_02390_amd import workloads as wl
+from gpu_util import DEV, ORACLE_THREADS, bits_equal, first_mismatch, np_f32, np_u32, synth
+
+pytestmark = pytest.mark.gpu
+
+ADAMW = (2e-4, 0.9, 0.95, 1e-8, 0.1, 0.3, 0.2)
+HALVES = {torch.bfloat16: ref.BF16, torch.float16: ref.F16}
+
+
+@pytest.fixture(autouse=True)
+def threads():
+    ref.set_threads(ORACLE_THREADS)
+    yield
+    ref.set_threads(1)
+
+
+def _dev(a, dtype=None):
+    t = torch.from_numpy(np.array(a)).to(DEV)
+    return t if dtype is None else t.to(dtype)
+
+
+def _moments(n, seed):
+    rng = np.random.default_rng(seed)
+    return (1e-4 * rng.standard_normal(n)).astype(np.float32), (1e-7 * rng.random(n)).astype(np.float32)
+
+
+def _same(codes, meta, want_codes, want_meta):
+    return np.array_equal(np_u32(codes), want_codes) and \
+        np.array_equal(np_u32(meta).reshape(-1), want_meta.view(np.uint32).reshape(-1))
+
+
+def _ragged(elements, B):
+    return elements // B * B + B // 2 + 3
+
+
+@pytest.mark.parametrize("B", [32, 96, 160, 416, 768, 1504])
+@pytest.mark.parametrize("g_dtype,x_dtype", [(torch.bfloat16, torch.float16), (torch.float16, torch.bfloat16)])
+def test_steps(B, g_dtype, x_dtype):
+    n = _ragged(1 << 19 if 32 < B < 1024 else 5 << 18, B)
+    x, g = synth(n, B)
+    gd = _dev(g, g_dtype)
+    g = gd.float().cpu().numpy()
+    for wbits, gbits, delta, flags in ((8, 4, 0.0, 0), (5, 3, 2.0 ** -8, 0), (6, 4, 0.0, qb.QSDP_FLAG_GRAD_SHIFT),
+                                       (8, 8, 0.0, qb.QSDP_FLAG_KEEP_MASTER)):
+        xd, sat = _dev(x), torch.zeros(1, dtype=torch.int64, device=DEV)
+        c, m = qb.alloc_packed(n, wbits, B, DEV)
+        x16 = torch.empty(n, dtype=x_dtype, device=DEV)
+        qb.qsdp_fused_step_mp(xd, gd, 1e-2, wbits, gbits, B, delta, 9, 8, flags, c, m.view(-1), x16, sat)
+        want, wc, wm, ws = ref.fused_step(x, g, 1e-2, wbits, gbits, B, delta, 9, index_offset=8, emit_codes=True,
+                                          flags=flags)
+        assert bits_equal(np_f32(xd), want) and int(sat) == ws and _same(c, m, wc, wm), (wbits, delta, flags)
+        half = ref.dequantize(wc, wm, n, wbits, B, HALVES[x_dtype])
+        assert np.array_equal(x16.cpu().view(torch.int16).numpy(), half.view(np.int16)), (wbits, delta, flags)
+
+
+@pytest.mark.parametrize("B", [96, 160, 416, 768, 1504])
+@pytest.mark.parametrize("elements", [1 << 19, 1 << 22])
+def test_adamw_steps(B, elements):
+    n = _ragged(elements, B)
+    x, g = synth(n, B)
+    mom, var = _moments(n, B + 1)
+    gd = _dev(g, torch.bfloat16)
+    g = gd.float().cpu().numpy()
+    for wbits, delta, flags in ((8, 0.0, 0), (5, 2.0 ** -8, qb.QSDP_FLAG_KEEP_MASTER)):
+        xd, md, vd = _dev(x), _dev(mom), _dev(var)
+        c, m = qb.alloc_packed(n, wbits, B, DEV)
+        x16 = torch.empty(n, dtype=torch.float16, device=DEV)
+        qb.qsdp_fused_adamw_step_mp(xd, gd, md, vd, *ADAMW, wbits, 4, B, delta, 9, 8, flags, c, m.view(-1), x16)
+        wx, wmo, wvo, wc, wm, _ = ref.fused_adamw_step(x, g, mom, var, *ADAMW, wbits, 4, B, delta, 9, 8, flags, True)
+        assert all(bits_equal(np_f32(t), a) for t, a in ((xd, wx), (md, wmo), (vd, wvo))), (wbits, delta)
+        half = ref.dequantize(wc, wm, n, wbits, B, ref.F16)
+        assert _same(c, m, wc, wm) and np.array_equal(x16.cpu().view(torch.int16).numpy(), half.view(np.int16))
+        g32 = _dev(g)
+        qb.qsdp_fused_adamw_step_codes(c, m.view(-1), g32, md, vd, *ADAMW, wbits, 4, B, delta, 10, 8)
+        w = ref.dequantize(wc, wm, n, wbits, B)
+        _, wmo, wvo, wc, wm, _ = ref.fused_adamw_step(w, g, wmo, wvo, *ADAMW, wbits, 4, B, delta, 10, 8, 0, True)
+        assert _same(c, m, wc, wm) and bits_equal(np_f32(md), wmo) and bits_equal(np_f32(vd), wvo), (wbits, delta)
+
+
+@pytest.mark.parametrize("B", [96, 160, 544, 768])
+@pytest.mark.parametrize("elements,peers", [(1 << 19, 3), (1 << 19, 8), (7 << 20, 3)])
+def test_receive_side(B, elements, peers):
+    n, gbits = _ragged(elements, B), 3
+    x, _ = synth(n, 3 * B)
+    mom, var = _moments(n, B)
+    cs, ms = zip(*(ref.quantize_grad(synth(n, 7 * B + p)[1], gbits, B, p) for p in range(peers)))
+    cs, ms = np.stack(cs), np.stack([m.reshape(-1) for m in ms])
+    rows = torch.zeros((peers, -(-cs.shape[1] // 4) * 4), dtype=torch.int32, device=DEV)  # rows of whole 16 bytes
+    floats = torch.zeros((peers, -(-ms.shape[1] // 4) * 4), dtype=torch.float32, device=DEV)
+    rows[:, :cs.shape[1]] = _dev(cs.view(np.int32))
+    floats[:, :ms.shape[1]] = _dev(ms)
+    for wbits, delta, flags in ((8, 0.0, 0), (6, 2.0 ** -9, qb.QSDP_FLAG_KEEP_MASTER)):
+        xd = _dev(x)
+        c, m = qb.alloc_packed(n, wbits, B, DEV)
+        qb.qsdp_recv_step(xd, rows, floats, peers, 1.0 / peers, 1e-2, wbits, gbits, B, delta, 11, flags, c, m.view(-1))
+        want, wc, wm, _ = ref.recv_step(x, cs, ms, peers, 1.0 / peers, 1e-2, wbits, gbits, B, delta, 11, flags, True)
+        assert bits_equal(np_f32(xd), want) and _same(c, m, wc, wm), (wbits, delta)
+        xd, md, vd = _dev(x), _dev(mom), _dev(var)
+        qb.qsdp_recv_adamw_step(xd, md, vd, rows, floats, peers, 1.0 / peers, *ADAMW, wbits, gbits, B, delta, 11, flags,
+                                c, m.view(-1))
+        wx, wmo, wvo, wc, wm, _ = ref.recv_adamw_step(x, mom, var, cs, ms, peers, 1.0 / peers, *ADAMW, wbits, gbits, B,
+                                                      delta, 11, flags, True)
+        assert all(bits_equal(np_f32(t), a) for t, a in ((xd, wx), (md, wmo), (vd, wvo))), (wbits, delta)
+        assert _same(c, m, wc, wm), (wbits, delta)
+
+
+@pytest.mark.parametrize("B,elements,tensors", [(32, 1 << 19, 40), (96, 1 << 19, 200), (160, 1 << 20, 9),
+                                                (416, 1 << 21, 100), (416, 1 << 21, 3), (768, 1 << 19, 25)])
+def test_tensors_that_end_inside_tiles(B, elements, tensors):
+    rng = np.random.default_rng(B + tensors)
+    sizes = [8 * int(s) for s in rng.integers(1, elements // 4 // tensors, tensors - 1)]
+    sizes.append(max(8, elements - sum(sizes)) + 5)
+    n, offsets = sum(sizes), np.concatenate([[0], np.cumsum(sizes)])
+    parts = [slice(a, b) for a, b in zip(offsets[:-1], offsets[1:])]
+    x, g = synth(n, B)
+    mom, var = _moments(n, B)
+    segs = qb.Segments(sizes, B, DEV)
+
+    c, m = segs.alloc_packed(3)
+    qb.qsdp_quantize_grad_segmented(_dev(g), segs, 3, 6, 64, c, m.view(-1))
+    wc, wm = zip(*(ref.quantize_grad(g[s], 3, B, 6, index_offset=64 + s.start) for s in parts))
+    assert _same(c, m, np.concatenate(wc), np.concatenate(wm))
+
+    for wbits, delta in ((8, 0.0), (5, 2.0 ** -8)):
+        c, m = segs.alloc_packed(wbits)
+        qb.qsdp_quantize_weight_segmented(_dev(x), segs, wbits, delta, 6, c, m.view(-1))
+        codes = [ref.quantize_weight(x[s], wbits, B, delta, 6)[:2] for s in parts]
+        assert _same(c, m, *map(np.concatenate, zip(*codes))), wbits
+        qb.qsdp_fused_step_codes_segmented(c, m.view(-1), _dev(g), segs, 1e-2, wbits, 4, delta, 7, 64)
+        codes = [ref.fused_step_codes(a, b, g[s], 1e-2, wbits, 4, B, delta, 7, index_offset=64 + s.start)[:2]
+                 for (a, b), s in zip(codes, parts)]
+        assert _same(c, m, *map(np.concatenate, zip(*codes))), wbits
+
+        xd, gd = _dev(x), _dev(g, torch.bfloat16)
+        x16 = torch.empty(n, dtype=torch.bfloat16, device=DEV)
+        qb.qsdp_fused_step_segmented_mp(xd, gd, segs, 1e-2, wbits, 4, delta, 8, 64, 0, c, m.view(-1), x16)
+        wide = gd.float().cpu().numpy()
+        want = [ref.fused_step(x[s], wide[s], 1e-2, wbits, 4, B, delta, 8, index_offset=64 + s.start, emit_codes=True)
+                for s in parts]
+        new = np.concatenate([w[0] for w in want])
+        assert bits_equal(np_f32(xd), new) and torch.equal(x16.cpu(), torch.from_numpy(new).bfloat16()), wbits
+        assert _same(c, m, np.concatenate([w[1] for w in want]), np.concatenate([w[2] for w in want])), wbits
+
+        xd, md, vd = _dev(x), _dev(mom), _dev(var)
+        qb.qsdp_fused_adamw_step_segmented(xd, _dev(g), md, vd, segs, *ADAMW, wbits, 4, delta, 9, 64, 0, c, m.view(-1))
+        want = [ref.fused_adamw_step(x[s], g[s], mom[s], var[s], *ADAMW, wbits, 4, B, delta, 9, 64 + s.start, 0, True)
+                for s in parts]
+        for t, a in zip((xd, md, vd), zip(*(w[:3] for w in want))):
+            assert bits_equal(np_f32(t), np.concatenate(a)), wbits
+        assert _same(c, m, np.concatenate([w[3] for w in want]), np.concatenate([w[4] for w in want])), wbits
+
+
+def test_a_step_large_enough_for_three_workgroups():
+    n, B = (3 << 25) + 100, 768
+    x, g = wl.weights(n, 1250, DEV), wl.grads_student_t3(n, 1251, DEV)
+    x_np, g_np = x.cpu().numpy(), g.cpu().numpy()
+    c, m = qb.alloc_packed(n, 8, B, DEV)
+    qb.qsdp_fused_step(x, g, 1e-3, 8, 8, B, 0.0, 3, 0, c, m.view(-1))
+    wc, wm = np.zeros(c.numel(), np.uint32), np.zeros((m.shape[0], 2), np.float32)
+    ref.fused_step_inplace(x_np, g_np, 1e-3, 8, 8, B, 0.0, 3, 0, wc, wm)
+    assert first_mismatch(x, x_np) == -1 and first_mismatch(c, wc.view(np.int32)) == -1
+    assert first_mismatch(m.view(-1), wm.reshape(-1)) == -1

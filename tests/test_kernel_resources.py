@@ -35,8 +35,8 @@ def test_waves_of_the_tile_kernel():
 
 
 def test_workgroups_of_the_level_fit():
-    """Buckets of up to 256: three workgroups to a compute unit's 160 KB of LDS. Six producers there and for tables of up
-    to 8 levels with buckets of up to 512, seven otherwise, and the consumer."""
+    """Buckets of up to 256: three workgroups to a compute unit's 160 KB of LDS. Six producers there and for tables of
+    up to 8 levels with buckets of up to 512, seven otherwise, and the consumer."""
     with ThreadPoolExecutor(2) as ex:
         assembly = dict(zip((4, 8), ex.map(
             lambda v: _assembly("qsdp_fit_inst.hip", f"-DQSDP_FIT_V={v}", "-DQSDP_FIT_W=1"), (4, 8))))

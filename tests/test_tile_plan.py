@@ -102,7 +102,7 @@ int main() {
 
 
 def test_tile_plan_of_a_call(tmp_path):
-    """Every tile of a call is a valid plan, and calls of the sizes in test_gpu_tile.py see the two that only they take."""
+    """Every tile of a call is a valid plan, the two that only some calls take among them."""
     src, exe = tmp_path / "call.cpp", tmp_path / "call"
     src.write_text(CALL_SOURCE)
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", lib_build.CSRC, str(src), "-o", str(exe)], check=True)
@@ -133,7 +133,7 @@ int main() {
 
 
 def test_tile_plan_of_a_multi_tensor_call(tmp_path):
-    """Tiles that meet tensors' ends are slow: no call over tensors takes tiles of more buckets than the general rule."""
+    """Tiles that meet tensors' ends are slow: such calls take no tiles of more buckets than the general rule's."""
     src, exe = tmp_path / "tensors.cpp", tmp_path / "tensors"
     src.write_text(TENSORS_SOURCE)
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", lib_build.CSRC, str(src), "-o", str(exe)], check=True)
@@ -157,7 +157,8 @@ int main() {
         bad += three(bucket, large, false, true) + three(bucket, large, false, false, 0);
         bad += three(bucket, large, false, false, 4) + three(bucket, large, false, false, 8, true);
     }
-    for (int bucket : {32, 160, 224, 288, 704, 736, 800, 1472, 2016, 2080, 4128, 4992, 8192}) bad += three(bucket, large);
+    for (int bucket : {32, 160, 224, 288, 704, 736, 800, 1472, 2016, 2080, 4128, 4992, 8192})
+        bad += three(bucket, large);
     return bad != 0;
 }
 """
@@ -167,5 +168,33 @@ def test_large_steps_in_full_tiles_run_three_workgroups(tmp_path):
     """... and no others: not over tensors, in tiles that are less full, on smaller vectors or with other outputs."""
     src, exe = tmp_path / "stream.cpp", tmp_path / "stream"
     src.write_text(STREAM_SOURCE)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", lib_build.CSRC, str(src), "-o", str(exe)], check=True)
+    assert subprocess.run([str(exe)]).returncode == 0
+
+
+SIZES_SOURCE = r"""
+#include "qsdp_tile_plan.hpp"
+#include <initializer_list>
+using namespace qsdp;
+static bool takes(int waves, int rows, int bucket, uint64_t n, TileWork work, bool tensors = false) {
+    const TilePlan t = choose_step_tile(bucket, (n + bucket - 1) / bucket, ~0ull, work, tensors);
+    return t.waves == waves && t.rows == rows && t.buckets == tile_groups(waves, rows) / (bucket / 32);
+}
+int main() {
+    int bad = 0;
+    for (int bucket : {96, 160, 416, 768}) bad += !takes(4, 2, bucket, 1 << 19, TILE_MEMORY);
+    for (int bucket : {32, 1504}) bad += !takes(4, 2, bucket, 5 << 18, TILE_MEMORY);
+    for (int bucket : {96, 160, 416, 768, 1504}) bad += !takes(4, 2, bucket, 1 << 22, TILE_ADAMW);
+    for (int bucket : {96, 160, 544}) bad += !takes(4, 6, bucket, 7 << 20, TILE_INSTRUCTIONS);
+    bad += !takes(4, 2, 416, 1 << 21, TILE_MEMORY, true);
+    return bad;
+}
+"""
+
+
+def test_sizes_that_take_the_tiles_of_their_own(tmp_path):
+    """The calls of test_gpu_tile_calls.py are of these sizes (32 with 2^19 elements takes a smaller tile)."""
+    src, exe = tmp_path / "sizes.cpp", tmp_path / "sizes"
+    src.write_text(SIZES_SOURCE)
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", lib_build.CSRC, str(src), "-o", str(exe)], check=True)
     assert subprocess.run([str(exe)]).returncode == 0
