@@ -96,7 +96,8 @@ _SIGNATURES = {
 }
 EXPORTS = tuple(_SIGNATURES)
 # Where the entry points take pointers, the stream left out.
-_POINTERS = {name: tuple(i for i, kind in enumerate(kinds[:-1]) if kind is _vp) for name, (_, kinds) in _SIGNATURES.items()}
+_POINTERS = {name: tuple(i for i, kind in enumerate(kinds[:-1]) if kind is _vp)
+             for name, (_, kinds) in _SIGNATURES.items()}
 
 _lib = None
 _lib_lock = threading.Lock()
@@ -286,8 +287,7 @@ def qsdp_quantize_grad_ex(g, bits, bucket, seed, index_offset, flags, codes, met
     _is(g, torch.float32); _is(codes, torch.int32); _is(meta, torch.float32)
     n = g.numel()
     _packed_ok(codes, meta, n, bits, bucket)
-    _launch(g, "qsdp_quantize_grad_ex", g, n, bits, bucket, seed, index_offset, flags, codes,
-            meta)
+    _launch(g, "qsdp_quantize_grad_ex", g, n, bits, bucket, seed, index_offset, flags, codes, meta)
 
 
 def qsdp_quantize_weight_ex(x, bits, bucket, delta, seed, flags, codes, meta, n_saturated=None):
@@ -296,8 +296,7 @@ def qsdp_quantize_weight_ex(x, bits, bucket, delta, seed, flags, codes, meta, n_
     _packed_ok(codes, meta, n, bits, bucket)
     if n_saturated is not None:
         _is(n_saturated, torch.int64)
-    _launch(x, "qsdp_quantize_weight_ex", x, n, bits, bucket, delta, seed, flags, codes, meta,
-            n_saturated)
+    _launch(x, "qsdp_quantize_weight_ex", x, n, bits, bucket, delta, seed, flags, codes, meta, n_saturated)
 
 
 def qsdp_fused_step_ex(x, g, lr, wbits, gbits, bucket, delta, seed, index_offset, flags, wcodes=None,
@@ -308,8 +307,8 @@ def qsdp_fused_step_ex(x, g, lr, wbits, gbits, bucket, delta, seed, index_offset
         raise ValueError("x and g differ in size")
     _step_outputs(wcodes, wmeta, n_saturated)
     _packed_ok(wcodes, wmeta, n, wbits, bucket)
-    _launch(x, "qsdp_fused_step_ex", x, g, n, lr, wbits, gbits, bucket, delta, seed, index_offset,
-            flags, wcodes, wmeta, n_saturated)
+    _launch(x, "qsdp_fused_step_ex", x, g, n, lr, wbits, gbits, bucket, delta, seed, index_offset, flags, wcodes, wmeta,
+            n_saturated)
 
 
 def qsdp_quantize_weight(x, bits, bucket, delta, seed, codes, meta, n_saturated=None):
@@ -318,8 +317,7 @@ def qsdp_quantize_weight(x, bits, bucket, delta, seed, codes, meta, n_saturated=
     _packed_ok(codes, meta, n, bits, bucket)
     if n_saturated is not None:
         _is(n_saturated, torch.int64)
-    _launch(x, "qsdp_quantize_weight", x, n, bits, bucket, delta, seed, codes, meta,
-            n_saturated)
+    _launch(x, "qsdp_quantize_weight", x, n, bits, bucket, delta, seed, codes, meta, n_saturated)
 
 
 def qsdp_dequantize(codes, meta, n, bits, bucket, out):
@@ -355,8 +353,7 @@ def qsdp_quantize_levels_stochastic(v, bits, bucket, levels, seed, index_offset,
     if levels.numel() != (1 << bits):
         raise ValueError("levels must hold 2^bits entries")
     _packed_ok(codes, meta, n, bits, bucket)
-    _launch(v, "qsdp_quantize_levels_stochastic", v, n, bits, bucket, levels, seed, index_offset,
-            codes, meta)
+    _launch(v, "qsdp_quantize_levels_stochastic", v, n, bits, bucket, levels, seed, index_offset, codes, meta)
 
 
 def qsdp_dequantize_levels(codes, meta, n, bits, bucket, levels, out):
@@ -386,8 +383,8 @@ def qsdp_dequantize_add(codes, meta, npeers, n, bits, bucket, alpha, out):
     if out.numel() < n:
         raise ValueError("out is too small")
     _rows_ok(codes, meta, n, bits, bucket)
-    _launch(out, "qsdp_dequantize_add", codes, codes.stride(0) * 4, meta, meta.stride(0) * 4, npeers, n,
-            bits, bucket, alpha, out)
+    _launch(out, "qsdp_dequantize_add", codes, codes.stride(0) * 4, meta, meta.stride(0) * 4, npeers, n, bits, bucket,
+            alpha, out)
 
 
 def qsdp_fused_step(x, g, lr, wbits, gbits, bucket, delta, seed, index_offset=0, wcodes=None,
@@ -398,8 +395,8 @@ def qsdp_fused_step(x, g, lr, wbits, gbits, bucket, delta, seed, index_offset=0,
         raise ValueError("x and g differ in size")
     _step_outputs(wcodes, wmeta, n_saturated)
     _packed_ok(wcodes, wmeta, n, wbits, bucket)
-    _launch(x, "qsdp_fused_step", x, g, n, lr, wbits, gbits, bucket, delta, seed, index_offset,
-            wcodes, wmeta, n_saturated)
+    _launch(x, "qsdp_fused_step", x, g, n, lr, wbits, gbits, bucket, delta, seed, index_offset, wcodes, wmeta,
+            n_saturated)
 
 
 def qsdp_fused_adamw_step(x, g, m, v, lr, beta1, beta2, eps, weight_decay, bias1, bias2, wbits, gbits, bucket,
@@ -410,9 +407,8 @@ def qsdp_fused_adamw_step(x, g, m, v, lr, beta1, beta2, eps, weight_decay, bias1
         raise ValueError("x, g, m, v differ in size")
     _step_outputs(wcodes, wmeta, n_saturated)
     _packed_ok(wcodes, wmeta, x.numel(), wbits, bucket)
-    _launch(x, "qsdp_fused_adamw_step", x, g, m, v, x.numel(), lr, beta1, beta2, eps,
-            weight_decay, bias1, bias2, wbits, gbits, bucket, delta, seed, index_offset, flags, wcodes,
-            wmeta, n_saturated)
+    _launch(x, "qsdp_fused_adamw_step", x, g, m, v, x.numel(), lr, beta1, beta2, eps, weight_decay, bias1, bias2, wbits,
+            gbits, bucket, delta, seed, index_offset, flags, wcodes, wmeta, n_saturated)
 
 
 def qsdp_fused_step_codes(wcodes, wmeta, g, lr, wbits, gbits, bucket, delta, seed, index_offset=0,
@@ -422,8 +418,8 @@ def qsdp_fused_step_codes(wcodes, wmeta, g, lr, wbits, gbits, bucket, delta, see
     if n_saturated is not None:
         _is(n_saturated, torch.int64)
     _packed_ok(wcodes, wmeta, n, wbits, bucket)
-    _launch(g, "qsdp_fused_step_codes", wcodes, wmeta, g, n, lr, wbits, gbits, bucket, delta,
-            seed, index_offset, flags, n_saturated)
+    _launch(g, "qsdp_fused_step_codes", wcodes, wmeta, g, n, lr, wbits, gbits, bucket, delta, seed, index_offset, flags,
+            n_saturated)
 
 
 class Segments:
@@ -465,8 +461,8 @@ def qsdp_quantize_grad_segmented(g, segs, bits, seed, index_offset, codes, meta)
     if g.numel() < segs.n:
         raise ValueError("g is smaller than the segments")
     segs.check_packed(codes, meta, bits)
-    _launch(g, "qsdp_quantize_grad_segmented", g, segs.device, segs.nseg, segs.total_buckets, bits,
-            segs.bucket, seed, index_offset, codes, meta)
+    _launch(g, "qsdp_quantize_grad_segmented", g, segs.device, segs.nseg, segs.total_buckets, bits, segs.bucket, seed,
+            index_offset, codes, meta)
 
 
 def qsdp_quantize_weight_segmented(x, segs, bits, delta, seed, codes, meta, n_saturated=None):
@@ -476,8 +472,8 @@ def qsdp_quantize_weight_segmented(x, segs, bits, delta, seed, codes, meta, n_sa
     if n_saturated is not None:
         _is(n_saturated, torch.int64)
     segs.check_packed(codes, meta, bits)
-    _launch(x, "qsdp_quantize_weight_segmented", x, segs.device, segs.nseg, segs.total_buckets, bits,
-            segs.bucket, delta, seed, codes, meta, n_saturated)
+    _launch(x, "qsdp_quantize_weight_segmented", x, segs.device, segs.nseg, segs.total_buckets, bits, segs.bucket,
+            delta, seed, codes, meta, n_saturated)
 
 
 def qsdp_fused_step_segmented(x, g, segs, lr, wbits, gbits, delta, seed, index_offset=0, wcodes=None,
@@ -487,8 +483,8 @@ def qsdp_fused_step_segmented(x, g, segs, lr, wbits, gbits, delta, seed, index_o
         raise ValueError("x or g is smaller than the segments")
     _step_outputs(wcodes, wmeta, n_saturated)
     segs.check_packed(wcodes, wmeta, wbits)
-    _launch(x, "qsdp_fused_step_segmented", x, g, segs.device, segs.nseg, segs.total_buckets, lr,
-            wbits, gbits, segs.bucket, delta, seed, index_offset, wcodes, wmeta, n_saturated)
+    _launch(x, "qsdp_fused_step_segmented", x, g, segs.device, segs.nseg, segs.total_buckets, lr, wbits, gbits,
+            segs.bucket, delta, seed, index_offset, wcodes, wmeta, n_saturated)
 
 
 def qsdp_dequantize_segmented(codes, meta, segs, bits, out):
@@ -499,8 +495,8 @@ def qsdp_dequantize_segmented(codes, meta, segs, bits, out):
         raise ValueError("out is smaller than the segments")
     if codes.numel() * 32 < segs.total_buckets * segs.bucket * bits or meta.numel() < 2 * segs.total_buckets:
         raise ValueError("codes or meta is smaller than the segments")
-    _launch(out, "qsdp_dequantize_segmented", codes, meta, segs.device, segs.nseg, segs.total_buckets,
-            bits, segs.bucket, dt, out)
+    _launch(out, "qsdp_dequantize_segmented", codes, meta, segs.device, segs.nseg, segs.total_buckets, bits,
+            segs.bucket, dt, out)
 
 
 def qsdp_dequantize_gathered(codes, meta, npeers, n, shard, bits, bucket, out, levels=None):
@@ -519,11 +515,11 @@ def qsdp_dequantize_gathered(codes, meta, npeers, n, shard, bits, bucket, out, l
         _is(levels, torch.float32)
         if levels.numel() != (1 << bits):
             raise ValueError("levels must hold 2^bits entries")
-        _launch(out, "qsdp_dequantize_levels_gathered", codes, codes.stride(0) * 4, meta,
-                meta.stride(0) * 4, npeers, n, shard, bits, bucket, levels, dt, out)
+        _launch(out, "qsdp_dequantize_levels_gathered", codes, codes.stride(0) * 4, meta, meta.stride(0) * 4, npeers, n,
+                shard, bits, bucket, levels, dt, out)
         return
-    _launch(out, "qsdp_dequantize_gathered", codes, codes.stride(0) * 4, meta, meta.stride(0) * 4, npeers,
-            n, shard, bits, bucket, dt, out)
+    _launch(out, "qsdp_dequantize_gathered", codes, codes.stride(0) * 4, meta, meta.stride(0) * 4, npeers, n, shard,
+            bits, bucket, dt, out)
 
 
 def qsdp_recv_step(x, gcodes, gmeta, npeers, alpha, lr, wbits, gbits, bucket, delta, seed, flags=0, wcodes=None,
@@ -536,9 +532,8 @@ def qsdp_recv_step(x, gcodes, gmeta, npeers, alpha, lr, wbits, gbits, bucket, de
     _step_outputs(wcodes, wmeta, n_saturated)
     _rows_ok(gcodes, gmeta, n, gbits, bucket)
     _packed_ok(wcodes, wmeta, n, wbits, bucket)
-    _launch(x, "qsdp_recv_step", x, gcodes, gcodes.stride(0) * 4, gmeta, gmeta.stride(0) * 4, npeers,
-            n, alpha, lr, wbits, gbits, bucket, delta, seed, flags, wcodes, wmeta,
-            n_saturated)
+    _launch(x, "qsdp_recv_step", x, gcodes, gcodes.stride(0) * 4, gmeta, gmeta.stride(0) * 4, npeers, n, alpha, lr,
+            wbits, gbits, bucket, delta, seed, flags, wcodes, wmeta, n_saturated)
 
 
 def qsdp_recv_adamw_step(x, m, v, gcodes, gmeta, npeers, alpha, lr, beta1, beta2, eps, weight_decay, bias1, bias2,
@@ -554,9 +549,9 @@ def qsdp_recv_adamw_step(x, m, v, gcodes, gmeta, npeers, alpha, lr, beta1, beta2
     _step_outputs(wcodes, wmeta, n_saturated)
     _rows_ok(gcodes, gmeta, x.numel(), gbits, bucket)
     _packed_ok(wcodes, wmeta, x.numel(), wbits, bucket)
-    _launch(x, "qsdp_recv_adamw_step", x, m, v, gcodes, gcodes.stride(0) * 4, gmeta,
-            gmeta.stride(0) * 4, npeers, x.numel(), alpha, lr, beta1, beta2, eps, weight_decay, bias1, bias2, wbits,
-            gbits, bucket, delta, seed, flags, wcodes, wmeta, n_saturated)
+    _launch(x, "qsdp_recv_adamw_step", x, m, v, gcodes, gcodes.stride(0) * 4, gmeta, gmeta.stride(0) * 4, npeers,
+            x.numel(), alpha, lr, beta1, beta2, eps, weight_decay, bias1, bias2, wbits, gbits, bucket, delta, seed,
+            flags, wcodes, wmeta, n_saturated)
 
 
 def qsdp_recv_step_segmented(x, segs, gcodes, gmeta, npeers, alpha, lr, wbits, gbits, delta, seed, flags=0,
@@ -573,17 +568,16 @@ def qsdp_recv_step_segmented(x, segs, gcodes, gmeta, npeers, alpha, lr, wbits, g
     segs.check_packed(wcodes, wmeta, wbits)
     if adamw is None:
         _launch(x, "qsdp_recv_step_segmented", x, segs.device, segs.nseg, segs.total_buckets, gcodes,
-                gcodes.stride(0) * 4, gmeta, gmeta.stride(0) * 4, npeers, alpha, lr, wbits, gbits, segs.bucket,
-                delta, seed, flags, wcodes, wmeta, n_saturated)
+                gcodes.stride(0) * 4, gmeta, gmeta.stride(0) * 4, npeers, alpha, lr, wbits, gbits, segs.bucket, delta,
+                seed, flags, wcodes, wmeta, n_saturated)
     else:
         m, v, b1, b2, eps, wd, c1, c2 = adamw
         _is(m, torch.float32); _is(v, torch.float32)
         if m.numel() < segs.n or v.numel() < segs.n:
             raise ValueError("m or v is smaller than the segments")
-        _launch(x, "qsdp_recv_adamw_step_segmented", x, m, v, segs.device, segs.nseg,
-                segs.total_buckets, gcodes, gcodes.stride(0) * 4, gmeta, gmeta.stride(0) * 4, npeers, alpha,
-                lr, b1, b2, eps, wd, c1, c2, wbits, gbits, segs.bucket, delta, seed, flags, wcodes, wmeta,
-                n_saturated)
+        _launch(x, "qsdp_recv_adamw_step_segmented", x, m, v, segs.device, segs.nseg, segs.total_buckets, gcodes,
+                gcodes.stride(0) * 4, gmeta, gmeta.stride(0) * 4, npeers, alpha, lr, b1, b2, eps, wd, c1, c2, wbits,
+                gbits, segs.bucket, delta, seed, flags, wcodes, wmeta, n_saturated)
 
 
 def qsdp_fused_adamw_step_segmented(x, g, m, v, segs, lr, beta1, beta2, eps, weight_decay, bias1, bias2, wbits, gbits,
@@ -594,9 +588,9 @@ def qsdp_fused_adamw_step_segmented(x, g, m, v, segs, lr, beta1, beta2, eps, wei
             raise ValueError("a tensor is smaller than the segments")
     _step_outputs(wcodes, wmeta, n_saturated)
     segs.check_packed(wcodes, wmeta, wbits)
-    _launch(x, "qsdp_fused_adamw_step_segmented", x, g, m, v, segs.device, segs.nseg,
-            segs.total_buckets, lr, beta1, beta2, eps, weight_decay, bias1, bias2, wbits, gbits, segs.bucket, delta,
-            seed, index_offset, flags, wcodes, wmeta, n_saturated)
+    _launch(x, "qsdp_fused_adamw_step_segmented", x, g, m, v, segs.device, segs.nseg, segs.total_buckets, lr, beta1,
+            beta2, eps, weight_decay, bias1, bias2, wbits, gbits, segs.bucket, delta, seed, index_offset, flags, wcodes,
+            wmeta, n_saturated)
 
 
 def qsdp_fused_step_codes_segmented(wcodes, wmeta, g, segs, lr, wbits, gbits, delta, seed, index_offset=0, flags=0,
@@ -607,8 +601,8 @@ def qsdp_fused_step_codes_segmented(wcodes, wmeta, g, segs, lr, wbits, gbits, de
     if n_saturated is not None:
         _is(n_saturated, torch.int64)
     segs.check_packed(wcodes, wmeta, wbits)
-    _launch(g, "qsdp_fused_step_codes_segmented", wcodes, wmeta, g, segs.device, segs.nseg,
-            segs.total_buckets, lr, wbits, gbits, segs.bucket, delta, seed, index_offset, flags, n_saturated)
+    _launch(g, "qsdp_fused_step_codes_segmented", wcodes, wmeta, g, segs.device, segs.nseg, segs.total_buckets, lr,
+            wbits, gbits, segs.bucket, delta, seed, index_offset, flags, n_saturated)
 
 
 def qsdp_fit_levels_segmented(v, segs, bits, lr, levels, max_batches=0):
@@ -618,8 +612,7 @@ def qsdp_fit_levels_segmented(v, segs, bits, lr, levels, max_batches=0):
         raise ValueError("v is smaller than the segments")
     if levels.numel() != segs.nseg * (1 << bits):
         raise ValueError("levels must hold nseg * 2^bits entries")
-    _launch(v, "qsdp_fit_levels_segmented", v, segs.device, segs.nseg, bits, segs.bucket, lr, max_batches,
-            levels)
+    _launch(v, "qsdp_fit_levels_segmented", v, segs.device, segs.nseg, bits, segs.bucket, lr, max_batches, levels)
 
 
 def qsdp_fused_step_dseed(x, g, lr, wbits, gbits, bucket, delta, seed, seed_dev, index_offset=0, flags=0, wcodes=None,
@@ -632,8 +625,8 @@ def qsdp_fused_step_dseed(x, g, lr, wbits, gbits, bucket, delta, seed, seed_dev,
         raise ValueError("x and g differ in size")
     _step_outputs(wcodes, wmeta, n_saturated)
     _packed_ok(wcodes, wmeta, n, wbits, bucket)
-    _launch(x, "qsdp_fused_step_dseed", x, g, n, lr, wbits, gbits, bucket, delta, seed,
-            seed_dev, index_offset, flags, wcodes, wmeta, n_saturated)
+    _launch(x, "qsdp_fused_step_dseed", x, g, n, lr, wbits, gbits, bucket, delta, seed, seed_dev, index_offset, flags,
+            wcodes, wmeta, n_saturated)
 
 
 def qsdp_quantize_levels_segmented(v, segs, bits, levels, codes, meta, stochastic=False, seed=0, index_offset=0):
@@ -644,8 +637,8 @@ def qsdp_quantize_levels_segmented(v, segs, bits, levels, codes, meta, stochasti
     if levels.numel() != segs.nseg * (1 << bits):
         raise ValueError("levels must hold nseg * 2^bits entries")
     segs.check_packed(codes, meta, bits)
-    _launch(v, "qsdp_quantize_levels_segmented", v, segs.device, segs.nseg, segs.total_buckets, bits,
-            segs.bucket, levels, int(bool(stochastic)), seed, index_offset, codes, meta)
+    _launch(v, "qsdp_quantize_levels_segmented", v, segs.device, segs.nseg, segs.total_buckets, bits, segs.bucket,
+            levels, int(bool(stochastic)), seed, index_offset, codes, meta)
 
 
 def qsdp_dequantize_levels_segmented(codes, meta, segs, bits, levels, out):
@@ -657,8 +650,8 @@ def qsdp_dequantize_levels_segmented(codes, meta, segs, bits, levels, out):
     if levels.numel() != segs.nseg * (1 << bits):
         raise ValueError("levels must hold nseg * 2^bits entries")
     segs.check_packed(codes, meta, bits)
-    _launch(out, "qsdp_dequantize_levels_segmented", codes, meta, segs.device, segs.nseg,
-            segs.total_buckets, bits, segs.bucket, levels, dt, out)
+    _launch(out, "qsdp_dequantize_levels_segmented", codes, meta, segs.device, segs.nseg, segs.total_buckets, bits,
+            segs.bucket, levels, dt, out)
 
 
 
@@ -672,8 +665,7 @@ def qsdp_quantize_grad_g16(g, bits, bucket, seed, index_offset, codes, meta, fla
     _is(g, g.dtype); _is(codes, torch.int32); _is(meta, torch.float32)
     n = g.numel()
     _packed_ok(codes, meta, n, bits, bucket)
-    _launch(g, "qsdp_quantize_grad_g16", g, _G16[g.dtype], n, bits, bucket, seed, index_offset, flags,
-            codes, meta)
+    _launch(g, "qsdp_quantize_grad_g16", g, _G16[g.dtype], n, bits, bucket, seed, index_offset, flags, codes, meta)
 
 
 def qsdp_fused_step_g16(x, g, lr, wbits, gbits, bucket, delta, seed, index_offset=0, flags=0, wcodes=None, wmeta=None,
@@ -687,8 +679,8 @@ def qsdp_fused_step_g16(x, g, lr, wbits, gbits, bucket, delta, seed, index_offse
         raise ValueError("x and g differ in size")
     _step_outputs(wcodes, wmeta, n_saturated)
     _packed_ok(wcodes, wmeta, n, wbits, bucket)
-    _launch(x, "qsdp_fused_step_g16", x, g, _G16[g.dtype], n, lr, wbits, gbits, bucket, delta, seed,
-            index_offset, flags, wcodes, wmeta, n_saturated)
+    _launch(x, "qsdp_fused_step_g16", x, g, _G16[g.dtype], n, lr, wbits, gbits, bucket, delta, seed, index_offset,
+            flags, wcodes, wmeta, n_saturated)
 
 
 def qsdp_fused_adamw_step_codes(wcodes, wmeta, g, m, v, lr, beta1, beta2, eps, weight_decay, bias1, bias2, wbits, gbits,
@@ -702,8 +694,8 @@ def qsdp_fused_adamw_step_codes(wcodes, wmeta, g, m, v, lr, beta1, beta2, eps, w
     if n_saturated is not None:
         _is(n_saturated, torch.int64)
     _packed_ok(wcodes, wmeta, n, wbits, bucket)
-    _launch(g, "qsdp_fused_adamw_step_codes", wcodes, wmeta, g, m, v, n, lr, beta1, beta2,
-            eps, weight_decay, bias1, bias2, wbits, gbits, bucket, delta, seed, index_offset, flags, n_saturated)
+    _launch(g, "qsdp_fused_adamw_step_codes", wcodes, wmeta, g, m, v, n, lr, beta1, beta2, eps, weight_decay, bias1,
+            bias2, wbits, gbits, bucket, delta, seed, index_offset, flags, n_saturated)
 
 
 def qsdp_fused_step_mp(x, g, lr, wbits, gbits, bucket, delta, seed, index_offset=0, flags=0, wcodes=None, wmeta=None,
@@ -726,8 +718,8 @@ def qsdp_fused_step_mp(x, g, lr, wbits, gbits, bucket, delta, seed, index_offset
         xdt = _G16[x16.dtype]
     _step_outputs(wcodes, wmeta, n_saturated)
     _packed_ok(wcodes, wmeta, n, wbits, bucket)
-    _launch(x, "qsdp_fused_step_mp", x, g, gdt, n, lr, wbits, gbits, bucket, delta, seed,
-            index_offset, flags, wcodes, wmeta, x16, xdt, n_saturated)
+    _launch(x, "qsdp_fused_step_mp", x, g, gdt, n, lr, wbits, gbits, bucket, delta, seed, index_offset, flags, wcodes,
+            wmeta, x16, xdt, n_saturated)
 
 
 def qsdp_fused_step_segmented_mp(x, g, segs, lr, wbits, gbits, delta, seed, index_offset=0, flags=0, wcodes=None,
@@ -747,9 +739,8 @@ def qsdp_fused_step_segmented_mp(x, g, segs, lr, wbits, gbits, delta, seed, inde
         xdt = _G16[x16.dtype]
     _step_outputs(wcodes, wmeta, n_saturated)
     segs.check_packed(wcodes, wmeta, wbits)
-    _launch(x, "qsdp_fused_step_segmented_mp", x, g, gdt, segs.device, segs.nseg, segs.total_buckets,
-            lr, wbits, gbits, segs.bucket, delta, seed, index_offset, flags, wcodes, wmeta, x16, xdt,
-            n_saturated)
+    _launch(x, "qsdp_fused_step_segmented_mp", x, g, gdt, segs.device, segs.nseg, segs.total_buckets, lr, wbits, gbits,
+            segs.bucket, delta, seed, index_offset, flags, wcodes, wmeta, x16, xdt, n_saturated)
 
 
 def qsdp_fused_adamw_step_mp(x, g, m, v, lr, beta1, beta2, eps, weight_decay, bias1, bias2, wbits, gbits, bucket, delta,
@@ -772,9 +763,8 @@ def qsdp_fused_adamw_step_mp(x, g, m, v, lr, beta1, beta2, eps, weight_decay, bi
         xdt = _G16[x16.dtype]
     _step_outputs(wcodes, wmeta, n_saturated)
     _packed_ok(wcodes, wmeta, n, wbits, bucket)
-    _launch(x, "qsdp_fused_adamw_step_mp", x, g, gdt, m, v, n, lr, beta1, beta2, eps,
-            weight_decay, bias1, bias2, wbits, gbits, bucket, delta, seed, index_offset, flags, wcodes,
-            wmeta, x16, xdt, n_saturated)
+    _launch(x, "qsdp_fused_adamw_step_mp", x, g, gdt, m, v, n, lr, beta1, beta2, eps, weight_decay, bias1, bias2, wbits,
+            gbits, bucket, delta, seed, index_offset, flags, wcodes, wmeta, x16, xdt, n_saturated)
 
 
 class StepOptions(C.Structure):

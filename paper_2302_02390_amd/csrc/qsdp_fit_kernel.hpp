@@ -21,8 +21,8 @@ namespace qsdp {
 // atomic is left in the chain; two LDS round trips for the boundary, one for the powers of 1 - lr and the reciprocals
 // of the counts. A team of W producer waves sorts a batch (the values stay in registers, at most 16 to a lane) and P
 // teams make a round: W = 1, P = 6 or 7 for buckets of up to 1024 values (one wave needs no barrier between its passes;
-// six sort more slowly than the consumer walks, 0.51 us per batch of 1024 where seven take 0.46, and eight are no
-// faster), W = 2, 4, 8 and P = 8 / W up to 2048, 4096, 8192 with a barrier after each of the four passes. The
+// at 1024 six sort more slowly than the consumer walks: 0.53 us per batch, 5 bits, where seven take 0.49, and eight are
+// no faster), W = 2, 4, 8 and P = 8 / W up to 2048, 4096, 8192 with a barrier after each of the four passes. The
 // consumer meanwhile walks the P batches of the round before; the slots are double-buffered.
 //
 // Measured (us per batch, 5-bit table, Gaussian values, buckets of 128 / 352 / 1024 / 4096 / 8192): 0.40 / 0.43 / 0.49

@@ -10,7 +10,7 @@
 // combine those of one bucket, and the bucket's grid comes back with one 16-byte LDS read per row.
 //
 // Bound by HBM where a tile is well filled: the step with code output on 125 million parameters in buckets of 768 (W8
-// G8) takes 0.265 ms = 6.2 TB/s, against 1.33 ms for a workgroup per bucket that stages its values in LDS and packs
+// G8) takes 0.266 ms = 6.1 TB/s, against 1.33 ms for a workgroup per bucket that stages its values in LDS and packs
 // its codes bit by bit; buckets of 96 on 8 million parameters 0.022 against 0.353 ms. P is the largest count that fits
 // (qsdp_tile_plan.hpp, which also says when a tile is smaller), so few slots idle; leaving out the arithmetic of a
 // wave's idle rows by branches cost the full tiles 3-10 % (the rows no longer overlap) and won 4 % at the worst fill,
@@ -117,6 +117,11 @@ struct TileArgs {
     uint32_t group_magic, word_magic;
 };
 
+// Workgroups to a compute unit that a kernel's registers must allow (1: what the compiler makes of it). The receive side
+// with AdamW fits four of them into 128 registers without spilling where it has up to four rows, and needs more if left
+// alone. us, left alone / four: eight peers, 2^25 elements in buckets of 96, 416, 800, 3488 202 / 194, 203 / 192, 197 /
+// 190, 209 / 195, two peers, 2^26 316 / 306, 304 / 302, 306 / 311, 319 / 303; 2^18, eight peers, 9.5 / 9.4, 9.5 / 9.4,
+// 10.5 / 10.4, 15.6 / 15.9.
 constexpr int tile_min_blocks(int mode, int waves, int rows) {
     if (mode_is_levels(mode)) return tile_resident(mode == MODE_LEVELS_COIN, waves, rows);
     if (mode == MODE_RECV_ADAMW && rows <= 4) return 4;

@@ -150,13 +150,13 @@ inline TilePlan choose_step_tile(int bucket, uint64_t num_buckets, uint64_t most
 
 // Whether a step on a flat vector, two fp32 operands in, weights and 8-bit codes on their min-max grids out, streams
 // faster with three workgroups to a compute unit than with the four that the registers of six rows allow: large vectors
-// in full tiles. us, four / three, buckets of 384, 768, 3040, where the tile is full: 96 * 2^20 elements 221 / 220, 220 /
-// 218, 220 / 217, 125M 275 / 270, 278 / 266, 273 / 267, 300 * 2^20 710 / 666, 713 / 673, 723 / 676, with a 16-bit copy
+// in full tiles. us, four / three, buckets of 384, 768, 3040, where the tile is full: 96 * 2^20 elements 221 / 220, 220
+// / 218, 220 / 217, 125M 275 / 270, 278 / 266, 273 / 267, 300 * 2^20 710 / 666, 713 / 673, 723 / 676, with a 16-bit copy
 // or an unquantized partition 1-6 % at all of them. Below, 2^26 elements 147 / 164, 149 / 150, 148 / 147. In tiles
-// filled to 96 % (704, 1504) 125M 266 / 281, 273 / 270, to 81 % (4992) 266 / 287. 4-bit codes 125M 252 / 254, 256 / 255,
-// on a lattice 266 / 265, 270 / 266, 263 / 263. Over tensors, which end inside tiles, 200 * 2^20 elements in buckets of
-// 768, five / a hundred to a tensor, 580 / 719, 456 / 487. Without codes 125M 241 / 245.
-// code_bits: 0 without codes.
+// filled to 92 % (704) 125M 266 / 281, to 97.9 % (1504) 273 / 270 and 2^26 147 / 150, to 81 % (4992) 125M 266 / 287.
+// 4-bit codes 125M 252 / 254, 256 / 255, 262 / 250, on a lattice 266 / 265, 270 / 266, 263 / 263. Over tensors, which
+// end inside tiles, 200 * 2^20 elements in buckets of 768, five / a hundred to a tensor, 580 / 719, 456 / 487. Without
+// codes 125M 241 / 245. code_bits: 0 without codes.
 inline bool three_workgroups_stream(int bucket, int buckets, int waves, int rows, uint64_t n, bool tensors,
                                     bool half_gradient, int code_bits, bool lattice) {
     return rows == 6 && n >= (3ull << 25) && 100 * buckets * (bucket / 32) >= 98 * tile_groups(waves, rows) &&

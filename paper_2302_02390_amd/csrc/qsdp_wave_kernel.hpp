@@ -25,9 +25,10 @@ namespace qsdp {
 // Lane l's rows of a tile of 4*G*R elements at `base`. `m` = how many of the tile's elements
 // exist; `partial` (wave-uniform) selects the guarded path for a short bucket.
 //
-// That path is run by one wave of a launch, the last one, so small calls wait for it. 16-byte accesses where the
-// elements exist, shifted ones at the end, against a branch, an access and an index for every element: calls of 200
-// buckets whose last one is short take (us; 128 / 1024) AdamW step from bf16 10.6 -> 8.2, 11.2 -> 8.5, step from bf16
+// That path is run by the waves that hold a tensor's short last bucket: those of one bucket of a flat vector, the last
+// of the launch, so small calls wait for them, and of up to one bucket per tensor of a multi-tensor call. 16-byte
+// accesses where the elements exist, shifted ones at the end, against a branch, an access and an index for every
+// element: calls of 200 buckets whose last one is short take (us; 128 / 1024) AdamW step from bf16 10.6 -> 8.2, 11.2 -> 8.5, step from bf16
 // 5.9 -> 4.7, 6.4 -> 5.0, eight peers with AdamW 10.0 -> 8.5, 10.6 -> 9.5; AdamW step over 4096 buckets of 1024 27.3
 // -> 24.1 (with all buckets full 6.7, 7.0, 3.9, 4.6, 7.7, 8.4; 24.0).
 
