@@ -230,13 +230,12 @@ int run(int mode, Params p, int stored_bits, hipStream_t s) {
             blocks = level_blocks(mode, blocks, bpw > 0 ? 4 : p.bucket / 1024, kLevelsResident, tensors);
         if (wl(mode, stored_bits, p, capped_grid(blocks), s) != hipSuccess) return QSDP_ELAUNCH;
     } else {
-        const TileWork work = mode_is_adamw(mode)                         ? TILE_ADAMW
-                              : mode == MODE_GRAD || mode == MODE_RECV ? TILE_INSTRUCTIONS
-                                                                       : TILE_MEMORY;
+        const TileWork work =
+            mode_is_adamw(mode) ? TILE_ADAMW : mode == MODE_GRAD ? TILE_INSTRUCTIONS : TILE_MEMORY;
         const uint64_t most_waves = 4 * (uint64_t)grid_cap();
         const TilePlan t = mode_is_levels(mode)
                                ? choose_tile(p.bucket, nb, tensors, most_waves)
-                               : choose_step_tile(p.bucket, nb, most_waves, work, p.segs != nullptr);
+                               : choose_step_tile(p.bucket, nb, most_waves, work, p.segs != nullptr ? p.nseg : 0);
         const uint64_t units = ceil_div(nb, (uint64_t)t.buckets);
         uint64_t blocks = t.waves == 1 ? ceil_div(units, 4) : units;
         if (mode_is_levels(mode))

@@ -101,8 +101,8 @@ inline TilePlan choose_tile(int bucket, uint64_t num_buckets, uint64_t tensors, 
 
 // What a mode is bound by in a full tile.
 enum TileWork {
-    TILE_MEMORY,        // the weight encoder, the steps; the code-resident one is bound by both
-    TILE_INSTRUCTIONS,  // gradient encoder, receive side
+    TILE_MEMORY,        // the weight encoder, the steps; the code-resident one and the receive side are bound by both
+    TILE_INSTRUCTIONS,  // the gradient encoder
     TILE_ADAMW,         // long chains of divisions: more waves in flight for longer
 };
 
@@ -116,34 +116,38 @@ inline TilePlan tile_plan_half(int bucket) { return tile_plan_for(bucket, 4, 2);
 // 9.3, 11.4 / 10.5, 12.1 / 10.8, 2^22 13.4 / 14.3, 13.6 / 15.1, 14.1 / 16.1, 14.3 / 16.2; AdamW step, 2^20 15.8 / 11.8,
 // 12.5 / 11.8, 16.9 / 12.9, 13.1 / 12.9, 2^22 27.3 / 25.7, 27.3 / 26.6, 28.1 / 27.6, 28.0 / 28.2. Below, at 2^16, the
 // small tile is 0-6 % faster (eight peers with AdamW 9.2 against 11.1).
-// The modes that instructions bind share what a tile costs among six rows rather than four where these are as full
-// (2^25 elements, buckets of 96, 416, 544: gradient encoder 31.8 / 28.7, 31.6 / 29.8, 31.6 / 29.5; steps bound by
-// memory 74.0 / 75.1, 74.3 / 75.4, 76.1 / 75.5), from four waves of theirs to a SIMD on (2^22, bucket 160, gradient
-// encoder from 16 bits 8.7 / 9.2). The code-resident step gains 3-5 % where codes are of 8 bits, and loses up to 8 % at
-// 5 bits (2^22.7 elements, buckets of 416, 544).
-// A multi-tensor call takes neither unless its tiles hold fewer buckets than those of choose_tile: a tile that meets a
-// tensor's end is not contiguous and goes element by element, all of it, so small tensors make a larger tile slower
-// throughout, and large ones end such a call late (us, the plan of choose_tile / the larger tile: 2^19 elements in
-// tensors of one bucket of 32 / forty of 96, steps 9.1 / 13.4, 6.3 / 8.8, AdamW steps 12.0 / 16.5, 8.3 / 13.2; 2^23 in
-// buckets of 32, gradient encoder 35.0 / 49.2, code-resident step 41.5 / 84.8; 2^25 in tensors of forty buckets of 160,
-// the last one short, receive side 84 / 112). Two rows with 4 buckets of 416 in place of four with 9 are 1.1-1.8 times
-// faster at 2^21 elements, in tensors of 1 to 500 buckets.
-inline TilePlan choose_step_tile(int bucket, uint64_t num_buckets, uint64_t most_waves, TileWork work, bool tensors) {
+// The gradient encoder, which instructions bind, shares what a tile costs among six rows rather than four where these
+// are as full (2^25 elements, buckets of 96, 416, 544 31.8 / 28.7, 31.6 / 29.8, 31.6 / 29.5), from four waves of
+// theirs to a SIMD on (2^22, bucket 160, from 16 bits 8.7 / 9.2). Others do not gain: steps bound by memory 74.0 /
+// 75.1, 74.3 / 75.4, 76.1 / 75.5, the code-resident step 3-5 % where codes are of 8 bits, losing up to 8 % at 5 bits,
+// the receive side at no size (two peers, 2^22.6 elements in buckets of 32, 160, 544 15.9 / 18.4, 16.1 / 18.9, 17.3 /
+// 18.4, eight peers, 2^25, 96, 544 105 / 108, 105 / 108).
+// Over tensors the tile of choose_tile stays, unless the other one holds fewer buckets or the tensors are very large:
+// a tile that meets a tensor's end is not contiguous and goes element by element, all of it, so small tensors make a
+// larger tile slower throughout, and large ones end such a call late (us, the plan of choose_tile / the larger tile:
+// 2^19 elements in tensors of one bucket of 32 / forty of 96, steps 9.1 / 13.4, 6.3 / 8.8, AdamW steps 12.0 / 16.5,
+// 8.3 / 13.2; 2^23 in tensors of one bucket of 32, gradient encoder 35.0 / 49.2). Two rows with 4 buckets of 416 in
+// place of four with 9 are 1.1-1.8 times faster at 2^21 elements, in tensors of 1 to 500 buckets. Six rows of the
+// gradient encoder, 4 bits in buckets of 160, tensors of 128 and 512 tiles that end in a short bucket: 2^23 elements
+// 13.5 / 15.8, 10.8 / 11.5, 2^25 38.1 / 38.2, 35.2 / 33.5, 100 * 2^20 101 / 101, 96 / 85.
+inline TilePlan choose_step_tile(int bucket, uint64_t num_buckets, uint64_t most_waves, TileWork work,
+                                 uint64_t tensors) {
     const TilePlan t = choose_tile(bucket, num_buckets, 0, most_waves), full = tile_plan(bucket);
     if (bucket <= 32 * tile_groups(4, 2)) {
         const TilePlan half = tile_plan_half(bucket);
         const uint64_t waves = (num_buckets + (uint64_t)half.buckets - 1) / (uint64_t)half.buckets * 4;
         if (waves >= 1024 && waves < (work == TILE_ADAMW ? 12288u : 6144u) && waves < most_waves &&
-            (!tensors || half.buckets < t.buckets))
+            (tensors == 0 || half.buckets < t.buckets))
             return half;
     }
-    if (work == TILE_INSTRUCTIONS && !tensors && t.rows == full.rows && t.waves == full.waves &&
-        t.buckets == full.buckets && t.rows == 4) {
+    if (work == TILE_INSTRUCTIONS && t.rows == full.rows && t.waves == full.waves && t.buckets == full.buckets &&
+        t.rows == 4) {
         const TilePlan six = tile_plan_for(bucket, 4, 6);
         const uint64_t waves = (num_buckets + (uint64_t)six.buckets - 1) / (uint64_t)six.buckets * 4;
         // as full: buckets a row, six rows against four
         const bool as_full = 100 * six.buckets * tile_groups(full.waves, 4) >= 95 * full.buckets * tile_groups(4, 6);
-        if (as_full && waves >= 4096) return six;
+        const bool few_ends = waves >= 20480 && num_buckets >= 512 * tensors * (uint64_t)six.buckets;
+        if (as_full && (tensors == 0 ? waves >= 4096 : few_ends)) return six;
     }
     return t;
 }
@@ -151,8 +155,8 @@ inline TilePlan choose_step_tile(int bucket, uint64_t num_buckets, uint64_t most
 // Whether a step on a flat vector, two fp32 operands in, weights and 8-bit codes on their min-max grids out, streams
 // faster with three workgroups to a compute unit than with the four that the registers of six rows allow: large vectors
 // in full tiles. us, four / three, buckets of 384, 768, 3040, where the tile is full: 96 * 2^20 elements 221 / 220, 220
-// / 218, 220 / 217, 125M 275 / 270, 278 / 266, 273 / 267, 300 * 2^20 710 / 666, 713 / 673, 723 / 676, with a 16-bit copy
-// or an unquantized partition 1-6 % at all of them. Below, 2^26 elements 147 / 164, 149 / 150, 148 / 147. In tiles
+// / 218, 220 / 217, 125M 275 / 270, 278 / 266, 273 / 267, 300 * 2^20 710 / 666, 713 / 673, 723 / 676, with a 16-bit
+// copy or an unquantized partition 1-6 % at all of them. Below, 2^26 elements 147 / 164, 149 / 150, 148 / 147. In tiles
 // filled to 92 % (704) 125M 266 / 281, to 97.9 % (1504) 273 / 270 and 2^26 147 / 150, to 81 % (4992) 125M 266 / 287.
 // 4-bit codes 125M 252 / 254, 256 / 255, 262 / 250, on a lattice 266 / 265, 270 / 266, 263 / 263. Over tensors, which
 // end inside tiles, 200 * 2^20 elements in buckets of 768, five / a hundred to a tensor, 580 / 719, 456 / 487. Without

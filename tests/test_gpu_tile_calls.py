@@ -1,7 +1,8 @@
 """The tile kernel against the oracle, bit for bit, in calls large enough for the tiles that only such calls take: two
 rows of four waves with several buckets (from about 2^19 elements, AdamW up to 2^23), six rows in the gradient encoder
-and the receive side (from about 2^22.5), three workgroups to a compute unit (large steps with codes). Every mode that
-is served, from 16-bit gradients, with 16-bit weights out, several peers, and over tensors that end inside tiles."""
+(from about 2^22.5, over a few large tensors 2^25), three workgroups to a compute unit (large steps with codes). Every
+mode that is served, from 16-bit gradients, with 16-bit weights out, several peers, and over tensors that end inside
+tiles."""
 import numpy as np
 import pytest
 import torch
@@ -85,6 +86,36 @@ def test_adamw_steps(B, elements):
         w = ref.dequantize(wc, wm, n, wbits, B)
         _, wmo, wvo, wc, wm, _ = ref.fused_adamw_step(w, g, wmo, wvo, *ADAMW, wbits, 4, B, delta, 10, 8, 0, True)
         assert _same(c, m, wc, wm) and bits_equal(np_f32(md), wmo) and bits_equal(np_f32(vd), wvo), (wbits, delta)
+
+
+@pytest.mark.parametrize("B", [32, 160, 544])
+def test_gradient_encoder(B):
+    n = _ragged(7 << 20, B)
+    _, g = synth(n, B, heavy=False)
+    for dtype, bits, flags in ((torch.float32, 3, 0), (torch.bfloat16, 4, 0),
+                               (torch.float16, 8, qb.QSDP_FLAG_GRAD_SHIFT)):
+        gd = _dev(g, dtype)
+        c, m = qb.alloc_packed(n, bits, B, DEV)
+        if dtype == torch.float32:
+            qb.qsdp_quantize_grad_ex(gd, bits, B, 5, 24, flags, c, m.view(-1))
+        else:
+            qb.qsdp_quantize_grad_g16(gd, bits, B, 5, 24, c, m.view(-1), flags)
+        assert _same(c, m, *ref.quantize_grad(gd.float().cpu().numpy(), bits, B, 5, 24, flags)), (dtype, bits)
+
+
+@pytest.mark.parametrize("B", [32, 160, 544])
+def test_gradients_of_a_few_large_tensors(B):
+    n = 9 << 22
+    sizes = [12 * (1 << 20) + 24, 11 * (1 << 20) - 8]
+    sizes.append(n - sum(sizes) + 5)
+    g = wl.grads_student_t3(sum(sizes), 1252, DEV).cpu()
+    segs = qb.Segments(sizes, B, DEV)
+    c, m = segs.alloc_packed(4)
+    qb.qsdp_quantize_grad_segmented(g.to(DEV), segs, 4, 6, 64, c, m.view(-1))
+    offsets = np.concatenate([[0], np.cumsum(sizes)])
+    wc, wm = zip(*(ref.quantize_grad(g.numpy()[a:b], 4, B, 6, index_offset=64 + int(a))
+                   for a, b in zip(offsets[:-1], offsets[1:])))
+    assert _same(c, m, np.concatenate(wc), np.concatenate(wm))
 
 
 @pytest.mark.parametrize("B", [96, 160, 544, 768])
