@@ -21,18 +21,19 @@ namespace qsdp {
 // atomic is left in the chain; two LDS round trips for the boundary, one for the powers of 1 - lr and the reciprocals
 // of the counts. A team of W producer waves sorts a batch (the values stay in registers, at most 16 to a lane) and P
 // teams make a round: W = 1, P = 6 or 7 for buckets of up to 1024 values (one wave needs no barrier between its passes;
-// at 1024 six sort more slowly than the consumer walks: 0.53 us per batch, 5 bits, where seven take 0.49, and eight are
+// at 1024 six sort more slowly than the consumer walks: 0.53 us per batch, 5 bits, where seven take 0.48, and eight are
 // no faster), W = 2, 4, 8 and P = 8 / W up to 2048, 4096, 8192 with a barrier after each of the four passes. The
 // consumer meanwhile walks the P batches of the round before; the slots are double-buffered.
 //
-// Measured (us per batch, 5-bit table, Gaussian values, buckets of 128 / 352 / 1024 / 4096 / 8192): 0.40 / 0.43 / 0.49
-// / 1.74 / 3.3, against 1.27 / - / 2.6 / 10.7 / 21 for a workgroup that stages one batch in LDS and assigns value by
+// Measured (us per batch, 5-bit table, Gaussian values, buckets of 128 / 352 / 1024 / 4096 / 8192): 0.40 / 0.43 / 0.48
+// / 1.73 / 3.3, against 1.27 / - / 2.6 / 10.7 / 21 for a workgroup that stages one batch in LDS and assigns value by
 // value with a barrier around each part; the 292 tables of the 350M model 2.85 -> 0.51 ms. The chain is latency: about
-// 950 cycles of dependent LDS reads, comparisons and binary64 steps per batch. The sorting is bound by LDS, about a
-// value per cycle and compute unit: an atomic, a read and a write to random places take 15 + 16 + 11 cycles for the 64
-// lanes of a wave. Lanes without a value therefore make none of them: on one place, as they did when they added zero to
-// their neighbour's cell, they meet in turn (buckets of 352 / 736, 5 bit: 0.56 / 0.69 -> 0.43 / 0.50 us per batch, 3040,
-// 4 bit: 2.4 -> 1.8).
+// 950 cycles of dependent LDS reads, comparisons and binary64 steps per batch. Beyond 512 values the sorting binds,
+// with LDS in use for half of the cycles (1024 / 4096: 607 of 1,170, 2,090 of 4,160, bank conflicts 340 and 1,240 of
+// them; an atomic, a read and a write to random places take 15 + 16 + 11 cycles for the 64 lanes of a wave) and
+// producers that wait for their answers pass after pass in the rest. Lanes without a value make no access: on one
+// place, as they did when they added zero to their neighbour's cell, they meet in turn (buckets of 352 / 736, 5 bit:
+// 0.56 / 0.69 -> 0.43 / 0.50 us per batch, 3040, 4 bit: 2.4 -> 1.8).
 // Tensors of few batches are bound by what a workgroup does before its first one, the table of powers above all (one
 // batch of 1024, 4 bit: 32 us when the whole table was filled first, 10 us now, against 16 us for the workgroup that
 // staged its batches), and by one workgroup of this size to a compute unit: 2000 such tensors 240 -> 46 us (53 us then;
@@ -62,11 +63,11 @@ template <int BITS, int VPT, int W>
 struct FitShape {
     static constexpr int kBucketMax = 64 * W * VPT;
     // Buckets of 129-256 keep six producers: seven ask for more than a third of a compute unit's LDS, and the chain is
-    // no faster with them (us, six / seven, 5 bits, buckets of 160 and 256: one tensor 163 / 163, 164 / 163 per 400
-    // batches, 700 tensors of two 8.6 / 11.5, 8.7 / 11.6; 2000 of three at 8 bits 30 / 37, 32 / 40). So do tables of up to
-    // 8 levels with buckets of 257-512: 200 tensors of one bucket of 512, 1 / 2 / 3 bits, 9.6 / 11.8, 8.3 / 10.0, 6.5 /
-    // 7.3, 400 batches of one tensor 173 / 173, 178 / 180, 177 / 178 (at 4 bits seven are as fast or faster: 2000
-    // tensors 17.1 for 18.8).
+    // no faster with them (us, six / seven, 5 bits, buckets of 160 and 256: 400 batches of one tensor 163 / 163, 164 /
+    // 163, 700 tensors of two 8.6 / 11.5, 8.7 / 11.6; 2000 of three at 8 bits 30 / 37, 32 / 40). So do tables of up to
+    // 8 levels with buckets of 257-512: 200 tensors of one bucket of 512, 1 / 2 / 3 bits, 9.6 / 11.8, 8.3 / 10.0, 6.5
+    // / 7.3, 400 batches of one tensor 173 / 173, 178 / 180, 177 / 178 (at 4 bits seven are faster: 2000 tensors 17.1
+    // for 18.8).
     static constexpr bool kSixProducers = VPT == 4 || (VPT == 8 && BITS <= 3);
     static constexpr int kBatches = W > 1 ? 8 / W : kSixProducers ? 6 : 7;  // P, batches per round
     static constexpr int kProducers = kBatches * W;              // producer waves; the consumer is one more
