@@ -156,14 +156,18 @@ inline TilePlan choose_step_tile(int bucket, uint64_t num_buckets, uint64_t most
 // faster with three workgroups to a compute unit than with the four that the registers of six rows allow: large vectors
 // in full tiles. us, four / three, buckets of 384, 768, 3040, where the tile is full: 96 * 2^20 elements 221 / 220, 220
 // / 218, 220 / 217, 125M 275 / 270, 278 / 266, 273 / 267, 300 * 2^20 710 / 666, 713 / 673, 723 / 676, with a 16-bit
-// copy or an unquantized partition 1-6 % at all of them. Below, 2^26 elements 147 / 164, 149 / 150, 148 / 147. In tiles
-// filled to 92 % (704) 125M 266 / 281, to 97.9 % (1504) 273 / 270 and 2^26 147 / 150, to 81 % (4992) 125M 266 / 287.
-// 4-bit codes 125M 252 / 254, 256 / 255, 262 / 250, on a lattice 266 / 265, 270 / 266, 263 / 263. Over tensors, which
-// end inside tiles, 200 * 2^20 elements in buckets of 768, five / a hundred to a tensor, 580 / 719, 456 / 487. Without
+// copy or an unquantized partition 1-6 % at all of them. Below, 2^26 elements 147 / 164, 149 / 150, 148 / 147. Tiles
+// filled to 95-98 %: of four waves (buckets of 1184, 2944, 3008, 5952, 6016) 3 * 2^25 elements 219 / 216, 212 / 214,
+// 228 / 220, 228 / 220, 221 / 214, 160M 361 / 342, 349 / 330, 347 / 335, 343 / 337, 358 / 342, 300 * 2^20 1-6 % faster;
+// of one wave (1472, 1504) 3 * 2^25 206 / 217, 218 / 220, 140 * 2^20 326 / 316, 327 / 318, 160M 356 / 344, 361 / 347,
+// 300 * 2^20 641 / 655, 645 / 656. To 92 % (704) 125M 264 / 275, 300 * 2^20 637 / 674, to 81 % (4992) 266 / 287. 4-bit
+// codes 125M 252 / 254, 256 / 255, 262 / 250, on a lattice 266 / 265, 270 / 266, 263 / 263. Over tensors, which end
+// inside tiles, 200 * 2^20 elements in buckets of 768, five / a hundred to a tensor, 580 / 719, 456 / 487. Without
 // codes 125M 241 / 245. code_bits: 0 without codes.
 inline bool three_workgroups_stream(int bucket, int buckets, int waves, int rows, uint64_t n, bool tensors,
                                     bool half_gradient, int code_bits, bool lattice) {
-    return rows == 6 && n >= (3ull << 25) && 100 * buckets * (bucket / 32) >= 98 * tile_groups(waves, rows) &&
+    const int filled = waves == 4 || n >= (1ull << 27) ? 95 : 98;
+    return rows == 6 && n >= (3ull << 25) && 100 * buckets * (bucket / 32) >= filled * tile_groups(waves, rows) &&
            !tensors && !half_gradient && code_bits == 8 && !lattice;
 }
 

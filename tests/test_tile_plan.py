@@ -157,13 +157,14 @@ static bool three(int bucket, uint64_t n, bool tensors = false, bool half = fals
 int main() {
     const uint64_t large = 3ull << 25;
     int bad = 0;
-    for (int bucket : {384, 608, 768, 864, 1536, 3040, 6048, 6144}) {
+    for (int bucket : {384, 608, 768, 864, 1184, 1536, 2944, 3008, 3040, 5952, 6016, 6048, 6144}) {
         bad += !three(bucket, large) + three(bucket, large - 1) + three(bucket, large, true);
         bad += three(bucket, large, false, true) + three(bucket, large, false, false, 0);
         bad += three(bucket, large, false, false, 4) + three(bucket, large, false, false, 8, true);
     }
-    for (int bucket : {32, 160, 224, 288, 704, 736, 800, 1472, 2016, 2080, 4128, 4992, 8192})
-        bad += three(bucket, large);
+    for (int bucket : {736, 1472, 1504}) bad += three(bucket, (1ull << 27) - 1) + !three(bucket, 1ull << 27);
+    for (int bucket : {32, 160, 224, 288, 416, 704, 800, 2016, 2080, 4128, 4992, 8192})
+        bad += three(bucket, large) + three(bucket, 1ull << 28);
     return bad != 0;
 }
 """
