@@ -36,7 +36,7 @@ WAVE_SHAPES = {128: (8, 4, 1), 256: (16, 4, 1), 512: (32, 4, 1), 1024: (64, 4, 1
 # team shapes of the tile kernel, which serves every other bucket size: (waves, rows)
 TILE_SHAPES = [(1, 2), (4, 2), (1, 4), (1, 6), (1, 8), (4, 4), (4, 6), (4, 8)]
 # shapes of the level fit: (values per lane, waves per batch), for buckets of up to 64 * values * waves
-FIT_SHAPES = [(2, 1), (4, 1), (8, 1), (16, 1), (16, 2), (16, 4), (16, 8)]
+FIT_SHAPES = [(2, 1), (4, 1), (8, 1), (16, 1), (32, 1), (16, 4), (16, 8)]
 
 
 def _units():

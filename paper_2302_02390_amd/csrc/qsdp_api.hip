@@ -103,7 +103,7 @@ static hipError_t launch_fit_levels(const FitParams& p, unsigned grid, hipStream
     if (p.bucket <= 256) return launch_fit_4_1(p, grid, s);
     if (p.bucket <= 512) return launch_fit_8_1(p, grid, s);
     if (p.bucket <= 1024) return launch_fit_16_1(p, grid, s);
-    if (p.bucket <= 2048) return launch_fit_16_2(p, grid, s);
+    if (p.bucket <= 2048) return launch_fit_32_1(p, grid, s);
     if (p.bucket <= 4096) return launch_fit_16_4(p, grid, s);
     return launch_fit_16_8(p, grid, s);
 }

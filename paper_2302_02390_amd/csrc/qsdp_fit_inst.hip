@@ -1,5 +1,7 @@
 // Instantiations of the level fit for one shape; compiled with -DQSDP_FIT_V=<values per lane> and
-// -DQSDP_FIT_W=<waves per batch>: buckets of up to 64 * V * W values.
+// -DQSDP_FIT_W=<waves per batch>: buckets of up to 64 * V * W values; W = 1
+// (qsdp_fit_kernel.hpp) or more (qsdp_fit_rounds.hpp).
+#include "qsdp_fit_rounds.hpp"
 #include "qsdp_launch.hpp"
 
 #if !defined(QSDP_FIT_V) || !defined(QSDP_FIT_W)
@@ -11,12 +13,18 @@
 
 namespace qsdp {
 
+#if QSDP_FIT_W > 1
+namespace kernels = fit_rounds;
+#else
+namespace kernels = qsdp;
+#endif
+
 namespace {
 
 template <int BITS>
 hipError_t go(const FitParams& p, unsigned grid, hipStream_t s) {
-    hipLaunchKernelGGL((fit_levels_kernel<BITS, QSDP_FIT_V, QSDP_FIT_W>), dim3(grid),
-                       dim3(FitShape<BITS, QSDP_FIT_V, QSDP_FIT_W>::kThreads), 0, s, p);
+    hipLaunchKernelGGL((kernels::fit_levels_kernel<BITS, QSDP_FIT_V, QSDP_FIT_W>), dim3(grid),
+                       dim3(kernels::FitShape<BITS, QSDP_FIT_V, QSDP_FIT_W>::kThreads), 0, s, p);
     return hipGetLastError();
 }
 

@@ -1,6 +1,8 @@
 // Level fitting (Algorithm 1 in batched form).
 #pragma once
 
+#include <type_traits>
+
 #include "qsdp_params.hpp"
 
 namespace qsdp {
@@ -14,31 +16,30 @@ namespace qsdp {
 // The serial chain of batches bounds this, so the chain holds as little as possible. What a batch needs from the
 // levels is, for each pair of neighbours, how many values lie on the lower one's side and their sum; the normalised
 // values themselves do not depend on the levels. Producer waves therefore sort the coming batches into cells of the
-// unit interval (a counting sort: one LDS atomic per value returns the place within the cell and adds up count and
-// sum, packed into one word; a prefix sum over the cells follows), and one consumer wave walks the chain: a lane per
-// pair of neighbours reads the prefix at the cell of the midpoint, compares the few values of that cell with the two
-// levels, and has count and sum below the boundary; differences between lanes are the levels' own. No barrier and no
-// atomic is left in the chain; two LDS round trips for the boundary, one for the powers of 1 - lr and the reciprocals
-// of the counts. A team of W producer waves sorts a batch (the values stay in registers, at most 16 to a lane) and P
-// teams make a round: W = 1, P = 6 or 7 for buckets of up to 1024 values (one wave needs no barrier between its passes;
-// at 1024 six sort more slowly than the consumer walks: 0.53 us per batch, 5 bits, where seven take 0.48, and eight are
-// no faster), W = 2, 4, 8 and P = 8 / W up to 2048, 4096, 8192 with a barrier after each of the four passes. The
-// consumer meanwhile walks the P batches of the round before; the slots are double-buffered.
+// unit interval (a counting sort: one LDS atomic per value returns the place within the cell, a prefix sum over the
+// cells follows), with count and sum before every fourth value of the sorted batch, and one consumer wave walks the
+// chain: a lane per pair of neighbours reads where the cell of the midpoint starts, compares the few values from there
+// on with the boundary, and adds what lies before them; differences between lanes are the levels' own.
 //
-// Measured (us per batch, 5-bit table, Gaussian values, buckets of 128 / 352 / 1024 / 4096 / 8192): 0.40 / 0.43 / 0.48
-// / 1.73 / 3.3, against 1.27 / - / 2.6 / 10.7 / 21 for a workgroup that stages one batch in LDS and assigns value by
-// value with a barrier around each part; the 292 tables of the 350M model 2.85 -> 0.51 ms. The chain is latency: about
-// 950 cycles of dependent LDS reads, comparisons and binary64 steps per batch. Beyond 512 values the sorting binds,
-// with LDS in use for half of the cycles (1024 / 4096: 607 of 1,170, 2,090 of 4,160, bank conflicts 340 and 1,240 of
-// them; an atomic, a read and a write to random places take 15 + 16 + 11 cycles for the 64 lanes of a wave) and
-// producers that wait for their answers pass after pass in the rest. Lanes without a value make no access: on one
-// place, as they did when they added zero to their neighbour's cell, they meet in turn (buckets of 352 / 736, 5 bit:
-// 0.56 / 0.69 -> 0.43 / 0.50 us per batch, 3040, 4 bit: 2.4 -> 1.8).
-// Tensors of few batches are bound by what a workgroup does before its first one, the table of powers above all (one
-// batch of 1024, 4 bit: 32 us when the whole table was filled first, 10 us now, against 16 us for the workgroup that
-// staged its batches), and by one workgroup of this size to a compute unit: 2000 such tensors 240 -> 46 us (53 us then;
-// 2 bit, whose counts ask for more powers: 240 -> 103 us, 57 us then). Producers without a batch sort nothing (they
-// sorted the last one again: 2000 tensors of one batch of 512, 4 bit, 25.8 -> 20.2 us).
+// A producer sorts a batch of up to 2048 values by itself (up to 32 to a lane, in registers; larger buckets:
+// qsdp_fit_rounds.hpp), so its passes need no barrier. P producers and the consumer share a ring of slots: a producer
+// starts on a slot when the consumer has counted the batch that it held as read, the consumer on a batch when the slot
+// shows its number. Both words are in LDS, whose accesses are processed in order for each wave, and all waves of the
+// workgroup are resident, so every wait ends. With a barrier per round of P batches in its place, and slots for two
+// rounds, the consumer waited for the slowest producer of each round.
+//
+// What bounds the chain is latency, in this order: an instruction that needs the result of the one before waits 8
+// cycles for it (others issue every 4), an LDS read takes 56-70, a branch on a lane's comparison 36, a taken one 20. So
+// everything that does not depend on the answer in flight is computed while it is on the way (the exact boundary while
+// the cells' places are read, the reciprocal of the count while its power is), one branch leaves the straight line for
+// everything that is rare, and what the next batch needs is requested a batch ahead. A boundary has one comparison per
+// value: the first value on its upper side is the rounded midpoint or the one after it. Measured (us per batch,
+// Gaussian values, one table of 32 levels, buckets of 128 / 352 / 512 / 1024 / 2048): 0.33 / 0.35 / 0.35 / 0.38 / 0.65,
+// against 0.40 / 0.43 / 0.44 / 0.48 / 0.91 with barriers, 64-bit words in the cells, two rounded distances per value
+// and a table of reciprocals; 6 bits, 1024: 0.58 -> 0.40; the 292 tables of the 350M model 507 -> 392 us. Up to 512
+// values the chain binds, 790 cycles; at 1024 both do (seven producers 0.39, nine 0.41, eleven 0.38, thirteen 0.39), at
+// 2048 the sorting, of which LDS holds room for eight slots. Tensors of few batches are bound by what a workgroup does
+// before its first one, the table of powers above all, and by one workgroup of this size to a compute unit.
 //
 // The boundary search needs levels that ascend by more than 2^-20 within [0, 1] (then the comparison of the two
 // rounded distances is monotone in the value and flips within 2^-22 of the midpoint) and cells that are not
@@ -55,59 +56,71 @@ struct FitParams {
     float lr;
 };
 
-// Shape of a workgroup: W waves to a batch of up to 64 * W * VPT values.
+// Shape of a workgroup: a producer sorts a batch of up to 64 * VPT values.
 template <int BMAX, int C>
 struct FitSlot;
 
 template <int BITS, int VPT, int W>
 struct FitShape {
-    static constexpr int kBucketMax = 64 * W * VPT;
-    // Buckets of 129-256 keep six producers: seven ask for more than a third of a compute unit's LDS, and the chain is
-    // no faster with them (us, six / seven, 5 bits, buckets of 160 and 256: 400 batches of one tensor 163 / 163, 164 /
-    // 163, 700 tensors of two 8.6 / 11.5, 8.7 / 11.6; 2000 of three at 8 bits 30 / 37, 32 / 40). So do tables of up to
-    // 8 levels with buckets of 257-512: 200 tensors of one bucket of 512, 1 / 2 / 3 bits, 9.6 / 11.8, 8.3 / 10.0, 6.5
-    // / 7.3, 400 batches of one tensor 173 / 173, 178 / 180, 177 / 178 (at 4 bits seven are faster: 2000 tensors 17.1
-    // for 18.8).
-    static constexpr bool kSixProducers = VPT == 4 || (VPT == 8 && BITS <= 3);
-    static constexpr int kBatches = W > 1 ? 8 / W : kSixProducers ? 6 : 7;  // P, batches per round
-    static constexpr int kProducers = kBatches * W;              // producer waves; the consumer is one more
-    static constexpr int kThreads = 64 * (kProducers + 1);
-    static constexpr int kBarriers = W == 1 ? 1 : 4;             // per round
-    // About a cell per value, as far as the 2 P slots leave LDS to spare. Half of that for buckets of 512 and up to
-    // 16 levels, where it lets two workgroups share a compute unit at no cost to the chain (2000 tensors of one
-    // batch, 4 bit: 33.7 -> 23.3 us; with more levels the chain loses: 5 bit 0.49 -> 0.53 us per batch, 6 bit 0.56 ->
-    // 0.65).
-    static constexpr int kCells = kBucketMax <= 256                ? kBucketMax
-                                  : kBucketMax == 512 && BITS <= 4 ? 256
-                                  : kBucketMax <= 2048             ? 512
-                                                                   : 1024;
+    static_assert(W == 1, "a wave to a batch");
+    static constexpr int kBucketMax = 64 * VPT;
+    // Six producers for buckets of 129-256 and, with up to 8 levels, of 257-512: seven leave room for fewer workgroups
+    // on a compute unit, and the chain is no faster with them. Eleven for 513-1024, three waves to a SIMD with the
+    // consumer; of the largest buckets LDS holds eight batches.
+    static constexpr int kProducers = VPT == 16                             ? 11
+                                      : VPT == 4 || (VPT == 8 && BITS <= 3) ? 6
+                                                                            : 7;
+    static constexpr int kSlots = VPT == 32 ? 8 : VPT == 16 ? 14 : 2 * kProducers;
+    static_assert(kProducers <= kSlots, "a slot for every producer");
+    static constexpr int kThreads = 64 * (kProducers + 1);  // and the consumer
+    // About a cell per value (the middle of a Gaussian batch has two and a half to a cell), with more levels two cells:
+    // a lane sees four or eight values from a group's start on at once, and one boundary that has more costs all of
+    // them another read (1024, 5 bits: 0.52 us per batch with half the cells).
+    static constexpr int kCells = VPT >= 16 ? 1024 : (BITS >= 5 ? 2 : 1) * kBucketMax;
     using Slot = FitSlot<kBucketMax, kCells>;
 };
 
 // Count and sum of a set of normalised values in one word: sum of at most 2^13 values of at most 2^32 below, count
 // above.
-constexpr int kFitCountShift = 46;
+constexpr int kFitCountShift = 48;
 constexpr uint64_t kFitSumMask = (1ull << kFitCountShift) - 1;
 
-// What follows the values of a batch: above every boundary, as many as the consumer reads at once.
-constexpr float kFitFiller = 2.0f;
-constexpr int kFitSpare = 16;
+// The normalised values are held in units of 2^-32, an exact scaling, so that their fixed-point form is a conversion.
+constexpr float kFitUnit = 0x1p32f;
 
-// z (in [0, 1]) in 32.32 fixed point, truncated: exact scaling, the integer and the fraction converted apart.
-__device__ __forceinline__ uint64_t fit_fixed(float z) {
-    const uint32_t whole = (uint32_t)z;
-    return ((uint64_t)whole << 32) | (uint32_t)((z - (float)whole) * 4294967296.0f);
+// What follows the values of a batch: above every boundary, as many as the consumer reads at once.
+constexpr float kFitFiller = 2.0f * kFitUnit;
+constexpr int kFitSpare = 20;
+
+// z (in [0, 1], units of 2^-32) as an integer, truncated, and a count of one. The conversion saturates at the largest
+// z, below 1 it never gives all ones.
+__device__ __forceinline__ uint64_t fit_word(float z) {
+    const uint32_t fraction = (uint32_t)z;
+    const bool one = fraction == ~0u;
+    return ((uint64_t)((1u << (kFitCountShift - 32)) + (one ? 1u : 0u)) << 32) | (one ? 0u : fraction);
 }
 
-// The cell of a value (or of a boundary): C cells of equal width from `from` on, what lies outside them in the first
-// and the last. Monotone, and in range whatever the argument (the conversion saturates).
+// The cell of a value: C cells of equal width, what lies outside them in the first and the last. Monotone, and in range
+// whatever the argument (the conversion saturates).
 struct FitCells {
-    float from, per_unit;
+    float origin, per_unit;
 };
 template <int C>
 __device__ __forceinline__ uint32_t fit_cell(float z, FitCells cells) {
-    const uint32_t c = (uint32_t)((z - cells.from) * cells.per_unit);
+    const uint32_t c = (uint32_t)fmaf(z, cells.per_unit, cells.origin);
     return c < (uint32_t)C ? c : (uint32_t)(C - 1);
+}
+
+// The same cells as the consumer asks for them, of a boundary halfway between two levels whose sum is s: the first
+// cell that may hold values on both sides is that of s * half_unit + before, the one past the last that of s *
+// half_unit + past. The margin of 2^-20 of the unit interval covers the 2^-22 within which the comparison flips and
+// the roundings here and in fit_cell (each below 2^-23; `origin`, with whatever error, is the same in both).
+struct FitBoundary {
+    float half_unit, before, past;
+};
+__device__ __forceinline__ FitBoundary fit_boundary(FitCells cells) {
+    const float margin = 0x1p-20f * cells.per_unit;
+    return {0.5f * cells.per_unit, cells.origin - margin, cells.origin + margin + 1.0f};
 }
 
 // The cells for a batch: over its mean +- four times its mean magnitude, within its range [lo, hi]. That is the whole
@@ -118,7 +131,8 @@ __device__ __forceinline__ FitCells fit_cells(const MinMaxGrid& grid, float hi, 
     const float from = fmaxf(grid.lo, mean - 4.0f * magnitude);
     const float to = fminf(hi, mean + 4.0f * magnitude);
     const float width = (to - from) * grid.inv;
-    const FitCells inner = {(from - grid.lo) * grid.inv, (float)C / width};
+    const float per_unit = (float)C / width;
+    const FitCells inner = {(grid.lo - from) * grid.inv * per_unit, per_unit};
     const FitCells all = {0.0f, (float)C};
     return width > 0x1p-20f && width <= 2.0f ? inner : all;
 }
@@ -144,44 +158,62 @@ __device__ __forceinline__ float fit_wave_sum(float v) {
     return a + b;
 }
 
-// Inclusive prefix sum over the lanes of a wave.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ uint64_t fit_scan_step(uint64_t v) {
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, ROWS, 0xF, false);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), CTRL, ROWS, 0xF, false);
-    return v + (((uint64_t)hi << 32) | lo);
+// Inclusive prefix sums over the lanes of a wave, of N values side by side.
+template <int CTRL, int ROWS, int N>
+__device__ __forceinline__ void fit_scan_step(uint32_t (&v)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v[i], CTRL, ROWS, 0xF, false);
 }
-__device__ __forceinline__ uint64_t fit_wave_scan(uint64_t v) {
-    v = fit_scan_step<0x111, 0xF>(v);  // row_shr:1, 2, 4, 8: within rows of 16 lanes
-    v = fit_scan_step<0x112, 0xF>(v);
-    v = fit_scan_step<0x114, 0xF>(v);
-    v = fit_scan_step<0x118, 0xF>(v);
-    v = fit_scan_step<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
-    v = fit_scan_step<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
-    return v;
+template <int N>
+__device__ __forceinline__ void fit_wave_scan(uint32_t (&v)[N]) {
+    fit_scan_step<0x111, 0xF>(v);  // row_shr:1, 2, 4, 8: within rows of 16 lanes
+    fit_scan_step<0x112, 0xF>(v);
+    fit_scan_step<0x114, 0xF>(v);
+    fit_scan_step<0x118, 0xF>(v);
+    fit_scan_step<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
+    fit_scan_step<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
 }
 
-// Sum over the lanes l, l + 64/S, l + 2 * 64/S, ... (S = 1, 2, 4).
+// Halves of a word of count and sum. Additions are of whole words (one instruction, with halves in registers of their
+// own two and a wait between them), so what the halves are put together to is hidden from the compiler.
+struct FitWord {
+    uint32_t low, high;
+};
+__device__ __forceinline__ FitWord fit_halves(uint64_t v) { return {(uint32_t)v, (uint32_t)(v >> 32)}; }
+__device__ __forceinline__ uint64_t fit_whole(FitWord v) {
+    uint64_t w = ((uint64_t)v.high << 32) | v.low;
+    asm("" : "+v"(w));
+    return w;
+}
+
+// Sum over the lanes l, l + 64/S, l + 2 * 64/S, ... (S = 1, 2, 4). The exchanges by hand: both copies, then one wait
+// for both (the compiler waits for each).
 template <int S>
-__device__ __forceinline__ uint64_t fit_sum_subs(uint64_t v) {
+__device__ __forceinline__ uint64_t fit_sum_subs(uint64_t sum) {
     if constexpr (S >= 2) {
-        const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)v, false, false);
-        const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(v >> 32), (uint32_t)(v >> 32), false, false);
-        v = (((uint64_t)hi[0] << 32) | lo[0]) + (((uint64_t)hi[1] << 32) | lo[1]);
+        FitWord v = fit_halves(sum), w;
+        asm("v_mov_b32 %2, %0\n\tv_mov_b32 %3, %1\n\ts_nop 1\n\tv_permlane32_swap_b32 %0, %2\n\t"
+            "v_permlane32_swap_b32 %1, %3" : "+v"(v.low), "+v"(v.high), "=&v"(w.low), "=&v"(w.high));
+        sum = fit_whole(v) + fit_whole(w);
     }
     if constexpr (S >= 4) {
-        const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)v, (uint32_t)v, false, false);
-        const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(v >> 32), (uint32_t)(v >> 32), false, false);
-        v = (((uint64_t)hi[0] << 32) | lo[0]) + (((uint64_t)hi[1] << 32) | lo[1]);
+        FitWord v = fit_halves(sum), w;
+        asm("v_mov_b32 %2, %0\n\tv_mov_b32 %3, %1\n\ts_nop 1\n\tv_permlane16_swap_b32 %0, %2\n\t"
+            "v_permlane16_swap_b32 %1, %3" : "+v"(v.low), "+v"(v.high), "=&v"(w.low), "=&v"(w.high));
+        sum = fit_whole(v) + fit_whole(w);
     }
-    return v;
+    return sum;
 }
 
 // Adds to a word in LDS and returns what it held. Relaxed: the callers put their own fences, and an ordered atomic
 // would wait for each one before the next.
-__device__ __forceinline__ uint64_t fit_add(uint64_t* word, uint64_t v) {
+template <typename T>
+__device__ __forceinline__ T fit_add(T* word, T v) {
     return __hip_atomic_fetch_add(word, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
+
+// Keeps the compiler from reordering LDS accesses of one wave, which are processed in order.
+__device__ __forceinline__ void fit_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
 // LDS traffic of one wave is processed in order; this keeps the compiler from reordering it.
 __device__ __forceinline__ void fit_wave_sync() {
@@ -203,23 +235,16 @@ template <int BMAX>
 struct FitPowers {
     static constexpr int kFine = BMAX < 1024 ? BMAX : 1024, kStep = 16, kCoarse = (BMAX - kFine) / kStep + 1;
     static_assert(kFine % 64 == 0, "grows by 64");
-    struct Entry {
-        double moved, reciprocal;  // 1 - (1-lr)^c, 1 / c
-    };
-    Entry fine[kFine + 1];
+    double fine[kFine + 1];  // 1 - (1-lr)^c
     double coarse[kCoarse];
 
-    __device__ void fill_reciprocals(int top, int thread, int threads) {
-        for (int c = thread; c <= kFine && c <= top; c += threads) fine[c].reciprocal = 1.0 / (double)(c > 0 ? c : 1);
-    }
-
     __device__ FitFilled start(int lane) {
-        if (lane == 0) fine[0].moved = 0.0;
+        if (lane == 0) fine[0] = 0.0;
         return {0, 1.0};
     }
 
     // The next 64 powers, or the next 16 of every kStep-th (one wave; the chain and its stores in one lane).
-    __device__ void extend(FitFilled& f, double one_minus, int lane) {
+    __device__ __forceinline__ void extend(FitFilled& f, double one_minus, int lane) {
         double keep = f.keep;
         if (f.count < kFine) {
             if (lane == 0) {
@@ -228,11 +253,11 @@ struct FitPowers {
 #pragma unroll 16
                 for (int i = 0; i < 64; ++i) {
                     keep *= one_minus;
-                    fine[first + i].moved = keep;
+                    fine[first + i] = keep;
                 }
             }
             fit_wave_sync();
-            double& mine = fine[f.count + 1 + lane].moved;
+            double& mine = fine[f.count + 1 + lane];
             mine = 1.0 - mine;
             f.count += 64;
         } else {
@@ -253,17 +278,23 @@ struct FitPowers {
         fit_wave_sync();
     }
 
-    // Where the level q lands after the c values of fixed-point sum `total` that are its own; c at most kFine. Without
-    // values it stays, whatever it holds.
-    static __device__ __forceinline__ float step(float level, uint32_t c, uint64_t total, Entry e) {
-        // total / c rounded once: t * (1/c) is off by at most 2 ulp, the remainder is exact (c is below 2^11, so it has
-        // at most 12 bits more than an ulp), and the corrected quotient is within 2^-50 ulp of t / c, which, t and c
-        // being integers below 2^46 and 2^11, is never closer than 2^-12 ulp to a rounding boundary without being
-        // a binary64 number itself
-        const double q = (double)level, t = (double)total;
-        const double a = t * e.reciprocal;
-        const double mean = fma(fma(-a, (double)c, t), e.reciprocal, a) * (1.0 / 4294967296.0);
-        return c == 0u ? level : (float)(q - e.moved * (q - mean));
+    // Where the level lands after the c values (at most kFine) of fixed-point sum `total` that are its own, given
+    // 1 - (1-lr)^c. Without values it stays, whatever it holds. Everything but the last three steps is computed while
+    // that power is on its way, the reciprocal of the count among it.
+    static __device__ __forceinline__ float step(float level, uint32_t c, uint64_t total, double moved) {
+        // total / c rounded once: r, the approximate reciprocal, is off by at most 2^-23 of itself, so a by 2^-22 and,
+        // corrected once, by 2^-44, 2^9 ulp; its remainder is exact (c is at most 2^10: below 2^20 ulp), and the
+        // quotient corrected again is within 2^-13 ulp of t / c, which, t * 2^32 and c being integers below 2^46 and
+        // 2^11, is never closer than 2^-11 ulp to a rounding boundary without being a binary64 number itself. (The
+        // first remainder, below 2^42 ulp, is exact too.) Without values it is not used.
+        const double n = (double)c;
+        const double r = (double)__builtin_amdgcn_rcpf((float)c);
+        const double q = (double)level;
+        const double t = fma((double)(uint32_t)total, 0x1p-32, (double)(uint32_t)(total >> 32));
+        const double rough = t * r;
+        const double a = fma(fma(-rough, n, t), r, rough);
+        const double mean = fma(fma(-a, n, t), r, a);
+        return c == 0u ? level : (float)(q - moved * (q - mean));
     }
 
     // The same for any c.
@@ -278,113 +309,193 @@ struct FitPowers {
     }
 };
 
-// A batch as the consumer reads it: the values grouped by cell (ascending cells, any order within one), and for every
-// cell count and sum of the values in the cells before it; cell C: of all values.
-// The prefix sum gives a lane kOwn cells in a row; one word of padding after each of these runs keeps the lanes off
-// one another's banks (without it all 64 lanes meet in two banks: 0.15 us more per batch of 1024).
+// A batch as the consumer reads it: the values grouped by cell (ascending cells, any order within one), the place of
+// every cell's first value, and count and sum of the values before every fourth one. The place of cell C is
+// the number of values rounded up to a multiple of four; the word before that place is that of all values.
 template <int BMAX, int C>
-struct FitSlot {
+struct alignas(16) FitSlot {
     static constexpr int kValues = BMAX;
-    static constexpr int kOwn = C / 64;
-    static __device__ __forceinline__ uint32_t at(uint32_t c) { return c + (kOwn > 1 ? c / kOwn : 0u); }
-    uint64_t cell[C + 64 + 1];  // cell c at at(c)
-    float z[BMAX + kFitSpare];  // grouped by cell, kFitSpare fillers past the last one
-    FitCells cells;
+    static constexpr int kGroups = BMAX / 4;
+    uint32_t cell[C + 1];  // the last one: the end
+    uint32_t ready;        // the batch's number + 1
+    FitBoundary boundary;
+    uint32_t unused[3];
+    uint64_t before[kGroups + 2];
+    float z[BMAX + kFitSpare];  // units of 2^-32, grouped by cell, kFitSpare fillers past the last one
 };
 
-// Level k of the table for lane l: k = 64 * i + (l mod (64 / S)), i < M. S lanes share a level's work.
+// Level k of the table for lane l: k = M * (l mod (64 / S)) + i, i < M. S lanes share a level's work.
 template <int BITS>
 struct FitLanes {
     static constexpr int K = 1 << BITS;
     static constexpr int S = K <= 16 ? 4 : K <= 32 ? 2 : 1;
     static constexpr int M = K <= 64 ? 1 : K / 64;
+    // Groups of four values that a lane reads at once: two where a level has one lane (us per batch of 128 / 1024, one
+    // group and two: 7 bits 0.74 / 0.82 and 0.54 / 0.64, 8 bits 1.25 / 1.43 and 0.94 / 1.19; 5 bits, two lanes to a
+    // level, 0.33 / 0.37 and 0.36 / 0.40).
+    static constexpr int G = S == 1 ? 2 : 1;
 };
 
-// One batch of the chain. lv[i]: the lane's levels, updated. lv_shared, acc: K entries of LDS each, for batches that
-// are assigned value by value.
-template <int BITS, typename Slot, typename Powers, int C>
-__device__ __forceinline__ void fit_batch(const Slot& slot, int m, Powers& powers, FitFilled& filled, double one_minus,
-                                          FitCells cells, float (&lv)[FitLanes<BITS>::M], float* lv_shared,
-                                          uint64_t* acc, int lane) {
-    constexpr int K = FitLanes<BITS>::K, S = FitLanes<BITS>::S, M = FitLanes<BITS>::M;
-    // Values a lane reads at once, one after the other in the slot: one address, no question of range (below), half
-    // the instructions of a read, test and sum for each on its own (6 bits 0.66 -> 0.59 us per batch of 1024, 5 bits
-    // 0.43 -> 0.40 per batch of 128). Eight of them where two lanes share a level are slower (0.46).
-    constexpr int U = M == 4 ? 2 : 4;
-    static_assert(S * U <= kFitSpare, "reads past the last value");
-    // values in a boundary's cells from which the plain assignment of the batch is faster
-    const uint32_t crowded = (uint32_t)(m * S * U / (48 * M)) + 64u;
+// What the consumer knows of the batch to come.
+struct FitNext {
+    FitBoundary boundary;
+    uint32_t ready;
+};
+template <typename Slot>
+__device__ __forceinline__ FitNext fit_next(const Slot& slot) {
+    FitNext next;
+    next.ready = __hip_atomic_load(&slot.ready, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    fit_order();
+    next.boundary = slot.boundary;
+    return next;
+}
+
+// The lanes with a level that is not in [0, 1]. One that is stays there: it moves towards a mean of values in [0, 1].
+template <int M>
+__device__ __forceinline__ uint64_t fit_outside(const float (&lv)[M]) {
+    uint64_t outside = 0;
+#pragma unroll
+    for (int i = 0; i < M; ++i) outside |= __builtin_amdgcn_ballot_w64(!(lv[i] >= 0.0f && lv[i] <= 1.0f));
+    return outside;
+}
+
+// One batch of the chain. lv[i]: the lane's levels, updated; next: what is known of the batch, and then of the one in
+// next_slot; outside: the lanes with a level that is not in [0, 1]; boundaries: those whose last level has one above
+// it; not_first: 0 in the lanes of the first level; crowded: values in a boundary's cells from which the plain
+// assignment is faster; count(): the batch's values; done(): the slot has been read; lv_shared, acc: K entries of LDS
+// each, for batches that are assigned value by value.
+template <int BITS, typename Slot, typename Powers, int C, typename Count, typename Done>
+__device__ __forceinline__ void fit_batch(const Slot& slot, const Slot& next_slot, FitNext& next, uint64_t& outside,
+                                          uint64_t boundaries, uint32_t not_first,
+                                          uint32_t crowded, int bucket, Count count, Done done, Powers& powers,
+                                          FitFilled& filled, double one_minus, float (&lv)[FitLanes<BITS>::M],
+                                          float* lv_shared, uint64_t* acc, int lane) {
+    constexpr int K = FitLanes<BITS>::K, S = FitLanes<BITS>::S, M = FitLanes<BITS>::M, G = FitLanes<BITS>::G;
+    static_assert(4 * S * G <= kFitSpare - 4, "reads past the last value");
     const int sub = S > 1 ? lane / (64 / S) : 0;
     const int k0 = S > 1 ? lane % (64 / S) : lane;
-    uint64_t upto[M];  // count and sum of the values of levels 0 .. k
-    float hi[M];
+    const FitBoundary boundary = next.boundary;
+    const float* values = slot.z + 4 * sub;
+    float threshold[M];  // the values below it are on the lower one's side
     uint32_t pos[M], end[M];
-    bool plain = false;
+    uint64_t narrow = 0;
+    float upper_level[M];
 #pragma unroll
     for (int i = 0; i < M; ++i) {
-        const int k = 64 * i + k0;
-        hi[i] = __uint_as_float(next_lane(__float_as_uint(lv[i])));
-        if (i + 1 < M) {
-            const float following = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lv[i + 1 < M ? i + 1 : 0]), 0));
-            hi[i] = lane == 63 ? following : hi[i];
+        const bool inner = M * k0 + i < K - 1;
+        upper_level[i] = i + 1 < M ? lv[i + 1 < M ? i + 1 : 0] : __uint_as_float(next_lane(__float_as_uint(lv[0])));
+        // a lane past the last boundary: the end
+        float both = lv[i] + upper_level[i];
+        if (M == 1) {  // the move is folded into this addition, as the sum is its only use
+            float again = lv[i];
+            asm volatile("" : "+v"(again));
+            both = lv[i] + __uint_as_float(next_lane(__float_as_uint(again)));
         }
-        const bool inner = k < K - 1;
-        const bool ok = inner ? hi[i] - lv[i] > 0x1p-20f && lv[i] >= 0.0f && hi[i] <= 1.0f : true;
-        const float mid = 0.5f * (lv[i] + hi[i]);
-        // past the last boundary: everything, no value left to compare
-        const uint32_t first = inner ? fit_cell<C>(mid - 0x1p-21f, cells) : (uint32_t)C;
-        const uint32_t last = inner ? fit_cell<C>(mid + 0x1p-21f, cells) + 1u : (uint32_t)C;
-        upto[i] = slot.cell[Slot::at(first)];
-        end[i] = (uint32_t)(slot.cell[Slot::at(last)] >> kFitCountShift);
-        pos[i] = (uint32_t)(upto[i] >> kFitCountShift);
-        plain = plain || !ok || end[i] - pos[i] > crowded;
+        const float from = __builtin_amdgcn_fmed3f(fmaf(both, boundary.half_unit, boundary.before),
+                                                   inner ? 0.0f : (float)C, inner ? (float)(C - 1) : (float)C);
+        const float to = __builtin_amdgcn_fmed3f(fmaf(both, boundary.half_unit, boundary.past),
+                                                 inner ? 1.0f : (float)C, (float)C);
+        pos[i] = slot.cell[(uint32_t)from];
+        end[i] = slot.cell[(uint32_t)to];
     }
-    uint64_t own[M];
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64(plain) == 0, 1)) {
+    next = fit_next(next_slot);
+#pragma unroll
+    for (int i = 0; i < M; ++i) {
+        // The first value that is closer to the upper level is the rounded midpoint or the one after it: the midpoint
+        // is off by half a step, so that a step further the distances differ by a step or more, and of them only the
+        // one to a level below half the value is rounded, by half a step.
+        const float mid = 0.5f * (lv[i] + upper_level[i]);
+        threshold[i] = kFitUnit * __uint_as_float(__float_as_uint(mid) +
+                                                  (fabsf(mid - upper_level[i]) < fabsf(mid - lv[i]) ? 0u : 1u));
+        asm volatile("" : "+v"(threshold[i]));  // here, while the places are on their way
+        narrow |= __builtin_amdgcn_ballot_w64(!(upper_level[i] - lv[i] > 0x1p-20f)) &
+                  (i + 1 < M ? ~0ull : boundaries);
+    }
+    uint64_t upto[M];  // count and sum of the values of levels 0 .. k
+    f4 z[M][G];
+    uint64_t rare = outside | narrow;
+    uint32_t group[M];
+#pragma unroll
+    for (int i = 0; i < M; ++i) {
+        group[i] = pos[i] & ~3u;
+#pragma unroll
+        for (int g = 0; g < G; ++g) z[i][g] = *reinterpret_cast<const f4*>(&values[group[i] + 4u * S * g]);
+        upto[i] = slot.before[group[i] >> 2];
+        rare |= __builtin_amdgcn_ballot_w64(end[i] > group[i] + 4u * S * G);
+    }
+    // count and sum of those of four values that are on the lower level's side: below 1 (the upper level is at most 1
+    // and closer), so 32 bits hold them. Values past the boundary's cells may be among the four, and fillers past the
+    // last one: above the boundary.
+    auto below_of = [&](f4 v, float t) -> uint64_t {
+        uint64_t w[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const bool lower = v[u] < t;
+            const uint32_t fixed = (uint32_t)v[u];
+            w[u] = ((uint64_t)(lower ? 1u << (kFitCountShift - 32) : 0u) << 32) | (lower ? fixed : 0u);
+        }
+        uint64_t left = w[0] + w[1], right = w[2] + w[3];
+        asm("" : "+v"(left), "+v"(right));  // side by side
+        return left + right;
+    };
+    bool by_value = false;
+    if (__builtin_expect(rare != 0, 0)) {
+        uint64_t plain = outside | narrow;
+#pragma unroll
+        for (int i = 0; i < M; ++i)
+            plain |= __builtin_amdgcn_ballot_w64(end[i] - group[i] > crowded && end[i] > group[i]);
+        by_value = plain != 0;
+        if (!by_value) {  // the groups that follow, of all the lane's levels side by side
+            uint64_t more[M] = {};
+            for (uint32_t next_group = 4u * S * G;; next_group += 4u * S) {
+                uint64_t left = 0;
+                f4 v[M];
+#pragma unroll
+                for (int i = 0; i < M; ++i) {
+                    const uint32_t p = group[i] + next_group;
+                    left |= __builtin_amdgcn_ballot_w64(p < end[i]);
+                    v[i] = *reinterpret_cast<const f4*>(&values[p < end[i] ? p : group[i]]);
+                }
+                if (left == 0) break;
+#pragma unroll
+                for (int i = 0; i < M; ++i) {
+                    const uint64_t w = below_of(v[i], threshold[i]);
+                    more[i] += group[i] + next_group < end[i] ? w : 0ull;
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < M; ++i) upto[i] += fit_sum_subs<S>(more[i]);
+        }
+    }
+    FitWord own[M];
+    if (__builtin_expect(!by_value, 1)) {
 #pragma unroll
         for (int i = 0; i < M; ++i) {
-            // The values at `end` and beyond are those of higher cells, or the fillers past the last one: above the
-            // boundary, so they may be read with the others. A lane past the last boundary compares with levels that
-            // have nothing on the lower one's side.
-            const bool inner = 64 * i + k0 < K - 1;
-            const float below_level = inner ? lv[i] : -4.0f, above_level = inner ? hi[i] : kFitFiller;
-            uint64_t below = 0;
-            uint32_t p = pos[i];
-            do {
-                const float* at = &slot.z[p + sub * U];
-                float z[U];
+            uint64_t below = below_of(z[i][0], threshold[i]);
 #pragma unroll
-                for (int u = 0; u < U; ++u) z[u] = at[u];
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    // on the lower level's side: below 1 (the upper level is at most 1 and closer), so 32 bits hold it
-                    const bool lower = !(fabsf(z[u] - above_level) < fabsf(z[u] - below_level));
-                    const uint32_t fixed = (uint32_t)(z[u] * 4294967296.0f);
-                    below += ((uint64_t)(lower ? 1u << (kFitCountShift - 32) : 0u) << 32) | (lower ? fixed : 0u);
-                }
-                p = p + S * U < end[i] ? p + S * U : end[i];  // the lanes that are done: nothing below any more
-            } while (__builtin_amdgcn_ballot_w64(p < end[i]) != 0);
+            for (int g = 1; g < G; ++g) below += below_of(z[i][g], threshold[i]);
             upto[i] += fit_sum_subs<S>(below);
         }
 #pragma unroll
         for (int i = 0; i < M; ++i) {
-            uint32_t lo_prev = previous_lane((uint32_t)upto[i]), hi_prev = previous_lane((uint32_t)(upto[i] >> 32));
             if (i > 0) {
-                const uint64_t preceding = upto[i > 0 ? i - 1 : 0];
-                const uint32_t lo_63 = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)preceding, 63);
-                const uint32_t hi_63 = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(preceding >> 32), 63);
-                lo_prev = lane == 0 ? lo_63 : lo_prev;
-                hi_prev = lane == 0 ? hi_63 : hi_prev;
+                own[i] = fit_halves(upto[i] - upto[i > 0 ? i - 1 : 0]);
+                continue;
             }
-            const uint64_t prev = 64 * i + k0 == 0 ? 0ull : ((uint64_t)hi_prev << 32) | lo_prev;
-            own[i] = upto[i] - prev;
+            const FitWord highest = fit_halves(upto[M - 1]);
+            FitWord previous = {previous_lane(highest.low), previous_lane(highest.high)};
+            if (S > 1) previous = {previous.low & not_first, previous.high & not_first};
+            // not folded into the subtraction: v_subrev_u32 with a DPP operand gave the negative difference here
+            asm volatile("" : "+v"(previous.low), "+v"(previous.high));
+            own[i] = fit_halves(upto[i] - (((uint64_t)previous.high << 32) | previous.low));
         }
     } else {
         // value by value against the table in LDS
+        const int m = count();
         fit_wave_sync();
 #pragma unroll
         for (int i = 0; i < M; ++i) {
-            const int k = 64 * i + k0;
+            const int k = M * k0 + i;
             if (sub == 0 && k < K) {
                 lv_shared[k] = lv[i];
                 acc[k] = 0;
@@ -395,36 +506,49 @@ __device__ __forceinline__ void fit_batch(const Slot& slot, int m, Powers& power
             float z[4];
             int k[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) z[u] = slot.z[p + 64 * u < m ? p + 64 * u : p];
+            for (int u = 0; u < 4; ++u) z[u] = slot.z[p + 64 * u < m ? p + 64 * u : p] * (1.0f / kFitUnit);
 #pragma unroll
             for (int u = 0; u < 4; ++u) k[u] = nearest_level<BITS>(z[u], lv_shared);
 #pragma unroll
             for (int u = 0; u < 4; ++u)
-                if (p + 64 * u < m) fit_add(&acc[k[u]], (1ull << kFitCountShift) | fit_fixed(z[u]));
+                if (p + 64 * u < m) fit_add<uint64_t>(&acc[k[u]], fit_word(z[u] * kFitUnit));
         }
         fit_wave_sync();
 #pragma unroll
         for (int i = 0; i < M; ++i) {
-            const int k = 64 * i + k0;
-            own[i] = k < K ? acc[k] : 0;
+            const int k = M * k0 + i;
+            own[i] = fit_halves(k < K ? acc[k] : 0);
         }
         fit_wave_sync();
     }
     // the powers are requested before it is known whether the table holds them: the answer comes while they are on
     // the way
     uint32_t c[M], most = 0;
-    typename Powers::Entry e[M];
+    double moved[M];
     auto request = [&] {
 #pragma unroll
-        for (int i = 0; i < M; ++i) e[i] = powers.fine[c[i] < (uint32_t)Powers::kFine ? c[i] : (uint32_t)Powers::kFine];
+        for (int i = 0; i < M; ++i) {
+            if constexpr (Powers::kFine == Slot::kValues) {
+                // eight bytes for every one of the count, the upper half of the word's upper half, in one instruction
+                static_assert(kFitCountShift == 48 && sizeof(double) == 8, "place of the count");
+                uint32_t at;
+                asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1"
+                    : "=v"(at) : "v"(3u), "v"(own[i].high));
+                moved[i] = *reinterpret_cast<const double*>(reinterpret_cast<const char*>(powers.fine) + at);
+            } else {
+                moved[i] = powers.fine[c[i] < (uint32_t)Powers::kFine ? c[i] : (uint32_t)Powers::kFine];
+            }
+        }
     };
 #pragma unroll
     for (int i = 0; i < M; ++i) {
-        c[i] = (uint32_t)(own[i] >> kFitCountShift);
+        c[i] = own[i].high >> (kFitCountShift - 32);
         most = c[i] > most ? c[i] : most;
     }
     request();
-    if (filled.count < m) {
+    done();
+    next.ready = __builtin_amdgcn_readfirstlane(next.ready);
+    if (filled.count < bucket) {
         while (__builtin_expect(__builtin_amdgcn_ballot_w64(most > (uint32_t)filled.count) != 0, 0)) {
             powers.extend(filled, one_minus, lane);
             request();
@@ -433,25 +557,28 @@ __device__ __forceinline__ void fit_batch(const Slot& slot, int m, Powers& power
     if (Powers::kFine == Slot::kValues ||
         __builtin_expect(__builtin_amdgcn_ballot_w64(most > (uint32_t)Powers::kFine) == 0, 1)) {
 #pragma unroll
-        for (int i = 0; i < M; ++i) lv[i] = Powers::step(lv[i], c[i], own[i] & kFitSumMask, e[i]);
+        for (int i = 0; i < M; ++i) lv[i] = Powers::step(lv[i], c[i], fit_whole(own[i]) & kFitSumMask, moved[i]);
     } else {
 #pragma unroll
-        for (int i = 0; i < M; ++i) lv[i] = powers.step_any(lv[i], c[i], own[i] & kFitSumMask, one_minus);
+        for (int i = 0; i < M; ++i) lv[i] = powers.step_any(lv[i], c[i], fit_whole(own[i]) & kFitSumMask, one_minus);
     }
+    if (__builtin_expect(outside != 0, 0)) outside = fit_outside<M>(lv);
 }
 
 template <int BITS, int VPT, int W>
 __global__ void __launch_bounds__((FitShape<BITS, VPT, W>::kThreads)) fit_levels_kernel(const FitParams p) {
     using Shape = FitShape<BITS, VPT, W>;
     using Slot = typename Shape::Slot;
-    constexpr int C = Shape::kCells, P = Shape::kBatches, K = 1 << BITS;
+    constexpr int C = Shape::kCells, P = Shape::kProducers, K = 1 << BITS;
+    constexpr uint32_t kSlots = Shape::kSlots;
     constexpr int M = FitLanes<BITS>::M, S = FitLanes<BITS>::S;
-    __shared__ Slot slots[2 * P];
+    __shared__ Slot slots[kSlots];
     typedef FitPowers<Shape::kBucketMax> Powers;
     __shared__ Powers powers;
     __shared__ float lv_shared[K];
     __shared__ uint64_t acc[K];
-    __shared__ float red[P][4][W];
+    __shared__ uint32_t consumed[64];  // batches that the consumer has read, one copy for every lane
+    __shared__ uint32_t nowhere[64];   // where lanes without a value count and write
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int B = p.bucket;
@@ -472,16 +599,17 @@ __global__ void __launch_bounds__((FitShape<BITS, VPT, W>::kThreads)) fit_levels
         const uint64_t left = n - j * (uint64_t)B;
         return left < (uint64_t)B ? (int)left : B;
     };
-    const uint64_t rounds = (num_batches + P - 1) / P;  // of the consumer; the producers are one ahead
     const double one_minus = 1.0 - (double)p.lr;
+    if (threadIdx.x < 64) consumed[threadIdx.x] = 0;
+    if (threadIdx.x < kSlots) slots[threadIdx.x].ready = 0;
+    __syncthreads();  // the only one: from here on a wave waits for the words that it needs
 
     if (wave == Shape::kProducers) {
-        // the consumer: round r walks the batches that were sorted in round r - 1
         __builtin_amdgcn_s_setprio(3);
         float lv[M];
 #pragma unroll
         for (int i = 0; i < M; ++i) {
-            const int k = 64 * i + (S > 1 ? lane % (64 / S) : lane);
+            const int k = M * (S > 1 ? lane % (64 / S) : lane) + i;
             lv[i] = k < K ? levels[k] : 0.0f;
         }
         FitFilled filled = powers.start(lane);
@@ -489,55 +617,66 @@ __global__ void __launch_bounds__((FitShape<BITS, VPT, W>::kThreads)) fit_levels
         // Gaussian batch on the uniform table does not reach; all of them for the smallest buckets
         while (filled.count < Powers::kFine && (Powers::kFine <= 256 || filled.count * K < 3 * B))
             powers.extend(filled, one_minus, lane);
-        for (int i = 0; i < Shape::kBarriers; ++i) __syncthreads();  // the producers' first round
-        for (uint64_t r = 0; r < rounds; ++r) {
-            const int buffer = (int)(r & 1u) * P;
-            FitCells cells[P];
-#pragma unroll
-            for (int i = 0; i < P; ++i) cells[i] = slots[buffer + i].cells;
-#pragma unroll
-            for (int i = 0; i < P; ++i) {
-                if (r * P + i < num_batches)
-                    fit_batch<BITS, Slot, Powers, C>(slots[buffer + i], batch_size(r * P + i), powers, filled,
-                                                     one_minus, cells[i], lv, lv_shared, acc, lane);
-                for (int b = 0; b < (W == 1 ? (i == P - 1 ? 1 : 0) : Shape::kBarriers / P); ++b) __syncthreads();
-            }
+        // values in a boundary's cells from which the plain assignment of the batch is faster
+        const uint32_t crowded = (uint32_t)(B * 4 * S / (48 * M)) + 64u;
+        uint64_t outside = fit_outside<M>(lv);
+        // the last levels' lanes have no boundary above them, the first level's nothing before
+        uint64_t boundaries = __builtin_amdgcn_ballot_w64(M * (S > 1 ? lane % (64 / S) : lane) + M - 1 < K - 1);
+        asm volatile("" : "+s"(boundaries));  // kept, not asked again
+        const uint32_t not_first = lane % (64 / S) == 0 ? 0u : ~0u;
+        FitNext next;
+        auto walk = [&](uint64_t j, uint32_t slot, uint32_t following) {
+            auto done = [&] {
+                fit_order();
+                __hip_atomic_store(&consumed[lane], (uint32_t)j + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            };
+            fit_batch<BITS, Slot, Powers, C>(slots[slot], slots[following], next, outside, boundaries, not_first,
+                                             crowded, B, [&] { return batch_size(j); }, done, powers, filled,
+                                             one_minus, lv, lv_shared, acc, lane);
+        };
+        auto look = [&](uint32_t slot) {
+            next = fit_next(slots[slot]);
+            next.ready = __builtin_amdgcn_readfirstlane(next.ready);
+        };
+        uint32_t slot = 0;
+        look(0);
+        for (uint64_t j = 0; j < num_batches; ++j) {
+            while (__builtin_expect(next.ready != (uint32_t)j + 1u, 0)) look(slot);
+            fit_order();
+            const uint32_t following = slot + 1 < kSlots ? slot + 1 : 0;
+            walk(j, slot, following);
+            slot = following;
         }
 #pragma unroll
         for (int i = 0; i < M; ++i) {
-            const int k = 64 * i + (S > 1 ? lane % (64 / S) : lane);
+            const int k = M * (S > 1 ? lane % (64 / S) : lane) + i;
             if ((S == 1 || lane < 64 / S) && k < K) levels[k] = lv[i];
         }
     } else {
-        // between the passes of a team
-        auto team_sync = [] {
-            if constexpr (W > 1) __syncthreads(); else fit_wave_sync();
-        };
-        // a producer: batch r * P + team in round r, this wave's 1/W of it; nothing but the barriers past the last one.
         // Lanes past the end of a batch fetch its last value, which changes no minimum or maximum, and enter nothing.
-        const int team = wave / W, part = wave % W;
-        const int scanner = W == 2 ? team / 2 : W == 4 ? team : 0;  // of the team's waves: on another SIMD for every team
-        const int first = part * 64 + lane;  // value q of the lane: first + q * 64 * W
         float next[VPT];
-        auto batch = [&](uint64_t r) -> uint64_t { return r * P + team; };
         auto fetch = [&](uint64_t j) {
             const int m = batch_size(j);
             const float* src = v + j * (uint64_t)B;
+            if (m == Shape::kBucketMax) {
 #pragma unroll
-            for (int q = 0; q < VPT; ++q) {
-                const int i = first + q * 64 * W;
-                next[q] = src[i < m ? i : m - 1];
+                for (int q = 0; q < VPT; ++q) next[q] = src[(uint32_t)(lane + 64 * q)];
+            } else {
+#pragma unroll
+                for (int q = 0; q < VPT; ++q) {
+                    const int i = lane + 64 * q;
+                    next[q] = src[(uint32_t)(i < m ? i : m - 1)];
+                }
             }
         };
-        fetch(batch(0) < num_batches ? batch(0) : num_batches - 1);
-        powers.fill_reciprocals(B, threadIdx.x, 64 * Shape::kProducers);
-        for (uint64_t r = 0; r <= rounds; ++r) {
-            if (batch(r) >= num_batches) {  // the consumer's last round among them
-                for (int i = 0; i < Shape::kBarriers; ++i) __syncthreads();
-                continue;
-            }
-            const int m = batch_size(batch(r));
-            Slot& slot = slots[(int)(r & 1u) * P + team];
+        uint32_t place_of = (uint32_t)wave;  // the batch's slot
+        // One batch; `full`: a value in every lane, so that nothing asks which are there.
+        auto sort = [&](uint64_t j, auto full_batch) {
+            constexpr bool full = decltype(full_batch)::value;
+            const int m = full ? Shape::kBucketMax : batch_size(j);
+            auto there = [&](int q) { return full || lane + 64 * q < m; };
+            Slot& slot = slots[place_of];
+            constexpr int kSampled = VPT >= 8 ? 4 : 1;  // every fourth value is enough to place the cells
             float z[VPT];
             float lo = next[0], hi = next[0], sum = 0.0f, absolute = 0.0f;
 #pragma unroll
@@ -545,82 +684,137 @@ __global__ void __launch_bounds__((FitShape<BITS, VPT, W>::kThreads)) fit_levels
                 z[q] = next[q];
                 lo = fminf(lo, z[q]);
                 hi = fmaxf(hi, z[q]);
-                sum += z[q];
-                absolute += fabsf(z[q]);
+                if (q % kSampled == 0) {
+                    sum += z[q];
+                    absolute += fabsf(z[q]);
+                }
             }
-            fetch(batch(r + 1) < num_batches ? batch(r + 1) : num_batches - 1);  // in flight while this batch is sorted
-            for (int c = first; c < C + 64; c += 64 * W) slot.cell[c] = 0;  // all but the last, written below
+            if (j + P < num_batches) fetch(j + P);  // in flight while this batch is sorted
             lo = group_min<64>(lo);
             hi = group_max<64>(hi);
             sum = fit_wave_sum(sum);
             absolute = fit_wave_sum(absolute);
-            if constexpr (W > 1) {
-                if (lane == 0) {
-                    red[team][0][part] = lo;
-                    red[team][1][part] = hi;
-                    red[team][2][part] = sum;
-                    red[team][3][part] = absolute;
-                }
-                __syncthreads();
-                sum = absolute = 0.0f;
+            // the slot is free once the consumer has read the batch that it held
+            while ((uint32_t)j - __builtin_amdgcn_readfirstlane(__hip_atomic_load(
+                                     &consumed[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) >= kSlots)
+                __builtin_amdgcn_s_sleep(1);
+            fit_wave_sync();
 #pragma unroll
-                for (int w = 0; w < W; ++w) {
-                    lo = fminf(lo, red[team][0][w]);
-                    hi = fmaxf(hi, red[team][1][w]);
-                    sum += red[team][2][w];
-                    absolute += red[team][3][w];
-                }
-            } else {
-                fit_wave_sync();
+            for (int c0 = 0; c0 < C; c0 += 256) {
+                const int c = c0 + 4 * lane;
+                if (C % 256 == 0 || c < C) *reinterpret_cast<u4*>(&slot.cell[c]) = u4{0u, 0u, 0u, 0u};
             }
+            fit_wave_sync();
             const MinMaxGrid grid = make_minmax_grid(lo, hi, 1.0f, false);
-            const FitCells cells = fit_cells<C>(grid, hi, sum * (1.0f / (64 * W * VPT)), absolute * (1.0f / (64 * W * VPT)));
-            uint32_t cell[VPT];
-            uint64_t held[VPT];  // the cell's word before this value came (both halves used: half of one dropped costs a wait)
-            auto enter = [&](int q) {
+            const FitCells cells = fit_cells<C>(grid, hi, sum * ((float)kSampled / (64 * VPT)),
+                                                absolute * ((float)kSampled / (64 * VPT)));
+            uint32_t* cell[VPT];
+            uint32_t held[VPT];  // the values that the cell held before this one came
+            // Rows of a wave's values eight at a time, so that what a short batch does not have is left out and the
+            // rest is straight-line code: a lane without a value uses words of its own.
+            auto rows = [&](auto each) {
+#pragma unroll
+                for (int q0 = 0; q0 < VPT; q0 += 8)
+                    if (full || 64 * q0 < m) {
+#pragma unroll
+                        for (int q = q0; q < q0 + 8 && q < VPT; ++q) each(q);
+                    }
+            };
+            rows([&](int q) {
                 z[q] = (z[q] - grid.lo) * grid.inv;
-                cell[q] = Slot::at(fit_cell<C>(z[q], cells));
-                held[q] = fit_add(&slot.cell[cell[q]], (1ull << kFitCountShift) | fit_fixed(z[q]));
-            };
-            const bool full = m == Shape::kBucketMax;
-            if (full) {
+                cell[q] = there(q) ? &slot.cell[fit_cell<C>(z[q], cells)] : &nowhere[lane];
+                z[q] *= kFitUnit;
+                held[q] = fit_add(cell[q], 1u);
+            });
+            fit_wave_sync();
+            // lane l has cells 4l .. 4l + 3 of every row of 256
+            constexpr int kCellRows = C >= 256 ? C / 256 : 1;
+            u4 own[kCellRows];
+            uint32_t sum4[kCellRows], upto[kCellRows], base_cell = 0;
 #pragma unroll
-                for (int q = 0; q < VPT; ++q) enter(q);
-            } else {
-#pragma unroll
-                for (int q = 0; q < VPT; ++q)
-                    if (first + q * 64 * W < m) enter(q);
+            for (int i = 0; i < kCellRows; ++i) {
+                const int c = 4 * (64 * i + lane);
+                own[i] = C >= 256 || c < C ? *reinterpret_cast<const u4*>(&slot.cell[c]) : u4{0u, 0u, 0u, 0u};
             }
-            team_sync();
-            if (part == scanner) {
-                constexpr int kOwn = Slot::kOwn;
-                uint64_t* own = &slot.cell[Slot::at(lane * kOwn)];
-                uint64_t before[kOwn], total = 0;
 #pragma unroll
-                for (int c = 0; c < kOwn; ++c) {
-                    before[c] = total;
-                    total += own[c];
+            for (int i = 0; i < kCellRows; ++i) upto[i] = sum4[i] = (own[i][0] + own[i][1]) + (own[i][2] + own[i][3]);
+            fit_wave_scan(upto);
+#pragma unroll
+            for (int i = 0; i < kCellRows; ++i) {
+                const int c = 4 * (64 * i + lane);
+                u4 at;
+                at[0] = base_cell + upto[i] - sum4[i];
+                at[1] = at[0] + own[i][0];
+                at[2] = at[1] + own[i][1];
+                at[3] = at[2] + own[i][2];
+                if (C >= 256 || c < C) *reinterpret_cast<u4*>(&slot.cell[c]) = at;
+                base_cell += (uint32_t)__builtin_amdgcn_readlane((int)upto[i], 63);
+            }
+            if (lane == 0) slot.cell[C] = (uint32_t)(m + 3) & ~3u;
+            fit_wave_sync();
+            // all places requested before the first one is waited for
+            rows([&](int q) { held[q] += *cell[q]; });
+            rows([&](int q) {
+                float* at = there(q) ? &slot.z[held[q]] : reinterpret_cast<float*>(&nowhere[lane]);
+                *at = z[q];
+            });
+            if (lane < kFitSpare) slot.z[m + lane] = kFitFiller;
+            fit_wave_sync();
+            // Count and sum before every group of four values, rows of 64 groups side by side; the sums of the
+            // values' upper and lower 16 bits apart, so that 32 bits hold them. A value of 1 (the conversion saturates)
+            // is one short here: it is past every boundary, so that only the word of all values has to know.
+            constexpr int kRows = VPT >= 4 ? VPT / 4 : 1;
+            constexpr bool kHalf = VPT < 4;  // half a row
+            uint32_t incl[2 * kRows], row[2 * kRows], ones = 0;
+            const uint32_t crest = slot.cell[fit_cell<C>(1.0f, cells)];  // where the values of the cell of 1 start
+#pragma unroll
+            for (int i = 0; i < kRows; ++i) {
+                const int g = 64 * i + (kHalf ? lane & 31 : lane);
+                const f4 four = *reinterpret_cast<const f4*>(&slot.z[4 * g]);
+                uint32_t low = 0, high = 0;
+                uint32_t fixed[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    fixed[u] = full || 4 * g + u < m ? (uint32_t)four[u] : 0u;
+                    low += fixed[u] & 0xFFFFu;
+                    high += fixed[u] >> 16;
                 }
-                const uint64_t incl = fit_wave_scan(total);
+                if ((uint32_t)__builtin_amdgcn_readfirstlane((int)crest) < 256u * (uint32_t)(i + 1)) {
 #pragma unroll
-                for (int c = 0; c < kOwn; ++c) own[c] = before[c] + (incl - total);
-                if (lane == 63) slot.cell[Slot::at(C)] = incl;
-                if (lane == 0) slot.cells = cells;
+                    for (int u = 0; u < 4; ++u) {
+                        const bool one = fixed[u] == ~0u && (!kHalf || lane < 32);
+                        ones += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(one));
+                    }
+                }
+                incl[2 * i] = row[2 * i] = low;
+                incl[2 * i + 1] = row[2 * i + 1] = high;
             }
-            team_sync();
-            auto place = [&](int q) {
-                slot.z[(uint32_t)((slot.cell[cell[q]] + held[q]) >> kFitCountShift)] = z[q];
-            };
-            if (full) {
+            fit_wave_scan(incl);
+            constexpr int kLast = kHalf ? 31 : 63;
+            auto last = [&](uint32_t x) { return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)x, kLast); };
+            uint64_t base = 0;
 #pragma unroll
-                for (int q = 0; q < VPT; ++q) place(q);
-            } else {
-#pragma unroll
-                for (int q = 0; q < VPT; ++q)
-                    if (first + q * 64 * W < m) place(q);
+            for (int i = 0; i < kRows; ++i) {
+                const int g = 64 * i + lane;
+                const uint32_t c = full || 4 * g < m ? (uint32_t)(4 * g) : (uint32_t)m;
+                const uint64_t before =
+                    base + (incl[2 * i] - row[2 * i]) + ((uint64_t)(incl[2 * i + 1] - row[2 * i + 1]) << 16);
+                if (!kHalf || lane < 32) slot.before[g] = before + ((uint64_t)c << kFitCountShift);
+                base += last(incl[2 * i]) + (last(incl[2 * i + 1]) << 16);
             }
-            if (part == 0 && lane < kFitSpare) slot.z[m + lane] = kFitFiller;
-            __syncthreads();
+            fit_wave_sync();
+            if (lane == 0) {
+                slot.before[(m + 3) >> 2] = base + ones + ((uint64_t)m << kFitCountShift);  // of all values
+                slot.boundary = fit_boundary(cells);
+                fit_order();
+                __hip_atomic_store(&slot.ready, (uint32_t)j + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+        };
+        if ((uint64_t)wave < num_batches) fetch((uint64_t)wave);
+        for (uint64_t j = (uint64_t)wave; j < num_batches; j += P) {
+            if (batch_size(j) == Shape::kBucketMax) sort(j, std::true_type{});
+            else sort(j, std::false_type{});
+            place_of = place_of + P < kSlots ? place_of + P : place_of + P - kSlots;
         }
     }
 }

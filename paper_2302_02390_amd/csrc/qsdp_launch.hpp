@@ -40,7 +40,7 @@ QSDP_DECLARE_FIT(2, 1)
 QSDP_DECLARE_FIT(4, 1)
 QSDP_DECLARE_FIT(8, 1)
 QSDP_DECLARE_FIT(16, 1)
-QSDP_DECLARE_FIT(16, 2)
+QSDP_DECLARE_FIT(32, 1)
 QSDP_DECLARE_FIT(16, 4)
 QSDP_DECLARE_FIT(16, 8)
 #undef QSDP_DECLARE_FIT

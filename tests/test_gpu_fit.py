@@ -105,3 +105,24 @@ def test_levels_without_values_stay_as_they_are(B, bits):
         qb.qsdp_fit_levels(torch.from_numpy(x).to(DEV), bits, B, 0.01, lv)
         got = np_f32(lv)
         assert np.array_equal(got[K // 2:], levels[K // 2:]) and (got[:K // 2] < 1.0).all(), fill
+
+
+@pytest.mark.parametrize("B", [96, 128, 512, 1024, 1056, 2048])
+@pytest.mark.parametrize("bits", [1, 4, 5, 6, 8])
+def test_sums_before_the_groups_of_a_batch(B, bits):
+    """The kernel keeps count and sum before every fourth value of the sorted batch, short by the values that are exactly
+    1 except in the word of all: many of them, in several of its rows, in batches that end inside a group; and cells that
+    an outlier outside the sample which places them makes so narrow that 1 is not in the last one."""
+    rng = np.random.default_rng(B + bits)
+    for cut in (0, 1, 2, 3, 30):
+        n = 17 * B - cut
+        top = rng.uniform(0.0, 1.0, n).astype(np.float32)
+        top[rng.random(n) < 0.4] = 1.0
+        top[::B] = 0.0
+        crest = (1.0 - rng.random(n) * 1e-4).astype(np.float32)
+        crest[70 % B::B] = -30.0
+        crest[71 % B::B] = 1.0
+        far = rng.uniform(0.0, 0.1, n).astype(np.float32)
+        far[70 % B::B] = -2.0e4
+        for v in (top, crest, far):
+            assert _same(v, bits, B, 0.03, ref.levels_uniform(bits)), cut
