@@ -103,7 +103,7 @@ _lib = None
 _lib_lock = threading.Lock()
 # The functions of this file that lib() replaces by native ones of the same name, where these are built for the running
 # torch. The native ones call them for the uncommon cases.
-_IN_PYTHON = dict.fromkeys(("_is", "_is_rows", "_packed_ok", "_rows_ok", "_step_outputs", "_launch"))
+_IN_PYTHON = dict.fromkeys(("_is", "_is_rows", "_packed_ok", "_rows_ok", "_step_outputs", "_launch", "_devices_ok"))
 
 
 class QsdpError(RuntimeError):
@@ -142,7 +142,7 @@ def _load():
 
 
 def _native_marshalling():
-    """The module of csrc/qsdp_marshal.cpp, which takes about 2.5 us of host time off a call, or None if it is not built
+    """The module of csrc/qsdp_marshal.cpp, which takes about 3.5 us of host time off a call, or None if it is not built
     or was compiled against another torch: it reads tensors through torch's C++ headers, and the functions of this file
     do the same without."""
     try:
@@ -837,21 +837,27 @@ def qsdp_fused_adamw_step_opts(x, g, m, v, lr, beta1, beta2, eps, weight_decay, 
                x16, seed_increment, wcodes, wmeta, n_saturated, (m, v, beta1, beta2, eps, weight_decay, bias1, bias2))
 
 
-def _one_device(fn):
+def _devices_ok(name, args, kwargs):
     """Every tensor argument of an entry point (and a segment table) must live on the same device: the
     kernel runs on the device of the first one and would fault on memory of another."""
+    device = None
+    for a in list(args) + list(kwargs.values()):
+        for t in (a if isinstance(a, (tuple, list)) else (a,)):
+            if isinstance(t, Segments):
+                t = t.device
+            if isinstance(t, torch.Tensor):
+                if device is None:
+                    device = t.device
+                elif t.device != device:
+                    raise ValueError(f"{name}: tensors on {device} and on {t.device}")
+
+
+def _one_device(fn):
+    name = fn.__name__
+
     @functools.wraps(fn)
     def checked(*args, **kwargs):
-        device = None
-        for a in list(args) + list(kwargs.values()):
-            for t in (a if isinstance(a, (tuple, list)) else (a,)):
-                if isinstance(t, Segments):
-                    t = t.device
-                if isinstance(t, torch.Tensor):
-                    if device is None:
-                        device = t.device
-                    elif t.device != device:
-                        raise ValueError(f"{fn.__name__}: tensors on {device} and on {t.device}")
+        _devices_ok(name, args, kwargs)
         return fn(*args, **kwargs)
     return checked
 

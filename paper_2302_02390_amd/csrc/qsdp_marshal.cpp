@@ -24,7 +24,7 @@ namespace {
 // The Python functions for everything else (see attach), and the binding's namespace: the stream is asked for through
 // its name `_raw_stream`.
 PyObject *is_in_python, *rows_in_python, *packed_in_python, *rows_ok_in_python, *outputs_in_python, *launch_in_python,
-    *names;
+    *devices_in_python, *names;
 PyObject* raw_stream_name;
 
 bool plain_tensor(PyObject* o) { return THPVariable_CheckExact(o); }
@@ -247,16 +247,53 @@ PyObject* rows_ok(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     return PyObject_Vectorcall(rows_ok_in_python, args, (size_t)nargs, nullptr);
 }
 
-// attach(names, is, is_rows, packed_ok, rows_ok, step_outputs, launch): the binding's namespace and its functions
-// for what is not common.
+// Numbers and None hold no tensor. (Subclasses of numbers neither, but they are Python's to ask.)
+bool plain_value(PyObject* o) {
+    return o == Py_None || PyLong_CheckExact(o) || PyFloat_CheckExact(o) || PyBool_Check(o);
+}
+
+// Whether o is a value or a tensor on the device of those before it (none yet: -2).
+bool same_device(PyObject* o, int& device) {
+    if (plain_value(o)) return true;
+    if (!plain_tensor(o)) return false;
+    try {
+        const at::Tensor& t = THPVariable_Unpack(o);
+        if (!t.is_cuda()) return false;
+        const int here = t.get_device();
+        if (device == -2) device = here;
+        return here == device;
+    } catch (const std::exception&) {
+        return false;
+    }
+}
+
+// devices_ok(name, args, kwargs): nothing if all tensors among the arguments are on one GPU. In a loop 1.1-1.5 us less
+// than in Python (fused step over 2^20 parameters 6.0 -> 4.5 us, encoder of 2^18 values 5.6 -> 4.5, gathered layer 6.4
+// -> 5.3, encoder and decoder 10.9 -> 8.9).
+PyObject* devices_ok(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
+    if (nargs == 3 && PyTuple_CheckExact(args[1]) && PyDict_CheckExact(args[2])) {
+        int device = -2;
+        bool ok = true;
+        for (Py_ssize_t i = 0; ok && i < PyTuple_GET_SIZE(args[1]); ++i)
+            ok = same_device(PyTuple_GET_ITEM(args[1], i), device);
+        PyObject *key, *value;
+        for (Py_ssize_t at = 0; ok && PyDict_Next(args[2], &at, &key, &value);) ok = same_device(value, device);
+        if (ok) Py_RETURN_NONE;
+    }
+    return PyObject_Vectorcall(devices_in_python, args, (size_t)nargs, nullptr);
+}
+
+// attach(names, is, is_rows, packed_ok, rows_ok, step_outputs, launch, devices_ok): the binding's namespace and its
+// functions for what is not common.
 PyObject* attach(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
-    if (nargs != 7 || !PyDict_Check(args[0])) {
-        PyErr_SetString(PyExc_TypeError, "attach(namespace, is, is_rows, packed_ok, rows_ok, step_outputs, launch)");
+    if (nargs != 8 || !PyDict_Check(args[0])) {
+        PyErr_SetString(PyExc_TypeError,
+                        "attach(namespace, is, is_rows, packed_ok, rows_ok, step_outputs, launch, devices_ok)");
         return nullptr;
     }
-    PyObject** const held[7] = {&names, &is_in_python, &rows_in_python, &packed_in_python, &rows_ok_in_python,
-                                &outputs_in_python, &launch_in_python};
-    for (int i = 0; i < 7; ++i) {
+    PyObject** const held[8] = {&names, &is_in_python, &rows_in_python, &packed_in_python, &rows_ok_in_python,
+                                &outputs_in_python, &launch_in_python, &devices_in_python};
+    for (int i = 0; i < 8; ++i) {
         Py_INCREF(args[i]);
         Py_XSETREF(*held[i], args[i]);
     }
@@ -269,7 +306,8 @@ PyMethodDef method(const char* name) {
 }
 PyMethodDef methods[] = {method<attach>("attach"), method<is_tensor>("is"), method<is_rows>("is_rows"),
                          method<packed_ok>("packed_ok"), method<rows_ok>("rows_ok"),
-                         method<step_outputs>("step_outputs"), method<launch>("launch"), {nullptr, nullptr, 0, nullptr}};
+                         method<step_outputs>("step_outputs"), method<launch>("launch"),
+                         method<devices_ok>("devices_ok"), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module_def = {PyModuleDef_HEAD_INIT, "_marshal", "Argument marshalling of the binding.", -1, methods};
 
 }  // namespace

@@ -84,3 +84,21 @@ def test_checks():
             for bits, bucket in ((8, 32), (4, 1024), (9, 32), (8, 33), (0, 32)):
                 for native, python in fits(codes, meta, n, bits, bucket):
                     assert native == python, (codes is None, meta is None, n, bits, bucket)
+
+
+def test_tensors_on_one_device():
+    gpu, cpu = torch.zeros(64, device=DEV), torch.zeros(64)
+    segs = qb.Segments([64], 32, DEV)
+    elsewhere = qb.Segments([64], 32, "cpu")
+    for args in ((), (gpu,), (cpu,), (gpu, gpu), (gpu, cpu), (cpu, gpu), (cpu, cpu), (gpu, 3, 1.5, None, True, gpu),
+                 (gpu, 3, cpu), (gpu, np.float32(1), gpu), (gpu, np.float32(1), cpu), (gpu, torch.nn.Parameter(gpu)),
+                 (gpu, torch.nn.Parameter(cpu)), (gpu, segs), (gpu, elsewhere), (cpu, segs), (gpu, (gpu, 1)),
+                 (gpu, [gpu, cpu]), (gpu, (cpu, 1.0)), (gpu, "cpu"), (gpu, torch.device("cpu")), (gpu, [])):
+        for kwargs in ({}, {"a": 1, "b": gpu}, {"a": cpu}, {"a": None, "segs": segs}, {"adamw": (gpu, cpu)}):
+            native, python = _call("_devices_ok", "an entry point", args, kwargs)
+            assert native == python, (args, kwargs)
+    with pytest.raises(ValueError, match="qsdp_quantize_grad: tensors on cuda:0 and on cpu"):
+        qb.qsdp_quantize_grad(gpu, 4, 32, 1, 0, cpu.to(torch.int32), cpu)
+    for args in ((), ("name",), ("name", [gpu, cpu], {}), ("name", (gpu, cpu), None), (1, 2, 3)):
+        native, python = _call("_devices_ok", *args)
+        assert native == python or native[0] is python[0], args
