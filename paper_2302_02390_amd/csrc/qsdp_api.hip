@@ -207,6 +207,11 @@ uint64_t level_blocks(int mode, uint64_t blocks, int waves, int resident, uint64
 // p.num_buckets must be set.
 int run(int mode, Params p, int stored_bits, hipStream_t s) {
     const uint64_t nb = p.num_buckets;
+    if (p.seed_dev == nullptr && !mode_is_levels(mode) && mode != MODE_SUM) {
+        const Shifts shifts = draw_shifts(p.flags, {p.key0, p.key1});
+        p.xi = shifts.xi;
+        p.xi_g = shifts.xi_g;
+    }
     int bpw = 1;
     WaveLauncher wl = wave_launcher(p.bucket, &bpw);
     if (mode == MODE_WEIGHT && p.bucket == 1024 && p.segs == nullptr) {

@@ -32,13 +32,13 @@ typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 // slower with it (fused step over the 1.3B vector 2.53 -> 2.56 ms, code-resident step over 350M 371 -> 382 us).
 // ---------------------------------------------------------------------------------------
 template <bool XOR3>
-__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+__host__ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
     if constexpr (XOR3) return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);  // truth table of a ^ b ^ c
     return a ^ b ^ c;
 }
 
 template <bool XOR3 = false>
-__device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
+__host__ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                               uint32_t k0, uint32_t k1, uint32_t (&out)[4]) {
 #pragma unroll
     for (int round = 0; round < 10; ++round) {
@@ -87,8 +87,9 @@ __device__ __forceinline__ uint32_t uniform16(const uint32_t (&h)[4], int i) {
     return (i & 1) ? (h[i >> 1] >> 16) : (h[i >> 1] & 0xFFFFu);
 }
 
-// A shift xi in [-1/2, 1/2): counter 0 of stream 1 (weights) or 2 (shared-shift gradients).
-__device__ __forceinline__ float stream_shift(uint32_t stream, uint32_t k0, uint32_t k1) {
+// A shift xi in [-1/2, 1/2): counter 0 of stream 1 (weights) or 2 (shared-shift gradients). Exact in both steps, so the
+// host draws the same.
+__host__ __device__ __forceinline__ float stream_shift(uint32_t stream, uint32_t k0, uint32_t k1) {
     uint32_t w[4];
     philox4x32_10(0u, 0u, stream, 0u, k0, k1, w);
     return (float)(w[0] >> 8) * 0x1p-24f - 0.5f;

@@ -241,7 +241,7 @@ __global__ void __launch_bounds__(256, kLevelsResident) levels_kernel(const Para
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint8_t* stage = reinterpret_cast<uint8_t*>(stage_all) + wave * kTileBytes;
     const uint32_t part0 = W > 1 ? wave * (uint32_t)T : 0u;
-    const PhiloxKey key = launch_key(p);
+    const PhiloxKey key = launch_key<MODE>(p);
     const bool per_tensor = segs != nullptr;
 
     // the buckets of this workgroup; within a piece of them its waves (W > 1: the workgroup) take the units in turn

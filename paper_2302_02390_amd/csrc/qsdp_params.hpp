@@ -101,6 +101,7 @@ struct Params {
     float delta, inv_delta;  // lattice mode when delta > 0
     int delta_pow2;
     uint32_t key0, key1;
+    float xi, xi_g;  // the shifts of the key, where the host knows it (seed_dev == nullptr)
     // optional device-resident seed increment (8-byte aligned): the Philox key is taken from
     // seed + *seed_dev, read when the kernel starts, so that a captured launch can be replayed
     // with a seed that other work in the graph advances
@@ -111,9 +112,14 @@ struct PhiloxKey {
     uint32_t k0, k1;
 };
 
+// Whether a mode can take part of its seed from device memory (Params::seed_dev): the fused steps' options block
+// offers it.
+constexpr bool mode_device_seed(int mode) { return mode == MODE_FUSED || mode == MODE_ADAMW; }
+
+template <int MODE>
 __device__ __forceinline__ PhiloxKey launch_key(const Params& p) {
     PhiloxKey k = {p.key0, p.key1};
-    if (p.seed_dev != nullptr) {
+    if (mode_device_seed(MODE) && p.seed_dev != nullptr) {
         const unsigned long long s = (((unsigned long long)p.key1 << 32) | p.key0) + *p.seed_dev;
         k.k0 = (uint32_t)s;
         k.k1 = (uint32_t)(s >> 32);
@@ -145,13 +151,23 @@ struct Shifts {
     float xi_g;  // gradient shift (FLAG_GRAD_SHIFT)
 };
 
-__device__ __forceinline__ Shifts draw_shifts(const Params& p, PhiloxKey key, bool weights) {
+__host__ __device__ __forceinline__ Shifts draw_shifts(uint32_t flags, PhiloxKey key) {
     Shifts s = {0.0f, 0.0f};
-    if (!(p.flags & FLAG_NO_SHIFT)) {
-        if (weights) s.xi = stream_shift(1u, key.k0, key.k1);
-        if (p.flags & FLAG_GRAD_SHIFT) s.xi_g = stream_shift(2u, key.k0, key.k1);
+    if (!(flags & FLAG_NO_SHIFT)) {
+        s.xi = stream_shift(1u, key.k0, key.k1);
+        if (flags & FLAG_GRAD_SHIFT) s.xi_g = stream_shift(2u, key.k0, key.k1);
     }
     return s;
+}
+
+// A wave draws the shifts itself only where the seed is in device memory: ten rounds for a single number are 150 scalar
+// instructions, each waiting for the one before, ahead of every wave's one bucket. 3M values, drawn by the waves / by the
+// host: step 9.2 / 8.4 us and 5-bit weights 10.5 / 9.6 in buckets of 96, receive side 8.3 / 7.6 in buckets of 128,
+// 5-bit weights 9.0 / 8.4 in buckets of 1024; 1.02-1.05 up to 100M values (step, 1024: 195.8 / 188.8), nothing beyond.
+template <int MODE>
+__device__ __forceinline__ Shifts launch_shifts(const Params& p, PhiloxKey key) {
+    if (mode_device_seed(MODE) && __builtin_expect(p.seed_dev != nullptr, 0)) return draw_shifts(p.flags, key);
+    return {p.xi, p.xi_g};
 }
 
 // The tensor of a segmented call that owns bucket `gb`, given a WAVE-UNIFORM bucket gb0 <= gb

@@ -163,8 +163,8 @@ __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
     const bool symmetric = (p.flags & FLAG_SYMMETRIC) != 0;
     const bool grad_shift = (p.flags & FLAG_GRAD_SHIFT) != 0;
     const bool keep_master = kWritesX && (p.flags & FLAG_KEEP_MASTER) != 0;
-    const PhiloxKey key = launch_key(p);
-    const Shifts shifts = draw_shifts(p, key, MODE != MODE_GRAD && !kLevels);
+    const PhiloxKey key = launch_key<MODE>(p);
+    const Shifts shifts = launch_shifts<MODE>(p, key);
     const float xi = shifts.xi;
     uint32_t saturated = 0;
 

@@ -516,8 +516,8 @@ __global__ void __launch_bounds__(256, mode_min_blocks(MODE)) wave_kernel(const 
     const bool grad_shift = (p.flags & FLAG_GRAD_SHIFT) != 0;
     constexpr bool kWritesX = MODE == MODE_FUSED || MODE == MODE_ADAMW || mode_is_recv(MODE);
     const bool keep_master = kWritesX && (p.flags & FLAG_KEEP_MASTER) != 0;
-    const PhiloxKey key = launch_key(p);
-    const Shifts shifts = draw_shifts(p, key, MODE != MODE_GRAD && MODE != MODE_SUM);
+    const PhiloxKey key = launch_key<MODE>(p);
+    const Shifts shifts = launch_shifts<MODE>(p, key);
     const float xi = shifts.xi;
     uint32_t saturated = 0;
 

@@ -88,3 +88,31 @@ def test_null_options_are_the_plain_fused_step_and_a_wrong_size_is_rejected():
     o.size = ctypes.sizeof(qb.StepOptions)
     assert L.qsdp_fused_adamw_step_opts(xd.data_ptr(), gd.data_ptr(), n, 1e-3, 8, 4, B, 0.0, 3, 0, ctypes.byref(o),
                                         stream) == qb.QSDP_EINVAL
+
+
+@pytest.mark.parametrize("B", [1024, 96, 320])   # one bucket a wave, several to a tile, several waves a bucket
+@pytest.mark.parametrize("flags", [0, qb.QSDP_FLAG_GRAD_SHIFT, qb.QSDP_FLAG_NO_SHIFT])
+@pytest.mark.parametrize("adamw", [False, True])
+def test_a_seed_in_device_memory_draws_the_shifts_of_the_same_seed(adamw, flags, B):
+    """The shifts come with the call where the host knows the seed; with part of it in device memory the waves draw
+    them. A sum that carries into the seed's high word included."""
+    n = 7 * B + 36
+    x, g = synth(n, 3 + B)
+    base, inc = (1 << 32) - 2, 5
+    gd = torch.from_numpy(g).to(DEV)
+    got = []
+    for seed, counter in ((base + inc, None), (base, torch.full((1,), inc, dtype=torch.int64, device=DEV))):
+        xd = torch.from_numpy(x).to(DEV)
+        wc, wm = qb.alloc_packed(n, 6, B, DEV)
+        args = dict(flags=flags, seed_increment=counter, wcodes=wc, wmeta=wm.reshape(-1))
+        if adamw:
+            m, v = torch.zeros(n, device=DEV), torch.zeros(n, device=DEV)
+            qb.qsdp_fused_adamw_step_opts(xd, gd, m, v, 2e-4, 0.9, 0.95, 1e-8, 0.05, 0.1, 0.05, 6, 4, B, 0.0, seed, 64, **args)
+        else:
+            qb.qsdp_fused_step_opts(xd, gd, 1e-3, 6, 4, B, 0.0, seed, 64, **args)
+        got.append((xd, wc, wm))
+    assert all(torch.equal(a, b) for a, b in zip(*got))
+    if not adamw:
+        want, wcodes, _, _ = ref.fused_step(x, g, 1e-3, 6, 4, B, 0.0, base + inc, index_offset=64, emit_codes=True,
+                                            flags=flags)
+        assert bits_equal(np_f32(got[0][0]), want) and np.array_equal(np_u32(got[0][1]), wcodes)
