@@ -108,6 +108,40 @@ struct Params {
     const unsigned long long* seed_dev;
 };
 
+// The Params of a kernel that takes them first, once more from its arguments.
+__device__ __forceinline__ Params params_again() {
+    typedef const __attribute__((address_space(4))) uint64_t* Words;
+    typedef const __attribute__((address_space(4))) char* Bytes;
+    typedef __attribute__((address_space(1))) void* Global;
+    Words from = (Words)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(from));
+    struct Image {
+        uint64_t words[sizeof(Params) / 8];
+    } image;
+    static_assert(sizeof(Image) == sizeof(Params), "");
+#pragma unroll
+    for (unsigned i = 0; i < sizeof(Params) / 8; ++i) image.words[i] = from[i];
+    Params p = __builtin_bit_cast(Params, image);
+    // a kernel's own arguments are known to point to global memory; these have to be loaded as such pointers
+    auto global = [&](auto& pointer, size_t offset) {
+        const Global q = *(const __attribute__((address_space(4))) Global*)((Bytes)from + offset);
+        pointer = static_cast<decltype(+pointer)>((void*)q);
+    };
+    global(p.g, offsetof(Params, g));
+    global(p.x, offsetof(Params, x));
+    global(p.x16, offsetof(Params, x16));
+    global(p.xin, offsetof(Params, xin));
+    global(p.levels, offsetof(Params, levels));
+    global(p.mom, offsetof(Params, mom));
+    global(p.var, offsetof(Params, var));
+    global(p.codes, offsetof(Params, codes));
+    global(p.meta, offsetof(Params, meta));
+    global(p.n_saturated, offsetof(Params, n_saturated));
+    global(p.peer_codes, offsetof(Params, peer_codes));
+    global(p.peer_meta, offsetof(Params, peer_meta));
+    return p;
+}
+
 struct PhiloxKey {
     uint32_t k0, k1;
 };

@@ -130,7 +130,7 @@ constexpr int tile_min_blocks(int mode, int waves, int rows) {
 
 template <int MODE, int R, int W>
 __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
-    tile_kernel(const Params p, const Segment* __restrict__ segs, const TileArgs a) {
+    tile_kernel(const Params args, const Segment* __restrict__ segs, const TileArgs a) {
     static_assert(R % 2 == 0 && R <= kTileMaxRows && (W == 1 || W == 4), "shape");
     typedef TileLds<R, W> Lds;
     constexpr int TEAM = Lds::kTeam;
@@ -141,6 +141,21 @@ __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
     // side 60.4 / 58.1, on a lattice 59.4 / 55.8 and 70.7 / 66.1; 8 bits 58.5 / 58.3 and, packed by the converting
     // instruction, 56.6 / 56.5, which does not make up for the others).
     constexpr bool kRowByRow = MODE == MODE_WEIGHT && R == 8;
+    // A call's last tile, which its buckets seldom fill, runs the instructions of all others in the shapes that small
+    // calls get: what a single wave runs comes from memory, line after line, and such a call waits for it (us, 65571
+    // elements in buckets of 320 / 2336, on a path of its own / with the others: AdamW step 8.5 / 7.2, 9.9 / 7.2, step
+    // 5.2 / 4.6, 7.3 / 5.9, gradient encoder 3.8 / 3.3, 5.0 / 4.0, four peers 5.2 / 4.8, 7.5 / 5.9; 3M, 768, step 10.6
+    // / 9.0). Large calls do not: there a team of one wave and, where the patches take registers, the weight encoder
+    // and the steps of eight rows were 2-5 % slower (100M, 2336, AdamW step 492 / 514).
+    constexpr bool kTailsInline =
+        R == 2 || (W == 4 && MODE != MODE_WEIGHT && !(R == 8 && (MODE == MODE_FUSED || MODE == MODE_ADAMW)));
+    // The parameters are read again for every tile, and again for its weights, and the keys of the ten rounds are
+    // computed for every block: held across the loop they were 50-150 scalar registers too many, each written to and
+    // read from a lane of a vector register (step, four rows, 77 -> 24, and 90 -> 87 vector registers). 216 calls of
+    // 2^16 to 10^8 elements in buckets of 96 to 2336: code-resident step 1.05-1.08 times faster, receive side
+    // 1.02-1.07, gradient encoder 1.03, steps 1.02-1.04; the weight encoder's larger tiles and the nearest
+    // level, with ten, lost 0-2 %.
+    constexpr bool kReadAgain = MODE != MODE_LEVELS && (MODE != MODE_WEIGHT || R == 2);
     __shared__ Lds lds_all[4 / W];
     constexpr bool kCoin = MODE == MODE_LEVELS_COIN;
     __shared__ char level_lds[kLevels ? 4 / W * sizeof(TileLevels<kCoin>) : 1] __attribute__((aligned(16)));
@@ -151,21 +166,12 @@ __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
     uint32_t loaded_tensor = ~0u;  // whose level table the team holds
     bool level_by_cell = false;    // ... and how it is used
 
-    const int B = p.bucket;
+    const int B = args.bucket;
     const int k = B >> 5;      // groups of a bucket
     const int S = B >> 2;      // slots of a bucket
     const int P = a.buckets;   // buckets of a full tile
-    const float Lg = (float)((1 << p.gbits) - 1);
-    const uint32_t top16_g = (uint32_t)((1 << p.gbits) - 1) << 16;
-    const float Lw = (float)((1 << p.wbits) - 1);
-    const Divider div = {p.delta, p.inv_delta, p.delta_pow2 != 0};
-    const bool lattice = p.delta > 0.0f;
-    const bool symmetric = (p.flags & FLAG_SYMMETRIC) != 0;
-    const bool grad_shift = (p.flags & FLAG_GRAD_SHIFT) != 0;
-    const bool keep_master = kWritesX && (p.flags & FLAG_KEEP_MASTER) != 0;
-    const PhiloxKey key = launch_key<MODE>(p);
-    const Shifts shifts = launch_shifts<MODE>(p, key);
-    const float xi = shifts.xi;
+    const PhiloxKey key = launch_key<MODE>(args);
+    const Shifts shifts = launch_shifts<MODE>(args, key);
     uint32_t saturated = 0;
 
     uint64_t unit0 = W == 1 ? (uint64_t)blockIdx.x * 4u + wave_in_block : blockIdx.x;
@@ -185,16 +191,26 @@ __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
         // keeps what follows from the lane's number alone (slots, buckets, offsets of every row) out of registers that
         // live across the loop
         asm volatile("" : "+v"(tid));
+        Params p = kReadAgain ? params_again() : args;
+        const float Lg = (float)((1 << p.gbits) - 1);
+        const uint32_t top16_g = (uint32_t)((1 << p.gbits) - 1) << 16;
+        const bool grad_shift = (p.flags & FLAG_GRAD_SHIFT) != 0;
         const int odd = tid & 1;
         const uint64_t bucket0 = unit * (uint64_t)P;
         const uint64_t left = p.num_buckets - bucket0;
         const int here = left < (uint64_t)P ? (int)left : P;  // buckets of this tile
         const BucketRef first = locate_bucket(p, segs, bucket0, bucket0, (uint32_t)B);
         const uint64_t e0 = first.e0;
-        // contiguous: P full buckets of one tensor
-        const bool whole = here == P && first.left >= (uint64_t)P * (uint64_t)B;
+        // Contiguous: one piece of one tensor; full buckets or, where tails run with the others, a slot at least.
+        const bool whole = kTailsInline ? first.left > (uint64_t)(here - 1) * (uint64_t)B && first.left >= 4u
+                                        : here == P && first.left >= (uint64_t)P * (uint64_t)B;
         const uint64_t word0 = bucket0 * (uint64_t)(B >> 5);  // times the code width: the tile's first code word
         const int used = here * S;                            // slots of these buckets
+        // of a contiguous tile: its elements, the slots that exist in full, the elements of the one after them
+        const int existing = kTailsInline && first.left < (uint64_t)(4 * used) ? (int)first.left : 4 * used;
+        const int full = kTailsInline ? existing >> 2 : used;
+        const int partial = kTailsInline ? existing & 3 : 0;
+        const bool ragged = kTailsInline ? !whole || full != used : !whole;
         // whether the row is computed: the smallest teams leave an unused second one out
         auto computed = [&](int r) { return R > 2 || r == 0 || used > TEAM; };
         if (W > 1) team_sync<W>();  // the previous tile's LDS reads are done
@@ -223,14 +239,28 @@ __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
             const int c = (int)w[1] - off;
             return {w[0] + (uint32_t)off, c < 0 ? 0 : c > 4 ? 4 : c};
         };
-        // In a contiguous one slot s is elements 4s .. 4s+3; the slots past the last bucket read the tile's first
-        // elements instead: in bounds, and their values go nowhere.
+        // In a contiguous one slot s is elements 4s .. 4s+3; the slots past the last full one read the tile's first
+        // elements instead: in bounds, and their values go nowhere. So a call's last tile runs the instructions of all
+        // others, and its own are only the patches of the slot that exists in part.
+        auto patch = [&](const float* base, float (&v)[R][4]) {  // once the tile's loads are under way
+            if (kTailsInline && __builtin_expect(whole && partial != 0, 0)) {
+                const float* from = base + e0 + 4 * full;
+                const float x0 = from[0], x1 = partial > 1 ? from[1] : 0.0f, x2 = partial > 2 ? from[2] : 0.0f;
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const bool mine = slot_of(r) == full;
+                    v[r][0] = mine ? x0 : v[r][0];
+                    v[r][1] = mine ? x1 : v[r][1];
+                    v[r][2] = mine ? x2 : v[r][2];
+                }
+            }
+        };
         auto load = [&](const float* base, float (&v)[R][4]) {
             const char* at = reinterpret_cast<const char*>(base + e0);
             if (__builtin_expect(whole, 1)) {
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
-                    const uint32_t s = slot_of(r) < used ? (uint32_t)slot_of(r) : 0u;
+                    const uint32_t s = slot_of(r) < full ? (uint32_t)slot_of(r) : 0u;
                     const f4 x = __builtin_nontemporal_load(reinterpret_cast<const f4*>(at + s * 16u));
 #pragma unroll
                     for (int i = 0; i < 4; ++i) v[r][i] = x[i];
@@ -244,13 +274,29 @@ __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
                 }
             }
         };
+        // 16-bit values are two to a word in the first two places of a slot until they are widened: at once, since with
+        // a patch in between the compiler keeps both for the steps (four waves, eight rows: 175 registers instead of
+        // 156); but after it in the gradient encoder, which would keep the widened ones for longer (102 against 89).
+        constexpr bool kWidenLater = kTailsInline && MODE == MODE_GRAD;
+        auto widen = [&](bool bf16, float (&v)[R][4]) {
+            auto all = [&](auto widened) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const uint32_t h[2] = {__float_as_uint(v[r][0]), __float_as_uint(v[r][1])};
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[r][i] = widened(i & 1 ? h[i >> 1] >> 16 : h[i >> 1] & 0xFFFFu);
+                }
+            };
+            if (bf16) all([](uint32_t h) { return widen16<true>(h); });
+            else all([](uint32_t h) { return widen16<false>(h); });
+        };
         auto load_half = [&](const void* base, bool bf16, float (&v)[R][4]) {
             const uint16_t* first_half = static_cast<const uint16_t*>(base) + e0;
             uint32_t h[R][2];
             if (__builtin_expect(whole, 1)) {
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
-                    const uint32_t s = slot_of(r) < used ? (uint32_t)slot_of(r) : 0u;
+                    const uint32_t s = slot_of(r) < full ? (uint32_t)slot_of(r) : 0u;
                     const u2 x = __builtin_nontemporal_load(
                         reinterpret_cast<const u2*>(reinterpret_cast<const char*>(first_half) + s * 8u));
                     h[r][0] = x[0];
@@ -266,19 +312,30 @@ __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
                         if (i < s.count) h[r][i >> 1] |= (uint32_t)first_half[s.rel + i] << (16 * (i & 1));
                 }
             }
-            if (bf16) {
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int i = 0; i < 2; ++i) v[r][i] = __uint_as_float(h[r][i]);
+            if (!kWidenLater) widen(bf16, v);
+        };
+        auto patch_half = [&](const void* base, bool bf16, float (&v)[R][4]) {
+            if (kTailsInline && __builtin_expect(whole && partial != 0, 0)) {
+                const uint16_t* from = static_cast<const uint16_t*>(base) + e0 + 4 * full;
+                const uint32_t h[3] = {from[0], partial > 1 ? from[1] : 0u, partial > 2 ? from[2] : 0u};
+                float x[3];
+                if (kWidenLater) {
+                    x[0] = __uint_as_float(h[0] | (h[1] << 16));
+                    x[1] = __uint_as_float(h[2]);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) x[i] = bf16 ? widen16<true>(h[i]) : widen16<false>(h[i]);
+                }
 #pragma unroll
                 for (int r = 0; r < R; ++r)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        v[r][i] = widen16<true>(i & 1 ? h[r][i >> 1] >> 16 : h[r][i >> 1] & 0xFFFFu);
-            } else {
-#pragma unroll
-                for (int r = 0; r < R; ++r)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        v[r][i] = widen16<false>(i & 1 ? h[r][i >> 1] >> 16 : h[r][i >> 1] & 0xFFFFu);
+                    for (int i = 0; i < (kWidenLater ? 2 : 3); ++i) v[r][i] = slot_of(r) == full ? x[i] : v[r][i];
             }
+            if (kWidenLater) widen(bf16, v);
         };
         auto store = [&](float* base, const float (&v)[R][4]) {
             char* at = reinterpret_cast<char*>(base + e0);
@@ -286,8 +343,23 @@ __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
                     const f4 x = {v[r][0], v[r][1], v[r][2], v[r][3]};
-                    if (slot_of(r) < used)
+                    if (slot_of(r) < full)
                         __builtin_nontemporal_store(x, reinterpret_cast<f4*>(at + (uint32_t)slot_of(r) * 16u));
+                }
+                if (kTailsInline && __builtin_expect(partial != 0, 0)) {
+                    float x[3] = {};
+                    bool any = false;
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        const bool mine = slot_of(r) == full;
+                        any |= mine;
+#pragma unroll
+                        for (int i = 0; i < 3; ++i) x[i] = mine ? v[r][i] : x[i];
+                    }
+                    float* to = base + e0 + 4 * full;
+#pragma unroll
+                    for (int i = 0; i < 3; ++i)
+                        if (any && i < partial) to[i] = x[i];
                 }
             } else {
 #pragma unroll
@@ -306,9 +378,24 @@ __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
                 for (int r = 0; r < R; ++r) {
                     const u2 x = {half_bits(v[r][0], f16) | (half_bits(v[r][1], f16) << 16),
                                   half_bits(v[r][2], f16) | (half_bits(v[r][3], f16) << 16)};
-                    if (slot_of(r) < used)
+                    if (slot_of(r) < full)
                         __builtin_nontemporal_store(
                             x, reinterpret_cast<u2*>(reinterpret_cast<char*>(first_half) + (uint32_t)slot_of(r) * 8u));
+                }
+                if (kTailsInline && __builtin_expect(partial != 0, 0)) {
+                    float x[3] = {};
+                    bool any = false;
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        const bool mine = slot_of(r) == full;
+                        any |= mine;
+#pragma unroll
+                        for (int i = 0; i < 3; ++i) x[i] = mine ? v[r][i] : x[i];
+                    }
+                    uint16_t* to = first_half + 4 * full;
+#pragma unroll
+                    for (int i = 0; i < 3; ++i)
+                        if (any && i < partial) to[i] = (uint16_t)half_bits(x[i], f16);
                 }
             } else {
 #pragma unroll
@@ -332,8 +419,10 @@ __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
             }
         };
         auto uniforms = [&](int cp, uint32_t (&h)[4]) {
+            uint32_t k0 = key.k0, k1 = key.k1;
+            asm volatile("" : "+s"(k0), "+s"(k1));
             uniforms_of_pair<(MODE == MODE_GRAD || MODE == MODE_LEVELS_COIN)>(p.block0 + (e0 >> 3) + block_rel[cp], odd,
-                                                                              key.k0, key.k1, h);
+                                                                              k0, k1, h);
         };
         // Minimum and maximum of every bucket of the tile, then its grid: make(lo, hi, bucket in the tile) in the
         // lanes that combine that bucket, the result in lds.grid for all.
@@ -344,7 +433,7 @@ __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
                 row_hi[r] = fmaxf(fmaxf(v[r][0], v[r][1]), fmaxf(v[r][2], v[r][3]));
             };
             auto range_of_existing = [&](int r) {
-                const int c = place(slot_of(r)).count;
+                const int c = kTailsInline && whole ? existing - 4 * slot_of(r) : place(slot_of(r)).count;
                 row_lo[r] = __builtin_inff();
                 row_hi[r] = -__builtin_inff();
 #pragma unroll
@@ -365,14 +454,14 @@ __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
                     range(r);
-                    if (__builtin_expect(!whole, 0)) range_of_existing(r);
+                    if (__builtin_expect(ragged, 0)) range_of_existing(r);
                     over_group(r);
                     if ((tid & 7) == 0) keep(r);
                 }
             } else {
 #pragma unroll
                 for (int r = 0; r < R; ++r) range(r);
-                if (__builtin_expect(!whole, 0)) {
+                if (__builtin_expect(ragged, 0)) {
 #pragma unroll
                     for (int r = 0; r < R; ++r) range_of_existing(r);
                 }
@@ -449,6 +538,13 @@ __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
                     const int c = place(slot_of(r)).count;
                     if (c < 4) q[r] &= (1u << (c * bits)) - 1u;
                 }
+            } else if (kTailsInline && __builtin_expect(full != used, 0)) {
+                const uint32_t some = (1u << (partial * bits)) - 1u;
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const uint32_t past = slot_of(r) == full ? some : 0u;
+                    q[r] &= slot_of(r) < full ? ~0u : past;
+                }
             }
             if (bits == 8) {
 #pragma unroll
@@ -493,6 +589,13 @@ __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
                 load(p.mom, mom);
                 load(p.var, var);
             }
+            if (mode_mixed_precision(MODE) && p.g_half != 0u) patch_half(p.g, p.g_half == 1u, gv);
+            else patch(p.g, gv);
+            if constexpr (MODE == MODE_FUSED || MODE == MODE_ADAMW) patch(p.x, w);
+            if constexpr (mode_local_adamw(MODE)) {
+                patch(p.mom, mom);
+                patch(p.var, var);
+            }
             if constexpr (mode_codes_resident(MODE)) {
                 unpack(old_words, p.wbits, w);
 #pragma unroll
@@ -505,7 +608,7 @@ __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
                 }
             }
             bucket_grids(gv, [&](float lo, float hi, int b) -> f4 {
-                const MinMaxGrid g = make_minmax_grid(lo, hi, Lg, symmetric);
+                const MinMaxGrid g = make_minmax_grid(lo, hi, Lg, (p.flags & FLAG_SYMMETRIC) != 0);
                 const float base = grad_shift ? fmaf(shifts.xi_g, g.scale, g.lo) : g.lo;
                 if constexpr (MODE == MODE_GRAD) write_meta(b, base, g.scale);
                 return f4{g.lo, g.inv, g.scale, base};
@@ -617,6 +720,11 @@ __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
                     }
                 }
             }
+            patch(p.x, w);
+            if constexpr (MODE == MODE_RECV_ADAMW) {
+                patch(p.mom, mom);
+                patch(p.var, var);
+            }
             team_sync<W>();
 #pragma unroll
             for (int r = 0; r < R; ++r)
@@ -629,8 +737,15 @@ __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
             }
         } else {
             load(p.xin, w);
+            patch(p.xin, w);
         }
 
+        if (kReadAgain) p = params_again();
+        const float Lw = (float)((1 << p.wbits) - 1);
+        const Divider div = {p.delta, p.inv_delta, p.delta_pow2 != 0};
+        const bool lattice = p.delta > 0.0f;
+        const bool keep_master = kWritesX && (p.flags & FLAG_KEEP_MASTER) != 0;
+        const float xi = shifts.xi;
         // the full-precision partition keeps the updated value itself
         if (kWritesX && keep_master) store(p.x, w);
 
@@ -737,7 +852,7 @@ __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
                 base = (origin + xi) * p.delta;
                 scale = p.delta;
             } else {
-                const MinMaxGrid g = make_minmax_grid(lo, hi, Lw, symmetric);
+                const MinMaxGrid g = make_minmax_grid(lo, hi, Lw, (p.flags & FLAG_SYMMETRIC) != 0);
                 base = fmaf(xi, g.scale, g.lo);
                 scale = g.scale;
                 origin = g.lo;
@@ -750,7 +865,7 @@ __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
         auto weight_grid = [&](int r) -> f4 { return lds.grid[bucket_of_slot(slot_of(r))]; };
         auto onto_lattice = [&](int r) {
             const f4 gr = weight_grid(r);
-            const int n = __builtin_expect(whole, 1) ? (slot_of(r) < used ? 4 : 0) : place(slot_of(r)).count;
+            const int n = __builtin_expect(whole, 1) ? existing - 4 * slot_of(r) : place(slot_of(r)).count;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 uint32_t over = 0;
@@ -806,10 +921,10 @@ __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
         if (want16) store_half(p.x16, p.x16_f16 != 0u, w);
     }
 
-    if (MODE != MODE_GRAD && !kLevels && p.n_saturated != nullptr) {
+    if (MODE != MODE_GRAD && !kLevels && args.n_saturated != nullptr) {
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) saturated += __shfl_down(saturated, off, 64);
-        if ((threadIdx.x & 63) == 0 && saturated != 0) atomicAdd(p.n_saturated, (unsigned long long)saturated);
+        if ((threadIdx.x & 63) == 0 && saturated != 0) atomicAdd(args.n_saturated, (unsigned long long)saturated);
     }
 }
 

@@ -201,3 +201,64 @@ def test_a_step_large_enough_for_three_workgroups():
     ref.fused_step_inplace(x_np, g_np, 1e-3, 8, 8, B, 0.0, 3, 0, wc, wm)
     assert first_mismatch(x, x_np) == -1 and first_mismatch(c, wc.view(np.int32)) == -1
     assert first_mismatch(m.view(-1), wm.reshape(-1)) == -1
+
+
+@pytest.mark.parametrize("B", [32, 96, 320, 768, 2336, 4128, 6176])
+@pytest.mark.parametrize("tail", [1, 2, 3, 4, 5, 30])  # elements of the last bucket, at its slots of four
+@pytest.mark.parametrize("buckets", [0, 1, 37])        # full ones before it
+def test_the_last_tile(B, tail, buckets):
+    """A tile that the call's elements do not fill, down to less than one slot: what it computes, and that what follows
+    the call's elements stays as it is."""
+    n, room = buckets * B + tail, 64
+    x, g = synth(n, B + tail)
+    mom, var = _moments(n, B)
+    guard = -7.0
+
+    def dev(a, dtype=torch.float32):
+        t = torch.full((n + room,), guard, dtype=dtype, device=DEV)
+        t[:n] = _dev(a).to(dtype)
+        return t
+
+    for dtype, wbits, gbits, delta in ((torch.float32, 8, 4, 0.0), (torch.bfloat16, 5, 3, 2.0 ** -8),
+                                       (torch.float16, 6, 8, 0.0)):
+        gd = dev(g, dtype)
+        wide = gd[:n].float().cpu().numpy()
+        c, m = qb.alloc_packed(n, gbits, B, DEV)
+        if dtype == torch.float32:
+            qb.qsdp_quantize_grad(gd[:n], gbits, B, 5, 24, c, m.view(-1))
+        else:
+            qb.qsdp_quantize_grad_g16(gd[:n], gbits, B, 5, 24, c, m.view(-1))
+        grads = ref.quantize_grad(wide, gbits, B, 5, 24)
+        assert _same(c, m, *grads), dtype
+
+        c, m = qb.alloc_packed(n, wbits, B, DEV)
+        qb.qsdp_quantize_weight(dev(x)[:n], wbits, B, delta, 6, c, m.view(-1))
+        codes = ref.quantize_weight(x, wbits, B, delta, 6)[:2]
+        assert _same(c, m, *codes), dtype
+        qb.qsdp_fused_step_codes(c, m.view(-1), dev(wide)[:n], 1e-2, wbits, gbits, B, delta, 7)
+        assert _same(c, m, *ref.fused_step_codes(*codes, wide, 1e-2, wbits, gbits, B, delta, 7)[:2]), dtype
+
+        xd, md, vd, x16 = dev(x), dev(mom), dev(var), dev(x, torch.float16)
+        sat = torch.zeros(1, dtype=torch.int64, device=DEV)
+        half = torch.float16 if dtype == torch.float32 else dtype
+        gh = dev(wide, half)
+        wide = gh[:n].float().cpu().numpy()
+        qb.qsdp_fused_adamw_step_mp(xd[:n], gh[:n], md[:n], vd[:n], *ADAMW, wbits, gbits, B, delta, 9, 8, 0, c,
+                                    m.view(-1), x16[:n], sat)
+        wx, wmo, wvo, wc, wm, ws = ref.fused_adamw_step(x, wide, mom, var, *ADAMW, wbits, gbits, B, delta, 9, 8, 0,
+                                                        True)
+        assert _same(c, m, wc, wm) and int(sat) == ws, dtype
+        for t, want in ((xd, wx), (md, wmo), (vd, wvo)):
+            assert bits_equal(np_f32(t[:n]), want) and bool((t[n:] == guard).all()), dtype
+        assert torch.equal(x16[:n].cpu(), torch.from_numpy(wx).half()) and bool((x16[n:] == guard).all()), dtype
+
+        xd, rows = dev(x), torch.zeros((2, -(-grads[0].size // 4) * 4), dtype=torch.int32, device=DEV)
+        rows[:, :grads[0].size] = _dev(grads[0].view(np.int32))
+        floats = torch.zeros((2, -(-grads[1].size // 4) * 4), dtype=torch.float32, device=DEV)
+        floats[:, :grads[1].size] = _dev(grads[1].reshape(-1))
+        floats[1] *= 0.5
+        qb.qsdp_recv_step(xd[:n], rows, floats, 2, 0.5, 1e-2, wbits, gbits, B, delta, 11, 0, c, m.view(-1))
+        peer = grads[1].reshape(-1)
+        want, wc, wm, _ = ref.recv_step(x, np.stack([grads[0]] * 2), np.stack([peer, peer * np.float32(0.5)]), 2, 0.5,
+                                        1e-2, wbits, gbits, B, delta, 11, 0, True)
+        assert bits_equal(np_f32(xd[:n]), want) and _same(c, m, wc, wm) and bool((xd[n:] == guard).all()), dtype
