@@ -198,9 +198,10 @@ __host__ __device__ __forceinline__ Shifts draw_shifts(uint32_t flags, PhiloxKey
 // instructions, each waiting for the one before, ahead of every wave's one bucket. 3M values, drawn by the waves / by the
 // host: step 9.2 / 8.4 us and 5-bit weights 10.5 / 9.6 in buckets of 96, receive side 8.3 / 7.6 in buckets of 128,
 // 5-bit weights 9.0 / 8.4 in buckets of 1024; 1.02-1.05 up to 100M values (step, 1024: 195.8 / 188.8), nothing beyond.
-template <int MODE>
+// DRAW: or where the caller asks for it.
+template <int MODE, bool DRAW = false>
 __device__ __forceinline__ Shifts launch_shifts(const Params& p, PhiloxKey key) {
-    if (mode_device_seed(MODE) && __builtin_expect(p.seed_dev != nullptr, 0)) return draw_shifts(p.flags, key);
+    if (DRAW || (mode_device_seed(MODE) && __builtin_expect(p.seed_dev != nullptr, 0))) return draw_shifts(p.flags, key);
     return {p.xi, p.xi_g};
 }
 
