@@ -146,16 +146,20 @@ __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
     // elements in buckets of 320 / 2336, on a path of its own / with the others: AdamW step 8.5 / 7.2, 9.9 / 7.2, step
     // 5.2 / 4.6, 7.3 / 5.9, gradient encoder 3.8 / 3.3, 5.0 / 4.0, four peers 5.2 / 4.8, 7.5 / 5.9; 3M, 768, step 10.6
     // / 9.0). Large calls do not: there a team of one wave and, where the patches take registers, the weight encoder
-    // and the steps of eight rows were 2-5 % slower (100M, 2336, AdamW step 492 / 514).
+    // and the steps of eight rows were 2-5 % slower (100M, 2336, AdamW step 492 / 514), and so was the gradient encoder of
+    // six and eight rows (125M, 4 bits, buckets of 2080 / 4128: 111.0 / 120.4 on a path of its own, 113.7 / 124.2).
     constexpr bool kTailsInline =
-        R == 2 || (W == 4 && MODE != MODE_WEIGHT && !(R == 8 && (MODE == MODE_FUSED || MODE == MODE_ADAMW)));
+        R == 2 || (W == 4 && MODE != MODE_WEIGHT && !(R == 8 && (MODE == MODE_FUSED || MODE == MODE_ADAMW)) &&
+                   !(R > 4 && MODE == MODE_GRAD));
     // The parameters are read again for every tile, and again for its weights, and the keys of the ten rounds are
     // computed for every block: held across the loop they were 50-150 scalar registers too many, each written to and
     // read from a lane of a vector register (step, four rows, 77 -> 24, and 90 -> 87 vector registers). 216 calls of
     // 2^16 to 10^8 elements in buckets of 96 to 2336: code-resident step 1.05-1.08 times faster, receive side
     // 1.02-1.07, gradient encoder 1.03, steps 1.02-1.04; the weight encoder's larger tiles and the nearest
-    // level, with ten, lost 0-2 %.
-    constexpr bool kReadAgain = MODE != MODE_LEVELS && (MODE != MODE_WEIGHT || R == 2);
+    // level, with ten, lost 0-2 %; the gradient encoder of four waves and six rows takes 78 vector registers so, at most
+    // 72 without, which is a wave more to a SIMD.
+    constexpr bool kReadAgain =
+        MODE != MODE_LEVELS && !(MODE == MODE_GRAD && W == 4 && R > 4) && (MODE != MODE_WEIGHT || R == 2);
     // The first team takes the call's last tile, which takes longer for its short bucket, and the last team the first;
     // all others keep theirs, so that a tile meets its codes in the same L2 as in the next call. us, each its own / so,
     // buckets of 768, 1504, 2336: 5M elements, step 12.7 / 11.7, 13.0 / 11.9, 14.7 / 12.8, AdamW step 35.8 / 31.0,
