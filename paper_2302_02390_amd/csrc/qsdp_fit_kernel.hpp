@@ -41,9 +41,9 @@ namespace qsdp {
 // 2048 the sorting, of which LDS holds room for eight slots. Tensors of few batches are bound by what a workgroup does
 // before its first one, the table of powers above all, and by one workgroup of this size to a compute unit.
 //
-// The boundary search needs levels that ascend by more than 2^-20 within [0, 1] (then the comparison of the two
-// rounded distances is monotone in the value and flips within 2^-22 of the midpoint) and cells that are not
-// crowded. A batch for which that does not hold is assigned value by value, by the same wave.
+// The boundary search needs levels that ascend by more than 2^-20 within [0, 1 + 2^-22] (then the comparison of the two
+// rounded distances is monotone in the value and flips within 2^-22 of the midpoint, which is below 1) and cells that
+// are not crowded. A batch for which that does not hold is assigned value by value, by the same wave.
 // ---------------------------------------------------------------------------------------
 struct FitParams {
     const float* v;
@@ -80,8 +80,8 @@ struct FitShape {
     using Slot = FitSlot<kBucketMax, kCells>;
 };
 
-// Count and sum of a set of normalised values in one word: sum of at most 2^13 values of at most 2^32 below, count
-// above.
+// Count and sum of a set of normalised values in one word: sum of at most 2^11 values of at most 2^32 + 2^10 below,
+// count above.
 constexpr int kFitCountShift = 48;
 constexpr uint64_t kFitSumMask = (1ull << kFitCountShift) - 1;
 
@@ -92,12 +92,20 @@ constexpr float kFitUnit = 0x1p32f;
 constexpr float kFitFiller = 2.0f * kFitUnit;
 constexpr int kFitSpare = 20;
 
-// z (in [0, 1], units of 2^-32) as an integer, truncated, and a count of one. The conversion saturates at the largest
-// z, below 1 it never gives all ones.
+// z (units of 2^-32) as an integer, truncated, and a count of one. The conversion saturates from 1 on, where z is a whole
+// number of units, 2^9 of them to a step of its last bit; below 1 it never gives all ones.
 __device__ __forceinline__ uint64_t fit_word(float z) {
     const uint32_t fraction = (uint32_t)z;
     const bool one = fraction == ~0u;
-    return ((uint64_t)((1u << (kFitCountShift - 32)) + (one ? 1u : 0u)) << 32) | (one ? 0u : fraction);
+    const uint32_t excess = (__float_as_uint(z) - __float_as_uint(kFitUnit)) << 9;
+    return ((uint64_t)((1u << (kFitCountShift - 32)) + (one ? 1u : 0u)) << 32) | (one ? excess : fraction);
+}
+
+// A bucket's range of more than 2^126 has a subnormal reciprocal, off by up to 2^-150, and the largest of its
+// normalised values can be 1 + 2^-23 or 1 + 2^-22; with any other range it is 1 at most (the product of a number and
+// its rounded reciprocal is within 2^-24 of 1).
+__device__ __forceinline__ bool fit_past_one(const MinMaxGrid& grid) {
+    return grid.inv > 0.0f && grid.inv < 0x1p-126f;
 }
 
 // The cell of a value: C cells of equal width, what lies outside them in the first and the last. Monotone, and in range
@@ -284,8 +292,8 @@ struct FitPowers {
     static __device__ __forceinline__ float step(float level, uint32_t c, uint64_t total, double moved) {
         // total / c rounded once: r, the approximate reciprocal, is off by at most 2^-23 of itself, so a by 2^-22 and,
         // corrected once, by 2^-44, 2^9 ulp; its remainder is exact (c is at most 2^10: below 2^20 ulp), and the
-        // quotient corrected again is within 2^-13 ulp of t / c, which, t * 2^32 and c being integers below 2^46 and
-        // 2^11, is never closer than 2^-11 ulp to a rounding boundary without being a binary64 number itself. (The
+        // quotient corrected again is within 2^-13 ulp of t / c, which, t * 2^32 and c being integers of at most 2^43
+        // and 2^10, is never closer than 2^-11 ulp to a rounding boundary without being a binary64 number itself. (The
         // first remainder, below 2^42 ulp, is exact too.) Without values it is not used.
         const double n = (double)c;
         const double r = (double)__builtin_amdgcn_rcpf((float)c);
@@ -350,7 +358,8 @@ __device__ __forceinline__ FitNext fit_next(const Slot& slot) {
     return next;
 }
 
-// The lanes with a level that is not in [0, 1]. One that is stays there: it moves towards a mean of values in [0, 1].
+// The lanes with a level that is not in [0, 1]. One that is stays within [0, 1 + 2^-22], as far as the values reach
+// (fit_past_one), towards a mean of which it moves.
 template <int M>
 __device__ __forceinline__ uint64_t fit_outside(const float (&lv)[M]) {
     uint64_t outside = 0;
@@ -423,8 +432,8 @@ __device__ __forceinline__ void fit_batch(const Slot& slot, const Slot& next_slo
         upto[i] = slot.before[group[i] >> 2];
         rare |= __builtin_amdgcn_ballot_w64(end[i] > group[i] + 4u * S * G);
     }
-    // count and sum of those of four values that are on the lower level's side: below 1 (the upper level is at most 1
-    // and closer), so 32 bits hold them. Values past the boundary's cells may be among the four, and fillers past the
+    // count and sum of those of four values that are on the lower level's side: below 1 (the boundary is), so 32 bits
+    // hold them. Values past the boundary's cells may be among the four, and fillers past the
     // last one: above the boundary.
     auto below_of = [&](f4 v, float t) -> uint64_t {
         uint64_t w[4];
@@ -706,6 +715,7 @@ __global__ void __launch_bounds__((FitShape<BITS, VPT, W>::kThreads)) fit_levels
             }
             fit_wave_sync();
             const MinMaxGrid grid = make_minmax_grid(lo, hi, 1.0f, false);
+            const bool past_one = __builtin_amdgcn_readfirstlane(fit_past_one(grid)) != 0;
             const FitCells cells = fit_cells<C>(grid, hi, sum * ((float)kSampled / (64 * VPT)),
                                                 absolute * ((float)kSampled / (64 * VPT)));
             uint32_t* cell[VPT];
@@ -762,7 +772,8 @@ __global__ void __launch_bounds__((FitShape<BITS, VPT, W>::kThreads)) fit_levels
             fit_wave_sync();
             // Count and sum before every group of four values, rows of 64 groups side by side; the sums of the
             // values' upper and lower 16 bits apart, so that 32 bits hold them. A value of 1 (the conversion saturates)
-            // is one short here: it is past every boundary, so that only the word of all values has to know.
+            // is one short here, one past 1 by more: they are above every boundary, so that only the word of all values
+            // has to know.
             constexpr int kRows = VPT >= 4 ? VPT / 4 : 1;
             constexpr bool kHalf = VPT < 4;  // half a row
             uint32_t incl[2 * kRows], row[2 * kRows], ones = 0;
@@ -801,6 +812,13 @@ __global__ void __launch_bounds__((FitShape<BITS, VPT, W>::kThreads)) fit_levels
                     base + (incl[2 * i] - row[2 * i]) + ((uint64_t)(incl[2 * i + 1] - row[2 * i + 1]) << 16);
                 if (!kHalf || lane < 32) slot.before[g] = before + ((uint64_t)c << kFitCountShift);
                 base += last(incl[2 * i]) + (last(incl[2 * i + 1]) << 16);
+            }
+            if (__builtin_expect(past_one, 0)) {  // what the conversion left out of values past 1
+                uint32_t excess[1] = {0};
+#pragma unroll 1
+                for (int i = lane; i < m; i += 64) excess[0] += slot.z[i] > kFitUnit ? (uint32_t)(slot.z[i] - kFitUnit) : 0u;
+                fit_wave_scan(excess);
+                base += (uint32_t)__builtin_amdgcn_readlane((int)excess[0], 63);
             }
             fit_wave_sync();
             if (lane == 0) {

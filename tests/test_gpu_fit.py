@@ -126,3 +126,42 @@ def test_sums_before_the_groups_of_a_batch(B, bits):
         far[70 % B::B] = -2.0e4
         for v in (top, crest, far):
             assert _same(v, bits, B, 0.03, ref.levels_uniform(bits)), cut
+
+
+def _steep_ranges(rng):
+    """Ranges whose reciprocal is subnormal and rounds up, so that the largest normalised value is past 1."""
+    r = rng.uniform(2.0 ** 126, 3.39e38, 4000).astype(np.float32)
+    r = r[r * (np.float32(1.0) / r) > np.float32(1.0)]
+    assert r.size > 400
+    return r
+
+
+@pytest.mark.parametrize("B", [32, 96, 128, 256, 512, 1024, 2048, 4096, 8192])
+@pytest.mark.parametrize("bits", [1, 3, 4, 5, 6, 8])
+def test_normalised_values_past_one(B, bits):
+    """Finite buckets with a range above 2^126, where the largest normalised value can be 1 + 2^-23 or 1 + 2^-22: its
+    excess enters the sums, on the way of the boundaries and value by value, and takes the last level past 1, from where
+    later batches start."""
+    rng = np.random.default_rng(B + bits)
+    ranges = _steep_ranges(rng)
+    K = 1 << bits
+    close = (1.0 - 2.0 ** -22 * np.arange(K, dtype=np.float64)[::-1]).astype(np.float32)  # gaps below the search's bound
+    past = False
+    for cut in (0, 1, 30):
+        n = 13 * B - cut
+        v = np.empty(n, np.float32)
+        for j in range(13):
+            b = v[j * B: (j + 1) * B]
+            r = ranges[rng.integers(ranges.size)]
+            lo, hi = -r * np.float32(0.5), r * np.float32(0.5)  # exact, and so is their difference
+            share = (0.3, 1.0, 0.02)[j % 3]
+            b[:] = np.where(rng.random(b.size) < share, hi, (rng.random(b.size) * r + lo).astype(np.float32))
+            b[0], b[-1] = lo, hi
+            assert (hi - lo) * (np.float32(1.0) / (hi - lo)) > np.float32(1.0)
+        ordinary = v.copy()
+        ordinary[7 * B:] = rng.standard_normal(n - 7 * B).astype(np.float32)  # later batches within [0, 1]
+        for x in (v, ordinary):
+            for levels in (ref.levels_uniform(bits), close):
+                past |= bool((ref.fit_levels(x, bits, B, 0.3, levels.copy(), max_batches=2) > 1.0).any())
+                assert _same(x, bits, B, 0.3, levels), cut
+    assert past
