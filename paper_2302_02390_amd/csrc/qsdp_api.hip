@@ -220,6 +220,16 @@ int run(int mode, Params p, int stored_bits, hipStream_t s) {
         // per wave), is faster with one wave per bucket
         wl = launch_wave_1024w2;
         bpw = 0;
+        // From 12 * 2^10 buckets on its waves stream slower when all of them start at once, so they draw the shift
+        // themselves: at 8 bits, and below 2^16 buckets at the other widths, 6 bits apart. Speed with the host's shift /
+        // with shifts drawn by the waves, against code that knew no other, at 2, 4, 5, 6, 8 bits: 3M elements 1.12 /
+        // 1.01, 1.14 / 1.01, 1.13 / 1.00, 1.14 / 1.01, 1.16 / 1.00; 10M 1.05 / 0.98, 1.03 / 0.97, 1.01 / 0.97, 1.03 /
+        // 0.97, 1.03 / 0.98; 14M, with other calls' data in the cache, 0.95-0.97 and 1.01-1.04 / 1.00; 25M 0.99 / 1.01,
+        // 0.95 / 1.00, 0.96 / 1.00, 1.01 / 1.00, 0.95 / 1.00; 50M 0.99 / 1.00, 0.98 / 1.00, 1.00 / 1.00, 1.02 / 1.00,
+        // 0.97 / 1.00; 125M 1.02 / 1.00, 1.00 / 1.00, 1.00 / 1.00, 1.04 / 1.01, 0.99 / 1.00; 350M 1.01 / 0.99, 1.01 /
+        // 1.00, 1.02 / 1.00, 1.03 / 1.00, 0.99 / 1.00. Buckets of 2048: 1.04 / 1.04 at 8M, 0.99 / 0.97 at 16M, the
+        // same beyond.
+        if (nb >= (12u << 10) && stored_bits != 6 && (stored_bits == 8 || nb < (1u << 16))) p.flags |= FLAG_WAVES_DRAW;
     }
     // learned levels with a table per tensor: how many there are
     const uint64_t tensors = mode_is_levels(mode) && p.levels_per_tensor != 0 ? (p.nseg < nb ? p.nseg : nb) : 0;

@@ -178,7 +178,9 @@ __device__ __forceinline__ float step_value(const Params& p, float x, float ghat
 
 // Quantizer variants (same values as the QSDP_FLAG_* of the C header)
 // FLAG_KEEP_MASTER (step modes): x receives the updated value itself, the codes still Q^w of it
-enum : uint32_t { FLAG_GRAD_SHIFT = 1u, FLAG_NO_SHIFT = 2u, FLAG_SYMMETRIC = 4u, FLAG_KEEP_MASTER = 8u };
+// FLAG_WAVES_DRAW (set by the launch, no caller's): the weight encoder of two waves to a bucket of 1024 draws its shift
+enum : uint32_t { FLAG_GRAD_SHIFT = 1u, FLAG_NO_SHIFT = 2u, FLAG_SYMMETRIC = 4u, FLAG_KEEP_MASTER = 8u,
+                  FLAG_WAVES_DRAW = 1u << 31 };
 
 struct Shifts {
     float xi;    // weight shift
@@ -198,10 +200,12 @@ __host__ __device__ __forceinline__ Shifts draw_shifts(uint32_t flags, PhiloxKey
 // instructions, each waiting for the one before, ahead of every wave's one bucket. 3M values, drawn by the waves / by the
 // host: step 9.2 / 8.4 us and 5-bit weights 10.5 / 9.6 in buckets of 96, receive side 8.3 / 7.6 in buckets of 128,
 // 5-bit weights 9.0 / 8.4 in buckets of 1024; 1.02-1.05 up to 100M values (step, 1024: 195.8 / 188.8), nothing beyond.
-// DRAW: or where the caller asks for it.
-template <int MODE, bool DRAW = false>
+// DRAW: or where the caller asks for it. ASK: or where the call does (FLAG_WAVES_DRAW).
+template <int MODE, bool DRAW = false, bool ASK = false>
 __device__ __forceinline__ Shifts launch_shifts(const Params& p, PhiloxKey key) {
-    if (DRAW || (mode_device_seed(MODE) && __builtin_expect(p.seed_dev != nullptr, 0))) return draw_shifts(p.flags, key);
+    if (DRAW || (ASK && (p.flags & FLAG_WAVES_DRAW) != 0) ||
+        (mode_device_seed(MODE) && __builtin_expect(p.seed_dev != nullptr, 0)))
+        return draw_shifts(p.flags, key);
     return {p.xi, p.xi_g};
 }
 

@@ -243,3 +243,21 @@ def test_non_finite_inputs_do_not_disturb_their_neighbours():
     torch.cuda.synchronize()
     wc2, wm2 = ref.quantize_levels(x, 4, B, ref.levels_uniform(4))
     assert np.array_equal(np_u32(c2).reshape(8, wpb)[clean], wc2.reshape(8, wpb)[clean])
+
+
+@pytest.mark.parametrize("bits", [3, 5, 6, 8])
+@pytest.mark.parametrize("buckets", [(12 << 10) - 1, 12 << 10, (1 << 16) - 1, 1 << 16])
+def test_who_draws_the_shift_of_large_weight_calls(bits, buckets):
+    """Buckets of 1024: the shift comes with the call or is drawn by its waves, by size and width; the last bucket is
+    short, and without a shift none is drawn."""
+    n = buckets * 1024 - 75
+    x = torch.randn(n, device=DEV)
+    x_np = x.cpu().numpy()
+    codes, meta = qb.alloc_packed(n, bits, 1024, DEV)
+    for delta, flags in ((0.0, 0), (2.0 ** -5, 0), (0.0, qb.QSDP_FLAG_NO_SHIFT)):
+        if flags:
+            qb.qsdp_quantize_weight_ex(x, bits, 1024, delta, 77, flags, codes, meta.view(-1))
+        else:
+            qb.qsdp_quantize_weight(x, bits, 1024, delta, 77, codes, meta.view(-1))
+        wc, wm, _ = ref.quantize_weight(x_np, bits, 1024, delta, 77, flags=flags)
+        assert np.array_equal(np_u32(codes), wc) and bits_equal(np_f32(meta.view(-1)), wm.reshape(-1)), (delta, flags)
