@@ -203,15 +203,20 @@ uint64_t level_blocks(int mode, uint64_t blocks, int waves, int resident, uint64
     return few > tensors ? few : tensors;
 }
 
+// The shifts that come with the call: those that its kernel reads.
+void set_shifts(int mode, bool wave, Params& p) {
+    if (p.seed_dev != nullptr || mode_is_levels(mode) || mode == MODE_SUM) return;
+    if (wave && (wave_kernel_draws(mode) || (p.flags & FLAG_WAVES_DRAW) != 0)) return;
+    if (mode == MODE_GRAD && (p.flags & FLAG_GRAD_SHIFT) == 0) return;
+    const Shifts shifts = draw_shifts(p.flags, {p.key0, p.key1});
+    p.xi = shifts.xi;
+    p.xi_g = shifts.xi_g;
+}
+
 // Buckets go to the wave kernel of the bucket's shape when there is one, else to the tile kernel.
 // p.num_buckets must be set.
 int run(int mode, Params p, int stored_bits, hipStream_t s) {
     const uint64_t nb = p.num_buckets;
-    if (p.seed_dev == nullptr && !mode_is_levels(mode) && mode != MODE_SUM) {
-        const Shifts shifts = draw_shifts(p.flags, {p.key0, p.key1});
-        p.xi = shifts.xi;
-        p.xi_g = shifts.xi_g;
-    }
     int bpw = 1;
     WaveLauncher wl = wave_launcher(p.bucket, &bpw);
     if (mode == MODE_WEIGHT && p.bucket == 1024 && p.segs == nullptr) {
@@ -238,7 +243,9 @@ int run(int mode, Params p, int stored_bits, hipStream_t s) {
     // 31-32; 300 of them 8.6-8.9 us either way, 8 bit 10-20 against 9-11).
     const bool many_small = tensors > kLevelsResident * kComputeUnits && p.bucket <= 1024 &&
                             nb / tensors * (uint64_t)p.bucket <= 1024;
-    if (wl != nullptr && !many_small) {
+    const bool wave = wl != nullptr && !many_small;
+    set_shifts(mode, wave, p);
+    if (wave) {
         // 4 waves per workgroup, each on bpw buckets; or one workgroup per bucket
         uint64_t blocks = bpw > 0 ? ceil_div(ceil_div(nb, (uint64_t)bpw), 4) : nb;
         if (mode_is_levels(mode))

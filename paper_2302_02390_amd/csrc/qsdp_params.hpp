@@ -200,6 +200,11 @@ __host__ __device__ __forceinline__ Shifts draw_shifts(uint32_t flags, PhiloxKey
 // instructions, each waiting for the one before, ahead of every wave's one bucket. 3M values, drawn by the waves / by the
 // host: step 9.2 / 8.4 us and 5-bit weights 10.5 / 9.6 in buckets of 96, receive side 8.3 / 7.6 in buckets of 128,
 // 5-bit weights 9.0 / 8.4 in buckets of 1024; 1.02-1.05 up to 100M values (step, 1024: 195.8 / 188.8), nothing beyond.
+// The wave kernels' gradient encoder (with a shared shift only) and code-resident step draw their shifts in every wave all
+// the same: at the size of a model they stream slower when all waves start at once (us, drawn by the host / by the waves:
+// 4-bit gradients of the 350M model's tensors 254.9 / 252.0, code-resident step on the same model 368.4 / 364.6).
+constexpr bool wave_kernel_draws(int mode) { return mode == MODE_GRAD || mode == MODE_FUSED_CODES; }
+
 // DRAW: or where the caller asks for it. ASK: or where the call does (FLAG_WAVES_DRAW).
 template <int MODE, bool DRAW = false, bool ASK = false>
 __device__ __forceinline__ Shifts launch_shifts(const Params& p, PhiloxKey key) {

@@ -517,11 +517,8 @@ __global__ void __launch_bounds__(256, mode_min_blocks(MODE)) wave_kernel(const 
     constexpr bool kWritesX = MODE == MODE_FUSED || MODE == MODE_ADAMW || mode_is_recv(MODE);
     const bool keep_master = kWritesX && (p.flags & FLAG_KEEP_MASTER) != 0;
     const PhiloxKey key = launch_key<MODE>(p);
-    // The gradient encoder (with a shared shift only) and the code-resident step draw their shifts in every wave: they
-    // stream slower when all waves start at once (us, drawn by the host / by the waves: 4-bit gradients of the 350M
-    // model's tensors 254.9 / 252.0, code-resident step on the same model 368.4 / 364.6).
-    constexpr bool kDraws = MODE == MODE_GRAD || MODE == MODE_FUSED_CODES;
-    const Shifts shifts = launch_shifts<MODE, kDraws, MODE == MODE_WEIGHT && W == 2 && R == 2>(p, key);
+    const Shifts shifts =
+        launch_shifts<MODE, wave_kernel_draws(MODE), MODE == MODE_WEIGHT && W == 2 && R == 2>(p, key);
     const float xi = shifts.xi;
     uint32_t saturated = 0;
 
