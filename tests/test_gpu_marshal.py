@@ -1,5 +1,7 @@
 """The native argument marshalling against the binding's own Python functions: the same results, and the same exceptions,
 for every form of argument that either takes."""
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -102,3 +104,47 @@ def test_tensors_on_one_device():
     for args in ((), ("name",), ("name", [gpu, cpu], {}), ("name", (gpu, cpu), None), (1, 2, 3)):
         native, python = _call("_devices_ok", *args)
         assert native == python or native[0] is python[0], args
+
+
+def test_segment_tables_on_one_device():
+    """A table's own tensor decides, also where it has none, another object, or a subclass of the table's type."""
+    gpu, cpu = torch.zeros(64, device=DEV), torch.zeros(64)
+
+    class Special(qb.Segments):
+        pass
+
+    tables = {"gpu": qb.Segments([64], 32, DEV), "cpu": qb.Segments([64], 32, "cpu"), "special": Special([64], 32, DEV),
+              "special cpu": Special([64], 32, "cpu")}
+    for name, value in (("none", None), ("text", "cpu"), ("parameter", torch.nn.Parameter(gpu)), ("missing", ...)):
+        tables[name] = qb.Segments([64], 32, DEV)
+        if value is ...:
+            del tables[name].device
+        else:
+            tables[name].device = value
+    for name, t in tables.items():
+        held = t.__dict__.get("device")
+        before = sys.getrefcount(held)
+        for args in ((t,), (gpu, t), (t, gpu), (cpu, t), (t, cpu), (gpu, t, 3, t), (t, tables["gpu"]), (tables["cpu"], t)):
+            for kwargs in ({}, {"segs": t}, {"segs": t, "x": gpu}, {"x": cpu}):
+                native, python = _call("_devices_ok", "an entry point", args, kwargs)
+                assert native == python, (name, len(args), sorted(kwargs))
+        assert held is None or sys.getrefcount(held) == before, name
+
+
+def test_segment_tables_are_looked_at_in_native_code():
+    gpu, segs = torch.zeros(64, device=DEV), qb.Segments([64], 32, DEV)
+    qb.lib()
+    native = qb._native_marshalling()
+    assert native is not None
+    in_python = list(qb._IN_PYTHON.values())
+
+    def not_called(*args):
+        raise AssertionError("left to Python")
+
+    native.attach(vars(qb), *in_python[:-1], not_called)
+    try:
+        assert qb._devices_ok("an entry point", (gpu, segs, 4, None), {"segs": segs}) is None
+        with pytest.raises(AssertionError, match="left to Python"):
+            qb._devices_ok("an entry point", (gpu, qb.Segments([64], 32, "cpu")), {})
+    finally:
+        native.attach(vars(qb), *in_python)
