@@ -1,11 +1,16 @@
 // Instantiations of the level fit for one shape; compiled with -DQSDP_FIT_V=<values per lane> and
 // -DQSDP_FIT_W=<waves per batch>: buckets of up to 64 * V * W values; W = 1
 // (qsdp_fit_kernel.hpp) or more (qsdp_fit_rounds.hpp).
-#include "qsdp_fit_rounds.hpp"
 #include "qsdp_launch.hpp"
 
 #if !defined(QSDP_FIT_V) || !defined(QSDP_FIT_W)
 #error "define QSDP_FIT_V and QSDP_FIT_W"
+#endif
+
+#if QSDP_FIT_W > 1
+#include "qsdp_fit_rounds.hpp"
+#else
+#include "qsdp_fit_kernel.hpp"
 #endif
 
 #define QSDP_CAT2(a, b, c, d) a##b##c##d

@@ -3,7 +3,7 @@
 
 #include <type_traits>
 
-#include "qsdp_params.hpp"
+#include "qsdp_fit_common.hpp"
 
 namespace qsdp {
 
@@ -45,17 +45,6 @@ namespace qsdp {
 // rounded distances is monotone in the value and flips within 2^-22 of the midpoint, which is below 1) and cells that
 // are not crowded. A batch for which that does not hold is assigned value by value, by the same wave.
 // ---------------------------------------------------------------------------------------
-struct FitParams {
-    const float* v;
-    float* levels;  // in/out, 2^bits floats (one table per tensor when segs is given)
-    uint64_t n;
-    uint64_t num_batches;  // with segs: the cap on the batches of every tensor (0 = none)
-    const Segment* segs;   // multi-tensor fit: workgroup t fits tensor t on its own table
-    int bucket;
-    int bits;
-    float lr;
-};
-
 // Shape of a workgroup: a producer sorts a batch of up to 64 * VPT values.
 template <int BMAX, int C>
 struct FitSlot;
@@ -92,8 +81,8 @@ constexpr float kFitUnit = 0x1p32f;
 constexpr float kFitFiller = 2.0f * kFitUnit;
 constexpr int kFitSpare = 20;
 
-// z (units of 2^-32) as an integer, truncated, and a count of one. The conversion saturates from 1 on, where z is a whole
-// number of units, 2^9 of them to a step of its last bit; below 1 it never gives all ones.
+// z (units of 2^-32) as an integer, truncated, and a count of one. The conversion saturates from 1 on, where z is a
+// whole number of units, 2^9 of them to a step of its last bit; below 1 it never gives all ones.
 __device__ __forceinline__ uint64_t fit_word(float z) {
     const uint32_t fraction = (uint32_t)z;
     const bool one = fraction == ~0u;
@@ -145,27 +134,6 @@ __device__ __forceinline__ FitCells fit_cells(const MinMaxGrid& grid, float hi, 
     return width > 0x1p-20f && width <= 2.0f ? inner : all;
 }
 
-// v of the next / previous lane of the wave (the last / first lane gets 0).
-__device__ __forceinline__ uint32_t next_lane(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x130, 0xF, 0xF, true);  // wave_shl:1
-}
-__device__ __forceinline__ uint32_t previous_lane(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x138, 0xF, 0xF, true);  // wave_shr:1
-}
-
-// Sum over the lanes of a wave, in all of them (any order: it only places the cells).
-__device__ __forceinline__ float fit_wave_sum(float v) {
-    v += dpp_move<0xB1>(v);
-    v += dpp_move<0x4E>(v);
-    v += dpp_move<0x141>(v);
-    v += dpp_move<0x140>(v);
-    float a, b;
-    swap16(v, a, b);
-    v = a + b;
-    swap32(v, a, b);
-    return a + b;
-}
-
 // Inclusive prefix sums over the lanes of a wave, of N values side by side.
 template <int CTRL, int ROWS, int N>
 __device__ __forceinline__ void fit_scan_step(uint32_t (&v)[N]) {
@@ -213,77 +181,23 @@ __device__ __forceinline__ uint64_t fit_sum_subs(uint64_t sum) {
     return sum;
 }
 
-// Adds to a word in LDS and returns what it held. Relaxed: the callers put their own fences, and an ordered atomic
-// would wait for each one before the next.
-template <typename T>
-__device__ __forceinline__ T fit_add(T* word, T v) {
-    return __hip_atomic_fetch_add(word, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
 // Keeps the compiler from reordering LDS accesses of one wave, which are processed in order.
 __device__ __forceinline__ void fit_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
-// LDS traffic of one wave is processed in order; this keeps the compiler from reordering it.
-__device__ __forceinline__ void fit_wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// (1 - lr)^c by repeated multiplication, the order in which c single steps compound, for c up to the bucket size:
-// every power up to kFine beside the reciprocal of the count, beyond that every kStep-th. The multiplications are a
-// serial chain (about 8 ns each), so the consumer extends it as the counts ask for it: most counts are a small share
-// of a bucket, and a tensor of few batches would wait for powers that it never reads. The reciprocals are the
-// producers' work, while their first loads are on the way.
-struct FitFilled {
-    int count;    // the powers of counts up to this one can be read
-    double keep;  // where the chain stands
-};
 template <int BMAX>
-struct FitPowers {
-    static constexpr int kFine = BMAX < 1024 ? BMAX : 1024, kStep = 16, kCoarse = (BMAX - kFine) / kStep + 1;
-    static_assert(kFine % 64 == 0, "grows by 64");
+struct FitPowers : FitChain<BMAX> {
+    using Chain = FitChain<BMAX>;
+    using Chain::kFine;
     double fine[kFine + 1];  // 1 - (1-lr)^c
-    double coarse[kCoarse];
+    typename Chain::Coarse coarse;
 
     __device__ FitFilled start(int lane) {
         if (lane == 0) fine[0] = 0.0;
         return {0, 1.0};
     }
 
-    // The next 64 powers, or the next 16 of every kStep-th (one wave; the chain and its stores in one lane).
     __device__ __forceinline__ void extend(FitFilled& f, double one_minus, int lane) {
-        double keep = f.keep;
-        if (f.count < kFine) {
-            if (lane == 0) {
-                uint32_t first = (uint32_t)f.count + 1u;
-                asm volatile("" : "+v"(first));  // one address register, the stores' offsets in the instructions
-#pragma unroll 16
-                for (int i = 0; i < 64; ++i) {
-                    keep *= one_minus;
-                    fine[first + i] = keep;
-                }
-            }
-            fit_wave_sync();
-            double& mine = fine[f.count + 1 + lane];
-            mine = 1.0 - mine;
-            f.count += 64;
-        } else {
-            const int first = (f.count + 1 - kFine) / kStep;
-            if (lane == 0) {
-                for (int k = first; k < first + 16; ++k) {
-                    if (k < kCoarse) coarse[k] = keep;
-#pragma unroll
-                    for (int i = 0; i < kStep; ++i) keep *= one_minus;
-                }
-            }
-            f.count = kFine + (first + 16) * kStep - 1;
-        }
-        const uint64_t bits = __builtin_bit_cast(uint64_t, keep);
-        const uint64_t low = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)bits);
-        const uint64_t high = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(bits >> 32));
-        f.keep = __builtin_bit_cast(double, (high << 32) | low);
-        fit_wave_sync();
+        Chain::extend(f, one_minus, lane, [&](uint32_t c) -> double& { return fine[c]; }, coarse);
     }
 
     // Where the level lands after the c values (at most kFine) of fixed-point sum `total` that are its own, given
@@ -308,12 +222,7 @@ struct FitPowers {
     // The same for any c.
     __device__ float step_any(float level, uint32_t c, uint64_t total, double one_minus) const {
         if (c <= (uint32_t)kFine) return step(level, c, total, fine[c]);
-        const int k = ((int)c - kFine) / kStep;
-        double keep = coarse[k];
-        for (int i = kFine + k * kStep; i < (int)c; ++i) keep *= one_minus;
-        const double q = (double)level;
-        const double mean = ((double)total / (double)c) * (1.0 / 4294967296.0);
-        return c == 0u ? level : (float)(q - (1.0 - keep) * (q - mean));
+        return Chain::step_past_fine(level, c, total, one_minus, coarse);
     }
 };
 
@@ -332,17 +241,11 @@ struct alignas(16) FitSlot {
     float z[BMAX + kFitSpare];  // units of 2^-32, grouped by cell, kFitSpare fillers past the last one
 };
 
-// Level k of the table for lane l: k = M * (l mod (64 / S)) + i, i < M. S lanes share a level's work.
+// Groups of four values that a lane reads at once: two where a level has one lane (us per batch of 128 / 1024, one
+// group and two: 7 bits 0.74 / 0.82 and 0.54 / 0.64, 8 bits 1.25 / 1.43 and 0.94 / 1.19; 5 bits, two lanes to a level,
+// 0.33 / 0.37 and 0.36 / 0.40).
 template <int BITS>
-struct FitLanes {
-    static constexpr int K = 1 << BITS;
-    static constexpr int S = K <= 16 ? 4 : K <= 32 ? 2 : 1;
-    static constexpr int M = K <= 64 ? 1 : K / 64;
-    // Groups of four values that a lane reads at once: two where a level has one lane (us per batch of 128 / 1024, one
-    // group and two: 7 bits 0.74 / 0.82 and 0.54 / 0.64, 8 bits 1.25 / 1.43 and 0.94 / 1.19; 5 bits, two lanes to a
-    // level, 0.33 / 0.37 and 0.36 / 0.40).
-    static constexpr int G = S == 1 ? 2 : 1;
-};
+constexpr int kFitGroups = FitLanes<BITS>::S == 1 ? 2 : 1;
 
 // What the consumer knows of the batch to come.
 struct FitNext {
@@ -368,18 +271,18 @@ __device__ __forceinline__ uint64_t fit_outside(const float (&lv)[M]) {
     return outside;
 }
 
-// One batch of the chain. lv[i]: the lane's levels, updated; next: what is known of the batch, and then of the one in
-// next_slot; outside: the lanes with a level that is not in [0, 1]; boundaries: those whose last level has one above
-// it; not_first: 0 in the lanes of the first level; crowded: values in a boundary's cells from which the plain
-// assignment is faster; count(): the batch's values; done(): the slot has been read; lv_shared, acc: K entries of LDS
-// each, for batches that are assigned value by value.
+// One batch of the chain. lv[i]: the lane's levels, level M * (lane mod (64 / S)) + i, updated; next: what is known of
+// the batch, and then of the one in next_slot; outside: the lanes with a level that is not in [0, 1]; boundaries: those
+// whose last level has one above it; not_first: 0 in the lanes of the first level; crowded: values in a boundary's
+// cells from which the plain assignment is faster; count(): the batch's values; done(): the slot has been read;
+// lv_shared, acc: K entries of LDS each, for batches that are assigned value by value.
 template <int BITS, typename Slot, typename Powers, int C, typename Count, typename Done>
 __device__ __forceinline__ void fit_batch(const Slot& slot, const Slot& next_slot, FitNext& next, uint64_t& outside,
                                           uint64_t boundaries, uint32_t not_first,
                                           uint32_t crowded, int bucket, Count count, Done done, Powers& powers,
                                           FitFilled& filled, double one_minus, float (&lv)[FitLanes<BITS>::M],
                                           float* lv_shared, uint64_t* acc, int lane) {
-    constexpr int K = FitLanes<BITS>::K, S = FitLanes<BITS>::S, M = FitLanes<BITS>::M, G = FitLanes<BITS>::G;
+    constexpr int K = FitLanes<BITS>::K, S = FitLanes<BITS>::S, M = FitLanes<BITS>::M, G = kFitGroups<BITS>;
     static_assert(4 * S * G <= kFitSpare - 4, "reads past the last value");
     const int sub = S > 1 ? lane / (64 / S) : 0;
     const int k0 = S > 1 ? lane % (64 / S) : lane;
@@ -499,36 +402,10 @@ __device__ __forceinline__ void fit_batch(const Slot& slot, const Slot& next_slo
             own[i] = fit_halves(upto[i] - (((uint64_t)previous.high << 32) | previous.low));
         }
     } else {
-        // value by value against the table in LDS
-        const int m = count();
-        fit_wave_sync();
-#pragma unroll
-        for (int i = 0; i < M; ++i) {
-            const int k = M * k0 + i;
-            if (sub == 0 && k < K) {
-                lv_shared[k] = lv[i];
-                acc[k] = 0;
-            }
-        }
-        fit_wave_sync();
-        for (int p = lane; p < m; p += 64 * 4) {  // four values a lane at once: the searches' LDS reads overlap
-            float z[4];
-            int k[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) z[u] = slot.z[p + 64 * u < m ? p + 64 * u : p] * (1.0f / kFitUnit);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) k[u] = nearest_level<BITS>(z[u], lv_shared);
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (p + 64 * u < m) fit_add<uint64_t>(&acc[k[u]], fit_word(z[u] * kFitUnit));
-        }
-        fit_wave_sync();
-#pragma unroll
-        for (int i = 0; i < M; ++i) {
-            const int k = M * k0 + i;
-            own[i] = fit_halves(k < K ? acc[k] : 0);
-        }
-        fit_wave_sync();
+        fit_by_value<BITS>(
+            count(), lv, sub == 0, [&](int i) { return M * k0 + i; },
+            [&](int p) { return slot.z[p] * (1.0f / kFitUnit); }, [](float z) { return fit_word(z * kFitUnit); },
+            [&](int i, uint64_t word) { own[i] = fit_halves(word); }, lv_shared, acc, lane);
     }
     // the powers are requested before it is known whether the table holds them: the answer comes while they are on
     // the way
@@ -816,7 +693,8 @@ __global__ void __launch_bounds__((FitShape<BITS, VPT, W>::kThreads)) fit_levels
             if (__builtin_expect(past_one, 0)) {  // what the conversion left out of values past 1
                 uint32_t excess[1] = {0};
 #pragma unroll 1
-                for (int i = lane; i < m; i += 64) excess[0] += slot.z[i] > kFitUnit ? (uint32_t)(slot.z[i] - kFitUnit) : 0u;
+                for (int i = lane; i < m; i += 64)
+                    excess[0] += slot.z[i] > kFitUnit ? (uint32_t)(slot.z[i] - kFitUnit) : 0u;
                 fit_wave_scan(excess);
                 base += (uint32_t)__builtin_amdgcn_readlane((int)excess[0], 63);
             }

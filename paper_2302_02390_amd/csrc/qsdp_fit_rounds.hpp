@@ -1,7 +1,8 @@
 // Level fitting for buckets of more than 2048 values (see qsdp_fit_kernel.hpp for the smaller ones and the definition).
+// The form of a batch (units of the values, cells, count and sum in a word) is this kernel's own.
 #pragma once
 
-#include "qsdp_fit_kernel.hpp"
+#include "qsdp_fit_common.hpp"
 
 namespace qsdp {
 namespace fit_rounds {
@@ -102,20 +103,17 @@ __device__ __forceinline__ uint64_t fit_sum_subs(uint64_t v) {
     return v;
 }
 
-// (1 - lr)^c by repeated multiplication, the order in which c single steps compound, for c up to the bucket size:
-// every power up to kFine beside the reciprocal of the count, beyond that every kStep-th. The multiplications are a
-// serial chain (about 8 ns each), so the consumer extends it as the counts ask for it: most counts are a small share
-// of a bucket, and a tensor of few batches would wait for powers that it never reads. The reciprocals are the
-// producers' work, while their first loads are on the way.
+// The powers beside the reciprocals of the counts, which are the producers' work while their first loads are on the
+// way.
 template <int BMAX>
-struct FitPowers {
-    static constexpr int kFine = BMAX < 1024 ? BMAX : 1024, kStep = 16, kCoarse = (BMAX - kFine) / kStep + 1;
-    static_assert(kFine % 64 == 0, "grows by 64");
+struct FitPowers : FitChain<BMAX> {
+    using Chain = FitChain<BMAX>;
+    using Chain::kFine;
     struct Entry {
         double moved, reciprocal;  // 1 - (1-lr)^c, 1 / c
     };
     Entry fine[kFine + 1];
-    double coarse[kCoarse];
+    typename Chain::Coarse coarse;
 
     __device__ void fill_reciprocals(int top, int thread, int threads) {
         for (int c = thread; c <= kFine && c <= top; c += threads) fine[c].reciprocal = 1.0 / (double)(c > 0 ? c : 1);
@@ -126,39 +124,8 @@ struct FitPowers {
         return {0, 1.0};
     }
 
-    // The next 64 powers, or the next 16 of every kStep-th (one wave; the chain and its stores in one lane).
-    __device__ void extend(FitFilled& f, double one_minus, int lane) {
-        double keep = f.keep;
-        if (f.count < kFine) {
-            if (lane == 0) {
-                uint32_t first = (uint32_t)f.count + 1u;
-                asm volatile("" : "+v"(first));  // one address register, the stores' offsets in the instructions
-#pragma unroll 16
-                for (int i = 0; i < 64; ++i) {
-                    keep *= one_minus;
-                    fine[first + i].moved = keep;
-                }
-            }
-            fit_wave_sync();
-            double& mine = fine[f.count + 1 + lane].moved;
-            mine = 1.0 - mine;
-            f.count += 64;
-        } else {
-            const int first = (f.count + 1 - kFine) / kStep;
-            if (lane == 0) {
-                for (int k = first; k < first + 16; ++k) {
-                    if (k < kCoarse) coarse[k] = keep;
-#pragma unroll
-                    for (int i = 0; i < kStep; ++i) keep *= one_minus;
-                }
-            }
-            f.count = kFine + (first + 16) * kStep - 1;
-        }
-        const uint64_t bits = __builtin_bit_cast(uint64_t, keep);
-        const uint64_t low = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)bits);
-        const uint64_t high = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(bits >> 32));
-        f.keep = __builtin_bit_cast(double, (high << 32) | low);
-        fit_wave_sync();
+    __device__ __forceinline__ void extend(FitFilled& f, double one_minus, int lane) {
+        Chain::extend(f, one_minus, lane, [&](uint32_t c) -> double& { return fine[c].moved; }, coarse);
     }
 
     // Where the level q lands after the c values of fixed-point sum `total` that are its own; c at most kFine. Without
@@ -177,12 +144,7 @@ struct FitPowers {
     // The same for any c.
     __device__ float step_any(float level, uint32_t c, uint64_t total, double one_minus) const {
         if (c <= (uint32_t)kFine) return step(level, c, total, fine[c]);
-        const int k = ((int)c - kFine) / kStep;
-        double keep = coarse[k];
-        for (int i = kFine + k * kStep; i < (int)c; ++i) keep *= one_minus;
-        const double q = (double)level;
-        const double mean = ((double)total / (double)c) * (1.0 / 4294967296.0);
-        return c == 0u ? level : (float)(q - (1.0 - keep) * (q - mean));
+        return Chain::step_past_fine(level, c, total, one_minus, coarse);
     }
 };
 
@@ -192,16 +154,15 @@ struct FitPowers {
 // one another's banks (without it all 64 lanes meet in two banks: 0.15 us more per batch of 1024).
 template <int BMAX, int C>
 struct FitSlot {
-    static constexpr int kValues = BMAX;
     static constexpr int kOwn = C / 64;
-    static __device__ __forceinline__ uint32_t at(uint32_t c) { return c + (kOwn > 1 ? c / kOwn : 0u); }
+    static __device__ __forceinline__ uint32_t at(uint32_t c) { return c + c / kOwn; }
     uint64_t cell[C + 64 + 1];  // cell c at at(c)
     float z[BMAX + kFitSpare];  // grouped by cell, kFitSpare fillers past the last one
     FitCells cells;
 };
 
-// One batch of the chain. lv[i]: the lane's levels, updated. lv_shared, acc: K entries of LDS each, for batches that
-// are assigned value by value.
+// One batch of the chain. lv[i]: the lane's levels, level 64 * i + lane mod (64 / S), updated. lv_shared, acc: K entries
+// of LDS each, for batches that are assigned value by value.
 template <int BITS, typename Slot, typename Powers, int C>
 __device__ __forceinline__ void fit_batch(const Slot& slot, int m, Powers& powers, FitFilled& filled, double one_minus,
                                           FitCells cells, float (&lv)[FitLanes<BITS>::M], float* lv_shared,
@@ -281,35 +242,10 @@ __device__ __forceinline__ void fit_batch(const Slot& slot, int m, Powers& power
             own[i] = upto[i] - prev;
         }
     } else {
-        // value by value against the table in LDS
-        fit_wave_sync();
-#pragma unroll
-        for (int i = 0; i < M; ++i) {
-            const int k = 64 * i + k0;
-            if (sub == 0 && k < K) {
-                lv_shared[k] = lv[i];
-                acc[k] = 0;
-            }
-        }
-        fit_wave_sync();
-        for (int p = lane; p < m; p += 64 * 4) {  // four values a lane at once: the searches' LDS reads overlap
-            float z[4];
-            int k[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) z[u] = slot.z[p + 64 * u < m ? p + 64 * u : p];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) k[u] = nearest_level<BITS>(z[u], lv_shared);
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (p + 64 * u < m) fit_add<uint64_t>(&acc[k[u]], (1ull << kFitCountShift) | fit_fixed(z[u]));
-        }
-        fit_wave_sync();
-#pragma unroll
-        for (int i = 0; i < M; ++i) {
-            const int k = 64 * i + k0;
-            own[i] = k < K ? acc[k] : 0;
-        }
-        fit_wave_sync();
+        fit_by_value<BITS>(
+            m, lv, sub == 0, [&](int i) { return 64 * i + k0; }, [&](int p) { return slot.z[p]; },
+            [](float z) { return (1ull << kFitCountShift) | fit_fixed(z); },
+            [&](int i, uint64_t word) { own[i] = word; }, lv_shared, acc, lane);
     }
     // the powers are requested before it is known whether the table holds them: the answer comes while they are on
     // the way
@@ -331,8 +267,7 @@ __device__ __forceinline__ void fit_batch(const Slot& slot, int m, Powers& power
             request();
         }
     }
-    if (Powers::kFine == Slot::kValues ||
-        __builtin_expect(__builtin_amdgcn_ballot_w64(most > (uint32_t)Powers::kFine) == 0, 1)) {
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(most > (uint32_t)Powers::kFine) == 0, 1)) {
 #pragma unroll
         for (int i = 0; i < M; ++i) lv[i] = Powers::step(lv[i], c[i], own[i] & kFitSumMask, e[i]);
     } else {
@@ -387,8 +322,8 @@ __global__ void __launch_bounds__((FitShape<BITS, VPT, W>::kThreads)) fit_levels
         }
         FitFilled filled = powers.start(lane);
         // while the producers sort the first round: up to three times the mean count, which the fullest level of a
-        // Gaussian batch on the uniform table does not reach; all of them for the smallest buckets
-        while (filled.count < Powers::kFine && (Powers::kFine <= 256 || filled.count * K < 3 * B))
+        // Gaussian batch on the uniform table does not reach
+        while (filled.count < Powers::kFine && filled.count * K < 3 * B)
             powers.extend(filled, one_minus, lane);
         for (int i = 0; i < Shape::kBarriers; ++i) __syncthreads();  // the producers' first round
         for (uint64_t r = 0; r < rounds; ++r) {
@@ -468,8 +403,8 @@ __global__ void __launch_bounds__((FitShape<BITS, VPT, W>::kThreads)) fit_levels
                 absolute += red[team][3][w];
             }
             const MinMaxGrid grid = make_minmax_grid(lo, hi, 1.0f, false);
-            const FitCells cells = fit_rounds::fit_cells<C>(grid, hi, sum * (1.0f / (64 * W * VPT)),
-                                                            absolute * (1.0f / (64 * W * VPT)));
+            const FitCells cells = fit_cells<C>(grid, hi, sum * (1.0f / (64 * W * VPT)),
+                                                absolute * (1.0f / (64 * W * VPT)));
             uint32_t cell[VPT];
             // the cell's word before this value came (both halves used: half of one dropped costs a wait)
             uint64_t held[VPT];

@@ -18,7 +18,8 @@
 //     whole buckets as fit; used for the bucket sizes the wave kernels are not instantiated for.
 // The modes and parameters are in qsdp_params.hpp, the two encoder families in qsdp_wave_kernel.hpp (with the learned-level
 // modes in qsdp_levels_kernel.hpp) and qsdp_tile_kernel.hpp, the decoders and the element-wise decode-and-sum in qsdp_decoders.hpp, the
-// level fit in qsdp_fit_kernel.hpp and, for buckets of more than 2048 values, qsdp_fit_rounds.hpp.
+// level fit in qsdp_fit_kernel.hpp and, for buckets of more than 2048 values, qsdp_fit_rounds.hpp, each included where it
+// is instantiated.
 #pragma once
 
 #include "qsdp_params.hpp"
@@ -27,4 +28,4 @@
 #include "qsdp_levels_kernel.hpp"
 #include "qsdp_tile_kernel.hpp"
 #include "qsdp_decoders.hpp"
-#include "qsdp_fit_kernel.hpp"
+#include "qsdp_fit_common.hpp"
