@@ -262,3 +262,56 @@ def test_the_last_tile(B, tail, buckets):
         want, wc, wm, _ = ref.recv_step(x, np.stack([grads[0]] * 2), np.stack([peer, peer * np.float32(0.5)]), 2, 0.5,
                                         1e-2, wbits, gbits, B, delta, 11, 0, True)
         assert bits_equal(np_f32(xd[:n]), want) and _same(c, m, wc, wm) and bool((xd[n:] == guard).all()), dtype
+
+
+def _levels(bits, seed):
+    """An ascending table over part of [0, 1], so that values lie below its first level and past its last."""
+    rng = np.random.default_rng(seed)
+    return np.sort(rng.uniform(0.05, 0.95, 1 << bits)).astype(np.float32)
+
+
+# tiles of two rows, and of the smallest team that holds a bucket (small calls); of one wave with four, six and eight rows
+# and of four with six (the others)
+@pytest.mark.parametrize("B,elements", [(32, 0), (96, 0), (320, 0), (768, 0), (2336, 0), (4128, 0), (6176, 0),
+                                        (32, 1 << 20), (96, 1 << 20), (768, 1 << 20), (2016, 1 << 22), (608, 1 << 20)])
+@pytest.mark.parametrize("tail", [1, 2, 3, 4, 5, 30])
+def test_the_last_tile_onto_levels(B, elements, tail):
+    """As above, with one table and, in small calls, a table to each of several tensors that end inside tiles."""
+    room = 64
+    for buckets in ((0, 1, 37) if elements == 0 else (elements // B,)):
+        n = buckets * B + tail
+        _, v = synth(n, B + tail)
+        vd = _dev(v)
+        for bits, coin in ((4, False), (4, True), (5, False), (3, True), (8, False)):
+            levels = _levels(bits, B + bits)
+            c, m = qb.alloc_packed(n, bits, B, DEV)
+            guarded = torch.full((c.numel() + room,), -7, dtype=torch.int32, device=DEV)
+            metas = torch.full((m.numel() + room,), -7.0, dtype=torch.float32, device=DEV)
+            c, m = guarded[:c.numel()], metas[:m.numel()]
+            if coin:
+                qb.qsdp_quantize_levels_stochastic(vd, bits, B, _dev(levels), 11, 16, c, m)
+                want = ref.quantize_levels_stochastic(v, bits, B, levels, 11, 16)
+            else:
+                qb.qsdp_quantize_levels(vd, bits, B, _dev(levels), c, m)
+                want = ref.quantize_levels(v, bits, B, levels)
+            assert _same(c, m, *want), (buckets, bits, coin)
+            assert bool((guarded[c.numel():] == -7).all()) and bool((metas[m.numel():] == -7.0).all()), (buckets, bits)
+    if elements:
+        return
+    sizes = [8 * (tail // 8 + 1), 3 * B, B + 8, 5 * B + tail]
+    segs = qb.Segments(sizes, B, DEV)
+    _, v = synth(sum(sizes), B)
+    for bits, coin in ((4, False), (3, True)):
+        tables = np.stack([_levels(bits, B + t) for t in range(len(sizes))])
+        c, m = segs.alloc_packed(bits)
+        qb.qsdp_quantize_levels_segmented(_dev(v), segs, bits, _dev(tables), c, m.view(-1), coin, 11, 16)
+        o = b = 0
+        for t, size in enumerate(sizes):
+            nb = -(-size // B)
+            got = c[b * B * bits // 32:(b + nb) * B * bits // 32], m[b:b + nb]
+            if coin:
+                want = ref.quantize_levels_stochastic(v[o:o + size].copy(), bits, B, tables[t], 11, 16 + o)
+            else:
+                want = ref.quantize_levels(v[o:o + size].copy(), bits, B, tables[t])
+            assert _same(*got, *want), (t, bits, coin)
+            o, b = o + size, b + nb
