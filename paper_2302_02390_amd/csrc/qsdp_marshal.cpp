@@ -255,14 +255,14 @@ bool plain_value(PyObject* o) {
 // Whether o is a value, or a tensor or segment table on the device of those before it (none yet: -2).
 bool same_device(PyObject* o, int& device) {
     if (plain_value(o)) return true;
-    if ((PyObject*)Py_TYPE(o) == PyDict_GetItem(names, segments_name)) {  // its table is the attribute `device`
+    if (!plain_tensor(o)) {  // a table's tensor is its attribute `device`
+        if ((PyObject*)Py_TYPE(o) != PyDict_GetItem(names, segments_name)) return false;
         PyObject* table = PyObject_GetAttr(o, device_name);
         if (table == nullptr) PyErr_Clear();
         const bool ok = table != nullptr && plain_tensor(table) && same_device(table, device);
         Py_XDECREF(table);
         return ok;
     }
-    if (!plain_tensor(o)) return false;
     try {
         const at::Tensor& t = THPVariable_Unpack(o);
         if (!t.is_cuda()) return false;
