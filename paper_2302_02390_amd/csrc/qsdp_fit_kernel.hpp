@@ -34,12 +34,17 @@ namespace qsdp {
 // the cells' places are read, the reciprocal of the count while its power is), one branch leaves the straight line for
 // everything that is rare, and what the next batch needs is requested a batch ahead. A boundary has one comparison per
 // value: the first value on its upper side is the rounded midpoint or the one after it. Measured (us per batch,
-// Gaussian values, one table of 32 levels, buckets of 128 / 352 / 512 / 1024 / 2048): 0.33 / 0.35 / 0.35 / 0.38 / 0.65,
+// Gaussian values, one table of 32 levels, buckets of 128 / 352 / 512 / 1024 / 2048): 0.32 / 0.34 / 0.34 / 0.37 / 0.62,
 // against 0.40 / 0.43 / 0.44 / 0.48 / 0.91 with barriers, 64-bit words in the cells, two rounded distances per value
-// and a table of reciprocals; 6 bits, 1024: 0.58 -> 0.40; the 292 tables of the 350M model 507 -> 392 us. Up to 512
-// values the chain binds, 790 cycles; at 1024 both do (seven producers 0.39, nine 0.41, eleven 0.38, thirteen 0.39), at
-// 2048 the sorting, of which LDS holds room for eight slots. Tensors of few batches are bound by what a workgroup does
-// before its first one, the table of powers above all, and by one workgroup of this size to a compute unit.
+// and a table of reciprocals; 6 bits, 1024: 0.58 -> 0.40; the 292 tables of the 350M model 507 -> 390 us. Up to 512
+// values the chain binds, 770-830 cycles a batch with LDS in use for 150-340 of them. At 1024 (890 cycles, LDS in use
+// for 540, half of these in bank conflicts) chain and producers are level: with seven, nine, ten, eleven, twelve and
+// thirteen producers a batch of 544 takes 0.45, 0.46, 0.43, 0.40, 0.55, 0.50, one of 1024 0.39, 0.41, 0.39, 0.37, 0.41,
+// 0.38 (12 waves are three to a SIMD, which more than eleven producers are not). At 2048 the sorting binds (1490
+// cycles, LDS in use for 900), of which LDS holds room for eight slots. Tensors of few batches are bound by what a
+// workgroup does before its first one, the table of powers above all, and by one workgroup of this size to a compute
+// unit: 2000 tensors of one batch of 128 / 512 / 1024 / 2048, 5 bits, 8.7 / 26.7 / 32.6 / 53.3 us with barriers, 8.0 /
+// 21.9 / 27.4 / 41.6 now, 300 of them 4.5 / 7.3 / 8.9 / 13.7 and 3.9 / 6.2 / 7.6 / 10.8.
 //
 // The boundary search needs levels that ascend by more than 2^-20 within [0, 1 + 2^-22] (then the comparison of the two
 // rounded distances is monotone in the value and flips within 2^-22 of the midpoint, which is below 1) and cells that
@@ -54,8 +59,8 @@ struct FitShape {
     static_assert(W == 1, "a wave to a batch");
     static constexpr int kBucketMax = 64 * VPT;
     // Six producers for buckets of 129-256 and, with up to 8 levels, of 257-512: seven leave room for fewer workgroups
-    // on a compute unit, and the chain is no faster with them. Eleven for 513-1024, three waves to a SIMD with the
-    // consumer; of the largest buckets LDS holds eight batches.
+    // on a compute unit, and the chain is no faster with them. Eleven for 513-1024 (above), which makes tensors of one
+    // batch 1-3 % slower than seven would; of the largest buckets LDS holds eight batches.
     static constexpr int kProducers = VPT == 16                             ? 11
                                       : VPT == 4 || (VPT == 8 && BITS <= 3) ? 6
                                                                             : 7;

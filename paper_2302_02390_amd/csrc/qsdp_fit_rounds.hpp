@@ -14,7 +14,7 @@ namespace fit_rounds {
 // cell come from the sort's own counting (count and sum in one 64-bit LDS atomic per value), which needs two passes
 // less than the other kernel's sums over groups of four: that is what counts where a batch has a compute unit's LDS to
 // itself and its passes come one after the other (us per batch, 5 bits, buckets of 4096 / 8192: 1.73 / 3.25, and 1.82 /
-// 4.77 in the other kernel's way with teams of two and four waves; a bucket of 2048 0.91 and 0.64).
+// 4.77 in the other kernel's way with teams of two and four waves; a bucket of 2048 0.91 and 0.62).
 // ---------------------------------------------------------------------------------------
 // Shape of a workgroup: W waves to a batch of up to 64 * W * VPT values.
 template <int BMAX, int C>
@@ -161,8 +161,8 @@ struct FitSlot {
     FitCells cells;
 };
 
-// One batch of the chain. lv[i]: the lane's levels, level 64 * i + lane mod (64 / S), updated. lv_shared, acc: K entries
-// of LDS each, for batches that are assigned value by value.
+// One batch of the chain. lv[i]: the lane's levels, level 64 * i + lane mod (64 / S), updated. lv_shared, acc: K
+// entries of LDS each, for batches that are assigned value by value.
 template <int BITS, typename Slot, typename Powers, int C>
 __device__ __forceinline__ void fit_batch(const Slot& slot, int m, Powers& powers, FitFilled& filled, double one_minus,
                                           FitCells cells, float (&lv)[FitLanes<BITS>::M], float* lv_shared,

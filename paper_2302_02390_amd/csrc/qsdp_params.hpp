@@ -197,12 +197,17 @@ __host__ __device__ __forceinline__ Shifts draw_shifts(uint32_t flags, PhiloxKey
 }
 
 // A wave draws the shifts itself only where the seed is in device memory: ten rounds for a single number are 150 scalar
-// instructions, each waiting for the one before, ahead of every wave's one bucket. 3M values, drawn by the waves / by the
-// host: step 9.2 / 8.4 us and 5-bit weights 10.5 / 9.6 in buckets of 96, receive side 8.3 / 7.6 in buckets of 128,
-// 5-bit weights 9.0 / 8.4 in buckets of 1024; 1.02-1.05 up to 100M values (step, 1024: 195.8 / 188.8), nothing beyond.
-// The wave kernels' gradient encoder (with a shared shift only) and code-resident step draw their shifts in every wave all
-// the same: at the size of a model they stream slower when all waves start at once (us, drawn by the host / by the waves:
-// 4-bit gradients of the 350M model's tensors 254.9 / 252.0, code-resident step on the same model 368.4 / 364.6).
+// instructions, each waiting for the one before, ahead of every wave's one bucket. us, drawn by the waves / by the
+// host: 3M values, step 9.2 / 8.4 and 5-bit weights 10.5 / 9.6 in buckets of 96, receive side 8.3 / 7.6 in buckets of
+// 128, 8-bit weights 4.7 / 4.0 in buckets of 1024; step in buckets of 1024, 12M to 250M, 1.00-1.03 times faster,
+// receive side in buckets of 128-512 1.04, code-resident AdamW step 1.04-1.06 up to 1M and 1.00-1.02 from 8M on, the
+// others at these sizes within 1 %, but for large weight calls, which the launch has drawn by the waves.
+//
+// The wave kernels' gradient encoder (with a shared shift only) and code-resident step draw their shifts in every wave
+// all the same: at the size of a model they stream slower when all waves start at once (us, drawn by the host / by the
+// waves: 4-bit gradients of the 350M model's tensors 254.9 / 252.0, code-resident step on the same model 368.4 /
+// 364.6). By mode and not by size, so that code-resident calls of 2^16 to 8M values take 1.01-1.05 times what they
+// would with the host's (from 20M on 0.98-1.01, buckets of 512 the lowest).
 constexpr bool wave_kernel_draws(int mode) { return mode == MODE_GRAD || mode == MODE_FUSED_CODES; }
 
 // DRAW: or where the caller asks for it. ASK: or where the call does (FLAG_WAVES_DRAW).
