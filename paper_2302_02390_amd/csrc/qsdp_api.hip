@@ -206,7 +206,7 @@ uint64_t level_blocks(int mode, uint64_t blocks, int waves, int resident, uint64
 // The shifts that come with the call: those that its kernel reads.
 void set_shifts(int mode, bool wave, Params& p) {
     if (p.seed_dev != nullptr || mode_is_levels(mode) || mode == MODE_SUM) return;
-    if (wave && (wave_kernel_draws(mode) || (p.flags & FLAG_WAVES_DRAW) != 0)) return;
+    if ((wave && wave_kernel_draws(mode)) || (p.flags & FLAG_WAVES_DRAW) != 0) return;
     if (mode == MODE_GRAD && (p.flags & FLAG_GRAD_SHIFT) == 0) return;
     const Shifts shifts = draw_shifts(p.flags, {p.key0, p.key1});
     p.xi = shifts.xi;
@@ -226,7 +226,7 @@ int run(int mode, Params p, int stored_bits, hipStream_t s) {
         wl = launch_wave_1024w2;
         bpw = 0;
         // From 12 * 2^10 buckets on its waves stream slower when all of them start at once, so they draw the shift
-        // themselves: at 8 bits, and below 2^16 buckets at the other widths, 6 bits apart. Speed with the host's shift /
+        // themselves: at 8 bits, and below 2^16 buckets at other widths, 6 bits apart. Speed with the host's shift /
         // with shifts drawn by the waves, against code that knew no other, at 2, 4, 5, 6, 8 bits: 3M elements 1.12 /
         // 1.01, 1.14 / 1.01, 1.13 / 1.00, 1.14 / 1.01, 1.16 / 1.00; 10M 1.05 / 0.98, 1.03 / 0.97, 1.01 / 0.97, 1.03 /
         // 0.97, 1.03 / 0.98; 14M, with other calls' data in the cache, 0.95-0.97 and 1.01-1.04 / 1.00; 25M 0.99 / 1.01,
@@ -244,8 +244,8 @@ int run(int mode, Params p, int stored_bits, hipStream_t s) {
     const bool many_small = tensors > kLevelsResident * kComputeUnits && p.bucket <= 1024 &&
                             nb / tensors * (uint64_t)p.bucket <= 1024;
     const bool wave = wl != nullptr && !many_small;
-    set_shifts(mode, wave, p);
     if (wave) {
+        set_shifts(mode, wave, p);
         // 4 waves per workgroup, each on bpw buckets; or one workgroup per bucket
         uint64_t blocks = bpw > 0 ? ceil_div(ceil_div(nb, (uint64_t)bpw), 4) : nb;
         if (mode_is_levels(mode))
@@ -258,6 +258,16 @@ int run(int mode, Params p, int stored_bits, hipStream_t s) {
         const TilePlan t = mode_is_levels(mode)
                                ? choose_tile(p.bucket, nb, tensors, most_waves)
                                : choose_step_tile(p.bucket, nb, most_waves, work, p.segs != nullptr ? p.nseg : 0);
+        // 8-bit weights over tensors, as above: in tiles of four rows they stream slower with the host's shift from
+        // 2^23 code slots on. Speed with it / drawn by the waves, against code that knew no other, buckets of 96, 320,
+        // 416: tensors of 2^20, 4M 1.02, 1.04, 1.05; 12M 0.96 / 1.00, 0.97 / 1.00, 0.99 / 1.00; 120 tensors of 28M
+        // 0.95 / 1.00, 0.95 / 1.00, 0.97 / 1.00; twenty of 6M 0.95 / 1.00, 0.95 / 1.00, 0.96 / 1.00. At 4 to 7 bits
+        // the host's is the faster one (1.01-1.07 / 1.00), in flat calls mostly (8M 1.04 / 1.01, 33M 1.01 / 1.00, 350M
+        // 0.99 / 1.00), and in tiles of six and eight rows both are within 2 %.
+        if (mode == MODE_WEIGHT && t.rows == 4 && p.segs != nullptr && stored_bits == 8 &&
+            nb * (uint64_t)p.bucket >= (1u << 23))
+            p.flags |= FLAG_WAVES_DRAW;
+        set_shifts(mode, wave, p);
         const uint64_t units = ceil_div(nb, (uint64_t)t.buckets);
         uint64_t blocks = t.waves == 1 ? ceil_div(units, 4) : units;
         if (mode_is_levels(mode))

@@ -178,7 +178,7 @@ __device__ __forceinline__ float step_value(const Params& p, float x, float ghat
 
 // Quantizer variants (same values as the QSDP_FLAG_* of the C header)
 // FLAG_KEEP_MASTER (step modes): x receives the updated value itself, the codes still Q^w of it
-// FLAG_WAVES_DRAW (set by the launch, no caller's): the weight encoder of two waves to a bucket of 1024 draws its shift
+// FLAG_WAVES_DRAW (set by the launch, no caller's): the weight encoder draws its shift in every wave
 enum : uint32_t { FLAG_GRAD_SHIFT = 1u, FLAG_NO_SHIFT = 2u, FLAG_SYMMETRIC = 4u, FLAG_KEEP_MASTER = 8u,
                   FLAG_WAVES_DRAW = 1u << 31 };
 
@@ -201,7 +201,8 @@ __host__ __device__ __forceinline__ Shifts draw_shifts(uint32_t flags, PhiloxKey
 // host: 3M values, step 9.2 / 8.4 and 5-bit weights 10.5 / 9.6 in buckets of 96, receive side 8.3 / 7.6 in buckets of
 // 128, 8-bit weights 4.7 / 4.0 in buckets of 1024; step in buckets of 1024, 12M to 250M, 1.00-1.03 times faster,
 // receive side in buckets of 128-512 1.04, code-resident AdamW step 1.04-1.06 up to 1M and 1.00-1.02 from 8M on, the
-// others at these sizes within 1 %, but for large weight calls, which the launch has drawn by the waves.
+// others at these sizes within 1 %, but for large calls of the weight encoder, whose waves the launch lets draw (run() in
+// qsdp_api.hip).
 //
 // The wave kernels' gradient encoder (with a shared shift only) and code-resident step draw their shifts in every wave
 // all the same: at the size of a model they stream slower when all waves start at once (us, drawn by the host / by the

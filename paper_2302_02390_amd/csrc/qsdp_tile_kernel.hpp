@@ -183,7 +183,7 @@ __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
     const int S = B >> 2;      // slots of a bucket
     const int P = a.buckets;   // buckets of a full tile
     const PhiloxKey key = launch_key<MODE>(args);
-    const Shifts shifts = launch_shifts<MODE>(args, key);
+    const Shifts shifts = launch_shifts<MODE, false, MODE == MODE_WEIGHT && R == 4>(args, key);
     uint32_t saturated = 0;
 
     uint64_t unit0 = W == 1 ? (uint64_t)blockIdx.x * 4u + wave_in_block : blockIdx.x;

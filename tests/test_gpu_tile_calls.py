@@ -315,3 +315,27 @@ def test_the_last_tile_onto_levels(B, elements, tail):
                 want = ref.quantize_levels(v[o:o + size].copy(), bits, B, tables[t])
             assert _same(*got, *want), (t, bits, coin)
             o, b = o + size, b + nb
+
+
+@pytest.mark.parametrize("B", [96, 416, 768])
+@pytest.mark.parametrize("bits", [5, 8])
+@pytest.mark.parametrize("last", [-1, 0])  # buckets of the last tensor against the number that makes 2^23 slots
+def test_who_draws_the_shift_of_weights_over_tensors(B, bits, last):
+    """From 2^23 code slots on the waves draw it at 8 bits in tiles of four rows, with less the host."""
+    total = -(-(1 << 23) // B) + last
+    sizes = [40 * B + 24, (total // 2) * B - 8, 8, B]
+    sizes.append((total - sum(-(-n // B) for n in sizes)) * B - 16)
+    segs = qb.Segments(sizes, B, DEV)
+    assert segs.total_buckets == total
+    x = torch.randn(segs.n, device=DEV)
+    c, m = segs.alloc_packed(bits)
+    for delta in (0.0, 2.0 ** -6):
+        sat = torch.zeros(1, dtype=torch.int64, device=DEV)
+        qb.qsdp_quantize_weight_segmented(x, segs, bits, delta, 12, c, m.view(-1), sat)
+        o = b = saturated = 0
+        for t, size in enumerate(sizes):
+            nb = -(-size // B)
+            wc, wm, ws = ref.quantize_weight(x[o:o + size].cpu().numpy(), bits, B, delta, 12)
+            assert _same(c[b * B * bits // 32:(b + nb) * B * bits // 32], m[b:b + nb], wc, wm), (t, delta)
+            o, b, saturated = o + size, b + nb, saturated + ws
+        assert int(sat) == saturated, delta
