@@ -9,8 +9,10 @@ from paper_2302_02390_amd import build as lib_build
 GRAD, WEIGHT, CODES = 0, 1, 3
 # most registers at which that many waves share a SIMD's 512, in steps of eight
 REGISTERS = {7: 72, 6: 80, 5: 96, 4: 128}
-# rows of a team of four waves -> mode -> waves to a SIMD
-NEEDED = {4: {GRAD: 7, WEIGHT: 7, CODES: 6}, 6: {GRAD: 7, WEIGHT: 7, CODES: 5}, 8: {WEIGHT: 7, CODES: 4}}
+# waves and rows of a team -> mode -> waves to a SIMD
+NEEDED = {(4, 4): {GRAD: 7, WEIGHT: 7, CODES: 6}, (4, 6): {GRAD: 7, WEIGHT: 7, CODES: 5}, (4, 8): {WEIGHT: 7, CODES: 4},
+          (1, 4): {GRAD: 7, WEIGHT: 7, CODES: 7}, (1, 6): {GRAD: 6, WEIGHT: 7, CODES: 5},
+          (1, 8): {GRAD: 5, WEIGHT: 7, CODES: 4}}
 
 
 def _assembly(source, *defines):
@@ -19,19 +21,20 @@ def _assembly(source, *defines):
     return subprocess.run(cmd, capture_output=True, text=True, check=True).stdout
 
 
-def _registers(rows):
-    asm = _assembly("qsdp_tile_inst.hip", "-DQSDP_TILE_W=4", f"-DQSDP_TILE_R={rows}")
-    found = re.findall(rf"\.name:\s+_ZN4qsdp11tile_kernelILi(\d+)ELi{rows}ELi4E.*?\.vgpr_count:\s+(\d+)", asm, re.S)
+def _registers(team):
+    waves, rows = team
+    asm = _assembly("qsdp_tile_inst.hip", f"-DQSDP_TILE_W={waves}", f"-DQSDP_TILE_R={rows}")
+    found = re.findall(rf"\.name:\s+_ZN4qsdp11tile_kernelILi(\d+)ELi{rows}ELi{waves}E.*?\.vgpr_count:\s+(\d+)", asm, re.S)
     return {int(mode): int(n) for mode, n in found}
 
 
 def test_waves_of_the_tile_kernel():
     """Rows side by side took registers and, with them, waves that the encoders and the code-resident step need."""
-    with ThreadPoolExecutor(3) as ex:
+    with ThreadPoolExecutor(len(NEEDED)) as ex:
         counts = dict(zip(NEEDED, ex.map(_registers, NEEDED)))
-    for rows, modes in NEEDED.items():
+    for team, modes in NEEDED.items():
         for mode, waves in modes.items():
-            assert counts[rows][mode] <= REGISTERS[waves], (rows, mode, counts)
+            assert counts[team][mode] <= REGISTERS[waves], (team, mode, counts)
 
 
 def _fit(values):
