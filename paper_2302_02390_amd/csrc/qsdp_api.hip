@@ -225,16 +225,16 @@ int run(int mode, Params p, int stored_bits, hipStream_t s) {
         // per wave), is faster with one wave per bucket
         wl = launch_wave_1024w2;
         bpw = 0;
-        // From 12 * 2^10 buckets on its waves stream slower when all of them start at once, so they draw the shift
-        // themselves: at 8 bits, and below 2^16 buckets at other widths, 6 bits apart. Speed with the host's shift /
-        // with shifts drawn by the waves, against code that knew no other, at 2, 4, 5, 6, 8 bits: 3M elements 1.12 /
-        // 1.01, 1.14 / 1.01, 1.13 / 1.00, 1.14 / 1.01, 1.16 / 1.00; 10M 1.05 / 0.98, 1.03 / 0.97, 1.01 / 0.97, 1.03 /
-        // 0.97, 1.03 / 0.98; 14M, with other calls' data in the cache, 0.95-0.97 and 1.01-1.04 / 1.00; 25M 0.99 / 1.01,
-        // 0.95 / 1.00, 0.96 / 1.00, 1.01 / 1.00, 0.95 / 1.00; 50M 0.99 / 1.00, 0.98 / 1.00, 1.00 / 1.00, 1.02 / 1.00,
-        // 0.97 / 1.00; 125M 1.02 / 1.00, 1.00 / 1.00, 1.00 / 1.00, 1.04 / 1.01, 0.99 / 1.00; 350M 1.01 / 0.99, 1.01 /
-        // 1.00, 1.02 / 1.00, 1.03 / 1.00, 0.99 / 1.00. Buckets of 2048: 1.04 / 1.04 at 8M, 0.99 / 0.97 at 16M, the
-        // same beyond.
-        if (nb >= (12u << 10) && stored_bits != 6 && (stored_bits == 8 || nb < (1u << 16))) p.flags |= FLAG_WAVES_DRAW;
+        // From 12 * 2^10 to 2^16 buckets its waves stream slower when all of them start at once, so they draw the shift
+        // themselves. Speed with the host's shift / drawn by the waves, against code that knew no other, at 4 and 8
+        // bits, on the same buffers again and again; on others in turn, which are not in the caches; and with a decode
+        // after it: 3M elements 1.14 / 1.00, 1.16 / 1.00; 1.00 / 1.01, 1.01 / 0.99; 8M 1.05 / 0.98, 1.05 / 0.98; 0.96 /
+        // 1.01, 0.96 / 1.01; 14M 0.99 / 1.01, 0.95 / 1.00; 0.95 / 1.01, 0.97 / 1.02; 0.97 / 0.98, 0.95 / 0.97; 25M 0.96
+        // / 1.00, 0.96 / 0.99; 0.92 / 1.00, 0.93 / 1.00; 0.98 / 1.00, 0.96 / 1.00; 50M 0.98 / 1.00, 0.98 / 1.00; 0.96 /
+        // 0.99, 0.96 / 1.00; 0.98 / 1.00, 0.98 / 1.00; 80M 1.00 / 1.00, 0.99 / 1.00; 0.99-1.01 / 0.99, 0.98-1.02 /
+        // 1.00; 1.00 / 1.00, 1.00 / 1.00; 350M 1.00 / 0.99, 0.99 / 1.00; 1.01 / 0.99, 1.00 / 1.00; 1.01 / 0.99, 1.00 /
+        // 1.00. Buckets of 2048 and one wave to a bucket: both within 2 %.
+        if (nb >= (12u << 10) && nb < (1u << 16)) p.flags |= FLAG_WAVES_DRAW;
     }
     // learned levels with a table per tensor: how many there are
     const uint64_t tensors = mode_is_levels(mode) && p.levels_per_tensor != 0 ? (p.nseg < nb ? p.nseg : nb) : 0;
@@ -258,14 +258,15 @@ int run(int mode, Params p, int stored_bits, hipStream_t s) {
         const TilePlan t = mode_is_levels(mode)
                                ? choose_tile(p.bucket, nb, tensors, most_waves)
                                : choose_step_tile(p.bucket, nb, most_waves, work, p.segs != nullptr ? p.nseg : 0);
-        // 8-bit weights over tensors, as above: in tiles of four rows they stream slower with the host's shift from
-        // 2^23 code slots on. Speed with it / drawn by the waves, against code that knew no other, buckets of 96, 320,
-        // 416: tensors of 2^20, 4M 1.02, 1.04, 1.05; 12M 0.96 / 1.00, 0.97 / 1.00, 0.99 / 1.00; 120 tensors of 28M
-        // 0.95 / 1.00, 0.95 / 1.00, 0.97 / 1.00; twenty of 6M 0.95 / 1.00, 0.95 / 1.00, 0.96 / 1.00. At 4 to 7 bits
-        // the host's is the faster one (1.01-1.07 / 1.00), in flat calls mostly (8M 1.04 / 1.01, 33M 1.01 / 1.00, 350M
-        // 0.99 / 1.00), and in tiles of six and eight rows both are within 2 %.
+        // 8-bit weights over tensors, as above, in tiles of four rows. Speed with the host's shift / drawn by the
+        // waves, against code that knew no other, buckets of 32, 96, 320, 416, on the same buffers again and again; on
+        // others in turn: tensors of 2^20, 12M 0.99, 0.96, 0.97, 0.99 / 1.00; 1.01, 1.02, 1.02, 1.03 / 1.00; 120
+        // tensors of 28M 0.98, 0.95, 0.95, 0.97 / 1.00; 1.02, 0.98, 0.97, 0.98 / 1.00; twenty of 6M 0.99, 0.95, 0.95,
+        // 0.96 / 1.00; 1.01, 0.98, 0.99, 1.00 / 1.00. At 4 to 7 bits the host's is the faster one (1.01-1.07 / 1.00),
+        // in flat calls mostly (8M 1.04 / 1.01, 33M 1.01 / 1.00, 350M 0.99 / 1.00), and in tiles of six and eight rows
+        // both are within 2 %.
         if (mode == MODE_WEIGHT && t.rows == 4 && p.segs != nullptr && stored_bits == 8 &&
-            nb * (uint64_t)p.bucket >= (1u << 23))
+            nb * (uint64_t)p.bucket >= (12u << 20))
             p.flags |= FLAG_WAVES_DRAW;
         set_shifts(mode, wave, p);
         const uint64_t units = ceil_div(nb, (uint64_t)t.buckets);

@@ -248,7 +248,7 @@ def test_non_finite_inputs_do_not_disturb_their_neighbours():
 @pytest.mark.parametrize("bits", [3, 5, 6, 8])
 @pytest.mark.parametrize("buckets", [(12 << 10) - 1, 12 << 10, (1 << 16) - 1, 1 << 16])
 def test_who_draws_the_shift_of_large_weight_calls(bits, buckets):
-    """Buckets of 1024: the shift comes with the call or is drawn by its waves, by size and width; the last bucket is
+    """Buckets of 1024: the shift comes with the call or is drawn by its waves, by size; the last bucket is
     short, and without a shift none is drawn."""
     n = buckets * 1024 - 75
     x = torch.randn(n, device=DEV)

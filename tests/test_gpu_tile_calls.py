@@ -319,10 +319,10 @@ def test_the_last_tile_onto_levels(B, elements, tail):
 
 @pytest.mark.parametrize("B", [96, 416, 768])
 @pytest.mark.parametrize("bits", [5, 8])
-@pytest.mark.parametrize("last", [-1, 0])  # buckets of the last tensor against the number that makes 2^23 slots
+@pytest.mark.parametrize("last", [-1, 0])  # buckets of the call against the number that makes 12 * 2^20 slots
 def test_who_draws_the_shift_of_weights_over_tensors(B, bits, last):
-    """From 2^23 code slots on the waves draw it at 8 bits in tiles of four rows, with less the host."""
-    total = -(-(1 << 23) // B) + last
+    """From 12 * 2^20 code slots on the waves draw it at 8 bits in tiles of four rows, with less the host."""
+    total = -(-(12 << 20) // B) + last
     sizes = [40 * B + 24, (total // 2) * B - 8, 8, B]
     sizes.append((total - sum(-(-n // B) for n in sizes)) * B - 16)
     segs = qb.Segments(sizes, B, DEV)
