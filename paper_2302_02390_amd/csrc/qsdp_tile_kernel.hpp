@@ -155,13 +155,12 @@ __global__ void __launch_bounds__(256, tile_min_blocks(MODE, W, R))
     // computed for every block: held across the loop they were 50-150 scalar registers too many, each written to and
     // read from a lane of a vector register (step, four rows, 77 -> 24, and 90 -> 87 vector registers). 216 calls of
     // 2^16 to 10^8 elements in buckets of 96 to 2336: code-resident step 1.05-1.08 times faster, receive side
-    // 1.02-1.07, gradient encoder 1.03, steps 1.02-1.04; the weight encoder's larger tiles and the nearest
-    // level, with ten, lost 0-2 %. Timing decides, not registers: the gradient encoder of six rows takes 78 vector
-    // registers so and at most 72 without, a wave more to a SIMD, but with teams of one wave it is the faster one (125M,
-    // 4 bits, buckets of 768, 96.3 / 94.7), with four it was not (2080 / 4128, eight and six rows, 111.0 / 121.6, and
-    // 113.7 / 124.2 with the last tile on the common path too).
-    constexpr bool kReadAgain =
-        MODE != MODE_LEVELS && !(MODE == MODE_GRAD && W == 4 && R > 4) && (MODE != MODE_WEIGHT || R == 2);
+    // 1.02-1.07, steps 1.02-1.04; the weight encoder's larger tiles and the nearest level, with ten, lost 0-2 %. The
+    // gradient encoder, whose keys alone are computed again, waits for the parameters before its loads: buckets of 32
+    // to 2016, read once against again, 1.01-1.04 times faster on 10^6 to 8*10^6 values that are not in the caches (8M
+    // in buckets of 1504, 13.1 -> 12.3 us, seven waves to a SIMD instead of six) and on 65571 ones, cached 0.98-1.03,
+    // large ones 0.99-1.02.
+    constexpr bool kReadAgain = MODE != MODE_LEVELS && MODE != MODE_GRAD && (MODE != MODE_WEIGHT || R == 2);
     // The first team takes the call's last tile, which takes longer for its short bucket, and the last team the first;
     // all others keep theirs, so that a tile meets its codes in the same L2 as in the next call. us, each its own / so,
     // buckets of 768, 1504, 2336: 5M elements, step 12.7 / 11.7, 13.0 / 11.9, 14.7 / 12.8, AdamW step 35.8 / 31.0,

@@ -11,7 +11,7 @@ GRAD, WEIGHT, CODES = 0, 1, 3
 REGISTERS = {7: 72, 6: 80, 5: 96, 4: 128}
 # waves and rows of a team -> mode -> waves to a SIMD
 NEEDED = {(4, 4): {GRAD: 7, WEIGHT: 7, CODES: 6}, (4, 6): {GRAD: 7, WEIGHT: 7, CODES: 5}, (4, 8): {WEIGHT: 7, CODES: 4},
-          (1, 4): {GRAD: 7, WEIGHT: 7, CODES: 7}, (1, 6): {GRAD: 6, WEIGHT: 7, CODES: 5},
+          (1, 4): {GRAD: 7, WEIGHT: 7, CODES: 7}, (1, 6): {GRAD: 7, WEIGHT: 7, CODES: 5},
           (1, 8): {GRAD: 5, WEIGHT: 7, CODES: 4}}
 
 
